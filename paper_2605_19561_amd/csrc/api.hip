@@ -602,7 +602,7 @@ int torq_block_gram(const void *x_bf16, int64_t M, int d, int G, double *Sigma, 
   if (misaligned(x_bf16) || misaligned(workspace) || (reinterpret_cast<uintptr_t>(Sigma) & 7u)) return TORQ_EALIGN;
   if (workspace_bytes < torq::block_gram_workspace_bytes(G)) return TORQ_EWORKSPACE;
   const int64_t TG = M * (int64_t)(d / TORQ_BLOCK / G);
-  hipError_t e = torq::launch_block_gram(x_bf16, TG, G, -1, Sigma, workspace, (hipStream_t)stream);
+  hipError_t e = torq::launch_block_gram(x_bf16, TG, G, false, Sigma, workspace, (hipStream_t)stream);
   return e == hipSuccess ? TORQ_OK : hip_fail(e);
 }
 
@@ -614,12 +614,8 @@ int torq_block_gram_positions(const void *x_bf16, int64_t M, int d, int G, doubl
   if (misaligned(x_bf16) || misaligned(workspace) || (reinterpret_cast<uintptr_t>(Sigma_pos) & 7u)) return TORQ_EALIGN;
   if (workspace_bytes < torq::block_gram_workspace_bytes(G)) return TORQ_EWORKSPACE;
   const int64_t TG = M * (int64_t)(d / TORQ_BLOCK / G);
-  // one pass per position: the partial sums in the workspace are reused in stream order
-  for (int k = 0; k < TORQ_BLOCK; ++k) {
-    hipError_t e = torq::launch_block_gram(x_bf16, TG, G, k, Sigma_pos + (size_t)k * G * G, workspace, (hipStream_t)stream);
-    if (e != hipSuccess) return hip_fail(e);
-  }
-  return TORQ_OK;
+  hipError_t e = torq::launch_block_gram(x_bf16, TG, G, true, Sigma_pos, workspace, (hipStream_t)stream);
+  return e == hipSuccess ? TORQ_OK : hip_fail(e);
 }
 
 // Algorithm 1 (Section 5.1) with the equalising angle.  One step takes the block p furthest above

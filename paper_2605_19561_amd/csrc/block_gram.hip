@@ -1,208 +1,366 @@
-// torq_block_gram: the statistic that the inter-block calibration starts from (Section 5.1,
-// Algorithm 1 input; Section 4.2, sigma_b^2 = E ||z_b||^2):
+// torq_block_gram / torq_block_gram_positions: the statistics that the inter-block calibration starts
+// from (Section 5.1, Algorithm 1 input; Section 4.2, sigma_b^2 = E ||z_b||^2 and the Sigma_k of Theorem 4.1):
 //
-//   Sigma[b][b'] = mean over token-groups of  sum_k X[b][k] X[b'][k]
+//   Sigma[b][b']    = mean over token-groups of  sum_k X[b][k] X[b'][k]
+//   Sigma_k[b][b']  = mean over token-groups of  X[b][k] X[b'][k]
 //
 // where a token-group is one run of G consecutive 32-element blocks of one row, i.e. G rows of
-// 64 contiguous bytes.  The contraction index is the position inside a block (K = 32), which is
-// exactly one v_mfma_f32_16x16x32_bf16: lane (m = l % 16, q = l / 16) of an operand holds the 8
-// consecutive elements 8 q .. 8 q + 7 of block row m -- 16 contiguous bytes of the row-major input,
-// so an operand is 16 rows x one 16-byte chunk and nothing is transposed.  bf16 products are exact
-// in fp32; the sums are fp32 per workgroup and fp64 across workgroups.
+// 64 contiguous bytes.  Both are products of a matrix with its own transpose on
+// v_mfma_f32_16x16x32_bf16 (bf16 products are exact in fp32; the sums are fp32 per workgroup and fp64
+// across workgroups), so both operands of an instruction come out of the same registers and only the
+// 16 x 16 tiles (r, c) with r <= c are computed; the reduce kernel writes both triangles.
 //
-// Workgroup = ceil(G / 32) waves; wave w owns the block rows 32 w .. 32 w + 31 (two 16-row tiles)
-// against all G columns (NT = G / 16 tiles): 2 NT accumulator tiles of 4 registers.  Every wave
-// needs the whole token-group as its column operand, so the workgroup stages it once through LDS
-// (global -> registers -> LDS, two stages, one barrier per trip of two token-groups) instead of
-// letting each wave fetch it from the L1 (that version was bound by the L1's request rate, 5 requests
-// per byte).  Workgroups are persistent; each writes its partial Sigma to the workspace, and two
-// small kernels add the partials in a fixed order in double and divide by the number of
-// token-groups.  HBM bound: 2 bytes per element, read once.
+// Sigma: the contraction index is the position inside a block (K = 32 = one instruction), the operand
+//   of tile row r is 16 block rows x 64 bytes = 1 KiB of consecutive input.
+// Sigma_k: the contraction index is the token-group; the workgroup transposes its input on the way
+//   into LDS (below).
+//
+// Up to 36 tiles (G <= 128) are one wave's accumulators; larger G runs as several launches, each with
+// its share of the tiles.  Partial sums: packed tiles, [tile][lane][4 floats] as the accumulators hold them.
 #include "torq_device.h"
 #include "torq_internal.h"
 
 namespace torq {
 
-constexpr int GRAM_MAX_WG = 512;      // partial results (2 resident workgroups per CU)
-constexpr int GRAM_GROUPS_PER_TRIP = 2;
+typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
 
+constexpr int GRAM_MAX_WG = 256;      // one workgroup per CU
+constexpr int GRAM_WAVES = 8;
+constexpr int GRAM_MAX_SLICES = 32;   // Sigma_k: pieces of the token-groups that run side by side
+constexpr int GRAM_MAX_TILES = 36;    // per wave: 144 accumulator registers
+
+// the tiles (r, c), r <= c < NT, row by row
 template <int NT>
-__global__ void __launch_bounds__(64 * ((NT + 1) / 2))
-block_gram_kernel(const uint4 *__restrict__ x, int64_t TG, int position, float *__restrict__ partial) {
-  constexpr int G = 16 * NT;
-  constexpr int NTHR = 64 * ((NT + 1) / 2);
-  constexpr int CHUNKS = 4 * G;                          // 16-byte chunks of one token-group
-  constexpr int CH = (CHUNKS + NTHR - 1) / NTHR;         // chunks per thread per token-group (2)
-  constexpr int U = GRAM_GROUPS_PER_TRIP;
-  constexpr int TG_BYTES = G * 64, STAGE_BYTES = U * TG_BYTES;
-  extern __shared__ __attribute__((aligned(16))) char lds[];   // two stages of U token-groups
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int m = lane & 15, q = lane >> 4;
-  const int rt0 = 2 * wave, rt1 = 2 * wave + 1;          // this wave's row tiles; rt1 may not exist
-  const bool has1 = rt1 < NT;
-
-  f32x4 acc0[NT], acc1[NT];
-#pragma unroll
-  for (int ct = 0; ct < NT; ++ct) acc0[ct] = acc1[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // Chunk c of a token-group = (block row c / 4, elements 8 (c % 4) .. + 7).  In LDS the chunk
-  // index inside a 64-byte row is XORed with (row >> 2) & 3, so that the 16 lanes that read one
-  // operand (16 consecutive rows, same chunk) hit 16 different bank groups.  For a tile's rows
-  // 16 t + m that term is (m >> 2) & 3: one lane offset serves every tile.
-  const int frag_off = m * 64 + ((q ^ ((m >> 2) & 3)) * 16);
-  int st_off[CH];
-#pragma unroll
-  for (int i = 0; i < CH; ++i) {
-    const int c = tid + i * NTHR, r = c >> 2;
-    st_off[i] = r * 64 + (((c & 3) ^ ((r >> 2) & 3)) * 16);
-  }
-
-  // Which bits of this thread's chunks count: all of them for Sigma (position < 0); for Sigma_k only
-  // element `position` of every block, i.e. one half of word (position / 2) % 4 of chunk position / 8.
-  uint32_t keep[CH][4];
-#pragma unroll
-  for (int i = 0; i < CH; ++i)
-#pragma unroll
-    for (int w = 0; w < 4; ++w)
-      keep[i][w] = position < 0 ? 0xFFFFFFFFu
-                 : ((((tid + i * NTHR) & 3) == ((position >> 3) & 3) && w == ((position >> 1) & 3))
-                        ? ((position & 1) ? 0xFFFF0000u : 0x0000FFFFu) : 0u);
-
-  // a trip = U token-groups; trips are dealt to the workgroups round robin
-  const int64_t ntrip = (TG + U - 1) / U;
-  uint4 regs[U][CH];
-  auto load_trip = [&](int64_t trip) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t tg = trip * U + u;
-#pragma unroll
-      for (int i = 0; i < CH; ++i) {
-        const int c = tid + i * NTHR;
-        regs[u][i] = (tg < TG && c < CHUNKS) ? x[tg * CHUNKS + c] : make_uint4(0, 0, 0, 0);
-        regs[u][i].x &= keep[i][0];
-        regs[u][i].y &= keep[i][1];
-        regs[u][i].z &= keep[i][2];
-        regs[u][i].w &= keep[i][3];
+struct GramTiles {
+  static constexpr int N = NT * (NT + 1) / 2;
+  int r[N] = {}, c[N] = {};
+  constexpr GramTiles() {
+    int i = 0;
+    for (int a = 0; a < NT; ++a)
+      for (int b = a; b < NT; ++b) {
+        r[i] = a;
+        c[i] = b;
+        ++i;
       }
-    }
-  };
-  auto store_trip = [&](int stage) {
+  }
+};
+
+// a launch's share of the tiles: parts of nearly equal size, at most GRAM_MAX_TILES each (fewer from
+// G = 224 on, where two chunk columns are staged per thread beside the accumulators)
+constexpr int gram_parts(int nt) {
+  const int most = nt < 14 ? GRAM_MAX_TILES : 28;
+  return (nt * (nt + 1) / 2 + most - 1) / most;
+}
+template <int NT, int PART>
+struct GramPart {
+  static constexpr int N = NT * (NT + 1) / 2;
+  static constexpr int PARTS = gram_parts(NT);
+  static constexpr int T0 = N * PART / PARTS, T1 = N * (PART + 1) / PARTS, COUNT = T1 - T0;
+  static constexpr int ROW0 = GramTiles<NT>().r[T0];   // tile rows below this one are not needed
+};
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t gram_rsrc(const void *p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
+}
+
+// Sigma.  Bound: HBM, 2 bytes per element, read once.  Every wave takes token-groups of its own (U at a
+// time, about 8 KiB), straight from memory into the operand registers: nothing is staged or shared, there
+// is no barrier in the loop, and two steps are in flight beyond the one being multiplied (128 KiB per CU).
+// A token-group past the end reads as zeros through the buffer's range check and adds nothing.  The
+// workgroup's waves add their tiles through LDS at the end: 256 partial results instead of the 512 of a
+// form that shared each token-group through LDS, and packed triangles instead of squares.  X [16384, 8192],
+// G = 128: this kernel 64 -> 51 us (5.2 TB/s, the rate of a copy), the reduction 14 us in two launches -> 4.7.
+template <int NT, int PART>
+__global__ void __launch_bounds__(64 * GRAM_WAVES)
+block_gram_kernel(const uint4 *__restrict__ x, int64_t TG, f32x4 *__restrict__ partial) {
+  using P = GramPart<NT, PART>;
+  constexpr GramTiles<NT> tiles;
+  constexpr int G = 16 * NT, NF = NT - P::ROW0, U = NT < 8 ? 8 / NT : 1;
+  constexpr int SETS = NF <= 9 ? 3 : 2;             // (two where the registers do not hold three)
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int voff = (lane & 15) * 64 + (lane >> 4) * 16;
+  // the workgroup's steps are one contiguous span, dealt to its waves in turn
+  const int64_t steps = (TG + U - 1) / U;
+  const int64_t per = (steps + gridDim.x - 1) / gridDim.x;
+  const int64_t s_end = (int64_t)(blockIdx.x + 1) * per < steps ? (int64_t)(blockIdx.x + 1) * per : steps;
+
+  f32x4 acc[P::COUNT];
+#pragma unroll
+  for (int i = 0; i < P::COUNT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  auto load = [&](u32x4 (&v)[U][NF], int64_t s) {
+    const int64_t left = s < s_end ? TG - s * U : 0;
+    const __amdgpu_buffer_rsrc_t rsrc =
+        gram_rsrc(x + (left > 0 ? s * U : 0) * (4 * G), (uint32_t)(left < U ? left : U) * (G * 64));
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int i = 0; i < CH; ++i)
-        if (tid + i * NTHR < CHUNKS)
-          *reinterpret_cast<uint4 *>(lds + stage * STAGE_BYTES + u * TG_BYTES + st_off[i]) = regs[u][i];
+      for (int f = 0; f < NF; ++f)
+        v[u][f] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, u * (G * 64) + (P::ROW0 + f) * 1024, 0);
+  };
+  auto multiply = [&](const u32x4 (&v)[U][NF]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < P::COUNT; ++i)
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            __builtin_bit_cast(bf16x8, v[u][tiles.r[P::T0 + i] - P::ROW0]),
+            __builtin_bit_cast(bf16x8, v[u][tiles.c[P::T0 + i] - P::ROW0]), acc[i], 0, 0, 0);
   };
 
-  int64_t trip = blockIdx.x;
-  if (trip < ntrip) {
-    load_trip(trip);
-    store_trip(0);
-  }
-  __syncthreads();
-  int stage = 0;
-  for (; trip < ntrip; trip += gridDim.x, stage ^= 1) {
-    const int64_t next = trip + gridDim.x;
-    const bool have_next = next < ntrip;
-    if (have_next) load_trip(next);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const char *g = lds + stage * STAGE_BYTES + u * TG_BYTES + frag_off;
-      const bf16x8 a0 = *reinterpret_cast<const bf16x8 *>(g + rt0 * 1024);
-      const bf16x8 a1 = *reinterpret_cast<const bf16x8 *>(g + (has1 ? rt1 : rt0) * 1024);
-#pragma unroll
-      for (int ct = 0; ct < NT; ++ct) {
-        const bf16x8 col = *reinterpret_cast<const bf16x8 *>(g + ct * 1024);
-        acc0[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, col, acc0[ct], 0, 0, 0);
-        acc1[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, col, acc1[ct], 0, 0, 0);
-      }
+  u32x4 v[SETS][U][NF];
+  int64_t s = (int64_t)blockIdx.x * per + wave;
+  if constexpr (SETS == 3) {
+    load(v[0], s);
+    load(v[1], s + GRAM_WAVES);
+    for (; s < s_end; s += 3 * GRAM_WAVES) {
+      load(v[2], s + 2 * GRAM_WAVES);
+      multiply(v[0]);
+      load(v[0], s + 3 * GRAM_WAVES);
+      multiply(v[1]);
+      load(v[1], s + 4 * GRAM_WAVES);
+      multiply(v[2]);
     }
-    if (have_next) store_trip(stage ^ 1);
+  } else {
+    load(v[0], s);
+    for (; s < s_end; s += 2 * GRAM_WAVES) {
+      load(v[1], s + GRAM_WAVES);
+      multiply(v[0]);
+      load(v[0], s + 2 * GRAM_WAVES);
+      multiply(v[1]);
+    }
+  }
+
+  // the upper half of the waves hand their tiles to the lower half, until one wave holds the sum
+  f32x4 *const box = reinterpret_cast<f32x4 *>(lds);
+#pragma unroll
+  for (int half = GRAM_WAVES / 2; half >= 1; half /= 2) {
+    if (wave >= half && wave < 2 * half) {
+#pragma unroll
+      for (int i = 0; i < P::COUNT; ++i) box[((wave - half) * P::COUNT + i) * 64 + lane] = acc[i];
+    }
+    __syncthreads();
+    if (wave < half) {
+#pragma unroll
+      for (int i = 0; i < P::COUNT; ++i) acc[i] += box[(wave * P::COUNT + i) * 64 + lane];
+    }
     __syncthreads();
   }
-
-  // accumulator lane (n = l % 16, q), register r: row 4 q + r of the row tile, column n of the column tile
-  float *out = partial + (size_t)blockIdx.x * (G * G);
+  if (wave == 0) {
 #pragma unroll
-  for (int ct = 0; ct < NT; ++ct)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      out[(16 * rt0 + 4 * q + r) * G + 16 * ct + m] = acc0[ct][r];
-      if (has1) out[(16 * rt1 + 4 * q + r) * G + 16 * ct + m] = acc1[ct][r];
-    }
-}
-
-// Two-stage sum of the partial results, in double and in a fixed order.  Stage 1: slice s of
-// GRAM_SLICES adds its share of the workgroups' partials; stage 2 adds the slices and divides by
-// the number of token-groups.
-constexpr int GRAM_SLICES = 16;
-
-__global__ void __launch_bounds__(256)
-block_gram_reduce1_kernel(const float *__restrict__ partial, int n_partial, int GG, double *__restrict__ slices) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= GG) return;
-  const int per = (n_partial + GRAM_SLICES - 1) / GRAM_SLICES;
-  const int p0 = blockIdx.y * per, p1 = (p0 + per < n_partial) ? p0 + per : n_partial;
-  double s = 0.0;
-  int p = p0;
-  for (; p + 8 <= p1; p += 8) {                  // eight loads in flight, added in order
-    float v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = partial[(size_t)(p + u) * GG + i];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) s += (double)v[u];
+    for (int i = 0; i < P::COUNT; ++i) partial[((size_t)blockIdx.x * P::COUNT + i) * 64 + lane] = acc[i];
   }
-  for (; p < p1; ++p) s += (double)partial[(size_t)p * GG + i];
-  slices[(size_t)blockIdx.y * GG + i] = s;
 }
 
-__global__ void __launch_bounds__(256)
-block_gram_reduce2_kernel(const double *__restrict__ slices, int GG, double inv_groups, double *__restrict__ Sigma) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= GG) return;
-  double s = 0.0;
+// Sigma_k, all 32 positions in one pass.  A workgroup takes the eight positions of one 16-byte chunk of
+// every block (four workgroups share the input's lines, through the L2 of the XCD that all four are on) and
+// a slice of the token-groups; wave j owns position 8 chunk + j and all of this launch's tiles.  The
+// contraction runs over token-groups, so an operand register holds one position of one block row for eight
+// of them: a thread loads its block's chunk of eight token-groups, pairs up their halves with byte
+// permutes and writes one 16-byte operand piece for each position to LDS, [position][octet][block row],
+// which is written and read in whole consecutive runs (no bank conflicts).  32 token-groups are one
+// instruction's K; a stage holds KST such steps so that the 512 threads have one chunk column each.
+// The bound is reading every line four times from the L2 plus the partial tiles (32 slices x 1.2 MB at
+// G = 128); a stage of 256 KB of lines against 36 matrix instructions per wave.  X [4096, 4096], G = 128:
+// 17.5 us and 8.4 for the reduction; a pass over X for each position took 32 x (12 + 9 + 3) us.
+template <int NT, int PART>
+__global__ void __launch_bounds__(64 * GRAM_WAVES)
+block_gram_positions_kernel(const uint4 *__restrict__ x, int64_t TG, int slices, f32x4 *__restrict__ partial) {
+  using P = GramPart<NT, PART>;
+  constexpr GramTiles<NT> tiles;
+  constexpr int G = 16 * NT, NF = NT - P::ROW0;
+  constexpr int KST = NT < 8 ? 8 / NT : 1;          // matrix k-steps of 32 token-groups per stage
+  constexpr int ITEMS = 4 * KST * G;                // (octet of token-groups, block row)
+  constexpr int THR = 64 * GRAM_WAVES, IT = (ITEMS + THR - 1) / THR;
+  constexpr int PLANE = ITEMS * 16, STAGE = 8 * PLANE;
+  constexpr bool TWO = 2 * STAGE <= 128 * 1024;     // two LDS stages, one barrier per stage
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // workgroup id mod 8 is the XCD: the four chunks of a slice share one
+  const int id = blockIdx.x, slice = (id >> 5) * 8 + (id & 7), chunk = (id >> 3) & 3;
+  const int64_t stages = (TG + 32 * KST - 1) / (32 * KST);
+  const int64_t st0 = stages * slice / slices, st1 = stages * (slice + 1) / slices;
+
+  int voff[IT];
 #pragma unroll
-  for (int p = 0; p < GRAM_SLICES; ++p) s += slices[(size_t)p * GG + i];
-  Sigma[i] = s * inv_groups;
+  for (int i = 0; i < IT; ++i) {
+    const int item = tid + i * THR;
+    voff[i] = item < ITEMS ? ((item / G) * 8 * G + item % G) * 64 + chunk * 16 : 0x7FFFFFF0;
+  }
+  u32x4 v[IT][8];
+  auto load = [&](int64_t st) {                     // a token-group past the end reads as zeros
+    const int64_t tg0 = st * (32 * KST), left = TG - tg0 < 32 * KST ? TG - tg0 : 32 * KST;
+    const __amdgpu_buffer_rsrc_t rsrc = gram_rsrc(x + tg0 * (4 * G), (uint32_t)left * (G * 64));
+#pragma unroll
+    for (int i = 0; i < IT; ++i)
+#pragma unroll
+      for (int t = 0; t < 8; ++t) v[i][t] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff[i], t * (G * 64), 0);
+  };
+  auto store = [&](char *stage) {
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+      if (ITEMS % THR != 0 && tid + i * THR >= ITEMS) continue;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        u32x4 even, odd;                            // positions 2 w and 2 w + 1 of the chunk
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          even[p] = __builtin_amdgcn_perm(v[i][2 * p + 1][w], v[i][2 * p][w], 0x05040100u);
+          odd[p] = __builtin_amdgcn_perm(v[i][2 * p + 1][w], v[i][2 * p][w], 0x07060302u);
+        }
+        *reinterpret_cast<u32x4 *>(stage + (2 * w) * PLANE + (tid + i * THR) * 16) = even;
+        *reinterpret_cast<u32x4 *>(stage + (2 * w + 1) * PLANE + (tid + i * THR) * 16) = odd;
+      }
+    }
+  };
+
+  f32x4 acc[P::COUNT];
+#pragma unroll
+  for (int i = 0; i < P::COUNT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  const int f_off = wave * PLANE + ((lane >> 4) * G + (lane & 15)) * 16;
+  if (st0 < st1) load(st0);
+  int buf = 0;
+  for (int64_t st = st0; st < st1; ++st) {
+    char *const stage = lds + (TWO ? buf * STAGE : 0);
+    store(stage);
+    if (st + 1 < st1) load(st + 1);
+    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < KST; ++ks) {
+      bf16x8 f[NF];
+#pragma unroll
+      for (int r = 0; r < NF; ++r)
+        f[r] = *reinterpret_cast<const bf16x8 *>(stage + f_off + (ks * 4 * G + (P::ROW0 + r) * 16) * 16);
+#pragma unroll
+      for (int i = 0; i < P::COUNT; ++i)
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[tiles.r[P::T0 + i] - P::ROW0],
+                                                         f[tiles.c[P::T0 + i] - P::ROW0], acc[i], 0, 0, 0);
+    }
+    if (!TWO) __syncthreads();
+    buf ^= 1;
+  }
+  f32x4 *const out = partial + ((size_t)slice * 32 + chunk * 8 + wave) * (P::COUNT * 64);
+#pragma unroll
+  for (int i = 0; i < P::COUNT; ++i) out[i * 64 + lane] = acc[i];
 }
 
-// [GRAM_MAX_WG][G * G] floats, then [GRAM_SLICES][G * G] doubles
-size_t block_gram_workspace_bytes(int G) {
-  return (size_t)GRAM_MAX_WG * G * G * sizeof(float) + (size_t)GRAM_SLICES * G * G * sizeof(double);
-}
-
-template <int NT>
-static hipError_t launch_nt(const void *x, int64_t TG, int position, double *Sigma, void *workspace, hipStream_t stream) {
+// Adds n partial results in double and in a fixed order, divides by the number of token-groups and writes
+// both triangles.  A workgroup adds 16 accumulator quads: thread (slice = t / 16, quad = t % 16) every
+// sixteenth partial, then the 16 slices meet in LDS.  blockIdx.y: the position (1 or 32 of them); a partial
+// result holds gridDim.y * tiles * 64 quads.
+template <int NT, int PART>
+__global__ void __launch_bounds__(256)
+block_gram_reduce_kernel(const f32x4 *__restrict__ partial, int n, double inv_groups, double *__restrict__ Sigma) {
+  using P = GramPart<NT, PART>;
+  constexpr GramTiles<NT> tiles;
   constexpr int G = 16 * NT;
-  float *partial = static_cast<float *>(workspace);
-  double *slices = reinterpret_cast<double *>(static_cast<char *>(workspace) + (size_t)GRAM_MAX_WG * G * G * sizeof(float));
-  const int64_t ntrip = (TG + GRAM_GROUPS_PER_TRIP - 1) / GRAM_GROUPS_PER_TRIP;
-  const int n_wg = (int)(ntrip < GRAM_MAX_WG ? ntrip : GRAM_MAX_WG);
-  const size_t lds_bytes = 2 * (size_t)GRAM_GROUPS_PER_TRIP * G * 64;
-  hipLaunchKernelGGL((block_gram_kernel<NT>), dim3(n_wg), dim3(64 * ((NT + 1) / 2)), lds_bytes, stream,
-                     reinterpret_cast<const uint4 *>(x), TG, position, partial);
+  __shared__ double part[16][16][4];
+  __shared__ double sum[16][4];
+  const int t = threadIdx.x, quad = t & 15, slice = t >> 4;
+  const size_t stride = (size_t)gridDim.y * (P::COUNT * 64);
+  const f32x4 *src = partial + (size_t)blockIdx.y * (P::COUNT * 64) + blockIdx.x * 16 + quad;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  int p = slice;
+  for (; p + 7 * 16 < n; p += 8 * 16) {             // eight loads in flight, added in order
+    f32x4 q[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) q[u] = src[(size_t)(p + 16 * u) * stride];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[e] += (double)q[u][e];
+  }
+  for (; p < n; p += 16) {
+    const f32x4 q = src[(size_t)p * stride];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[e] += (double)q[e];
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) part[slice][quad][e] = s[e];
+  __syncthreads();
+  // the workgroup's quads are 16 lanes of one tile: rows 4 q .. 4 q + 3, columns 0 .. 15
+  const int tile = P::T0 + blockIdx.x / 4, row0 = 4 * (blockIdx.x & 3);
+  const int r = tiles.r[tile] * 16 + row0, c = tiles.c[tile] * 16;
+  double *const out = Sigma + (size_t)blockIdx.y * (G * G);
+  if (t < 64) {
+    const int e = t >> 4;
+    double total = 0.0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) total += part[i][quad][e];
+    total *= inv_groups;
+    sum[quad][e] = total;
+    out[(size_t)(r + e) * G + c + quad] = total;
+  }
+  __syncthreads();
+  if (t < 64 && tiles.r[tile] != tiles.c[tile]) out[(size_t)(c + (t >> 2)) * G + r + (t & 3)] = sum[t >> 2][t & 3];
+}
+
+// the slices' partial tiles of all 32 positions (Sigma's one set per workgroup is smaller)
+size_t block_gram_workspace_bytes(int G) {
+  const size_t nt = (size_t)(G / 16), tiles = nt * (nt + 1) / 2, parts = (size_t)gram_parts(G / 16);
+  const size_t most = (tiles + parts - 1) / parts;
+  return (size_t)GRAM_MAX_SLICES * 32 * most * 1024;
+}
+
+template <int NT, int PART>
+static hipError_t launch_part(const void *x, int64_t TG, bool positions, double *Sigma, void *workspace, hipStream_t stream) {
+  using P = GramPart<NT, PART>;
+  const uint4 *xp = static_cast<const uint4 *>(x);
+  f32x4 *partial = static_cast<f32x4 *>(workspace);
+  int n, n_pos = 1;
+  auto raise = [](auto kern, size_t bytes) {        // the dynamic LDS limit, once per process and kernel
+    return bytes <= 64 * 1024 ? hipSuccess
+                              : hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  };
+  if (positions) {
+    constexpr int KST = NT < 8 ? 8 / NT : 1;
+    constexpr size_t stage = (size_t)8 * 4 * KST * 16 * NT * 16, lds = 2 * stage <= 128 * 1024 ? 2 * stage : stage;
+    const int64_t stages = (TG + 32 * KST - 1) / (32 * KST);
+    n = stages >= GRAM_MAX_SLICES ? GRAM_MAX_SLICES : (int)((stages + 7) / 8 * 8);   // a multiple of the XCDs
+    n_pos = 32;
+    static const hipError_t raised = raise(block_gram_positions_kernel<NT, PART>, lds);
+    if (raised != hipSuccess) return raised;
+    hipLaunchKernelGGL((block_gram_positions_kernel<NT, PART>), dim3(4 * n), dim3(64 * GRAM_WAVES), lds, stream, xp, TG, n, partial);
+  } else {
+    constexpr int U = NT < 8 ? 8 / NT : 1;
+    constexpr size_t lds = (size_t)GRAM_WAVES / 2 * P::COUNT * 1024;
+    // two steps for every wave before another workgroup pays for its partial result
+    const int64_t want = ((TG + U - 1) / U + 2 * GRAM_WAVES - 1) / (2 * GRAM_WAVES);
+    n = (int)(want < GRAM_MAX_WG ? want : GRAM_MAX_WG);
+    static const hipError_t raised = raise(block_gram_kernel<NT, PART>, lds);
+    if (raised != hipSuccess) return raised;
+    hipLaunchKernelGGL((block_gram_kernel<NT, PART>), dim3(n), dim3(64 * GRAM_WAVES), lds, stream, xp, TG, partial);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(block_gram_reduce1_kernel, dim3((G * G + 255) / 256, GRAM_SLICES), dim3(256), 0, stream, partial,
-                     n_wg, G * G, slices);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(block_gram_reduce2_kernel, dim3((G * G + 255) / 256), dim3(256), 0, stream, slices, G * G,
+  hipLaunchKernelGGL((block_gram_reduce_kernel<NT, PART>), dim3(P::COUNT * 4, n_pos), dim3(256), 0, stream, partial, n,
                      1.0 / (double)TG, Sigma);
   return hipGetLastError();
 }
 
+template <int NT, int PART = 0>
+static hipError_t launch_nt(const void *x, int64_t TG, bool positions, double *Sigma, void *workspace, hipStream_t stream) {
+  // the parts reuse the workspace in stream order
+  const hipError_t e = launch_part<NT, PART>(x, TG, positions, Sigma, workspace, stream);
+  if constexpr (PART + 1 < GramPart<NT, 0>::PARTS)
+    return e != hipSuccess ? e : launch_nt<NT, PART + 1>(x, TG, positions, Sigma, workspace, stream);
+  else
+    return e;
+}
+
 // G a multiple of 16 in [16, 256], TG > 0 token-groups, workspace of block_gram_workspace_bytes(G)
-// position: -1 for Sigma, 0 .. 31 for the per-position matrix Sigma_k (every other element of a block
-// counts as zero)
-hipError_t launch_block_gram(const void *x_bf16, int64_t TG, int G, int position, double *Sigma, void *workspace,
+// positions: the 32 matrices Sigma_k instead of Sigma
+hipError_t launch_block_gram(const void *x_bf16, int64_t TG, int G, bool positions, double *Sigma, void *workspace,
                              hipStream_t stream) {
   switch (G / 16) {
 #define TORQ_GRAM_CASE(NT_) \
-  case NT_: return launch_nt<NT_>(x_bf16, TG, position, Sigma, workspace, stream);
+  case NT_: return launch_nt<NT_>(x_bf16, TG, positions, Sigma, workspace, stream);
     TORQ_GRAM_CASE(1) TORQ_GRAM_CASE(2) TORQ_GRAM_CASE(3) TORQ_GRAM_CASE(4)
     TORQ_GRAM_CASE(5) TORQ_GRAM_CASE(6) TORQ_GRAM_CASE(7) TORQ_GRAM_CASE(8)
     TORQ_GRAM_CASE(9) TORQ_GRAM_CASE(10) TORQ_GRAM_CASE(11) TORQ_GRAM_CASE(12)

@@ -630,6 +630,22 @@ def test_block_gram_positions_against_oracle(tq, oracle, M, d, G):
     assert np.array_equal(_np(tq.torq_block_gram_positions(xd, G)), got)          # deterministic
 
 
+@pytest.mark.parametrize("TG,G", [(n, G) for G in range(16, 257, 16) for n in (1, 33)]
+                         + [(2200, 128), (1100, 32), (4111, 16), (1057, 160), (1030, 256)])
+def test_block_gram_both_forms_at_the_edges_of_their_stages(tq, oracle, TG, G):
+    # every number of tiles (one to five launches), a single token-group, one past a stage of 32, and more
+    # stages than slices; fp32 chains of fewer than 128 additions of exact products, each rounding at most
+    # 2^-24 of sum |x x'| <= the largest diagonal entry
+    x = synth.activations(TG, 32 * G, seed=400 + G + TG)
+    want = oracle.block_gram_positions(synth.bf16_bits(x), G)
+    xd = x.to(DEV)
+    got, S = _np(tq.torq_block_gram_positions(xd, G)), _np(tq.torq_block_gram(xd, G))
+    bound = 128 * 2.0 ** -24
+    assert (np.abs(got - want).max(axis=(1, 2)) <= bound * np.abs(want).max(axis=(1, 2))).all()
+    assert np.abs(S - want.sum(axis=0)).max() <= bound * np.abs(want.sum(axis=0)).max()
+    assert np.array_equal(got, got.transpose(0, 2, 1)) and np.array_equal(S, S.T)
+
+
 def test_calibrated_rotation_equalizes_block_energies_on_the_gpu(tq, oracle):
     # Gram of a sample (GPU) -> Algorithm 1 (host) -> rotation handle -> rotate the sample (GPU):
     # the rotated sample's block energies are all tr(Sigma) / G (Theorem 4.1's equality condition)
