@@ -658,6 +658,17 @@ static double tiled_us(int tile, int s, bool deep, int64_t M, int64_t N, int d) 
 static double skinny_us(int64_t M, int64_t N, int d) {
   const double mt = (double)((M + 15) / 16), iters = (double)((d + 255) / 256);
   const double w_mb = (double)N * (double)d * 0.53125 / 1e6;
+  const int ns = mxfp4_gemm_skinny_strips(M, N, d);
+  const int64_t wgs = ((N + 15) / 16 + ns - 1) / ns;
+  if (M > 16 && (ns == 4 || (ns == 2 && wgs <= 256))) {
+    // two or four strips in a workgroup, one workgroup a CU and round: within 12 % of what [24 .. 64, 1024 .. 28672]
+    // x 4224 .. 28672 measured, weights from HBM
+    const double rounds = (double)((wgs + 255) / 256);
+    const double work = ns == 2 ? 2.45 + 0.2 * mt + iters * (0.16 + 0.0725 * mt)
+                                : rounds * (2.2 + 0.75 * mt + iters * (0.31 + 0.08 * mt));
+    const double read = 2.75 + 0.2104 * w_mb;
+    return work > read ? work : read;
+  }
   // beyond d = 16384 a workgroup no longer keeps its activation rows across strips: every further 16-row
   // activation tile costs up to 2.3 times more (d = 28672)
   const double f = d > 16384 ? 1.0 + 1.74 * (double)(d - 16384) / 16384.0 : 1.0;
@@ -697,9 +708,10 @@ static GemmPlan choose_plan(int64_t M, int64_t N, int d, bool allow_split) {
     }
   }
   if (can_skinny) {
-    // near a tie the streaming kernel wins: one launch, no tile padding
+    // near a tie the streaming kernel wins: one launch, no tile padding (not from 17 rows on with four strips a
+    // workgroup, where the tiles are full enough: [64, 14336] x 14336 40.3 us against 37.8)
     const double t = skinny_us(M, N, d);
-    if (0.95 * t <= plan.us) plan = GemmPlan{true, 0, 1, false, t};
+    if ((M > 16 && mxfp4_gemm_skinny_strips(M, N, d) == 4 ? 1.0 : 0.95) * t <= plan.us) plan = GemmPlan{true, 0, 1, false, t};
   }
   return plan;
 }

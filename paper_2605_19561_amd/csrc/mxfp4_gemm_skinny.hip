@@ -4,8 +4,8 @@
 //   out[m][n] = sum_kb 2^(A_s[m][kb] + W_s[n][kb] - 254) * sum_{k<32} val(A[m][32kb+k]) val(W[n][32kb+k])
 //
 // With so few rows the work is reading the weights once, so the layout of the job follows the
-// memory system, not the matrix cores: one workgroup per strip of 16 weight rows (or two strips),
-// so that N / 16 workgroups keep every CU streaming; its 8 waves split the k range between them;
+// memory system, not the matrix cores: one workgroup per strip of 16 weight rows (or two or four strips),
+// so that every CU streams; its 8 waves split the k range between them;
 // the codes go global -> registers directly in the operand layout of
 // v_mfma_scale_f32_16x16x128_f8f6f4 (lane = (row l % 16, microscaling block l / 16), 16 code
 // bytes), all loads of a trip in flight at once; the scale bytes of the strip and of the
@@ -19,6 +19,8 @@
 #include "rotate32_resident.h"
 #include "torq_device.h"
 #include "torq_internal.h"
+
+#include <atomic>
 
 namespace torq {
 
@@ -102,7 +104,7 @@ __device__ __forceinline__ void skinny_reduce_store(f32x4 (&acc)[NS][MT], unsign
 }
 
 // MT = number of 16-row activation tiles (M <= 16 MT); NS = 16-row weight strips per workgroup
-// (1 or 2; they share the activation loads); PT = line pairs per wave and trip.
+// (1, 2 or 4; they share the activation loads); PT = line pairs per wave and trip.
 // PERSIST: a workgroup takes the strip groups blockIdx.x, blockIdx.x + gridDim.x, ... and loads the
 // activations' codes (and scale bytes) ONCE, keeping the codes in registers across its groups; only
 // when one trip covers the k range (d / 256 <= PT * WAVES line pairs), where those registers are the
@@ -645,6 +647,25 @@ torq_linear_local_kernel(const uint4 *__restrict__ x, int TG, int G, const uint4
 #undef TORQ_LOAD_W
 }
 
+// raise a kernel's dynamic LDS limit once per process and device (the call is slow); `raised`: one bit a device
+static hipError_t raise_lds_limit(const void *kernel, std::atomic<uint64_t> &raised) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;
+  if (raised.load(std::memory_order_acquire) & bit) return hipSuccess;
+  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SKINNY_MAX_LDS);
+  if (e == hipSuccess) raised.fetch_or(bit, std::memory_order_release);
+  return e;
+}
+
+static size_t skinny_lds_bytes(int MT, int NS, int d) {
+  const int pd = d / 128 + 1;                      // padded dwords per scale row
+  const size_t scale_bytes = (size_t)((16 * NS * pd + 63) / 64 + (16 * MT * pd + 63) / 64) * 256;
+  const size_t red_bytes = (size_t)WAVES * NS * MT * 4 * 64 * sizeof(float);
+  return scale_bytes > red_bytes ? scale_bytes : red_bytes;
+}
+
 template <int MT, int NS, int PT>
 static hipError_t launch_cfg(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q, const uint8_t *W_s,
                              void *out, int64_t M, int64_t N, int d, hipStream_t stream, const DecodeArgs *fused) {
@@ -652,9 +673,8 @@ static hipError_t launch_cfg(const uint8_t *A_q, const uint8_t *A_s, const uint8
   if (groups > 0x7FFFFFF0) return hipErrorInvalidValue;
   const int pd = d / 128 + 1;                      // padded dwords per scale row
   const size_t scale_bytes = (size_t)((16 * NS * pd + 63) / 64 + (16 * MT * pd + 63) / 64) * 256;
-  const size_t red_bytes = (size_t)WAVES * NS * MT * 4 * 64 * sizeof(float);
-  size_t lds_bytes = scale_bytes > red_bytes ? scale_bytes : red_bytes;
-  if (fused) {
+  size_t lds_bytes = skinny_lds_bytes(MT, NS, d);
+  if constexpr (NS <= 2 && PT <= (MT + NS <= 3 ? 4 : 2)) if (fused) {
     // + the "ready" word behind the scales; at least the rotation's four token-group places
     lds_bytes = lds_bytes > scale_bytes + 16 ? lds_bytes : scale_bytes + 16;
     const size_t rot_bytes = 4 * (size_t)RotCfg<4>::TG_LDS_BYTES;
@@ -678,13 +698,13 @@ static hipError_t launch_cfg(const uint8_t *A_q, const uint8_t *A_s, const uint8
   // The persistent form (activation codes loaded once per workgroup and kept in registers): 8 - 16 rows,
   // one trip over the k range, and weights enough for the re-reads to cost more than the parallelism
   // given up (measured: [16, 8192] x 28672 34.2 -> 28.4 us, [8, 8192] x 28672 32.2 -> 27.4,
-  // [16, 8192] x 8192 10.7 -> 9.7, [16, 4096] x 14336 9.2 -> 9.0; below 24 MB of weights it loses).  Each
+  // [16, 4096] x 14336 9.2 -> 9.0; below 24 MB of weights it loses).  Each
   // workgroup takes `per` groups, the smallest power of two that leaves at most 256 workgroups (one per CU,
   // evenly loaded: 3 or 7 groups per workgroup measured 15 - 20 % slower than 4, and half as many
   // workgroups as CUs 30 % slower than one each).
   const int KP = (d / 128 + 1) / 2;
-  const size_t p_bytes = scale_bytes + red_bytes;
-  if (MT == 1 && M >= 8 && KP <= PT * WAVES && (double)N * (double)d * 0.53125 >= 24e6 && p_bytes <= 64 * 1024) {
+  const size_t p_bytes = scale_bytes + (size_t)WAVES * NS * MT * 4 * 64 * sizeof(float);
+  if constexpr (MT == 1) if (M >= 8 && KP <= PT * WAVES && (double)N * (double)d * 0.53125 >= 24e6 && p_bytes <= 64 * 1024) {
     int64_t per = 1;
     while ((groups + per - 1) / per > 256) per *= 2;
     if (per > 1) {
@@ -696,14 +716,9 @@ static hipError_t launch_cfg(const uint8_t *A_q, const uint8_t *A_s, const uint8
   }
   if (lds_bytes > SKINNY_MAX_LDS) return hipErrorInvalidValue;
   if (lds_bytes > 64 * 1024) {
-    // raise the dynamic LDS limit once per process and kernel variant (the call is slow)
-    static bool raised = false;
-    if (!raised) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(mxfp4_gemm_skinny_kernel<MT, NS, PT>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)SKINNY_MAX_LDS);
-      if (e != hipSuccess) return e;
-      raised = true;
-    }
+    static std::atomic<uint64_t> raised{0};
+    const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(mxfp4_gemm_skinny_kernel<MT, NS, PT>), raised);
+    if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((mxfp4_gemm_skinny_kernel<MT, NS, PT>), dim3((unsigned)groups), dim3(64 * WAVES), lds_bytes,
                      stream, A_q, A_s, W_q, W_s, reinterpret_cast<uint16_t *>(out), (int)M, N, d);
@@ -721,16 +736,65 @@ static hipError_t launch_mt_ns(const uint8_t *A_q, const uint8_t *A_s, const uin
   return launch_cfg<MT, NS, (MT + NS <= 3 ? 4 : 2)>(A_q, A_s, W_q, W_s, out, M, N, d, stream, fused);
 }
 
+// Strips per workgroup of the weight-streaming GEMM.  Every workgroup reads all activation rows from the L2,
+// which from 17 rows on is as many bytes as its weights or more, and a CU that gets a second workgroup
+// reads them a second time: the fewest strips that leave every CU at most one workgroup win, since a
+// strip more in a workgroup shares those reads and a workgroup more on a CU does not.
+// Up to 256 strips: one (x 4096, 24 - 64 rows: two measured 13 - 28 % slower).  Up to 512: two, from 8 rows
+// on, against one, us, weights from HBM: [64, 4096] x 4224 14.5 -> 9.6, [16, 8192] x 5120 11.4 -> 9.9,
+// [32, 8192] x 5120 17.1 -> 12.0, [64, 8192] x 8192 26.7 -> 18.5, [45, 5120] x 8192 14.3 -> 11.1,
+// [32, 25600] x 5120 46.4 -> 32.3, [48, 28672] x 8192 61.4 -> 45.5, [16, 28672] x 8192 34.7 -> 30.6.
+// Beyond, from 17 rows on: four (two workgroups a CU past 1024 strips), [32, 8192] x 8448 24.3 -> 18.1,
+// [64, 4096] x 12288 22.4 -> 14.8, [48, 5120] x 25600 40.5 -> 30.0.  At 17 - 32 rows the reads saved are fewer, and
+// the larger reduction of four strips or a nearly empty second round of them costs more: two from 768
+// strips on up to d = 4096 ([17, 4096] x 16384 10.2 against 10.8, [17, 1024] x 14336 5.0 against 5.4) and just
+// past 1024 strips, one below 768 strips and d = 2048 ([17, 1024] x 8448 4.7 against 5.1; [32, 3072] x 11264
+// gains, 11.4 -> 9.4).  8 - 16 rows beyond 512 strips: two from 768 strips on, mostly in the persistent form
+// (two against four, [16, 8192] x 28672 28.8 / 32.3); 1 - 7 rows re-read too little to gain.
+int mxfp4_gemm_skinny_strips(int64_t M, int64_t N, int d) {
+  const int MT = (int)((M + 15) / 16);
+  const int64_t strips = (N + 15) / 16;
+  int NS = 1;
+  if (M >= 8 && strips > 256 && strips <= 512) NS = 2;
+  else if (MT == 1) NS = M >= 8 && strips >= 2 * SKINNY_MIN_GROUPS ? 2 : 1;
+  else if (strips > 512) {
+    if (MT == 2 && strips >= 2 * SKINNY_MIN_GROUPS && (d <= 4096 || (strips > 1024 && strips <= 1280))) NS = 2;
+    else NS = MT == 2 && d < 2048 ? 1 : 4;
+  }
+  while (NS > 1 && skinny_lds_bytes(MT, NS, d) > SKINNY_MAX_LDS) NS /= 2;
+  return NS;
+}
+
 template <int MT>
 static hipError_t launch_mt(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q, const uint8_t *W_s,
                             void *out, int64_t M, int64_t N, int d, hipStream_t stream, const DecodeArgs *fused) {
-  // Two strips per workgroup share the activation loads.  That pays when the activations are
-  // real traffic (not a row or two) and there are still enough workgroups to keep every CU
-  // streaming; deeper sharing costs more in registers (fewer loads in flight) than it saves.
-  const int64_t strips = (N + 15) / 16;
-  if (MT <= 2 && M >= 8 && strips >= 2 * SKINNY_MIN_GROUPS)
-    return launch_mt_ns<MT, (MT <= 2 ? 2 : 1)>(A_q, A_s, W_q, W_s, out, M, N, d, stream, fused);
-  return launch_mt_ns<MT, 1>(A_q, A_s, W_q, W_s, out, M, N, d, stream, fused);
+  if (fused) {
+    // the decode form's consumers: two strips where there are workgroups enough
+    if (MT <= 2 && M >= 8 && (N + 15) / 16 >= 2 * SKINNY_MIN_GROUPS)
+      return launch_mt_ns<MT, (MT <= 2 ? 2 : 1)>(A_q, A_s, W_q, W_s, out, M, N, d, stream, fused);
+    return launch_mt_ns<MT, 1>(A_q, A_s, W_q, W_s, out, M, N, d, stream, fused);
+  }
+  const int NS = mxfp4_gemm_skinny_strips(M, N, d);
+  const int pairs_per_wave = ((d / 128 + 1) / 2 + WAVES - 1) / WAVES;
+  if constexpr (MT >= 2) {
+    // four strips: a deeper trip measured 1 - 8 % slower (64 accumulators and the weights leave no room)
+    if (NS == 4) return launch_cfg<MT, 4, 1>(A_q, A_s, W_q, W_s, out, M, N, d, stream, nullptr);
+  }
+  if (NS == 2) {
+    // one trip of four pairs where it covers the k range exactly (d about 8192: [45, 8192] x 8192 15.6 -> 14.5 us
+    // against two trips of two; at 64 rows 18.4 -> 20.3, its registers), else trips of two
+    if (pairs_per_wave <= 1) return launch_cfg<MT, 2, 1>(A_q, A_s, W_q, W_s, out, M, N, d, stream, nullptr);
+    if constexpr (MT <= 3) {
+      if (pairs_per_wave == 4) return launch_cfg<MT, 2, 4>(A_q, A_s, W_q, W_s, out, M, N, d, stream, nullptr);
+    }
+    if constexpr (MT == 1) {
+      // past 512 strips: the depth that lets the persistent form cover the k range
+      if (pairs_per_wave > 2 && (N + 15) / 16 > 512)
+        return launch_cfg<MT, 2, 4>(A_q, A_s, W_q, W_s, out, M, N, d, stream, nullptr);
+    }
+    return launch_cfg<MT, 2, 2>(A_q, A_s, W_q, W_s, out, M, N, d, stream, nullptr);
+  }
+  return launch_mt_ns<MT, 1>(A_q, A_s, W_q, W_s, out, M, N, d, stream, nullptr);
 }
 
 // Whether the scale rows of (up to two) strips and of the activations fit the LDS.

@@ -277,6 +277,19 @@ def test_gemm_random_codes(tq, oracle, M, N, d):
     _assert_every_output_within_one_ulp(_bits(got), want)
 
 
+# The weight-streaming kernel at the edges of its strips-per-workgroup rule: one, two and four 16-row strips, the first
+# and last strip count of each, 8, 16, 17 and 33 rows, ragged N and M, trips of one, two and four line pairs per wave.
+STRIP_EDGES = [(7, 4100, 512), (8, 4100, 512), (16, 4096, 640), (16, 8200, 640), (17, 4097, 1152), (33, 4100, 2176),
+               (45, 4112, 8192), (48, 8200, 640), (64, 8192, 384), (32, 8200, 2176), (17, 8200, 1920), (49, 9001, 1408),
+               (20, 12288, 256), (33, 16384, 640)]
+
+
+@pytest.mark.parametrize("M,N,d", STRIP_EDGES)
+def test_gemm_weight_streaming_strips(tq, oracle, M, N, d):
+    assert tq.mxfp4_gemm_plan(M, N, d)[0], "this shape is meant to take the weight-streaming kernel"
+    test_gemm_random_codes(tq, oracle, M, N, d)
+
+
 def _random_gemm_shapes(n, seed):
     rng = np.random.default_rng(seed)
     return [(int(rng.integers(1, 700)), int(rng.integers(1, 900)), 128 * int(rng.integers(1, 17))) for _ in range(n)]
