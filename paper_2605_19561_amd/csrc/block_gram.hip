@@ -314,9 +314,8 @@ static hipError_t launch_part(const void *x, int64_t TG, bool positions, double 
   const uint4 *xp = static_cast<const uint4 *>(x);
   f32x4 *partial = static_cast<f32x4 *>(workspace);
   int n, n_pos = 1;
-  auto raise = [](auto kern, size_t bytes) {        // the dynamic LDS limit, once per process and kernel
-    return bytes <= 64 * 1024 ? hipSuccess
-                              : hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  auto raise = [](auto kern, size_t bytes, std::atomic<uint64_t> &raised) {
+    return bytes <= 64 * 1024 ? hipSuccess : raise_lds_limit(reinterpret_cast<const void *>(kern), bytes, raised);
   };
   if (positions) {
     constexpr int KST = NT < 8 ? 8 / NT : 1;
@@ -324,8 +323,9 @@ static hipError_t launch_part(const void *x, int64_t TG, bool positions, double 
     const int64_t stages = (TG + 32 * KST - 1) / (32 * KST);
     n = stages >= GRAM_MAX_SLICES ? GRAM_MAX_SLICES : (int)((stages + 7) / 8 * 8);   // a multiple of the XCDs
     n_pos = 32;
-    static const hipError_t raised = raise(block_gram_positions_kernel<NT, PART>, lds);
-    if (raised != hipSuccess) return raised;
+    static std::atomic<uint64_t> raised{0};
+    const hipError_t e = raise(block_gram_positions_kernel<NT, PART>, lds, raised);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((block_gram_positions_kernel<NT, PART>), dim3(4 * n), dim3(64 * GRAM_WAVES), lds, stream, xp, TG, n, partial);
   } else {
     constexpr int U = NT < 8 ? 8 / NT : 1;
@@ -333,8 +333,9 @@ static hipError_t launch_part(const void *x, int64_t TG, bool positions, double 
     // two steps for every wave before another workgroup pays for its partial result
     const int64_t want = ((TG + U - 1) / U + 2 * GRAM_WAVES - 1) / (2 * GRAM_WAVES);
     n = (int)(want < GRAM_MAX_WG ? want : GRAM_MAX_WG);
-    static const hipError_t raised = raise(block_gram_kernel<NT, PART>, lds);
-    if (raised != hipSuccess) return raised;
+    static std::atomic<uint64_t> raised{0};
+    const hipError_t e = raise(block_gram_kernel<NT, PART>, lds, raised);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL((block_gram_kernel<NT, PART>), dim3(n), dim3(64 * GRAM_WAVES), lds, stream, xp, TG, partial);
   }
   hipError_t e = hipGetLastError();

@@ -559,14 +559,9 @@ static hipError_t launch_tile(const uint8_t *A_q, const uint8_t *A_s, const uint
     if ((tiles_m * tiles_n) % 8 == 0 && grid >= 8) grid -= grid % 8;
   }
   if (lds_bytes > 64 * 1024) {
-    // raise the dynamic LDS limit once per process and kernel variant (the call is slow)
-    static bool raised = false;
-    if (!raised) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-      if (e != hipSuccess) return e;
-      raised = true;
-    }
+    static std::atomic<uint64_t> raised{0};
+    const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(kern), lds_bytes, raised);
+    if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)grid, SPLIT ? splits : 1), dim3(256), lds_bytes, stream, A_q,
                      A_s, W_q, W_s, reinterpret_cast<uint16_t *>(out), partial, M, N, d, (int)tiles_m, (int)tiles_n, ldc);

@@ -20,8 +20,6 @@
 #include "torq_device.h"
 #include "torq_internal.h"
 
-#include <atomic>
-
 namespace torq {
 
 namespace {
@@ -647,18 +645,6 @@ torq_linear_local_kernel(const uint4 *__restrict__ x, int TG, int G, const uint4
 #undef TORQ_LOAD_W
 }
 
-// raise a kernel's dynamic LDS limit once per process and device (the call is slow); `raised`: one bit a device
-static hipError_t raise_lds_limit(const void *kernel, std::atomic<uint64_t> &raised) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;
-  if (raised.load(std::memory_order_acquire) & bit) return hipSuccess;
-  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SKINNY_MAX_LDS);
-  if (e == hipSuccess) raised.fetch_or(bit, std::memory_order_release);
-  return e;
-}
-
 static size_t skinny_lds_bytes(int MT, int NS, int d) {
   const int pd = d / 128 + 1;                      // padded dwords per scale row
   const size_t scale_bytes = (size_t)((16 * NS * pd + 63) / 64 + (16 * MT * pd + 63) / 64) * 256;
@@ -681,13 +667,10 @@ static hipError_t launch_cfg(const uint8_t *A_q, const uint8_t *A_s, const uint8
     lds_bytes = lds_bytes > rot_bytes ? lds_bytes : rot_bytes;
     if (lds_bytes > SKINNY_MAX_LDS) return hipErrorInvalidValue;
     if (lds_bytes > 64 * 1024) {
-      static bool raised_fused = false;
-      if (!raised_fused) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(torq_linear_decode_kernel<MT, NS, PT>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)SKINNY_MAX_LDS);
-        if (e != hipSuccess) return e;
-        raised_fused = true;
-      }
+      static std::atomic<uint64_t> raised{0};
+      const hipError_t e =
+          raise_lds_limit(reinterpret_cast<const void *>(torq_linear_decode_kernel<MT, NS, PT>), SKINNY_MAX_LDS, raised);
+      if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((torq_linear_decode_kernel<MT, NS, PT>), dim3((unsigned)(groups + fused->P)), dim3(64 * WAVES),
                        lds_bytes, stream, fused->x, fused->TG, fused->inter_hi, fused->inter_lo, fused->intra_hi_frag,
@@ -717,7 +700,8 @@ static hipError_t launch_cfg(const uint8_t *A_q, const uint8_t *A_s, const uint8
   if (lds_bytes > SKINNY_MAX_LDS) return hipErrorInvalidValue;
   if (lds_bytes > 64 * 1024) {
     static std::atomic<uint64_t> raised{0};
-    const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(mxfp4_gemm_skinny_kernel<MT, NS, PT>), raised);
+    const hipError_t e =
+        raise_lds_limit(reinterpret_cast<const void *>(mxfp4_gemm_skinny_kernel<MT, NS, PT>), SKINNY_MAX_LDS, raised);
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((mxfp4_gemm_skinny_kernel<MT, NS, PT>), dim3((unsigned)groups), dim3(64 * WAVES), lds_bytes,

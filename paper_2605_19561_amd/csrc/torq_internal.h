@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "../../include/torq.h"
 
 struct torq_rotation {
@@ -32,6 +34,20 @@ constexpr int DECODE_CTR_WORDS = 32 * 131;
 constexpr int DECODE_ERR = 32 * 130;      // the sticky "a workgroup gave up" word among them
 
 namespace torq {
+
+// Raises a kernel's dynamic LDS limit to `bytes`, once for each device it is launched on (the limit belongs to
+// the function on one device, and the call is slow).  `raised`: the caller's, one per kernel, a bit a device;
+// a failed call leaves the bit clear, so the next launch tries again.
+inline hipError_t raise_lds_limit(const void *kernel, size_t bytes, std::atomic<uint64_t> &raised) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;
+  if (raised.load(std::memory_order_acquire) & bit) return hipSuccess;
+  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e == hipSuccess) raised.fetch_or(bit, std::memory_order_release);
+  return e;
+}
 
 // fp32 rows -> a 4-bit block format (FMT_* of torq_device.h = TORQ_FMT_* of torq.h).  nblk = number
 // of 32-element blocks (M * d / 32); global_scale is NVFP4's tensor-wide scale, else ignored.

@@ -1,0 +1,128 @@
+"""What the library asks of the HIP runtime, recorded on the CPU: a stand-in for the runtime's entry points takes the
+launches (function, grid, dynamic LDS, current device) and the calls that raise a function's LDS limit.  Nothing is
+dereferenced on the way to a launch, so the device addresses are made up."""
+import ctypes as C
+import json
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+from paper_2605_19561_amd import build
+
+STUB = r"""
+#include <hip/hip_runtime.h>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+static int device = 0;
+static FILE *events = nullptr;
+static thread_local struct { dim3 g, b; size_t lds; hipStream_t s; } config;
+extern "C" {
+void stub_open(const char *path) { events = fopen(path, "w"); }
+void stub_close() { fclose(events); }
+void stub_device(int d) { device = d; }
+hipError_t hipGetDevice(int *d) { *d = device; return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int) {
+  memset(p, 0, sizeof *p);
+  strcpy(p->gcnArchName, "gfx950");
+  return hipSuccess;
+}
+hipError_t hipMalloc(void **p, size_t n) { return posix_memalign(p, 256, n) ? hipErrorOutOfMemory : hipSuccess; }
+hipError_t hipFree(void *p) { free(p); return hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void *f, hipFuncAttribute, int v) {
+  fprintf(events, "{\"raise\": %zu, \"bytes\": %d, \"device\": %d}\n", (size_t)f, v, device);
+  return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *f, dim3 g, dim3, void **, size_t lds, hipStream_t) {
+  fprintf(events, "{\"launch\": %zu, \"grid\": [%u, %u], \"lds\": %zu, \"device\": %d}\n", (size_t)f, g.x, g.y, lds, device);
+  return hipSuccess;
+}
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t lds, hipStream_t s) { config = {g, b, lds, s}; return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *lds, hipStream_t *s) {
+  *g = config.g; *b = config.b; *lds = config.lds; *s = config.s;
+  return hipSuccess;
+}
+}
+"""
+
+# the child loads the stand-in globally before the library, so that the library's calls bind to it
+CHILD = """
+import ctypes as C, sys
+stub = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+L = C.CDLL(sys.argv[2])
+stub.stub_open(sys.argv[3].encode())
+vp, i64, sz = C.c_void_p, C.c_int64, C.c_size_t
+for name in ("torq_block_gram_workspace_bytes", "torq_linear_workspace_bytes_n", "mxfp4_gemm_workspace_bytes"):
+    getattr(L, name).restype = sz
+P, BIG = vp(1 << 20), sz(1 << 40)
+def gram(fn, M, d, G, ws=BIG):
+    return fn(P, i64(M), d, G, P, P, ws, None)
+def gemm(M, N, d):
+    return L.mxfp4_gemm_ws(P, P, P, P, P, i64(M), i64(N), d, P, BIG, None)
+def on(device):
+    stub.stub_device(device)
+"""
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("stub")
+    src, lib = str(tmp / "stub.cpp"), str(tmp / "libstub.so")
+    open(src, "w").write(STUB)
+    subprocess.run(["g++", "-shared", "-fPIC", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", src, "-o", lib], check=True)
+    return lib
+
+
+@pytest.fixture
+def record(stub, tmp_path):
+    def run(body):
+        if not os.path.exists(build.LIB):
+            build.build()
+        events = str(tmp_path / "events")
+        code = CHILD + textwrap.dedent(body) + "\nstub.stub_close()\n"
+        subprocess.run([sys.executable, "-c", code, stub, build.LIB, events], check=True, timeout=120)
+        return [json.loads(line) for line in open(events)]
+    return run
+
+
+LDS_CALLS = {
+    "gram": "assert gram(L.torq_block_gram, 65536, 4096, 128) == 0",
+    "positions": "assert gram(L.torq_block_gram_positions, 4096, 4096, 128) == 0",
+    "tiled": "assert gemm(2048, 14336, 4096) == 0",
+    "streaming": "assert gemm(33, 15616, 15872) == 0",
+    "one_launch": """
+        import array
+        G, d = 128, 28672
+        I = array.array("f", [0.0]) * (G * G)
+        for i in range(G): I[i * G + i] = 1.0
+        J = array.array("f", [0.0]) * 1024
+        for i in range(32): J[i * 33] = 1.0
+        adr = lambda a: vp(a.buffer_info()[0])
+        r = vp()
+        assert L.torq_rotation_create(C.byref(r), d, G, adr(I), adr(J)) == 0
+        assert L.torq_linear_single_launch_probe(r, P, P, P, P, i64(64), i64(4096), P, BIG, 1, 0, None) == 0
+        """,
+}
+
+
+@pytest.mark.parametrize("name", sorted(LDS_CALLS))
+def test_lds_limit_is_raised_on_every_device(record, name):
+    # 64 KB is what a launch may ask for without; the limit belongs to a function on ONE device
+    call = textwrap.dedent(LDS_CALLS[name])
+    events = record("for device in (0, 1, 0):\n    on(device)\n" + textwrap.indent(call, "    "))
+    limit, checked = {}, 0
+    for e in events:
+        if "raise" in e:
+            limit[e["raise"], e["device"]] = e["bytes"]
+        elif e["lds"] > 64 * 1024:
+            checked += 1
+            assert limit.get((e["launch"], e["device"]), 0) >= e["lds"], e
+    assert checked >= 3, "this call is meant to need more than 64 KB of LDS"
+    assert len([e for e in events if "raise" in e]) == len(limit), "once for each function and device"
