@@ -277,8 +277,9 @@ int torq_linear_single_launch_probe(const torq_rotation_t *r, const void *x_bf16
  *   Sigma_pos[k][b][b'] = mean over token-groups of X[b][k] X[b'][k],   k < 32,
  * whose sum over k is Sigma.  Arguments as torq_block_gram, with
  *   Sigma_pos  device, 32*G*G doubles, [k][b][b'], overwritten
- * One pass over x for all positions.  Each matrix can be handed to torq_equalize_inter; the online
- * path of Algorithm 3 applies ONE R_inter to all positions, so a per-position rotation is not something torq_rotation_create takes.
+ * One pass over x for all positions (several for G > 128).  Each matrix can be handed to
+ * torq_equalize_inter; the online path of Algorithm 3 applies ONE R_inter to all positions, so a
+ * per-position rotation is not something torq_rotation_create takes.
  *
  * torq_equalize_inter: Algorithm 1 on the HOST, in double.  Plane rotations of the pair (block
  * furthest above the mean energy c = tr(Sigma)/G, block furthest below it) until every diagonal

@@ -11,12 +11,13 @@
 // 16 x 16 tiles (r, c) with r <= c are computed; the reduce kernel writes both triangles.
 //
 // Sigma: the contraction index is the position inside a block (K = 32 = one instruction), the operand
-//   of tile row r is 16 block rows x 64 bytes = 1 KiB of consecutive input.
+//   of tile row r is 16 block rows x 64 bytes = 1 KiB of consecutive input.  Two forms, both one pass
+//   over the input: waves that work alone, and waves that share each token-group through LDS.
 // Sigma_k: the contraction index is the token-group; the workgroup transposes its input on the way
-//   into LDS (below).
+//   into LDS (below).  Up to 36 tiles (G <= 128) are one wave's accumulators; larger G runs as several
+//   launches, each with its share of the tiles.
 //
-// Up to 36 tiles (G <= 128) are one wave's accumulators; larger G runs as several launches, each with
-// its share of the tiles.  Partial sums: packed tiles, [tile][lane][4 floats] as the accumulators hold them.
+// Partial sums: packed tiles, [tile][lane][4 floats] as the accumulators hold them.
 #include "torq_device.h"
 #include "torq_internal.h"
 
@@ -24,7 +25,9 @@ namespace torq {
 
 typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
 
-constexpr int GRAM_MAX_WG = 256;      // one workgroup per CU
+constexpr int GRAM_MAX_WG = 256;      // Sigma, waves alone: one workgroup per CU
+constexpr int GRAM_SHARED_WG = 512;   // Sigma, shared token-groups: two workgroups per CU
+constexpr int GRAM_SHARED_U = 2;      // ... and token-groups per trip
 constexpr int GRAM_WAVES = 8;
 constexpr int GRAM_MAX_SLICES = 32;   // Sigma_k: pieces of the token-groups that run side by side
 constexpr int GRAM_MAX_TILES = 36;    // per wave: 144 accumulator registers
@@ -59,24 +62,29 @@ struct GramPart {
   static constexpr int ROW0 = GramTiles<NT>().r[T0];   // tile rows below this one are not needed
 };
 
+// tile number i of the triangle -> its row; i becomes its place in that row (column - row)
+__device__ __forceinline__ int gram_tile_row(int nt, int &i) {
+  int r = 0;
+  while (i >= nt - r) i -= nt - r++;
+  return r;
+}
+
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t gram_rsrc(const void *p, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
 }
 
-// Sigma.  Bound: HBM, 2 bytes per element, read once.  Every wave takes token-groups of its own (U at a
+// Sigma, G <= 128.  Bound: HBM, 2 bytes per element, read once.  Every wave takes token-groups of its own (U at a
 // time, about 8 KiB), straight from memory into the operand registers: nothing is staged or shared, there
 // is no barrier in the loop, and two steps are in flight beyond the one being multiplied (128 KiB per CU).
 // A token-group past the end reads as zeros through the buffer's range check and adds nothing.  The
 // workgroup's waves add their tiles through LDS at the end: 256 partial results instead of the 512 of a
 // form that shared each token-group through LDS, and packed triangles instead of squares.  X [16384, 8192],
 // G = 128: this kernel 64 -> 51 us (5.2 TB/s, the rate of a copy), the reduction 14 us in two launches -> 4.7.
-template <int NT, int PART>
+template <int NT>
 __global__ void __launch_bounds__(64 * GRAM_WAVES)
 block_gram_kernel(const uint4 *__restrict__ x, int64_t TG, f32x4 *__restrict__ partial) {
-  using P = GramPart<NT, PART>;
   constexpr GramTiles<NT> tiles;
-  constexpr int G = 16 * NT, NF = NT - P::ROW0, U = NT < 8 ? 8 / NT : 1;
-  constexpr int SETS = NF <= 9 ? 3 : 2;             // (two where the registers do not hold three)
+  constexpr int G = 16 * NT, COUNT = GramTiles<NT>::N, U = NT < 8 ? 8 / NT : 1;
   extern __shared__ __attribute__((aligned(16))) char lds[];
 
   const int lane = threadIdx.x & 63;
@@ -87,51 +95,41 @@ block_gram_kernel(const uint4 *__restrict__ x, int64_t TG, f32x4 *__restrict__ p
   const int64_t per = (steps + gridDim.x - 1) / gridDim.x;
   const int64_t s_end = (int64_t)(blockIdx.x + 1) * per < steps ? (int64_t)(blockIdx.x + 1) * per : steps;
 
-  f32x4 acc[P::COUNT];
+  f32x4 acc[COUNT];
 #pragma unroll
-  for (int i = 0; i < P::COUNT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < COUNT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  auto load = [&](u32x4 (&v)[U][NF], int64_t s) {
+  auto load = [&](u32x4 (&v)[U][NT], int64_t s) {
     const int64_t left = s < s_end ? TG - s * U : 0;
     const __amdgpu_buffer_rsrc_t rsrc =
         gram_rsrc(x + (left > 0 ? s * U : 0) * (4 * G), (uint32_t)(left < U ? left : U) * (G * 64));
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int f = 0; f < NF; ++f)
-        v[u][f] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, u * (G * 64) + (P::ROW0 + f) * 1024, 0);
+      for (int f = 0; f < NT; ++f)
+        v[u][f] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, u * (G * 64) + f * 1024, 0);
   };
-  auto multiply = [&](const u32x4 (&v)[U][NF]) {
+  auto multiply = [&](const u32x4 (&v)[U][NT]) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int i = 0; i < P::COUNT; ++i)
+      for (int i = 0; i < COUNT; ++i)
         acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-            __builtin_bit_cast(bf16x8, v[u][tiles.r[P::T0 + i] - P::ROW0]),
-            __builtin_bit_cast(bf16x8, v[u][tiles.c[P::T0 + i] - P::ROW0]), acc[i], 0, 0, 0);
+            __builtin_bit_cast(bf16x8, v[u][tiles.r[i]]),
+            __builtin_bit_cast(bf16x8, v[u][tiles.c[i]]), acc[i], 0, 0, 0);
   };
 
-  u32x4 v[SETS][U][NF];
+  u32x4 v[3][U][NT];
   int64_t s = (int64_t)blockIdx.x * per + wave;
-  if constexpr (SETS == 3) {
-    load(v[0], s);
-    load(v[1], s + GRAM_WAVES);
-    for (; s < s_end; s += 3 * GRAM_WAVES) {
-      load(v[2], s + 2 * GRAM_WAVES);
-      multiply(v[0]);
-      load(v[0], s + 3 * GRAM_WAVES);
-      multiply(v[1]);
-      load(v[1], s + 4 * GRAM_WAVES);
-      multiply(v[2]);
-    }
-  } else {
-    load(v[0], s);
-    for (; s < s_end; s += 2 * GRAM_WAVES) {
-      load(v[1], s + GRAM_WAVES);
-      multiply(v[0]);
-      load(v[0], s + 2 * GRAM_WAVES);
-      multiply(v[1]);
-    }
+  load(v[0], s);
+  load(v[1], s + GRAM_WAVES);
+  for (; s < s_end; s += 3 * GRAM_WAVES) {
+    load(v[2], s + 2 * GRAM_WAVES);
+    multiply(v[0]);
+    load(v[0], s + 3 * GRAM_WAVES);
+    multiply(v[1]);
+    load(v[1], s + 4 * GRAM_WAVES);
+    multiply(v[2]);
   }
 
   // the upper half of the waves hand their tiles to the lower half, until one wave holds the sum
@@ -140,18 +138,110 @@ block_gram_kernel(const uint4 *__restrict__ x, int64_t TG, f32x4 *__restrict__ p
   for (int half = GRAM_WAVES / 2; half >= 1; half /= 2) {
     if (wave >= half && wave < 2 * half) {
 #pragma unroll
-      for (int i = 0; i < P::COUNT; ++i) box[((wave - half) * P::COUNT + i) * 64 + lane] = acc[i];
+      for (int i = 0; i < COUNT; ++i) box[((wave - half) * COUNT + i) * 64 + lane] = acc[i];
     }
     __syncthreads();
     if (wave < half) {
 #pragma unroll
-      for (int i = 0; i < P::COUNT; ++i) acc[i] += box[(wave * P::COUNT + i) * 64 + lane];
+      for (int i = 0; i < COUNT; ++i) acc[i] += box[(wave * COUNT + i) * 64 + lane];
     }
     __syncthreads();
   }
   if (wave == 0) {
 #pragma unroll
-    for (int i = 0; i < P::COUNT; ++i) partial[((size_t)blockIdx.x * P::COUNT + i) * 64 + lane] = acc[i];
+    for (int i = 0; i < COUNT; ++i) partial[((size_t)blockIdx.x * COUNT + i) * 64 + lane] = acc[i];
+  }
+}
+
+// Sigma for larger G: one wave's registers do not hold the tiles, and splitting them over launches reads the
+// input once for each (two launches at G = 144 to five at 256).  So the workgroup shares each token-group
+// through LDS: wave w owns the block rows 32 w .. 32 w + 31 (two tile rows) against all NT columns, trips of two
+// token-groups go global -> registers -> LDS with two stages and one barrier a trip.  Workgroups are
+// persistent, two per CU; only the tiles of the triangle are written.  Bound: HBM, read once.  X [16384, 8192],
+// G = 256, with the reduction: 98 us against 208 in five launches; G = 160 (X [16384, 5120]): 44 against 65.
+template <int NT>
+__global__ void __launch_bounds__(64 * ((NT + 1) / 2))
+block_gram_shared_kernel(const uint4 *__restrict__ x, int64_t TG, f32x4 *__restrict__ partial) {
+  constexpr int G = 16 * NT, NTHR = 64 * ((NT + 1) / 2), U = GRAM_SHARED_U;
+  constexpr int CHUNKS = 4 * G;                          // 16-byte chunks of one token-group
+  constexpr int CH = (CHUNKS + NTHR - 1) / NTHR;         // chunks per thread per token-group (2)
+  constexpr int TG_BYTES = G * 64, STAGE_BYTES = U * TG_BYTES;
+  __shared__ __attribute__((aligned(16))) char lds[2 * STAGE_BYTES];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m = lane & 15, q = lane >> 4;
+  const int rt0 = 2 * wave, rt1 = 2 * wave + 1;          // this wave's tile rows; rt1 may not exist
+  const bool has1 = rt1 < NT;
+
+  f32x4 acc0[NT], acc1[NT];
+#pragma unroll
+  for (int ct = 0; ct < NT; ++ct) acc0[ct] = acc1[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // chunk c of a token-group = (block row c / 4, elements 8 (c % 4) .. + 7).  In LDS the chunk index inside a
+  // 64-byte row is XORed with (row >> 2) & 3, so that the 16 lanes that read one operand (16 consecutive rows,
+  // same chunk) hit 16 different bank groups; for a tile's rows 16 t + m that term is (m >> 2) & 3
+  const int frag_off = m * 64 + ((q ^ ((m >> 2) & 3)) * 16);
+  int st_off[CH];
+#pragma unroll
+  for (int i = 0; i < CH; ++i) {
+    const int c = tid + i * NTHR, r = c >> 2;
+    st_off[i] = r * 64 + (((c & 3) ^ ((r >> 2) & 3)) * 16);
+  }
+
+  const int64_t ntrip = (TG + U - 1) / U;                // dealt to the workgroups round robin
+  uint4 regs[U][CH];
+  auto load_trip = [&](int64_t trip) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < CH; ++i) {
+        const int c = tid + i * NTHR;
+        regs[u][i] = (trip * U + u < TG && c < CHUNKS) ? x[(trip * U + u) * CHUNKS + c] : make_uint4(0, 0, 0, 0);
+      }
+  };
+  auto store_trip = [&](int stage) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < CH; ++i)
+        if (tid + i * NTHR < CHUNKS)
+          *reinterpret_cast<uint4 *>(lds + stage * STAGE_BYTES + u * TG_BYTES + st_off[i]) = regs[u][i];
+  };
+
+  int64_t trip = blockIdx.x;
+  if (trip < ntrip) {
+    load_trip(trip);
+    store_trip(0);
+  }
+  __syncthreads();
+  int stage = 0;
+  for (; trip < ntrip; trip += gridDim.x, stage ^= 1) {
+    const int64_t next = trip + gridDim.x;
+    const bool have_next = next < ntrip;
+    if (have_next) load_trip(next);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const char *g = lds + stage * STAGE_BYTES + u * TG_BYTES + frag_off;
+      const bf16x8 a0 = *reinterpret_cast<const bf16x8 *>(g + rt0 * 1024);
+      const bf16x8 a1 = *reinterpret_cast<const bf16x8 *>(g + (has1 ? rt1 : rt0) * 1024);
+#pragma unroll
+      for (int ct = 0; ct < NT; ++ct) {
+        const bf16x8 col = *reinterpret_cast<const bf16x8 *>(g + ct * 1024);
+        acc0[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, col, acc0[ct], 0, 0, 0);
+        acc1[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, col, acc1[ct], 0, 0, 0);
+      }
+    }
+    if (have_next) store_trip(stage ^ 1);
+    __syncthreads();
+  }
+
+  f32x4 *const out = partial + (size_t)blockIdx.x * (GramTiles<NT>::N * 64) + lane;
+  const int row0 = rt0 * NT - rt0 * (rt0 - 1) / 2 - rt0, row1 = rt1 * NT - rt1 * (rt1 - 1) / 2 - rt1;
+#pragma unroll
+  for (int ct = 0; ct < NT; ++ct) {
+    if (ct >= rt0) out[(row0 + ct) * 64] = acc0[ct];
+    if (has1 && ct >= rt1) out[(row1 + ct) * 64] = acc1[ct];
   }
 }
 
@@ -253,18 +343,16 @@ block_gram_positions_kernel(const uint4 *__restrict__ x, int64_t TG, int slices,
 // Adds n partial results in double and in a fixed order, divides by the number of token-groups and writes
 // both triangles.  A workgroup adds 16 accumulator quads: thread (slice = t / 16, quad = t % 16) every
 // sixteenth partial, then the 16 slices meet in LDS.  blockIdx.y: the position (1 or 32 of them); a partial
-// result holds gridDim.y * tiles * 64 quads.
-template <int NT, int PART>
+// result holds gridDim.y * tiles * 64 quads, of the tiles from t0 on.
 __global__ void __launch_bounds__(256)
-block_gram_reduce_kernel(const f32x4 *__restrict__ partial, int n, double inv_groups, double *__restrict__ Sigma) {
-  using P = GramPart<NT, PART>;
-  constexpr GramTiles<NT> tiles;
-  constexpr int G = 16 * NT;
+block_gram_reduce_kernel(const f32x4 *__restrict__ partial, int n, int nt, int t0, double inv_groups,
+                         double *__restrict__ Sigma) {
+  const int G = 16 * nt;
   __shared__ double part[16][16][4];
   __shared__ double sum[16][4];
   const int t = threadIdx.x, quad = t & 15, slice = t >> 4;
-  const size_t stride = (size_t)gridDim.y * (P::COUNT * 64);
-  const f32x4 *src = partial + (size_t)blockIdx.y * (P::COUNT * 64) + blockIdx.x * 16 + quad;
+  const size_t per_position = (size_t)gridDim.x * 16, stride = gridDim.y * per_position;
+  const f32x4 *src = partial + blockIdx.y * per_position + blockIdx.x * 16 + quad;
   double s[4] = {0.0, 0.0, 0.0, 0.0};
   int p = slice;
   for (; p + 7 * 16 < n; p += 8 * 16) {             // eight loads in flight, added in order
@@ -285,9 +373,10 @@ block_gram_reduce_kernel(const f32x4 *__restrict__ partial, int n, double inv_gr
   for (int e = 0; e < 4; ++e) part[slice][quad][e] = s[e];
   __syncthreads();
   // the workgroup's quads are 16 lanes of one tile: rows 4 q .. 4 q + 3, columns 0 .. 15
-  const int tile = P::T0 + blockIdx.x / 4, row0 = 4 * (blockIdx.x & 3);
-  const int r = tiles.r[tile] * 16 + row0, c = tiles.c[tile] * 16;
-  double *const out = Sigma + (size_t)blockIdx.y * (G * G);
+  int place = t0 + blockIdx.x / 4;
+  const int tile_row = gram_tile_row(nt, place);
+  const int r = tile_row * 16 + 4 * (blockIdx.x & 3), c = (tile_row + place) * 16;
+  double *const out = Sigma + (size_t)blockIdx.y * G * G;
   if (t < 64) {
     const int e = t >> 4;
     double total = 0.0;
@@ -298,59 +387,65 @@ block_gram_reduce_kernel(const f32x4 *__restrict__ partial, int n, double inv_gr
     out[(size_t)(r + e) * G + c + quad] = total;
   }
   __syncthreads();
-  if (t < 64 && tiles.r[tile] != tiles.c[tile]) out[(size_t)(c + (t >> 2)) * G + r + (t & 3)] = sum[t >> 2][t & 3];
+  if (t < 64 && place != 0) out[(size_t)(c + (t >> 2)) * G + r + (t & 3)] = sum[t >> 2][t & 3];
 }
 
-// the slices' partial tiles of all 32 positions (Sigma's one set per workgroup is smaller)
+// the larger of the two statistics' partial results: Sigma_k's slices of 32 positions, Sigma's workgroups
 size_t block_gram_workspace_bytes(int G) {
   const size_t nt = (size_t)(G / 16), tiles = nt * (nt + 1) / 2, parts = (size_t)gram_parts(G / 16);
   const size_t most = (tiles + parts - 1) / parts;
-  return (size_t)GRAM_MAX_SLICES * 32 * most * 1024;
+  const size_t pos = (size_t)GRAM_MAX_SLICES * 32 * most * 1024, sigma = (size_t)GRAM_SHARED_WG * tiles * 1024;
+  return pos > sigma ? pos : sigma;
 }
 
-template <int NT, int PART>
-static hipError_t launch_part(const void *x, int64_t TG, bool positions, double *Sigma, void *workspace, hipStream_t stream) {
-  using P = GramPart<NT, PART>;
-  const uint4 *xp = static_cast<const uint4 *>(x);
-  f32x4 *partial = static_cast<f32x4 *>(workspace);
-  int n, n_pos = 1;
-  auto raise = [](auto kern, size_t bytes, std::atomic<uint64_t> &raised) {
-    return bytes <= 64 * 1024 ? hipSuccess : raise_lds_limit(reinterpret_cast<const void *>(kern), bytes, raised);
-  };
-  if (positions) {
-    constexpr int KST = NT < 8 ? 8 / NT : 1;
-    constexpr size_t stage = (size_t)8 * 4 * KST * 16 * NT * 16, lds = 2 * stage <= 128 * 1024 ? 2 * stage : stage;
-    const int64_t stages = (TG + 32 * KST - 1) / (32 * KST);
-    n = stages >= GRAM_MAX_SLICES ? GRAM_MAX_SLICES : (int)((stages + 7) / 8 * 8);   // a multiple of the XCDs
-    n_pos = 32;
-    static std::atomic<uint64_t> raised{0};
-    const hipError_t e = raise(block_gram_positions_kernel<NT, PART>, lds, raised);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((block_gram_positions_kernel<NT, PART>), dim3(4 * n), dim3(64 * GRAM_WAVES), lds, stream, xp, TG, n, partial);
-  } else {
-    constexpr int U = NT < 8 ? 8 / NT : 1;
-    constexpr size_t lds = (size_t)GRAM_WAVES / 2 * P::COUNT * 1024;
-    // two steps for every wave before another workgroup pays for its partial result
-    const int64_t want = ((TG + U - 1) / U + 2 * GRAM_WAVES - 1) / (2 * GRAM_WAVES);
-    n = (int)(want < GRAM_MAX_WG ? want : GRAM_MAX_WG);
-    static std::atomic<uint64_t> raised{0};
-    const hipError_t e = raise(block_gram_kernel<NT, PART>, lds, raised);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((block_gram_kernel<NT, PART>), dim3(n), dim3(64 * GRAM_WAVES), lds, stream, xp, TG, partial);
-  }
-  hipError_t e = hipGetLastError();
+static hipError_t launch_reduce(const f32x4 *partial, int n, int nt, int t0, int tiles, int positions, int64_t TG,
+                                double *Sigma, hipStream_t stream) {
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((block_gram_reduce_kernel<NT, PART>), dim3(P::COUNT * 4, n_pos), dim3(256), 0, stream, partial, n,
+  hipLaunchKernelGGL(block_gram_reduce_kernel, dim3(tiles * 4, positions), dim3(256), 0, stream, partial, n, nt, t0,
                      1.0 / (double)TG, Sigma);
   return hipGetLastError();
 }
 
+template <int NT>
+static hipError_t launch_sigma(const uint4 *x, int64_t TG, double *Sigma, f32x4 *partial, hipStream_t stream) {
+  constexpr int TILES = GramTiles<NT>::N;
+  int n;
+  if constexpr (TILES <= GRAM_MAX_TILES) {
+    constexpr int U = NT < 8 ? 8 / NT : 1;
+    constexpr size_t lds = (size_t)GRAM_WAVES / 2 * TILES * 1024;
+    // two steps for every wave before another workgroup pays for its partial result
+    const int64_t want = ((TG + U - 1) / U + 2 * GRAM_WAVES - 1) / (2 * GRAM_WAVES);
+    n = (int)(want < GRAM_MAX_WG ? want : GRAM_MAX_WG);
+    if constexpr (lds > 64 * 1024) {
+      static std::atomic<uint64_t> raised{0};
+      const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(block_gram_kernel<NT>), lds, raised);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((block_gram_kernel<NT>), dim3(n), dim3(64 * GRAM_WAVES), lds, stream, x, TG, partial);
+  } else {
+    const int64_t trips = (TG + GRAM_SHARED_U - 1) / GRAM_SHARED_U;
+    n = (int)(trips < GRAM_SHARED_WG ? trips : GRAM_SHARED_WG);
+    hipLaunchKernelGGL((block_gram_shared_kernel<NT>), dim3(n), dim3(64 * ((NT + 1) / 2)), 0, stream, x, TG, partial);
+  }
+  return launch_reduce(partial, n, NT, 0, TILES, 1, TG, Sigma, stream);
+}
+
 template <int NT, int PART = 0>
-static hipError_t launch_nt(const void *x, int64_t TG, bool positions, double *Sigma, void *workspace, hipStream_t stream) {
+static hipError_t launch_positions(const uint4 *x, int64_t TG, double *Sigma, f32x4 *partial, hipStream_t stream) {
+  using P = GramPart<NT, PART>;
+  constexpr int KST = NT < 8 ? 8 / NT : 1;
+  constexpr size_t stage = (size_t)8 * 4 * KST * 16 * NT * 16, lds = 2 * stage <= 128 * 1024 ? 2 * stage : stage;
+  const int64_t stages = (TG + 32 * KST - 1) / (32 * KST);
+  const int n = stages >= GRAM_MAX_SLICES ? GRAM_MAX_SLICES : (int)((stages + 7) / 8 * 8);   // a multiple of the XCDs
+  static std::atomic<uint64_t> raised{0};
+  hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(block_gram_positions_kernel<NT, PART>), lds, raised);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((block_gram_positions_kernel<NT, PART>), dim3(4 * n), dim3(64 * GRAM_WAVES), lds, stream, x, TG, n, partial);
+  e = launch_reduce(partial, n, NT, P::T0, P::COUNT, 32, TG, Sigma, stream);
   // the parts reuse the workspace in stream order
-  const hipError_t e = launch_part<NT, PART>(x, TG, positions, Sigma, workspace, stream);
-  if constexpr (PART + 1 < GramPart<NT, 0>::PARTS)
-    return e != hipSuccess ? e : launch_nt<NT, PART + 1>(x, TG, positions, Sigma, workspace, stream);
+  if constexpr (PART + 1 < P::PARTS)
+    return e != hipSuccess ? e : launch_positions<NT, PART + 1>(x, TG, Sigma, partial, stream);
   else
     return e;
 }
@@ -359,9 +454,11 @@ static hipError_t launch_nt(const void *x, int64_t TG, bool positions, double *S
 // positions: the 32 matrices Sigma_k instead of Sigma
 hipError_t launch_block_gram(const void *x_bf16, int64_t TG, int G, bool positions, double *Sigma, void *workspace,
                              hipStream_t stream) {
+  const uint4 *x = static_cast<const uint4 *>(x_bf16);
+  f32x4 *partial = static_cast<f32x4 *>(workspace);
   switch (G / 16) {
 #define TORQ_GRAM_CASE(NT_) \
-  case NT_: return launch_nt<NT_>(x_bf16, TG, positions, Sigma, workspace, stream);
+  case NT_: return positions ? launch_positions<NT_>(x, TG, Sigma, partial, stream) : launch_sigma<NT_>(x, TG, Sigma, partial, stream);
     TORQ_GRAM_CASE(1) TORQ_GRAM_CASE(2) TORQ_GRAM_CASE(3) TORQ_GRAM_CASE(4)
     TORQ_GRAM_CASE(5) TORQ_GRAM_CASE(6) TORQ_GRAM_CASE(7) TORQ_GRAM_CASE(8)
     TORQ_GRAM_CASE(9) TORQ_GRAM_CASE(10) TORQ_GRAM_CASE(11) TORQ_GRAM_CASE(12)

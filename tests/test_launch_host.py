@@ -126,3 +126,13 @@ def test_lds_limit_is_raised_on_every_device(record, name):
             assert limit.get((e["launch"], e["device"]), 0) >= e["lds"], e
     assert checked >= 3, "this call is meant to need more than 64 KB of LDS"
     assert len([e for e in events if "raise" in e]) == len(limit), "once for each function and device"
+
+
+@pytest.mark.parametrize("G", range(16, 257, 16))
+def test_block_gram_reads_its_input_in_one_launch(record, G):
+    # one pass over the input and one reduction, whatever the number of tiles
+    events = record(f"""
+        for M in (1, 4096, 70000):
+            assert gram(L.torq_block_gram, M, 32 * {G}, {G}) == 0
+        """)
+    assert len([e for e in events if "launch" in e]) == 3 * 2
