@@ -62,6 +62,9 @@ struct GramPart {
   static constexpr int ROW0 = GramTiles<NT>().r[T0];   // tile rows below this one are not needed
 };
 
+// how many of a wave's tiles go through LDS at once when the waves of a workgroup add theirs
+constexpr int gram_box_tiles(int tiles) { return tiles * GRAM_WAVES <= 144 ? tiles : (tiles + 1) / 2; }
+
 // tile number i of the triangle -> its row; i becomes its place in that row (column - row)
 __device__ __forceinline__ int gram_tile_row(int nt, int &i) {
   int r = 0;
@@ -77,9 +80,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t gram_rsrc(const void *p, uint3
 // time, about 8 KiB), straight from memory into the operand registers: nothing is staged or shared, there
 // is no barrier in the loop, and two steps are in flight beyond the one being multiplied (128 KiB per CU).
 // A token-group past the end reads as zeros through the buffer's range check and adds nothing.  The
-// workgroup's waves add their tiles through LDS at the end: 256 partial results instead of the 512 of a
-// form that shared each token-group through LDS, and packed triangles instead of squares.  X [16384, 8192],
-// G = 128: this kernel 64 -> 51 us (5.2 TB/s, the rate of a copy), the reduction 14 us in two launches -> 4.7.
+// workgroup's waves add their tiles at the end: 256 partial results instead of the 512 of the form that
+// shares each token-group.  X [16384, 8192], G = 128: this kernel 51 us against 64 (5.2 TB/s, the rate of a copy).
 template <int NT>
 __global__ void __launch_bounds__(64 * GRAM_WAVES)
 block_gram_kernel(const uint4 *__restrict__ x, int64_t TG, f32x4 *__restrict__ partial) {
@@ -132,30 +134,34 @@ block_gram_kernel(const uint4 *__restrict__ x, int64_t TG, f32x4 *__restrict__ p
     multiply(v[2]);
   }
 
-  // the upper half of the waves hand their tiles to the lower half, until one wave holds the sum
+  // The waves' tiles meet in LDS, half of them at a time where they do not all fit, and are added in double: one
+  // rounding to fp32 for each partial sum, so that it is the waves' chains alone that round.
+  constexpr int BATCH = gram_box_tiles(COUNT);
   f32x4 *const box = reinterpret_cast<f32x4 *>(lds);
 #pragma unroll
-  for (int half = GRAM_WAVES / 2; half >= 1; half /= 2) {
-    if (wave >= half && wave < 2 * half) {
+  for (int t0 = 0; t0 < COUNT; t0 += BATCH) {
+    constexpr int THR = 64 * GRAM_WAVES;
+    if (t0) __syncthreads();
 #pragma unroll
-      for (int i = 0; i < COUNT; ++i) box[((wave - half) * COUNT + i) * 64 + lane] = acc[i];
-    }
+    for (int i = t0; i < t0 + BATCH && i < COUNT; ++i) box[(wave * BATCH + i - t0) * 64 + lane] = acc[i];
     __syncthreads();
-    if (wave < half) {
+    const int quads = (COUNT - t0 < BATCH ? COUNT - t0 : BATCH) * 64;
+    for (int i = threadIdx.x; i < quads; i += THR) {
+      double sum[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int i = 0; i < COUNT; ++i) acc[i] += box[(wave * COUNT + i) * 64 + lane];
+      for (int w = 0; w < GRAM_WAVES; ++w) {
+        const f32x4 v = box[w * BATCH * 64 + i];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[e] += (double)v[e];
+      }
+      partial[((size_t)blockIdx.x * COUNT + t0) * 64 + i] = f32x4{(float)sum[0], (float)sum[1], (float)sum[2], (float)sum[3]};
     }
-    __syncthreads();
-  }
-  if (wave == 0) {
-#pragma unroll
-    for (int i = 0; i < COUNT; ++i) partial[((size_t)blockIdx.x * COUNT + i) * 64 + lane] = acc[i];
   }
 }
 
-// Sigma for larger G: one wave's registers do not hold the tiles, and splitting them over launches reads the
-// input once for each (two launches at G = 144 to five at 256).  So the workgroup shares each token-group
-// through LDS: wave w owns the block rows 32 w .. 32 w + 31 (two tile rows) against all NT columns, trips of two
+// Sigma for short inputs and for G > 128, where one wave's registers do not hold the tiles and splitting them over
+// launches reads the input once for each (two launches at G = 144 to five at 256).  The workgroup shares each
+// token-group through LDS: wave w owns the block rows 32 w .. 32 w + 31 (two tile rows) against all NT columns, trips of two
 // token-groups go global -> registers -> LDS with two stages and one barrier a trip.  Workgroups are
 // persistent, two per CU; only the tiles of the triangle are written.  Bound: HBM, read once.  X [16384, 8192],
 // G = 256, with the reduction: 98 us against 208 in five launches; G = 160 (X [16384, 5120]): 44 against 65.
@@ -410,24 +416,27 @@ static hipError_t launch_reduce(const f32x4 *partial, int n, int nt, int t0, int
 template <int NT>
 static hipError_t launch_sigma(const uint4 *x, int64_t TG, double *Sigma, f32x4 *partial, hipStream_t stream) {
   constexpr int TILES = GramTiles<NT>::N;
-  int n;
   if constexpr (TILES <= GRAM_MAX_TILES) {
+    // Waves alone where each wave of 256 workgroups has a step.  Shorter inputs take the other form, which spreads them
+    // over up to 512 partial sums: with fewer workgroups than CUs this one is further from the sum in 64 bits, 1.8
+    // times at X [512, 4096], G = 128, and seven times at [512, 1024], G = 32, of Gaussian values.  us, this form
+    // against the other: [64, 4096] 11.5 / 6.7, [4096, 512] 9.3 / 7.3, [1024, 4096] 13.9 / 17.4 (the price of the
+    // smaller error), [2048, 4096] 15.1 / 17.8, [16384, 512] 9.1 / 12.7.
     constexpr int U = NT < 8 ? 8 / NT : 1;
-    constexpr size_t lds = (size_t)GRAM_WAVES / 2 * TILES * 1024;
-    // two steps for every wave before another workgroup pays for its partial result
-    const int64_t want = ((TG + U - 1) / U + 2 * GRAM_WAVES - 1) / (2 * GRAM_WAVES);
-    n = (int)(want < GRAM_MAX_WG ? want : GRAM_MAX_WG);
-    if constexpr (lds > 64 * 1024) {
-      static std::atomic<uint64_t> raised{0};
-      const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(block_gram_kernel<NT>), lds, raised);
-      if (e != hipSuccess) return e;
+    if (TG / U >= GRAM_WAVES * GRAM_MAX_WG) {
+      constexpr size_t lds = (size_t)GRAM_WAVES * gram_box_tiles(TILES) * 1024;
+      if constexpr (lds > 64 * 1024) {
+        static std::atomic<uint64_t> raised{0};
+        const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(block_gram_kernel<NT>), lds, raised);
+        if (e != hipSuccess) return e;
+      }
+      hipLaunchKernelGGL((block_gram_kernel<NT>), dim3(GRAM_MAX_WG), dim3(64 * GRAM_WAVES), lds, stream, x, TG, partial);
+      return launch_reduce(partial, GRAM_MAX_WG, NT, 0, TILES, 1, TG, Sigma, stream);
     }
-    hipLaunchKernelGGL((block_gram_kernel<NT>), dim3(n), dim3(64 * GRAM_WAVES), lds, stream, x, TG, partial);
-  } else {
-    const int64_t trips = (TG + GRAM_SHARED_U - 1) / GRAM_SHARED_U;
-    n = (int)(trips < GRAM_SHARED_WG ? trips : GRAM_SHARED_WG);
-    hipLaunchKernelGGL((block_gram_shared_kernel<NT>), dim3(n), dim3(64 * ((NT + 1) / 2)), 0, stream, x, TG, partial);
   }
+  const int64_t trips = (TG + GRAM_SHARED_U - 1) / GRAM_SHARED_U;
+  const int n = (int)(trips < GRAM_SHARED_WG ? trips : GRAM_SHARED_WG);
+  hipLaunchKernelGGL((block_gram_shared_kernel<NT>), dim3(n), dim3(64 * ((NT + 1) / 2)), 0, stream, x, TG, partial);
   return launch_reduce(partial, n, NT, 0, TILES, 1, TG, Sigma, stream);
 }
 

@@ -659,6 +659,28 @@ def test_block_gram_both_forms_at_the_edges_of_their_stages(tq, oracle, TG, G):
     assert np.array_equal(got, got.transpose(0, 2, 1)) and np.array_equal(S, S.T)
 
 
+def _block_gram_float64(x, G):
+    """The 32 matrices Sigma_k in float64 on the GPU, undivided."""
+    v = x.view(-1, G, 32)
+    out = torch.zeros((32, G, G), dtype=torch.float64, device=x.device)
+    for t in range(0, v.shape[0], 1 << 14):
+        for k in range(32):
+            m = v[t:t + (1 << 14), :, k].double()
+            out[k] += m.t().contiguous() @ m
+    return out
+
+
+@pytest.mark.parametrize("TG,G", [(64, 128), (512, 128), (1024, 128), (512, 32), (1024, 16), (1024, 64), (256, 256)])
+def test_block_gram_of_short_inputs_rounds_no_partial_sum(tq, TG, G):
+    # values k / 128 in [1/2, 3/2]: products are whole multiples of 2^-14 of at most 2.25, so an fp32 sum of two
+    # token-groups (64 products, below 2^8) is exact, while one of sixteen is not; the mean over 2^n is exact too
+    g = torch.Generator(device=DEV)
+    g.manual_seed(TG + G)
+    x = (torch.randint(64, 193, (TG, 32 * G), generator=g, device=DEV) / 128.0).to(torch.bfloat16)
+    want = _block_gram_float64(x, G).sum(0) / TG
+    assert torch.equal(tq.torq_block_gram(x, G), want)
+
+
 def test_calibrated_rotation_equalizes_block_energies_on_the_gpu(tq, oracle):
     # Gram of a sample (GPU) -> Algorithm 1 (host) -> rotation handle -> rotate the sample (GPU):
     # the rotated sample's block energies are all tr(Sigma) / G (Theorem 4.1's equality condition)
