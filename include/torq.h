@@ -269,7 +269,8 @@ int torq_linear_single_launch_probe(const torq_rotation_t *r, const void *x_bf16
  *   Sigma      device, G*G doubles, row-major, overwritten (symmetric)
  *   workspace  device, at least torq_block_gram_workspace_bytes(G) bytes, 16-byte aligned, scratch
  * M = 0 is TORQ_EINVAL (a mean over nothing).  Sums are fp32 inside a workgroup and double across
- * workgroups, in a fixed order: the result is deterministic.
+ * workgroups (torq_block_gram_positions: double throughout), in a fixed order: the result is
+ * deterministic.
  *
  * torq_block_gram_positions: the same statistic kept apart by the position k inside a block, the
  * covariance matrices Sigma_k of Theorem 4.1 (Section 4.2; the calibration cost analysis of the
@@ -277,9 +278,9 @@ int torq_linear_single_launch_probe(const torq_rotation_t *r, const void *x_bf16
  *   Sigma_pos[k][b][b'] = mean over token-groups of X[b][k] X[b'][k],   k < 32,
  * whose sum over k is Sigma.  Arguments as torq_block_gram, with
  *   Sigma_pos  device, 32*G*G doubles, [k][b][b'], overwritten
- * One pass over x for all positions (several for G > 128).  Each matrix can be handed to
- * torq_equalize_inter; the online path of Algorithm 3 applies ONE R_inter to all positions, so a
- * per-position rotation is not something torq_rotation_create takes.
+ * One pass over x for all positions.  Each matrix can be handed to torq_equalize_inter; the online
+ * path of Algorithm 3 applies ONE R_inter to all positions, so a per-position rotation is not
+ * something torq_rotation_create takes.
  *
  * torq_equalize_inter: Algorithm 1 on the HOST, in double.  Plane rotations of the pair (block
  * furthest above the mean energy c = tr(Sigma)/G, block furthest below it) until every diagonal

@@ -5,32 +5,31 @@
 //   Sigma_k[b][b']  = mean over token-groups of  X[b][k] X[b'][k]
 //
 // where a token-group is one run of G consecutive 32-element blocks of one row, i.e. G rows of
-// 64 contiguous bytes.  Both are products of a matrix with its own transpose on
-// v_mfma_f32_16x16x32_bf16 (bf16 products are exact in fp32; the sums are fp32 per workgroup and fp64
-// across workgroups), so both operands of an instruction come out of the same registers and only the
-// 16 x 16 tiles (r, c) with r <= c are computed; the reduce kernel writes both triangles.
+// 64 contiguous bytes.  Both are products of a matrix with its own transpose on the matrix cores, of which
+// only the 16 x 16 tiles (r, c) with r <= c are computed; the reduce kernel writes both triangles.
 //
 // Sigma: the contraction index is the position inside a block (K = 32 = one instruction), the operand
 //   of tile row r is 16 block rows x 64 bytes = 1 KiB of consecutive input.  Two forms, both one pass
 //   over the input: waves that work alone, and waves that share each token-group through LDS.
+//   bf16 products are exact in fp32; the sums are fp32 along a chain of instructions and double across them.
 // Sigma_k: the contraction index is the token-group; the workgroup transposes its input on the way
-//   into LDS (below).  Up to 36 tiles (G <= 128) are one wave's accumulators; larger G runs as several
-//   launches, each with its share of the tiles.
+//   into LDS (below).  The sums are double throughout.
 //
-// Partial sums: packed tiles, [tile][lane][4 floats] as the accumulators hold them.
+// Partial sums: packed tiles, [tile][lane][4 floats or doubles] as the accumulators hold them.
 #include "torq_device.h"
 #include "torq_internal.h"
 
 namespace torq {
 
 typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
+typedef __attribute__((__vector_size__(4 * sizeof(double)))) double f64x4;
 
+constexpr int GRAM_WAVES = 8;
 constexpr int GRAM_MAX_WG = 256;      // Sigma, waves alone: one workgroup per CU
+constexpr int GRAM_MAX_TILES = 36;    // ... and 144 accumulator registers
 constexpr int GRAM_SHARED_WG = 512;   // Sigma, shared token-groups: two workgroups per CU
 constexpr int GRAM_SHARED_U = 2;      // ... and token-groups per trip
-constexpr int GRAM_WAVES = 8;
-constexpr int GRAM_MAX_SLICES = 32;   // Sigma_k: pieces of the token-groups that run side by side
-constexpr int GRAM_MAX_TILES = 36;    // per wave: 144 accumulator registers
+constexpr int GRAM_POS_TILES = 9;     // Sigma_k: tiles of a wave, 72 registers
 
 // the tiles (r, c), r <= c < NT, row by row
 template <int NT>
@@ -46,20 +45,6 @@ struct GramTiles {
         ++i;
       }
   }
-};
-
-// a launch's share of the tiles: parts of nearly equal size, at most GRAM_MAX_TILES each (fewer from
-// G = 224 on, where two chunk columns are staged per thread beside the accumulators)
-constexpr int gram_parts(int nt) {
-  const int most = nt < 14 ? GRAM_MAX_TILES : 28;
-  return (nt * (nt + 1) / 2 + most - 1) / most;
-}
-template <int NT, int PART>
-struct GramPart {
-  static constexpr int N = NT * (NT + 1) / 2;
-  static constexpr int PARTS = gram_parts(NT);
-  static constexpr int T0 = N * PART / PARTS, T1 = N * (PART + 1) / PARTS, COUNT = T1 - T0;
-  static constexpr int ROW0 = GramTiles<NT>().r[T0];   // tile rows below this one are not needed
 };
 
 // how many of a wave's tiles go through LDS at once when the waves of a workgroup add theirs
@@ -252,23 +237,26 @@ block_gram_shared_kernel(const uint4 *__restrict__ x, int64_t TG, f32x4 *__restr
 }
 
 // Sigma_k, all 32 positions in one pass.  A workgroup takes the eight positions of one 16-byte chunk of
-// every block (four workgroups share the input's lines, through the L2 of the XCD that all four are on) and
-// a slice of the token-groups; wave j owns position 8 chunk + j and all of this launch's tiles.  The
+// every block, a slice of the token-groups and a part of the tiles; the workgroups of a slice share the
+// input's lines through the L2 of the XCD that all of them are on.  Wave j owns position 8 chunk + j.  The
 // contraction runs over token-groups, so an operand register holds one position of one block row for eight
 // of them: a thread loads its block's chunk of eight token-groups, pairs up their halves with byte
 // permutes and writes one 16-byte operand piece for each position to LDS, [position][octet][block row],
-// which is written and read in whole consecutive runs (no bank conflicts).  32 token-groups are one
-// instruction's K; a stage holds KST such steps so that the 512 threads have one chunk column each.
-// The bound is reading every line four times from the L2 plus the partial tiles (32 slices x 1.2 MB at
-// G = 128); a stage of 256 KB of lines against 36 matrix instructions per wave.  X [4096, 4096], G = 128:
-// 17.5 us and 8.4 for the reduction; a pass over X for each position took 32 x (12 + 9 + 3) us.
-template <int NT, int PART>
+// which is written and read in whole consecutive runs (no bank conflicts).  A stage holds KST steps of 32
+// token-groups so that the 512 threads have one chunk column each.
+//
+// v_mfma_f64_16x16x4_f64, eight of them for 32 token-groups: the four k of an instruction are the four octets
+// (any order of the token-groups will do, as long as both operands have the same).  Products and sums are double:
+// bf16 instructions round 32 products at a time to 24 bits and lose the small ones beside an outlier, 5.5e-8 against
+// 2.1e-8 relative for sums of one product after the other (activations with outlier channels, X [8192, 8192],
+// G = 128), and still 2.5e-8 with four products an instruction added up in double.  Bound: the matrix cores at the
+// double rate, 50 TFLOP/s measured (the same without the loads or without the conversions).  X [4096, 4096], G = 128: 69 us with the reduction (26 with bf16 instructions,
+// 736 with a pass over x for each position), [8192, 28672] 745 (235 and 3470).
+template <int NT>
 __global__ void __launch_bounds__(64 * GRAM_WAVES)
-block_gram_positions_kernel(const uint4 *__restrict__ x, int64_t TG, int slices, f32x4 *__restrict__ partial) {
-  using P = GramPart<NT, PART>;
-  constexpr GramTiles<NT> tiles;
-  constexpr int G = 16 * NT, NF = NT - P::ROW0;
-  constexpr int KST = NT < 8 ? 8 / NT : 1;          // matrix k-steps of 32 token-groups per stage
+block_gram_positions_kernel(const uint4 *__restrict__ x, int64_t TG, int slices, int parts, f64x4 *__restrict__ partial) {
+  constexpr int G = 16 * NT, TILES = NT * (NT + 1) / 2;
+  constexpr int KST = NT < 8 ? 8 / NT : 1;          // steps of 32 token-groups per stage
   constexpr int ITEMS = 4 * KST * G;                // (octet of token-groups, block row)
   constexpr int THR = 64 * GRAM_WAVES, IT = (ITEMS + THR - 1) / THR;
   constexpr int PLANE = ITEMS * 16, STAGE = 8 * PLANE;
@@ -277,10 +265,25 @@ block_gram_positions_kernel(const uint4 *__restrict__ x, int64_t TG, int slices,
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // workgroup id mod 8 is the XCD: the four chunks of a slice share one
-  const int id = blockIdx.x, slice = (id >> 5) * 8 + (id & 7), chunk = (id >> 3) & 3;
+  // workgroup id mod 8 is the XCD: the chunks and parts of a slice share one
+  const int id = blockIdx.x, units = 4 * parts, unit = (id >> 3) % units, chunk = unit & 3, part = unit >> 2;
+  const int slice = (id >> 3) / units * 8 + (id & 7);
+  if (slice >= slices) return;
   const int64_t stages = (TG + 32 * KST - 1) / (32 * KST);
   const int64_t st0 = stages * slice / slices, st1 = stages * (slice + 1) / slices;
+
+  // this part's tiles: LDS offsets of their operands' rows
+  const int tile0 = TILES * part / parts, count = TILES * (part + 1) / parts - tile0;
+  int row_off[GRAM_POS_TILES], col_off[GRAM_POS_TILES];
+  {
+    int place = tile0, r = gram_tile_row(NT, place), c = r + place;
+#pragma unroll
+    for (int i = 0; i < GRAM_POS_TILES; ++i) {
+      row_off[i] = r * 256;
+      col_off[i] = c * 256;
+      if (++c == NT) c = ++r;
+    }
+  }
 
   int voff[IT];
 #pragma unroll
@@ -315,9 +318,9 @@ block_gram_positions_kernel(const uint4 *__restrict__ x, int64_t TG, int slices,
     }
   };
 
-  f32x4 acc[P::COUNT];
+  f64x4 acc[GRAM_POS_TILES];
 #pragma unroll
-  for (int i = 0; i < P::COUNT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < GRAM_POS_TILES; ++i) acc[i] = f64x4{0.0, 0.0, 0.0, 0.0};
 
   const int f_off = wave * PLANE + ((lane >> 4) * G + (lane & 15)) * 16;
   if (st0 < st1) load(st0);
@@ -327,94 +330,124 @@ block_gram_positions_kernel(const uint4 *__restrict__ x, int64_t TG, int slices,
     store(stage);
     if (st + 1 < st1) load(st + 1);
     __syncthreads();
-#pragma unroll
+#pragma unroll 1
     for (int ks = 0; ks < KST; ++ks) {
-      bf16x8 f[NF];
+      const char *const f = stage + f_off + ks * (4 * G * 16);
 #pragma unroll
-      for (int r = 0; r < NF; ++r)
-        f[r] = *reinterpret_cast<const bf16x8 *>(stage + f_off + (ks * 4 * G + (P::ROW0 + r) * 16) * 16);
+      for (int i = 0; i < GRAM_POS_TILES; ++i) {
+        if (i < count) {
+          const u32x4 a = *reinterpret_cast<const u32x4 *>(f + row_off[i]);
+          const u32x4 b = *reinterpret_cast<const u32x4 *>(f + col_off[i]);
 #pragma unroll
-      for (int i = 0; i < P::COUNT; ++i)
-        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[tiles.r[P::T0 + i] - P::ROW0],
-                                                         f[tiles.c[P::T0 + i] - P::ROW0], acc[i], 0, 0, 0);
+          for (int w = 0; w < 4; ++w) {
+            acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)__builtin_bit_cast(float, a[w] << 16),
+                                                          (double)__builtin_bit_cast(float, b[w] << 16), acc[i], 0, 0, 0);
+            acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)__builtin_bit_cast(float, a[w] & 0xFFFF0000u),
+                                                          (double)__builtin_bit_cast(float, b[w] & 0xFFFF0000u), acc[i], 0, 0, 0);
+          }
+        }
+      }
     }
     if (!TWO) __syncthreads();
     buf ^= 1;
   }
-  f32x4 *const out = partial + ((size_t)slice * 32 + chunk * 8 + wave) * (P::COUNT * 64);
+  f64x4 *const out = partial + (((size_t)slice * 32 + chunk * 8 + wave) * TILES + tile0) * 64 + lane;
 #pragma unroll
-  for (int i = 0; i < P::COUNT; ++i) out[i * 64 + lane] = acc[i];
+  for (int i = 0; i < GRAM_POS_TILES; ++i)
+    if (i < count) out[i * 64] = acc[i];
 }
 
 // Adds n partial results in double and in a fixed order, divides by the number of token-groups and writes
-// both triangles.  A workgroup adds 16 accumulator quads: thread (slice = t / 16, quad = t % 16) every
-// sixteenth partial, then the 16 slices meet in LDS.  blockIdx.y: the position (1 or 32 of them); a partial
-// result holds gridDim.y * tiles * 64 quads, of the tiles from t0 on.
+// both triangles.  A workgroup adds QUADS accumulator quads: thread (slice = t / QUADS, quad = t % QUADS) every
+// SLICES-th partial, then the slices meet in LDS.  Sigma: 16 quads, so that its few tiles make four times as
+// many workgroups, and 16 slices for 256 or 512 partials; Sigma_k: whole tiles, at most 64 partials.
+// blockIdx.y: the position (1 or 32 of them); a partial result holds gridDim.y * tiles * 64 quads.
+// A lane's quad: column lane % 16, and four rows of the tile: 4 (lane / 16) + e of a 32-bit accumulator,
+// lane / 16 + 4 e of a 64-bit one.
+template <typename Quad, int QUADS>
 __global__ void __launch_bounds__(256)
-block_gram_reduce_kernel(const f32x4 *__restrict__ partial, int n, int nt, int t0, double inv_groups,
-                         double *__restrict__ Sigma) {
+block_gram_reduce_kernel(const Quad *__restrict__ partial, int n, int nt, double inv_groups, double *__restrict__ Sigma) {
+  constexpr int SLICES = 256 / QUADS, PER_TILE = 64 / QUADS;
+  constexpr bool F64_ROWS = sizeof(Quad) == 32;
+  static_assert(QUADS == (F64_ROWS ? 64 : 16), "the transposed store's rows");
   const int G = 16 * nt;
-  __shared__ double part[16][16][4];
-  __shared__ double sum[16][4];
-  const int t = threadIdx.x, quad = t & 15, slice = t >> 4;
-  const size_t per_position = (size_t)gridDim.x * 16, stride = gridDim.y * per_position;
-  const f32x4 *src = partial + blockIdx.y * per_position + blockIdx.x * 16 + quad;
+  __shared__ double part[SLICES][QUADS][4];
+  __shared__ double sum[QUADS][4];
+  const int t = threadIdx.x, quad = t % QUADS, slice = t / QUADS;
+  const size_t per_position = (size_t)gridDim.x * QUADS, stride = gridDim.y * per_position;
+  const Quad *src = partial + blockIdx.y * per_position + blockIdx.x * QUADS + quad;
   double s[4] = {0.0, 0.0, 0.0, 0.0};
+  constexpr int FLY = QUADS == 16 ? 8 : 4;          // loads in flight, added in order
   int p = slice;
-  for (; p + 7 * 16 < n; p += 8 * 16) {             // eight loads in flight, added in order
-    f32x4 q[8];
+  for (; p + (FLY - 1) * SLICES < n; p += FLY * SLICES) {
+    Quad q[FLY];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) q[u] = src[(size_t)(p + 16 * u) * stride];
+    for (int u = 0; u < FLY; ++u) q[u] = src[(size_t)(p + SLICES * u) * stride];
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
+    for (int u = 0; u < FLY; ++u)
 #pragma unroll
       for (int e = 0; e < 4; ++e) s[e] += (double)q[u][e];
   }
-  for (; p < n; p += 16) {
-    const f32x4 q = src[(size_t)p * stride];
+  for (; p < n; p += SLICES) {
+    const Quad q = src[(size_t)p * stride];
 #pragma unroll
     for (int e = 0; e < 4; ++e) s[e] += (double)q[e];
   }
 #pragma unroll
   for (int e = 0; e < 4; ++e) part[slice][quad][e] = s[e];
   __syncthreads();
-  // the workgroup's quads are 16 lanes of one tile: rows 4 q .. 4 q + 3, columns 0 .. 15
-  int place = t0 + blockIdx.x / 4;
-  const int tile_row = gram_tile_row(nt, place);
-  const int r = tile_row * 16 + 4 * (blockIdx.x & 3), c = (tile_row + place) * 16;
+  int place = blockIdx.x / PER_TILE;
+  const int tile_row = gram_tile_row(nt, place), lane0 = blockIdx.x % PER_TILE * QUADS;
+  const int r = tile_row * 16, c = (tile_row + place) * 16;
+  auto row = [&](int lane, int e) { return F64_ROWS ? lane / 16 + 4 * e : lane / 16 * 4 + e; };
   double *const out = Sigma + (size_t)blockIdx.y * G * G;
-  if (t < 64) {
-    const int e = t >> 4;
+  if (t < 4 * QUADS) {
+    const int e = t / QUADS;
     double total = 0.0;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) total += part[i][quad][e];
+    for (int i = 0; i < SLICES; ++i) total += part[i][quad][e];
     total *= inv_groups;
     sum[quad][e] = total;
-    out[(size_t)(r + e) * G + c + quad] = total;
+    out[(size_t)(r + row(lane0 + quad, e)) * G + c + (quad & 15)] = total;
   }
   __syncthreads();
-  if (t < 64 && place != 0) out[(size_t)(c + (t >> 2)) * G + r + (t & 3)] = sum[t >> 2][t & 3];
+  // the other triangle, along its rows: column j of the tile, the workgroup's rows of it
+  if (t < 4 * QUADS && place != 0) {
+    const int j = t / (QUADS / 4), i = t % (QUADS / 4);              // QUADS / 4 rows of the tile
+    const int q = F64_ROWS ? (i & 3) * 16 + j : (i >> 2) * 16 + j, e = F64_ROWS ? i >> 2 : i & 3;
+    out[(size_t)(c + j) * G + r + row(lane0 + q, e)] = sum[q][e];
+  }
 }
+
+// Sigma_k: how a launch is cut.  256 or 512 workgroups of nearly equal work (four chunks x parts x slices) for at
+// most GRAM_POS_TILES tiles a part; the slices are a multiple of the XCDs.  X [4096, 4096], G = 128: four parts and
+// 16 slices 69 us, eight and eight 73 (each part reads the lines from the L2 again).
+static int gram_pos_parts(int nt) {
+  const int tiles = nt * (nt + 1) / 2, fit = (tiles + GRAM_POS_TILES - 1) / GRAM_POS_TILES;
+  return fit > 8 ? 16 : fit > 4 ? 8 : tiles < 4 ? tiles : 4;
+}
+static int gram_pos_slices(int nt) { return nt == 1 ? 64 : gram_pos_parts(nt) <= 4 ? 16 : 8; }
 
 // the larger of the two statistics' partial results: Sigma_k's slices of 32 positions, Sigma's workgroups
 size_t block_gram_workspace_bytes(int G) {
-  const size_t nt = (size_t)(G / 16), tiles = nt * (nt + 1) / 2, parts = (size_t)gram_parts(G / 16);
-  const size_t most = (tiles + parts - 1) / parts;
-  const size_t pos = (size_t)GRAM_MAX_SLICES * 32 * most * 1024, sigma = (size_t)GRAM_SHARED_WG * tiles * 1024;
+  const int nt = G / 16;
+  const size_t tiles = (size_t)nt * (nt + 1) / 2;
+  const size_t pos = (size_t)gram_pos_slices(nt) * 32 * tiles * 2048, sigma = (size_t)GRAM_SHARED_WG * tiles * 1024;
   return pos > sigma ? pos : sigma;
 }
 
-static hipError_t launch_reduce(const f32x4 *partial, int n, int nt, int t0, int tiles, int positions, int64_t TG,
-                                double *Sigma, hipStream_t stream) {
+template <typename Quad, int QUADS>
+static hipError_t launch_reduce(const Quad *partial, int n, int nt, int positions, int64_t TG, double *Sigma, hipStream_t stream) {
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(block_gram_reduce_kernel, dim3(tiles * 4, positions), dim3(256), 0, stream, partial, n, nt, t0,
-                     1.0 / (double)TG, Sigma);
+  hipLaunchKernelGGL((block_gram_reduce_kernel<Quad, QUADS>), dim3(nt * (nt + 1) / 2 * (64 / QUADS), positions), dim3(256), 0, stream,
+                     partial, n, nt, 1.0 / (double)TG, Sigma);
   return hipGetLastError();
 }
 
 template <int NT>
-static hipError_t launch_sigma(const uint4 *x, int64_t TG, double *Sigma, f32x4 *partial, hipStream_t stream) {
+static hipError_t launch_sigma(const uint4 *x, int64_t TG, double *Sigma, void *workspace, hipStream_t stream) {
+  f32x4 *const partial = static_cast<f32x4 *>(workspace);
   constexpr int TILES = GramTiles<NT>::N;
   if constexpr (TILES <= GRAM_MAX_TILES) {
     // Waves alone where each wave of 256 workgroups has a step.  Shorter inputs take the other form, which spreads them
@@ -431,32 +464,28 @@ static hipError_t launch_sigma(const uint4 *x, int64_t TG, double *Sigma, f32x4 
         if (e != hipSuccess) return e;
       }
       hipLaunchKernelGGL((block_gram_kernel<NT>), dim3(GRAM_MAX_WG), dim3(64 * GRAM_WAVES), lds, stream, x, TG, partial);
-      return launch_reduce(partial, GRAM_MAX_WG, NT, 0, TILES, 1, TG, Sigma, stream);
+      return launch_reduce<f32x4, 16>(partial, GRAM_MAX_WG, NT, 1, TG, Sigma, stream);
     }
   }
   const int64_t trips = (TG + GRAM_SHARED_U - 1) / GRAM_SHARED_U;
   const int n = (int)(trips < GRAM_SHARED_WG ? trips : GRAM_SHARED_WG);
   hipLaunchKernelGGL((block_gram_shared_kernel<NT>), dim3(n), dim3(64 * ((NT + 1) / 2)), 0, stream, x, TG, partial);
-  return launch_reduce(partial, n, NT, 0, TILES, 1, TG, Sigma, stream);
+  return launch_reduce<f32x4, 16>(partial, n, NT, 1, TG, Sigma, stream);
 }
 
-template <int NT, int PART = 0>
-static hipError_t launch_positions(const uint4 *x, int64_t TG, double *Sigma, f32x4 *partial, hipStream_t stream) {
-  using P = GramPart<NT, PART>;
+template <int NT>
+static hipError_t launch_positions(const uint4 *x, int64_t TG, double *Sigma, void *workspace, hipStream_t stream) {
   constexpr int KST = NT < 8 ? 8 / NT : 1;
   constexpr size_t stage = (size_t)8 * 4 * KST * 16 * NT * 16, lds = 2 * stage <= 128 * 1024 ? 2 * stage : stage;
+  f64x4 *const partial = static_cast<f64x4 *>(workspace);
   const int64_t stages = (TG + 32 * KST - 1) / (32 * KST);
-  const int n = stages >= GRAM_MAX_SLICES ? GRAM_MAX_SLICES : (int)((stages + 7) / 8 * 8);   // a multiple of the XCDs
+  const int parts = gram_pos_parts(NT), most = gram_pos_slices(NT), n = (int)(stages < most ? stages : most);
   static std::atomic<uint64_t> raised{0};
-  hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(block_gram_positions_kernel<NT, PART>), lds, raised);
+  const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(block_gram_positions_kernel<NT>), lds, raised);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((block_gram_positions_kernel<NT, PART>), dim3(4 * n), dim3(64 * GRAM_WAVES), lds, stream, x, TG, n, partial);
-  e = launch_reduce(partial, n, NT, P::T0, P::COUNT, 32, TG, Sigma, stream);
-  // the parts reuse the workspace in stream order
-  if constexpr (PART + 1 < P::PARTS)
-    return e != hipSuccess ? e : launch_positions<NT, PART + 1>(x, TG, Sigma, partial, stream);
-  else
-    return e;
+  hipLaunchKernelGGL((block_gram_positions_kernel<NT>), dim3((n + 7) / 8 * 8 * 4 * parts), dim3(64 * GRAM_WAVES), lds,
+                     stream, x, TG, n, parts, partial);
+  return launch_reduce<f64x4, 64>(partial, n, NT, 32, TG, Sigma, stream);
 }
 
 // G a multiple of 16 in [16, 256], TG > 0 token-groups, workspace of block_gram_workspace_bytes(G)
@@ -464,10 +493,9 @@ static hipError_t launch_positions(const uint4 *x, int64_t TG, double *Sigma, f3
 hipError_t launch_block_gram(const void *x_bf16, int64_t TG, int G, bool positions, double *Sigma, void *workspace,
                              hipStream_t stream) {
   const uint4 *x = static_cast<const uint4 *>(x_bf16);
-  f32x4 *partial = static_cast<f32x4 *>(workspace);
   switch (G / 16) {
 #define TORQ_GRAM_CASE(NT_) \
-  case NT_: return positions ? launch_positions<NT_>(x, TG, Sigma, partial, stream) : launch_sigma<NT_>(x, TG, Sigma, partial, stream);
+  case NT_: return positions ? launch_positions<NT_>(x, TG, Sigma, workspace, stream) : launch_sigma<NT_>(x, TG, Sigma, workspace, stream);
     TORQ_GRAM_CASE(1) TORQ_GRAM_CASE(2) TORQ_GRAM_CASE(3) TORQ_GRAM_CASE(4)
     TORQ_GRAM_CASE(5) TORQ_GRAM_CASE(6) TORQ_GRAM_CASE(7) TORQ_GRAM_CASE(8)
     TORQ_GRAM_CASE(9) TORQ_GRAM_CASE(10) TORQ_GRAM_CASE(11) TORQ_GRAM_CASE(12)

@@ -681,6 +681,18 @@ def test_block_gram_of_short_inputs_rounds_no_partial_sum(tq, TG, G):
     assert torch.equal(tq.torq_block_gram(x, G), want)
 
 
+@pytest.mark.parametrize("TG,G", [(1, 128), (64, 128), (300, 64), (2048, 128), (5000, 32), (4100, 16), (1057, 160), (700, 256)])
+@pytest.mark.parametrize("gaussian", [False, True])
+def test_block_gram_positions_sums_in_double(tq, TG, G, gaussian):
+    # two sums of TG exact products in float64, in any order: at most TG roundings of 2^-53 of the largest entry each
+    d = 32 * G
+    x = synth.weights(TG, d, seed=TG + G, device=DEV) if gaussian else synth.activations(TG, d, seed=TG + G, device=DEV)
+    want = _block_gram_float64(x, G) / TG
+    got = tq.torq_block_gram_positions(x, G)
+    assert ((got - want).abs().amax(dim=(1, 2)) <= 2 * TG * 2.0 ** -53 * want.abs().amax(dim=(1, 2))).all()
+    assert torch.equal(got, got.transpose(1, 2))
+
+
 def test_calibrated_rotation_equalizes_block_energies_on_the_gpu(tq, oracle):
     # Gram of a sample (GPU) -> Algorithm 1 (host) -> rotation handle -> rotate the sample (GPU):
     # the rotated sample's block energies are all tr(Sigma) / G (Theorem 4.1's equality condition)

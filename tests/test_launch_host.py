@@ -134,5 +134,6 @@ def test_block_gram_reads_its_input_in_one_launch(record, G):
     events = record(f"""
         for M in (1, 4096, 70000):
             assert gram(L.torq_block_gram, M, 32 * {G}, {G}) == 0
+            assert gram(L.torq_block_gram_positions, M, 32 * {G}, {G}) == 0
         """)
-    assert len([e for e in events if "launch" in e]) == 3 * 2
+    assert len([e for e in events if "launch" in e]) == 3 * 2 * 2
