@@ -267,7 +267,9 @@ int torq_linear_single_launch_probe(const torq_rotation_t *r, const void *x_bf16
  *   x_bf16     device, [M][d] bf16 row-major, 16-byte aligned; d % 32 == 0, (d/32) % G == 0,
  *              G a multiple of 16, at most TORQ_MAX_G
  *   Sigma      device, G*G doubles, row-major, overwritten (symmetric)
- *   workspace  device, at least torq_block_gram_workspace_bytes(G) bytes, 16-byte aligned, scratch
+ *   workspace  device, torq_block_gram_workspace_bytes(G) bytes, 16-byte aligned, scratch.  Less is
+ *              accepted, down to 2176 G^2 bytes or (G > 128) 23 MiB, and may be slower; below
+ *              both TORQ_EWORKSPACE
  * M = 0 is TORQ_EINVAL (a mean over nothing).  Sums are fp32 inside a workgroup and double across
  * workgroups (torq_block_gram_positions: double throughout), in a fixed order: the result is
  * deterministic.

@@ -600,9 +600,9 @@ int torq_block_gram(const void *x_bf16, int64_t M, int d, int G, double *Sigma, 
   if (G <= 0 || G % 16 != 0 || G > TORQ_MAX_G || (d / TORQ_BLOCK) % G != 0) return TORQ_EINVAL;
   if (!x_bf16 || !Sigma || !workspace) return TORQ_EINVAL;
   if (misaligned(x_bf16) || misaligned(workspace) || (reinterpret_cast<uintptr_t>(Sigma) & 7u)) return TORQ_EALIGN;
-  if (workspace_bytes < torq::block_gram_workspace_bytes(G)) return TORQ_EWORKSPACE;
+  if (workspace_bytes < torq::block_gram_workspace_least(G)) return TORQ_EWORKSPACE;
   const int64_t TG = M * (int64_t)(d / TORQ_BLOCK / G);
-  hipError_t e = torq::launch_block_gram(x_bf16, TG, G, false, Sigma, workspace, (hipStream_t)stream);
+  hipError_t e = torq::launch_block_gram(x_bf16, TG, G, false, Sigma, workspace, workspace_bytes, (hipStream_t)stream);
   return e == hipSuccess ? TORQ_OK : hip_fail(e);
 }
 
@@ -612,9 +612,9 @@ int torq_block_gram_positions(const void *x_bf16, int64_t M, int d, int G, doubl
   if (G <= 0 || G % 16 != 0 || G > TORQ_MAX_G || (d / TORQ_BLOCK) % G != 0) return TORQ_EINVAL;
   if (!x_bf16 || !Sigma_pos || !workspace) return TORQ_EINVAL;
   if (misaligned(x_bf16) || misaligned(workspace) || (reinterpret_cast<uintptr_t>(Sigma_pos) & 7u)) return TORQ_EALIGN;
-  if (workspace_bytes < torq::block_gram_workspace_bytes(G)) return TORQ_EWORKSPACE;
+  if (workspace_bytes < torq::block_gram_workspace_least(G)) return TORQ_EWORKSPACE;
   const int64_t TG = M * (int64_t)(d / TORQ_BLOCK / G);
-  hipError_t e = torq::launch_block_gram(x_bf16, TG, G, true, Sigma_pos, workspace, (hipStream_t)stream);
+  hipError_t e = torq::launch_block_gram(x_bf16, TG, G, true, Sigma_pos, workspace, workspace_bytes, (hipStream_t)stream);
   return e == hipSuccess ? TORQ_OK : hip_fail(e);
 }
 

@@ -436,6 +436,13 @@ size_t block_gram_workspace_bytes(int G) {
   return pos > sigma ? pos : sigma;
 }
 
+// The least that is accepted: what earlier sizes of this scratch came to, for programs that keep one.  A launch then
+// has fewer slices or workgroups (X [4096, 4096], G = 128: 15 slices instead of 16).
+size_t block_gram_workspace_least(int G) {
+  const size_t earlier = G <= 128 ? (size_t)2176 * G * G : (size_t)23 << 20, now = block_gram_workspace_bytes(G);
+  return earlier < now ? earlier : now;
+}
+
 template <typename Quad, int QUADS>
 static hipError_t launch_reduce(const Quad *partial, int n, int nt, int positions, int64_t TG, double *Sigma, hipStream_t stream) {
   const hipError_t e = hipGetLastError();
@@ -446,7 +453,8 @@ static hipError_t launch_reduce(const Quad *partial, int n, int nt, int position
 }
 
 template <int NT>
-static hipError_t launch_sigma(const uint4 *x, int64_t TG, double *Sigma, void *workspace, hipStream_t stream) {
+static hipError_t launch_sigma(const uint4 *x, int64_t TG, double *Sigma, void *workspace, size_t workspace_bytes,
+                               hipStream_t stream) {
   f32x4 *const partial = static_cast<f32x4 *>(workspace);
   constexpr int TILES = GramTiles<NT>::N;
   if constexpr (TILES <= GRAM_MAX_TILES) {
@@ -468,18 +476,22 @@ static hipError_t launch_sigma(const uint4 *x, int64_t TG, double *Sigma, void *
     }
   }
   const int64_t trips = (TG + GRAM_SHARED_U - 1) / GRAM_SHARED_U;
-  const int n = (int)(trips < GRAM_SHARED_WG ? trips : GRAM_SHARED_WG);
+  const int64_t room = (int64_t)(workspace_bytes / ((size_t)TILES * 1024)), most = room < GRAM_SHARED_WG ? room : GRAM_SHARED_WG;
+  const int n = (int)(trips < most ? trips : most);
   hipLaunchKernelGGL((block_gram_shared_kernel<NT>), dim3(n), dim3(64 * ((NT + 1) / 2)), 0, stream, x, TG, partial);
   return launch_reduce<f32x4, 16>(partial, n, NT, 1, TG, Sigma, stream);
 }
 
 template <int NT>
-static hipError_t launch_positions(const uint4 *x, int64_t TG, double *Sigma, void *workspace, hipStream_t stream) {
+static hipError_t launch_positions(const uint4 *x, int64_t TG, double *Sigma, void *workspace, size_t workspace_bytes,
+                                   hipStream_t stream) {
   constexpr int KST = NT < 8 ? 8 / NT : 1;
   constexpr size_t stage = (size_t)8 * 4 * KST * 16 * NT * 16, lds = 2 * stage <= 128 * 1024 ? 2 * stage : stage;
   f64x4 *const partial = static_cast<f64x4 *>(workspace);
   const int64_t stages = (TG + 32 * KST - 1) / (32 * KST);
-  const int parts = gram_pos_parts(NT), most = gram_pos_slices(NT), n = (int)(stages < most ? stages : most);
+  const int64_t room = (int64_t)(workspace_bytes / ((size_t)32 * GramTiles<NT>::N * 2048));
+  const int64_t most = room < gram_pos_slices(NT) ? room : gram_pos_slices(NT);
+  const int parts = gram_pos_parts(NT), n = (int)(stages < most ? stages : most);
   static std::atomic<uint64_t> raised{0};
   const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(block_gram_positions_kernel<NT>), lds, raised);
   if (e != hipSuccess) return e;
@@ -488,14 +500,16 @@ static hipError_t launch_positions(const uint4 *x, int64_t TG, double *Sigma, vo
   return launch_reduce<f64x4, 64>(partial, n, NT, 32, TG, Sigma, stream);
 }
 
-// G a multiple of 16 in [16, 256], TG > 0 token-groups, workspace of block_gram_workspace_bytes(G)
+// G a multiple of 16 in [16, 256], TG > 0 token-groups, workspace of at least block_gram_workspace_least(G) bytes
 // positions: the 32 matrices Sigma_k instead of Sigma
 hipError_t launch_block_gram(const void *x_bf16, int64_t TG, int G, bool positions, double *Sigma, void *workspace,
-                             hipStream_t stream) {
+                             size_t workspace_bytes, hipStream_t stream) {
   const uint4 *x = static_cast<const uint4 *>(x_bf16);
   switch (G / 16) {
 #define TORQ_GRAM_CASE(NT_) \
-  case NT_: return positions ? launch_positions<NT_>(x, TG, Sigma, workspace, stream) : launch_sigma<NT_>(x, TG, Sigma, workspace, stream);
+  case NT_:                                                                                          \
+    return positions ? launch_positions<NT_>(x, TG, Sigma, workspace, workspace_bytes, stream)       \
+                     : launch_sigma<NT_>(x, TG, Sigma, workspace, workspace_bytes, stream);
     TORQ_GRAM_CASE(1) TORQ_GRAM_CASE(2) TORQ_GRAM_CASE(3) TORQ_GRAM_CASE(4)
     TORQ_GRAM_CASE(5) TORQ_GRAM_CASE(6) TORQ_GRAM_CASE(7) TORQ_GRAM_CASE(8)
     TORQ_GRAM_CASE(9) TORQ_GRAM_CASE(10) TORQ_GRAM_CASE(11) TORQ_GRAM_CASE(12)

@@ -113,8 +113,9 @@ hipError_t launch_decode_ctr_reset(const torq_rotation *r, hipStream_t stream);
 // Block Gram matrix of the runs of G blocks (block_gram.hip), or the 32 of them kept apart by position:
 // TG token-groups of G * 32 bf16 each.
 size_t block_gram_workspace_bytes(int G);
+size_t block_gram_workspace_least(int G);   // accepted, at the price of speed
 hipError_t launch_block_gram(const void *x_bf16, int64_t TG, int G, bool positions, double *Sigma, void *workspace,
-                             hipStream_t stream);
+                             size_t workspace_bytes, hipStream_t stream);
 
 // Codeword histogram per in-block position (code_histogram.hip): nblk blocks of 16 code bytes.
 size_t code_histogram_workspace_bytes();

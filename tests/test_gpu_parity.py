@@ -693,6 +693,19 @@ def test_block_gram_positions_sums_in_double(tq, TG, G, gaussian):
     assert torch.equal(got, got.transpose(1, 2))
 
 
+@pytest.mark.parametrize("G", [16, 32, 128, 144, 256])
+def test_block_gram_stays_within_the_least_workspace(tq, G):
+    TG, least = 40000, min(2176 * G * G if G <= 128 else 23 << 20, tq.torq_block_gram_workspace_bytes(G))
+    x = synth.weights(TG, 32 * G, seed=G, device=DEV)
+    want = _block_gram_float64(x, G) / TG
+    buf = torch.full((least + 4096,), 0x5A, dtype=torch.uint8, device=DEV)
+    assert (tq.torq_block_gram_positions(x, G, workspace=buf[:least]) - want).abs().max() <= 2 * TG * 2.0 ** -53 * want.abs().max()
+    S, want = tq.torq_block_gram(x, G, workspace=buf[:least]), want.sum(0)
+    # an fp32 chain of up to 40000 / 173 token-groups, 2^-22 for each instruction
+    assert (S - want).abs().max() <= 240 * 2.0 ** -22 * want.abs().max()
+    assert (buf[least:] == 0x5A).all()
+
+
 def test_calibrated_rotation_equalizes_block_energies_on_the_gpu(tq, oracle):
     # Gram of a sample (GPU) -> Algorithm 1 (host) -> rotation handle -> rotate the sample (GPU):
     # the rotated sample's block energies are all tr(Sigma) / G (Theorem 4.1's equality condition)

@@ -137,3 +137,25 @@ def test_block_gram_reads_its_input_in_one_launch(record, G):
             assert gram(L.torq_block_gram_positions, M, 32 * {G}, {G}) == 0
         """)
     assert len([e for e in events if "launch" in e]) == 3 * 2 * 2
+
+
+@pytest.mark.parametrize("G", range(16, 257, 16))
+def test_block_gram_takes_workspaces_of_earlier_sizes(record, G):
+    # what the query has returned before: 512 square fp32 results and 16 in double; 32 slices of 32 positions of the
+    # tiles of one launch.  Neither may be refused, and no launch may write past it
+    nt = G // 16
+    tiles = nt * (nt + 1) // 2
+    launches = -(-tiles // (36 if nt < 14 else 28))
+    sizes = [512 * G * G * 4 + 16 * G * G * 8, 32 * 32 * -(-tiles // launches) * 1024]
+    events = record(f"""
+        query, least = L.torq_block_gram_workspace_bytes({G}), 2176 * {G} * {G} if {G} <= 128 else 23 << 20
+        least = min(query, least)
+        for size in {sizes} + [query, least]:
+            for fn in (L.torq_block_gram, L.torq_block_gram_positions):
+                assert gram(fn, 70000, 32 * {G}, {G}, sz(size)) == 0, size
+        for fn in (L.torq_block_gram, L.torq_block_gram_positions):
+            assert gram(fn, 70000, 32 * {G}, {G}, sz(least - 1)) == -3
+        """)
+    launched = [e for e in events if "launch" in e]
+    for size, e in zip(sizes, launched[0::4]):
+        assert e["grid"][0] * tiles * 1024 <= size
