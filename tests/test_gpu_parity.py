@@ -645,18 +645,43 @@ def test_block_gram_positions_against_oracle(tq, oracle, M, d, G):
 
 @pytest.mark.parametrize("TG,G", [(n, G) for G in range(16, 257, 16) for n in (1, 33)]
                          + [(2200, 128), (1100, 32), (4111, 16), (1057, 160), (1030, 256)])
-def test_block_gram_both_forms_at_the_edges_of_their_stages(tq, oracle, TG, G):
-    # every number of tiles (one to five launches), a single token-group, one past a stage of 32, and more
-    # stages than slices; fp32 chains of fewer than 128 additions of exact products, each rounding at most
-    # 2^-24 of sum |x x'| <= the largest diagonal entry
+def test_block_gram_both_forms_of_short_inputs(tq, oracle, TG, G):
+    # every number of tiles, a single token-group, one past a stage of 32 and a few trips; Sigma's fp32 chains are of
+    # at most ten token-groups (4111 of them on 512 workgroups, two at a time), 2^-22 for each instruction
     x = synth.activations(TG, 32 * G, seed=400 + G + TG)
     want = oracle.block_gram_positions(synth.bf16_bits(x), G)
     xd = x.to(DEV)
     got, S = _np(tq.torq_block_gram_positions(xd, G)), _np(tq.torq_block_gram(xd, G))
-    bound = 128 * 2.0 ** -24
-    assert (np.abs(got - want).max(axis=(1, 2)) <= bound * np.abs(want).max(axis=(1, 2))).all()
-    assert np.abs(S - want.sum(axis=0)).max() <= bound * np.abs(want.sum(axis=0)).max()
+    assert (np.abs(got - want).max(axis=(1, 2)) <= 2 * TG * 2.0 ** -53 * np.abs(want).max(axis=(1, 2))).all()
+    assert np.abs(S - want.sum(axis=0)).max() <= 10 * 2.0 ** -22 * np.abs(want.sum(axis=0)).max()
     assert np.array_equal(got, got.transpose(0, 2, 1)) and np.array_equal(S, S.T)
+
+
+def _gram_edges():
+    cases = []
+    for G in (16, 32, 48, 64, 80, 96, 112, 128):
+        u = max(1, 8 * 16 // G)                   # token-groups of a wave's step; 8 waves of 256 workgroups
+        cases += [(2048 * u - 1, G), (2048 * u, G), (2048 * 7 * u + u + 1, G)]    # other form / one step each / three turns
+    cases += [(n, G) for G in (144, 160, 192, 240, 256) for n in (1023, 1025, 3 * 1024 + 3)]   # trips of 2 on 512 workgroups
+    for G in (16, 32, 48, 80, 128, 144, 256):     # Sigma_k's stages: one past one, three turns of the buffers and a rest
+        stage = 32 * max(1, 8 * 16 // G)
+        cases += [(stage + 1, G), (3 * stage * (64 if G == 16 else 16 if G <= 128 else 8) + 17, G)]
+    return cases
+
+
+@pytest.mark.parametrize("TG,G", _gram_edges())
+def test_block_gram_at_the_edges_of_steps_trips_and_stages(tq, TG, G):
+    # token-groups past the end count as zeros: what lies behind the input is a NaN
+    buf = torch.full((TG + 256, 32 * G), float("nan"), dtype=torch.bfloat16, device=DEV)
+    x = buf[:TG]
+    x.copy_(synth.weights(TG, 32 * G, seed=G + TG, device=DEV))
+    want = _block_gram_float64(x, G) / TG
+    got, S, W = tq.torq_block_gram_positions(x, G), tq.torq_block_gram(x, G), want.sum(0)
+    assert ((got - want).abs().amax(dim=(1, 2)) <= 2 * TG * 2.0 ** -53 * want.abs().amax(dim=(1, 2))).all()
+    # Sigma: an fp32 chain of at most 64 token-groups (eight steps of eight, G = 16) and a rounding of the sum of eight
+    # waves, 2^-22 for each instruction; a wave's step in the wrong place is a part in 15000 of the sum or more
+    assert (S - W).abs().max() <= 65 * 2.0 ** -22 * W.abs().max()
+    assert torch.equal(got, got.transpose(1, 2)) and torch.equal(S, S.T)
 
 
 def _block_gram_float64(x, G):
