@@ -650,26 +650,34 @@ static double tiled_us(int tile, int s, bool deep, int64_t M, int64_t N, int d) 
   return t;
 }
 
-static double skinny_us(int64_t M, int64_t N, int d) {
+// one strip of weight rows in a workgroup (or two that share nothing but the activation loads)
+static double skinny_one_us(int64_t M, int64_t N, int d) {
   const double mt = (double)((M + 15) / 16), iters = (double)((d + 255) / 256);
   const double w_mb = (double)N * (double)d * 0.53125 / 1e6;
-  const int ns = mxfp4_gemm_skinny_strips(M, N, d);
-  const int64_t wgs = ((N + 15) / 16 + ns - 1) / ns;
-  if (M > 16 && (ns == 4 || (ns == 2 && wgs <= 256))) {
-    // two or four strips in a workgroup, one workgroup a CU and round: within 12 % of what [24 .. 64, 1024 .. 28672]
-    // x 4224 .. 28672 measured, weights from HBM
-    const double rounds = (double)((wgs + 255) / 256);
-    const double work = ns == 2 ? 2.45 + 0.2 * mt + iters * (0.16 + 0.0725 * mt)
-                                : rounds * (2.2 + 0.75 * mt + iters * (0.31 + 0.08 * mt));
-    const double read = 2.75 + 0.2104 * w_mb;
-    return work > read ? work : read;
-  }
   // beyond d = 16384 a workgroup no longer keeps its activation rows across strips: every further 16-row
   // activation tile costs up to 2.3 times more (d = 28672)
   const double f = d > 16384 ? 1.0 + 1.74 * (double)(d - 16384) / 16384.0 : 1.0;
   const double latency = 2.66 + iters * (0.0565 + 0.0801 * mt * f);
   const double stream = 2.75 + w_mb * (0.2104 + 0.0726 * (mt - 1.0) * f);
   return latency > stream ? latency : stream;
+}
+
+// two or four strips in a workgroup, one workgroup a CU and round (0: neither)
+static int skinny_several(int64_t M, int64_t N, int d) {
+  const int ns = mxfp4_gemm_skinny_strips(M, N, d);
+  return M > 16 && (ns == 4 || (ns == 2 && (N + 15) / 16 <= 512)) ? ns : 0;
+}
+
+// within 12 % of what [17 .. 64, 4112 .. 16128] x 1024 .. 28160 measured, weights from HBM (four strips at 17 - 32
+// rows and d of 22016 and more: up to 22 % too low)
+static double skinny_several_us(int ns, int64_t M, int64_t N, int d) {
+  const double mt = (double)((M + 15) / 16), iters = (double)((d + 255) / 256);
+  const int64_t wgs = ((N + 15) / 16 + ns - 1) / ns;
+  const double rounds = (double)((wgs + 255) / 256);
+  const double work = ns == 2 ? 2.45 + 0.2 * mt + iters * (0.16 + 0.0725 * mt)
+                              : rounds * (2.2 + 0.75 * mt + iters * (0.31 + 0.08 * mt));
+  const double read = 2.75 + 0.2104 * (double)N * (double)d * 0.53125 / 1e6;
+  return work > read ? work : read;
 }
 
 static GemmPlan choose_plan(int64_t M, int64_t N, int d, bool allow_split) {
@@ -703,10 +711,22 @@ static GemmPlan choose_plan(int64_t M, int64_t N, int d, bool allow_split) {
     }
   }
   if (can_skinny) {
-    // near a tie the streaming kernel wins: one launch, no tile padding (not from 17 rows on with four strips a
-    // workgroup, where the tiles are full enough: [64, 14336] x 14336 40.3 us against 37.8)
-    const double t = skinny_us(M, N, d);
-    if ((M > 16 && mxfp4_gemm_skinny_strips(M, N, d) == 4 ? 1.0 : 0.95) * t <= plan.us) plan = GemmPlan{true, 0, 1, false, t};
+    // Near a tie the streaming kernel wins: one launch, no tile padding.  With four strips a workgroup it has no such
+    // allowance: the tiles are full enough there ([64, 14336] x 14336 40.3 us against 37.8).
+    const double one = skinny_one_us(M, N, d);
+    const int ns = skinny_several(M, N, d);
+    const double t = ns ? skinny_several_us(ns, M, N, d) : one;
+    double factor = ns == 4 ? 1.0 : 0.95;
+    // Where a workgroup's one strip would have lost to the tiles, several have to be ahead by what the two models miss.
+    // A k range cut in two to four or six to nine is priced up to a sixth too high: streaming against tiled, us,
+    // [32, 7936] x 18432 25.5 / 22.7, [26, 15616] x 24576 56.6 / 48.5, [36, 7424] x 23552 35.7 / 32.2,
+    // [18, 13536] x 23040 47.0 / 43.1.  In five or ten and more it is priced too low: [19, 16128] x 23040 47.9 / 56.1,
+    // [21, 7584] x 25600 30.6 / 36.4.  Four strips against whole tiles: [43, 14528] x 5120 15.9 / 15.1.
+    if (ns && 0.95 * one > plan.us) {
+      if (plan.splits != 1 && plan.splits != 5 && plan.splits < 10) factor = 1.18;
+      else if (ns == 4 && plan.splits == 1) factor = 1.03;
+    }
+    if (factor * t <= plan.us) plan = GemmPlan{true, 0, 1, false, t};
   }
   return plan;
 }

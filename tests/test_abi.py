@@ -157,6 +157,19 @@ def test_gemm_workspace_entry_points_validate_and_plan_on_the_host():
     assert L.mxfp4_gemm_plan(4, 4, 128, 0, None, C.byref(v[1]), C.byref(v[2]), C.byref(v[3])) == binding.TORQ_EINVAL
 
 
+# 17 - 64 rows where the tiled kernel with its k range cut and the streaming kernel with several strips a workgroup come
+# close: shapes where one of the two measured 5 % or more ahead of the other, weights from HBM
+@pytest.mark.parametrize("M,N,d,streaming", [
+    (32, 7936, 18432, False), (28, 8080, 18432, False), (26, 15616, 24576, False), (30, 14592, 17408, False),
+    (36, 7424, 23552, False), (33, 4480, 23552, False), (46, 8080, 23552, False), (18, 16128, 13312, False),
+    (17, 13536, 23040, False), (32, 8080, 25088, False), (32, 7584, 27648, False), (43, 14528, 5120, False),
+    (64, 14336, 14336, False), (19, 16128, 23040, True), (38, 15616, 12800, True), (21, 7584, 25600, True),
+    (18, 7584, 28160, True), (49, 4352, 24064, True), (54, 6912, 24064, True), (64, 8192, 5120, True),
+    (57, 5600, 4096, True), (20, 4608, 8192, True), (25, 12048, 7168, True)])
+def test_gemm_planner_between_streaming_and_a_cut_k_range(M, N, d, streaming):
+    assert binding.mxfp4_gemm_plan(M, N, d, 1 << 40)[0] is streaming
+
+
 def test_gemm_planner_invariants_over_random_shapes():
     # whatever the cost model prefers, a plan has to be one the kernels can run: pieces that divide the k range
     # into whole pairs of iterations, fp32 rows that are 16-byte aligned, a workspace that holds them, a first
