@@ -133,7 +133,12 @@ GEMM_FULL = [
     (4096, 8192, 5120),       # Qwen3-32B q projection
     (16, 28672, 8192),        # LLaMA3-70B MLP up at decode size: workgroups that keep the activations across four strip groups
     (12, 28000, 8192),        # ... with ragged rows and a ragged last group
-    (8, 8192, 8192),          # ... one strip per group, two groups per workgroup
+    (16, 11008, 4096),        # ... one strip per group, four groups per workgroup
+    (12, 8210, 8192),         # ... with ragged rows and a ragged last group
+    (8, 8192, 8192),          # two strips per workgroup, one group each, the k range in one trip
+    (32, 5120, 8192),         # ... with two 16-row activation tiles
+    (64, 5120, 8192),         # ... with four, in two trips
+    (17, 8200, 54528),        # two where the scale rows of four do not fit the LDS
     (4096, 5120, 5120),       # Qwen3-32B attention output: a round and a quarter of tiles, run as two products
     (4000, 5000, 5120),       # ... with ragged last tiles in both
 ]

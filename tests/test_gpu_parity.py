@@ -278,10 +278,17 @@ def test_gemm_random_codes(tq, oracle, M, N, d):
 
 
 # The weight-streaming kernel at the edges of its strips-per-workgroup rule: one, two and four 16-row strips, the first
-# and last strip count of each, 8, 16, 17 and 33 rows, ragged N and M, trips of one, two and four line pairs per wave.
+# and last strip count of each, 8, 16, 17 and 33 rows, ragged N and M; and each form that the rule dispatches, 16-row
+# activation tiles x strips x line pairs per wave and trip, with several trips where it has them
 STRIP_EDGES = [(7, 4100, 512), (8, 4100, 512), (16, 4096, 640), (16, 8200, 640), (17, 4097, 1152), (33, 4100, 2176),
                (45, 4112, 8192), (48, 8200, 640), (64, 8192, 384), (32, 8200, 2176), (17, 8200, 1920), (49, 9001, 1408),
-               (20, 12288, 256), (33, 16384, 640)]
+               (20, 12288, 256), (33, 16384, 640),
+               (16, 4112, 2304), (16, 4112, 12288),           # 1 x 2 x 2, one trip and four
+               (32, 4112, 2304), (32, 4112, 12288),           # 2 x 2 x 2
+               (32, 4112, 8192), (16, 4100, 7936),            # 2 x 2 x 4, 1 x 2 x 4
+               (64, 4100, 2176), (64, 4112, 8192),            # 4 x 2 x 2
+               (24, 8200, 4224), (48, 8200, 4224), (64, 8200, 4224),   # 2, 3 and 4 x 4 x 1, three trips
+               (20, 16400, 4352)]                             # two strips just past 1024 of them
 
 
 @pytest.mark.parametrize("M,N,d", STRIP_EDGES)
