@@ -809,7 +809,7 @@ def gram_line(tq, x, G, steps, warmup):
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / steps
     gbs = M * d * 2.0 / (ms * 1e-3) / 1e9
-    # the per-position matrices Sigma_k: 32 passes of the same kernel over x
+    # the per-position matrices Sigma_k: one pass over x, sums in double
     Sp = torch.empty((32, G, G), dtype=torch.float64, device=x.device)
     tq.torq_block_gram_positions(xs[0], G, Sigma_pos=Sp, workspace=ws)
     e0.record()

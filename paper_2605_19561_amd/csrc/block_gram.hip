@@ -249,9 +249,11 @@ block_gram_shared_kernel(const uint4 *__restrict__ x, int64_t TG, f32x4 *__restr
 // (any order of the token-groups will do, as long as both operands have the same).  Products and sums are double:
 // bf16 instructions round 32 products at a time to 24 bits and lose the small ones beside an outlier, 5.5e-8 against
 // 2.1e-8 relative for sums of one product after the other (activations with outlier channels, X [8192, 8192],
-// G = 128), and still 2.5e-8 with four products an instruction added up in double.  Bound: the matrix cores at the
-// double rate, 50 TFLOP/s measured (the same without the loads or without the conversions).  X [4096, 4096], G = 128: 69 us with the reduction (26 with bf16 instructions,
-// 736 with a pass over x for each position), [8192, 28672] 745 (235 and 3470).
+// G = 128), and still 2.5e-8 with eight products a sum, added up in double.  Bound: the matrix cores at the double rate;
+// an instruction is 64 cycles and no vector instruction runs beside it, so with the conversions it takes 97 (45
+// TFLOP/s).  X [4096, 4096], G = 128: 69 us with the reduction (26 with bf16 instructions, 736 with a pass over x for
+// each position), [8192, 28672] 745 (235 and 3470).  Operands widened once a tile row, the next tile's read ahead or
+// tiles interleaved changed nothing.
 template <int NT>
 __global__ void __launch_bounds__(64 * GRAM_WAVES)
 block_gram_positions_kernel(const uint4 *__restrict__ x, int64_t TG, int slices, int parts, f64x4 *__restrict__ partial) {

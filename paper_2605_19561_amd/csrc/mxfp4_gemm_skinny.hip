@@ -734,7 +734,8 @@ static hipError_t launch_mt_ns(const uint8_t *A_q, const uint8_t *A_s, const uin
 // strips on up to d = 4096 ([17, 4096] x 16384 10.2 against 10.8, [17, 1024] x 14336 5.0 against 5.4) and just
 // past 1024 strips, one below 768 strips and d = 2048 ([17, 1024] x 8448 4.7 against 5.1; [32, 3072] x 11264
 // gains, 11.4 -> 9.4).  8 - 16 rows beyond 512 strips: two from 768 strips on, mostly in the persistent form
-// (two against four, [16, 8192] x 28672 28.8 / 32.3); 1 - 7 rows re-read too little to gain.
+// (two against four, [16, 8192] x 28672 28.8 / 32.3; below 768 strips two, with trips of four, have measured ahead too,
+// [16, 8192] x 8448 15.5 -> 14.1, and are not taken yet); 1 - 7 rows re-read too little to gain.
 int mxfp4_gemm_skinny_strips(int64_t M, int64_t N, int d) {
   const int MT = (int)((M + 15) / 16);
   const int64_t strips = (N + 15) / 16;

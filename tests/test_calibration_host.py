@@ -49,7 +49,9 @@ def test_equalize_inter_trivial_and_invalid_inputs():
     with pytest.raises(binding.TorqError) as ei:
         binding.torq_equalize_inter(S, eps=0.0)
     assert ei.value.status == binding.TORQ_ECONVERGE
-    assert binding.torq_block_gram_workspace_bytes(128) >= 512 * 128 * 128 * 4
+    for G in range(16, 257, 16):      # 512 fp32 partial triangles, or 8 slices of 32 in double, in tiles of 16 x 16
+        tiles = G // 16 * (G // 16 + 1) // 2
+        assert binding.torq_block_gram_workspace_bytes(G) >= tiles * max(512 * 1024, 8 * 32 * 2048)
     assert binding.torq_block_gram_workspace_bytes(24) == 0 and binding.torq_block_gram_workspace_bytes(512) == 0
     good = C.c_void_p(0x1000)
     assert L.torq_block_gram(good, 0, 4096, 128, good, good, 1 << 30, None) == binding.TORQ_EINVAL
