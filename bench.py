@@ -561,9 +561,10 @@ def plan_sweep(tq, torch, grid):
     """Every plan of the tiled GEMM kernel on every shape of a grid (up to one round of 256x256 tiles), timed as
     HIP-graph replays over weight copies of at least 600 MB in all, so that weights come from HBM and activations
     from the caches, as in a model.  One JSON line per shape: the planner's choice with and without a workspace and
-    its time, then [tile, k_pieces, deep, us] for every candidate (tile 0 ... 3 = 256x256, 256x128, 128x128, 128x64)."""
+    its time, then [tile rows, tile columns, staging, k_pieces, us] for every candidate (staging: "registers", "deep" or "ring")."""
     dev = "cuda:0"
-    tile_m, tile_n = (256, 256, 128, 128), (256, 128, 128, 64)
+    forms = [(256, 256, "registers", 0), (256, 128, "registers", 1), (128, 128, "deep", 2)]
+    forms += [(m, n, "ring", None) for m in (128, 64) for n in (128, 64)]
 
     def graph_us(fn, n):
         side = torch.cuda.Stream()
@@ -613,19 +614,20 @@ def plan_sweep(tq, torch, grid):
                     A_q, A_s, wq, wsc, out=out, workspace=ws[:max(need, 16)])), calls)
                 rec["us_without"] = graph_us(cycling(lambda wq, wsc: tq.mxfp4_gemm(A_q, A_s, wq, wsc, out=out)), calls)
                 cands = []
-                for tile in range(4):
-                    tiles = ((M + tile_m[tile] - 1) // tile_m[tile]) * ((N + tile_n[tile] - 1) // tile_n[tile])
-                    if tiles > 1024:
-                        continue
+                for tile_m, tile_n, staging, tile in forms:
+                    tiles = ((M + tile_m - 1) // tile_m) * ((N + tile_n - 1) // tile_n)
                     for pieces in (1, 2, 4, 5, 7, 8, 10, 14, 16):
-                        if pieces > 1 and ((d // 512) % pieces or tile == 0 or tiles * pieces > 1024 or N % 8):
+                        if pieces == 1 and tiles > 2048 or (tile != 1 and staging != "ring" and pieces > 1):
                             continue
-                        for deep in ((False, True) if (tile >= 2 and pieces == 1) else (False,)):
-                            us = graph_us(cycling(lambda wq, wsc: tq.torq_diag_gemm_plan(
-                                A_q, A_s, wq, wsc, tile, pieces, deep, out=out, workspace=ws)), calls)
-                            cands.append([tile, pieces, int(deep), us])
+                        if pieces > 1 and ((d // 512) % pieces or tiles * pieces > 640 or N % 8):
+                            continue
+                        if staging == "ring":
+                            one = lambda wq, wsc: tq.torq_diag_gemm_ring(A_q, A_s, wq, wsc, tile_m, tile_n, pieces, out=out, workspace=ws)
+                        else:
+                            one = lambda wq, wsc: tq.torq_diag_gemm_plan(A_q, A_s, wq, wsc, tile, pieces, staging == "deep", out=out, workspace=ws)
+                        cands.append([tile_m, tile_n, staging, pieces, graph_us(cycling(one), calls)])
                 rec["candidates"] = cands
-                rec["best"] = min(cands, key=lambda c: c[3])
+                rec["best"] = min(cands, key=lambda c: c[4])
                 print(json.dumps(rec), flush=True)
                 del A_q, A_s, W_q, W_s, out, ws
 

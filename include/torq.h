@@ -157,7 +157,7 @@ size_t mxfp4_gemm_workspace_bytes(int64_t M, int64_t N, int d);
 /* Which kernel the product of that shape runs on, given a workspace of that many bytes (0: as
  * mxfp4_gemm) and 16-byte aligned scale arrays: *weight_streaming = 1 for the kernel that streams
  * 16-row weight strips (at most 64 activation rows), else 0 and *tile_m x *tile_n is the output
- * tile; *k_pieces > 1 if the k range is cut.  Host only, launches nothing; for logs and tests. */
+ * tile (128 rows also where two workgroups share them, 64 each); *k_pieces > 1 if the k range is cut.  Host only, launches nothing; for logs and tests. */
 int mxfp4_gemm_plan(int64_t M, int64_t N, int d, size_t workspace_bytes, int *weight_streaming, int *tile_m,
                     int *tile_n, int *k_pieces);
 /* A tile count just above a whole number of rounds (one 256 x 256 tile per compute unit) would leave
@@ -436,15 +436,24 @@ int torq_diag_gemm_persistent(const uint8_t *A_q, const uint8_t *A_s, const uint
  * kernel on shapes small enough to compare every output.  Never the weight-streaming kernel, the
  * persistent form or two launches.  The result is mxfp4_gemm's bit for bit when k_pieces = 1, and
  * mxfp4_gemm_ws's for the same tile and k_pieces otherwise.
- *   tile        0: 256 x 256 output tile, 1: 256 x 128, 2: 128 x 128, 3: 128 x 64
+ *   tile        0: 256 x 256 output tile, 1: 256 x 128, 2: 128 x 128, 3: 128 x 64 (3, and 2 where it is cut: the form
+ *               staged in a ring)
  *   k_pieces    1, or into how many pieces the k range is cut: d / 512 must be a multiple of it, N a multiple of
  *               8, and workspace (device, 16-byte aligned) hold k_pieces * M * N floats
- *   deep        != 0: the deeper load pipeline (tiles 2 and 3 only)
+ *   deep        != 0: the deeper load pipeline (refused for tiles 0 and 1; only tile 2 where it is not cut has another)
  *   tile 3, k_pieces > 1 and deep need d a multiple of 512 and 16-byte aligned scale arrays
  * Anything else: TORQ_EINVAL / TORQ_EALIGN. */
 int torq_diag_gemm_plan(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q, const uint8_t *W_s,
                         void *out_bf16, int64_t M, int64_t N, int d, int tile, int k_pieces, int deep,
                         void *workspace, size_t workspace_bytes, void *stream);
+/* The same for the form of the tiled kernel that stages its operands in a ring: tile_m x tile_n is 128 x 128, 128 x 64,
+ * 64 x 128 or 64 x 64, d a multiple of 512, all pointers 16-byte aligned; k_pieces and workspace as above.
+ *   on_chip     != 0: the k range halved inside a workgroup (64 x 64, k_pieces = 2, d a multiple of 1024; no workspace):
+ *               the bits of k_pieces = 2
+ * Anything else: TORQ_EINVAL / TORQ_EALIGN. */
+int torq_diag_gemm_ring(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q, const uint8_t *W_s,
+                        void *out_bf16, int64_t M, int64_t N, int d, int tile_m, int tile_n, int k_pieces,
+                        int on_chip, void *workspace, size_t workspace_bytes, void *stream);
 /* A plain device-to-device copy of n_bytes (a multiple of 16; src and dst 16-byte aligned, not
  * overlapping) by a kernel of this library, `torq::diag_copy_kernel`: it reads n_bytes and writes
  * n_bytes, nothing else, which makes it the yardstick for memory-traffic counters (run it in the same

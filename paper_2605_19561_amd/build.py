@@ -9,7 +9,8 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtorq.so")
-SOURCES = ["api.hip", "quantize.hip", "rotate_quant.hip", "rotate_butterfly.hip", "mxfp4_gemm.hip", "mxfp4_gemm_skinny.hip", "block_gram.hip", "code_histogram.hip",
+SOURCES = ["api.hip", "quantize.hip", "rotate_quant.hip", "rotate_butterfly.hip", "mxfp4_gemm.hip", "mxfp4_gemm_ring.hip",
+           "mxfp4_gemm_skinny.hip", "block_gram.hip", "code_histogram.hip",
            "intra_calib.hip", "diag.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
@@ -21,9 +22,10 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
 # The rotate kernel post-processes its MFMA results with vector ALU code, so its accumulators are
 # kept in ordinary VGPRs (no v_accvgpr_read traffic); the GEMM needs the AGPR half for its tile.
 # rotate_quant.hip writes m0 in inline assembly (the LDS address of a buffer load into LDS) and says so in the
-# clobber list; the compiler warns about every such statement, since it reserves m0 for itself -- nothing
+# clobber list (mxfp4_gemm_ring.hip the same); the compiler warns about every such statement, since it reserves m0 for itself -- nothing
 # else in that kernel uses it.
 EXTRA = {"rotate_quant.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-Wno-inline-asm"],
+         "mxfp4_gemm_ring.hip": ["-Wno-inline-asm"],
          "rotate_butterfly.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
          "mxfp4_gemm_skinny.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 

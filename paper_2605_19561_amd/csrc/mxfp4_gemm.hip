@@ -27,6 +27,8 @@
 // LDS rows are 128 bytes; the 16-byte chunk index is XOR-swizzled with
 // (row >> 1) & 7, which makes both the row-wise stores and the column-wise
 // 16-byte fragment reads bank-conflict free.
+#include <cmath>
+
 #include "torq_device.h"
 #include "torq_internal.h"
 
@@ -513,6 +515,14 @@ mxfp4_gemm_splitk_reduce_kernel(const float *__restrict__ partial, int splits, i
   *reinterpret_cast<u64x2 *>(out + o0) = u64x2{__builtin_bit_cast(uint64_t, a), __builtin_bit_cast(uint64_t, b)};
 }
 
+static hipError_t launch_splitk_reduce(const float *partial, int splits, int64_t M, int64_t N, int64_t ldc, void *out,
+                                       hipStream_t stream) {
+  const int64_t MN = M * N;
+  hipLaunchKernelGGL(mxfp4_gemm_splitk_reduce_kernel, dim3((unsigned)((MN / 8 + 255) / 256)), dim3(256), 0, stream,
+                     partial, splits, MN, N, ldc, reinterpret_cast<uint16_t *>(out));
+  return hipGetLastError();
+}
+
 // compute units of the current device (256 on this part), asked once
 static int compute_units() {
   static int cus = 0;
@@ -566,11 +576,7 @@ static hipError_t launch_tile(const uint8_t *A_q, const uint8_t *A_s, const uint
   hipLaunchKernelGGL(kern, dim3((unsigned)grid, SPLIT ? splits : 1), dim3(256), lds_bytes, stream, A_q,
                      A_s, W_q, W_s, reinterpret_cast<uint16_t *>(out), partial, M, N, d, (int)tiles_m, (int)tiles_n, ldc);
   hipError_t e = hipGetLastError();
-  if (!SPLIT || e != hipSuccess) return e;
-  const int64_t MN = M * N;
-  hipLaunchKernelGGL(mxfp4_gemm_splitk_reduce_kernel, dim3((unsigned)((MN / 8 + 255) / 256)), dim3(256), 0, stream,
-                     partial, splits, MN, N, ldc, reinterpret_cast<uint16_t *>(out));
-  return hipGetLastError();
+  return SPLIT && e == hipSuccess ? launch_splitk_reduce(partial, splits, M, N, ldc, out, stream) : e;
 }
 
 // Which output tile: 0 = 256 x 256, 1 = 256 x 128, 2 = 128 x 128.  Every CU holds one workgroup
@@ -584,16 +590,19 @@ static int choose_tile(int64_t M, int64_t N) {
   return c1 <= c2 ? 1 : 2;
 }
 
-// the tile shapes: 0 = 256 x 256, 1 = 256 x 128, 2 = 128 x 128, 3 = 128 x 64
-static const int TILE_M[4] = {256, 256, 128, 128}, TILE_N[4] = {256, 128, 128, 64};
+// the tiled forms: 0 = 256 x 256, 1 = 256 x 128, 2 = 128 x 128 staged through registers (above); 3 = 128 x 64,
+// 4 = 64 x 128, 5 = 64 x 64, 6 = 128 x 128 staged in a ring (mxfp4_gemm_ring.hip); 7 = 5 with the k range halved inside
+// the workgroup
+constexpr int FORMS = 8, HALVED = 7;
+static const int TILE_M[FORMS] = {256, 256, 128, 128, 64, 64, 128, 64}, TILE_N[FORMS] = {256, 128, 128, 64, 128, 64, 128, 64};
 
 // How a product is run: the weight-streaming kernel (mxfp4_gemm_skinny.hip), or the tiled kernel
-// with tile shape `cfg` and its k range cut into `splits` pieces (1 = not cut).
+// in form `cfg` with its k range cut into `splits` pieces (1 = not cut).
 struct GemmPlan {
   bool skinny;
   int cfg;
   int splits;
-  bool deep;      // the tiled kernel's deeper load pipeline (128-row-wide tiles, weight-bound shapes)
+  bool deep;      // form 2's deeper load pipeline (up to a round of 256 x 256 tiles)
   double us;      // the model's estimate of the launch time
 };
 
@@ -613,41 +622,63 @@ static double rounds_us(int cfg, double tiles, double KT, int64_t N, int d) {
   return t > stream ? t : stream;
 }
 
-// Up to one round of 256 x 256 tiles the choice is wide: four tile shapes, the k range whole or cut into
-// pieces that run side by side (a piece is a whole even number of iterations; the pieces' fp32 tiles go
-// through the caller's workspace and a second kernel adds them), the deeper load pipeline for the two small
-// tiles, and with at most 64 activation rows the weight-streaming kernel.  The planner prices every
-// candidate with a model fitted to measurements and takes the cheapest.  The measurements: 238 shapes
-// (M = 1 ... 2048, N = 1024 ... 28672, d = 4096 ... 28672, powers of two and not), every candidate of each
-// forced through torq_diag_gemm_plan, HIP-graph replays over weight copies of 600 MB in all (weights come
-// from HBM, as they do in a model; activations from the caches).  Microseconds:
-//   tiled:  a + b * iterations of one workgroup,  b = (b_lo + (b_hi - b_lo) * clamp((w - 128) / 128, 0, 1)) *
-//           (1 + (rounds - 1) * m)  with rounds = ceil(workgroups / 256) and w = workgroups / rounds: up to
-//           half the CUs busy an iteration costs b_lo (latency), a full round b_hi (the power limit), a CU
-//           that holds several workgroups m times more for each further one; never less than the weights'
-//           stream from HBM; a cut adds the second launch, the pieces' traffic and 0.25 us per piece.
-//   weight-streaming:  the larger of a latency term (iterations x 16-row activation tiles) and the stream.
-// Over the measured shapes the choice is within 0.5 % of the best candidate on average (5 - 13 % before, when
-// the 128 x 64 tile did not exist and cuts were priced by rule of thumb); the worst case is 7 %.
-struct TileCost { double a, b_lo, b_hi; };
-static const TileCost TILE_COST[4][2] = {      // [tile][deep]
-    {{7.47, 1.40, 2.11}, {7.47, 1.40, 2.11}}, {{5.24, 0.96, 1.10}, {5.24, 0.96, 1.10}},
-    {{4.65, 0.84, 0.76}, {3.75, 0.68, 0.83}}, {{4.36, 0.67, 0.65}, {3.12, 0.59, 0.63}}};
-static const double TILE_SHARE[4] = {1.0, 1.11, 0.82, 0.70};
+// Up to one round of 256 x 256 tiles the choice is wide: the tiled forms, the k range whole or cut into pieces that
+// run side by side (a piece is a whole even number of iterations; the pieces' fp32 tiles go through the caller's
+// workspace and a second kernel adds them), and with at most 64 activation rows the weight-streaming kernel.  The
+// planner prices every candidate with a model fitted to measurements and takes the cheapest.  All measurements: HIP-graph
+// replays over weight copies of up to 600 MB in all (weights from HBM, as in a model; activations from the caches).
+//
+// More than 64 rows: 900 random shapes (M = 65 ... 2048, N = 256 ... 28672, d = 1024 ... 28672), every candidate of each.
+// Microseconds, for w workgroups a CU, rounds = ceil(w / those that share a CU), e = al ceil(w) + (1 - al) w:
+//   a + a2 (rounds - 1) + iterations of one workgroup * (b + q e)   (a CU's workgroups share its path from the L2, and a
+//   full chip the path behind it), never less than a + the weights' bytes * (stream + rows * tile rows); a cut adds the
+//   second launch, the pieces' traffic and a little per piece.
+// On 200 shapes that the fit had not seen the choice is 1.3 % off the best candidate on average, 3 % at the 90th percentile,
+// 28 % at worst; against the planner before, which had no ring, 1.19 times faster on average over 320.
+struct TileCost { double a, b, q, al, a2, stream, rows, cut, cut_mn, cut_s; };
+static const TileCost TILE_COST[HALVED] = {
+    {12, 0.864, 1.067, 0.238, 3.631, 0.143, 0.02, 0, 0, 0},
+    {5.699, 0.062, 1.158, 0.641, 4.019, 0.227, 0.065, 1.689, 1.24, 0.127},
+    {3.973, 0, 0.836, 0.548, 2.895, 0.211, 0.057, 0, 0, 0},
+    {3.119, 0.018, 0.483, 0.682, 1.998, 0.251, 0.075, 2.134, 1.675, 0.127},
+    {3.152, 0, 0.555, 0.629, 2.255, 0.126, 0.127, 2.393, 1.294, 0.146},
+    {2.823, 0.015, 0.298, 0.749, 1.208, 0.134, 0.144, 1.848, 1.847, 0.136},
+    {4.053, 0.053, 0.763, 0.573, 3.755, 0.195, 0.061, 2.248, 1.298, 0.172}};
+static const int TILE_SHARE[HALVED] = {1, 1, 2, 1, 1, 2, 1};      // workgroups that share a CU (by their LDS)
 
-static double tiled_us(int tile, int s, bool deep, int64_t M, int64_t N, int d) {
-  const double tiles = (double)(((M + TILE_M[tile] - 1) / TILE_M[tile]) * ((N + TILE_N[tile] - 1) / TILE_N[tile]));
-  const double wgs = tiles * s, iters = (double)((d + 255) / 256) / s;
-  const TileCost &c = TILE_COST[tile][deep ? 1 : 0];
-  const double rounds = (double)(int64_t)((wgs + 255.0) / 256.0), w = wgs / rounds;
+static double tiled_us(int form, int s, int64_t M, int64_t N, int d) {
+  const double tiles_m = (double)((M + TILE_M[form] - 1) / TILE_M[form]), tiles_n = (double)((N + TILE_N[form] - 1) / TILE_N[form]);
+  const double w = tiles_m * tiles_n * s / 256.0, iters = (double)((d + 255) / 256) / s;
+  const TileCost &c = TILE_COST[form];
+  const double rounds = std::ceil(w / TILE_SHARE[form]);
+  double t = c.a + c.a2 * (rounds - 1.0) + iters * (c.b + c.q * (c.al * std::ceil(w) + (1.0 - c.al) * w));
+  const double stream = c.a + (double)N * (double)d * 0.53125 / 1e6 * (c.stream + c.rows * tiles_m);
+  if (t < stream) t = stream;
+  if (s > 1) t += c.cut + c.cut_mn * (double)s * (double)M * (double)N / 1e6 + c.cut_s * s;
+  return t;
+}
+
+// At most 64 rows: 128 x 128 (row 0) and 128 x 64 tiles, whole or (second entry) on the deeper load pipeline, priced as
+// they ran before the ring: that is what the weight-streaming kernel's border was measured against ([64, 8192] x 5120 and
+// its like), and the ring's tiles of half the rows take the same cuts, 10 % faster at these sizes ([45, 5120] x 25600 21.2
+// -> 19.0, [45, 25600] x 5120 24.6 -> 21.9).  a + b * iterations of one workgroup, b from b_lo up to half the CUs busy
+// (latency) to b_hi at a full round, `share` times more for each further workgroup of a CU; never less than the weights'
+// stream at 4.7 TB/s; a cut adds the second launch, the pieces' traffic and 0.25 us per piece.
+struct FewRowsCost { double a, b_lo, b_hi; };
+static const FewRowsCost FEW_ROWS_COST[2][2] = {
+    {{4.65, 0.84, 0.76}, {3.75, 0.68, 0.83}}, {{4.36, 0.67, 0.65}, {3.12, 0.59, 0.63}}};
+static const double FEW_ROWS_SHARE[2] = {0.82, 0.70};
+
+static double few_rows_us(int wide, int s, int64_t N, int d) {
+  const int tile_n = wide ? 128 : 64;
+  const double wgs = (double)((N + tile_n - 1) / tile_n) * s, iters = (double)((d + 255) / 256) / s;
+  const FewRowsCost &c = FEW_ROWS_COST[wide ? 0 : 1][d % 512 == 0 && s == 1 ? 1 : 0];
+  const double rounds = std::ceil(wgs / 256.0), w = wgs / rounds;
   double ramp = (w - 128.0) / 128.0;
   ramp = ramp < 0.0 ? 0.0 : ramp > 1.0 ? 1.0 : ramp;
-  const double b = (c.b_lo + (c.b_hi - c.b_lo) * ramp) * (1.0 + (rounds - 1.0) * TILE_SHARE[tile]);
-  double t = c.a + b * iters;
-  const double stream = c.a + (double)N * (double)d * 0.53125 / 1e6 * 0.211;     // 4.7 TB/s
-  if (t < stream) t = stream;
-  if (s > 1) t += 0.72 + 1.75 * (double)s * (double)M * (double)N / 1e6 + 0.25 * s;
-  return t;
+  const double b = (c.b_lo + (c.b_hi - c.b_lo) * ramp) * (1.0 + (rounds - 1.0) * FEW_ROWS_SHARE[wide ? 0 : 1]);
+  const double t = c.a + b * iters, stream = c.a + (double)N * (double)d * 0.53125 / 1e6 * 0.211;
+  return t < stream ? stream : t;
 }
 
 // one strip of weight rows in a workgroup (or two that share nothing but the activation loads)
@@ -683,31 +714,45 @@ static double skinny_several_us(int ns, int64_t M, int64_t N, int d) {
 static GemmPlan choose_plan(int64_t M, int64_t N, int d, bool allow_split) {
   const bool can_skinny = mxfp4_gemm_skinny_fits(M, d);
   const double KT = (d + 255) / 256;
-  auto tiles_of = [&](int tile) { return ((M + TILE_M[tile] - 1) / TILE_M[tile]) * ((N + TILE_N[tile] - 1) / TILE_N[tile]); };
+  auto tiles_of = [&](int form) { return ((M + TILE_M[form] - 1) / TILE_M[form]) * ((N + TILE_N[form] - 1) / TILE_N[form]); };
   GemmPlan plan{false, 0, 1, false, 0.0};
   if (tiles_of(0) > 256) {
     // more than a round of the largest tile: by rounds (choose_tile), never cut
     plan.cfg = choose_tile(M, N);
     plan.us = rounds_us(plan.cfg, (double)tiles_of(plan.cfg), KT, N, d);
   } else {
-    const bool may_split = allow_split && d % 512 == 0 && N % 8 == 0;
+    const bool whole = d % 512 == 0, may_split = allow_split && whole && N % 8 == 0;
     const int pairs = d / 512;
     double best = -1.0;
-    for (int tile = 0; tile < 4; ++tile) {
-      if (tile == 3 && d % 512 != 0) continue;                       // (the 128 x 64 tile only has the whole-pieces form)
-      for (int s = 1; s <= 16 && s <= (may_split && tile != 0 ? pairs : 1); ++s) {   // the largest tile is never cut
-        if (s > 1 && (pairs % s != 0 || tiles_of(tile) * s > 1024)) continue;
-        if (s == 1 && tile != 0 && tiles_of(tile) > 1024) continue;
-        // the two small tiles, not cut, always on the deeper load pipeline: 10 - 19 % faster up to 256 tiles
-        // with weights from HBM, within 3 % beyond; cut, up to 256 workgroups (2 - 7 % faster there, 1 - 2 %
-        // slower beyond; priced like the plain pipeline)
-        const bool deep = tile >= 2 && d % 512 == 0 && (s == 1 || tiles_of(tile) * s <= 256);
-        const double t = tiled_us(tile, s, deep && s == 1, M, N, d);
-        if (best < 0.0 || t < best) {
-          best = t;
-          plan = GemmPlan{false, tile, s, deep, t};
+    auto offer = [&](int form, int s, double t) {
+      if (best >= 0.0 && t >= best) return;
+      best = t;
+      plan = GemmPlan{false, form, s, form == 2 && whole, t};
+    };
+    if (M <= 64) {
+      // (d not a multiple of 512: only the plain 128 x 128 form takes it)
+      for (int wide = 1; wide >= (whole ? 0 : 1); --wide)
+        for (int s = 1; s <= 16 && s <= (may_split ? pairs : 1); ++s) {
+          if (s > 1 && (pairs % s != 0 || (N + (wide ? 127 : 63)) / (wide ? 128 : 64) * s > 1024)) continue;
+          const double cut = s > 1 ? 0.72 + 1.75 * (double)s * (double)M * (double)N / 1e6 + 0.25 * s : 0.0;
+          offer(!whole ? 2 : wide ? 4 : 5, s, few_rows_us(wide, s, N, d) + cut);
+        }
+    } else {
+      for (int form = 0; form < HALVED; ++form) {
+        if (form > 2 && !whole) continue;                            // the ring only takes whole pieces
+        const bool cut = may_split && form != 0 && form != 2;        // the largest tile and form 2 are never cut
+        for (int s = 1; s <= 16 && s <= (cut ? pairs : 1); ++s) {
+          if (s > 1 && (pairs % s != 0 || tiles_of(form) * s > 640)) continue;
+          if (s == 1 && form != 0 && tiles_of(form) > 2048) continue;
+          offer(form, s, tiled_us(form, s, M, N, d));
         }
       }
+      // Form 7, a cut in two that stays on the chip (it asks for the scratch of two pieces like any cut, so that a call
+      // without scratch keeps the uncut sum).  As a rule form 5's two workgroups a CU do the same (form 7 2 - 14 % slower
+      // on 500 shapes); where the last tile row is nearly empty and the k range long it is ahead: us, form 5 / 7, [257,
+      // 7168] x 2048 9.6 / 9.1, [129, 11264] x 1536 13.0 / 12.0, [130, 16384] x 512 17.4 / 15.3, [193, 9216] x 1024 11.1 / 10.5.
+      if (may_split && d % 1024 == 0 && d >= 24 * 256 && tiles_of(HALVED) <= 256 && (M - 1) % 64 < 8)
+        offer(HALVED, 2, 0.94 * tiled_us(5, 1, M, N, d));
     }
   }
   if (can_skinny) {
@@ -758,15 +803,11 @@ static int64_t choose_main_columns(int64_t M, int64_t N, int d, bool allow_split
   const double two = rounds_us(0, (double)(tiles_m * cols), KT) + tail.us;
   return two < 0.985 * one ? 256 * cols : N;
 }
-#ifndef GEMM_PLAN
-#define GEMM_PLAN(M_, N_, d_, allow_) choose_plan(M_, N_, d_, allow_)
-#endif
-
 // the plan of a product given the workspace it may use (a cut k range needs its pieces' fp32 tiles there)
 static GemmPlan plan_with(int64_t M, int64_t N, int d, bool allow_split, size_t workspace_bytes) {
-  GemmPlan plan = GEMM_PLAN(M, N, d, allow_split);
+  GemmPlan plan = choose_plan(M, N, d, allow_split);
   if (plan.splits > 1 && workspace_bytes < (size_t)plan.splits * (size_t)M * (size_t)N * sizeof(float))
-    plan = GEMM_PLAN(M, N, d, false);
+    plan = choose_plan(M, N, d, false);
   return plan;
 }
 
@@ -780,16 +821,17 @@ void mxfp4_gemm_plan(int64_t M, int64_t N, int d, size_t workspace_bytes, int *s
   GemmPlan plan = plan_with(M, N, d, d % 512 == 0, workspace_bytes);
   if (mxfp4_gemm_main_columns(M, N, d, workspace_bytes) < N) plan = GemmPlan{false, 0, 1, false, 0.0};   // the first launch
   *skinny = plan.skinny;
-  *tile_m = plan.skinny ? 0 : TILE_M[plan.cfg];
+  // a tile of 64 rows is half of one of 128 that two workgroups share
+  *tile_m = plan.skinny ? 0 : TILE_M[plan.cfg] < 128 ? 128 : TILE_M[plan.cfg];
   *tile_n = plan.skinny ? 16 : TILE_N[plan.cfg];
   *splits = plan.splits;
 }
 
 size_t mxfp4_gemm_workspace_bytes(int64_t M, int64_t N, int d) {
-  const GemmPlan plan = GEMM_PLAN(M, N, d, true);
+  const GemmPlan plan = choose_plan(M, N, d, true);
   const int64_t main_n = choose_main_columns(M, N, d, true, ~(size_t)0, plan);
   if (main_n < N) {
-    const GemmPlan tail = GEMM_PLAN(M, N - main_n, d, true);
+    const GemmPlan tail = choose_plan(M, N - main_n, d, true);
     return tail.splits > 1 ? (size_t)tail.splits * (size_t)M * (size_t)(N - main_n) * sizeof(float) : 0;
   }
   return plan.splits > 1 ? (size_t)plan.splits * (size_t)M * (size_t)N * sizeof(float) : 0;
@@ -802,16 +844,15 @@ static hipError_t launch_by_plan(const GemmPlan &plan, const uint8_t *A_q, const
                                  const uint8_t *W_s, void *out_bf16, int64_t M, int64_t N, int d, int64_t ldc,
                                  bool fullk, bool persist, float *partial, hipStream_t stream) {
   const int splits = plan.splits;
-  if ((splits > 1 || plan.deep || plan.cfg == 3) && !fullk) return hipErrorInvalidValue;
+  if ((splits > 1 || plan.deep || plan.cfg > 2) && !fullk) return hipErrorInvalidValue;
   if (splits > 1 && !partial) return hipErrorInvalidValue;
-  if (plan.deep && splits > 1)
-    return plan.cfg == 2   ? launch_tile<2, 2, true, true, true>(A_q, A_s, W_q, W_s, out_bf16, partial, splits, M, N, d, stream, 0, ldc)
-           : plan.cfg == 3 ? launch_tile<2, 1, true, true, true>(A_q, A_s, W_q, W_s, out_bf16, partial, splits, M, N, d, stream, 0, ldc)
-                           : hipErrorInvalidValue;
-  if (plan.deep)
-    return plan.cfg == 2   ? launch_tile<2, 2, true, false, true>(A_q, A_s, W_q, W_s, out_bf16, nullptr, 1, M, N, d, stream, 0, ldc)
-           : plan.cfg == 3 ? launch_tile<2, 1, true, false, true>(A_q, A_s, W_q, W_s, out_bf16, nullptr, 1, M, N, d, stream, 0, ldc)
-                           : hipErrorInvalidValue;
+  if (plan.cfg == HALVED)
+    return launch_mxfp4_gemm_ring(64, 64, 2, A_q, A_s, W_q, W_s, out_bf16, nullptr, 1, M, N, d, ldc, stream);
+  if (plan.cfg > 2 || (plan.cfg == 2 && splits > 1)) {
+    const hipError_t e = launch_mxfp4_gemm_ring(TILE_M[plan.cfg], TILE_N[plan.cfg], 1, A_q, A_s, W_q, W_s, out_bf16, partial, splits,
+                                                M, N, d, ldc, stream);
+    return splits > 1 && e == hipSuccess ? launch_splitk_reduce(partial, splits, M, N, ldc, out_bf16, stream) : e;
+  }
 #define TORQ_GEMM_LAUNCH(WM_, WN_)                                                                             \
   if (persist && splits == 1 && fullk && ldc == N &&                                                           \
       persistent_pays(((M + 64 * WM_ - 1) / (64 * WM_)) * ((N + 64 * WN_ - 1) / (64 * WN_)), d))               \
@@ -824,12 +865,9 @@ static hipError_t launch_by_plan(const GemmPlan &plan, const uint8_t *A_q, const
 #undef TORQ_GEMM_LAUNCH
   // (two workgroups of the 128 x 128 tile share a CU: the persistent form, one per CU, measured slower)
   if (plan.cfg == 2)
-    return splits > 1 ? launch_tile<2, 2, true, true>(A_q, A_s, W_q, W_s, out_bf16, partial, splits, M, N, d, stream, 0, ldc)
-           : fullk    ? launch_tile<2, 2, true, false>(A_q, A_s, W_q, W_s, out_bf16, nullptr, 1, M, N, d, stream, 0, ldc)
-                      : launch_tile<2, 2, false, false>(A_q, A_s, W_q, W_s, out_bf16, nullptr, 1, M, N, d, stream, 0, ldc);
-  if (plan.cfg == 3)
-    return splits > 1 ? launch_tile<2, 1, true, true>(A_q, A_s, W_q, W_s, out_bf16, partial, splits, M, N, d, stream, 0, ldc)
-                      : launch_tile<2, 1, true, false>(A_q, A_s, W_q, W_s, out_bf16, nullptr, 1, M, N, d, stream, 0, ldc);
+    return plan.deep ? launch_tile<2, 2, true, false, true>(A_q, A_s, W_q, W_s, out_bf16, nullptr, 1, M, N, d, stream, 0, ldc)
+           : fullk   ? launch_tile<2, 2, true, false>(A_q, A_s, W_q, W_s, out_bf16, nullptr, 1, M, N, d, stream, 0, ldc)
+                     : launch_tile<2, 2, false, false>(A_q, A_s, W_q, W_s, out_bf16, nullptr, 1, M, N, d, stream, 0, ldc);
   return hipErrorInvalidValue;
 }
 
@@ -844,7 +882,7 @@ static hipError_t launch_planned(const uint8_t *A_q, const uint8_t *A_s, const u
   }
   if (!fullk) {                                           // the plain form of the three larger tiles takes any d
     plan.deep = false;
-    if (plan.cfg == 3) plan.cfg = 2;
+    if (plan.cfg > 2) plan.cfg = 2;
   }
   return launch_by_plan(plan, A_q, A_s, W_q, W_s, out_bf16, M, N, d, ldc, fullk, true, static_cast<float *>(workspace), stream);
 }
@@ -862,8 +900,28 @@ hipError_t launch_mxfp4_gemm_forced(const uint8_t *A_q, const uint8_t *A_s, cons
     if (workspace_bytes < (size_t)k_pieces * (size_t)M * (size_t)N * sizeof(float)) return hipErrorInvalidValue;
   }
   if (deep && tile < 2) return hipErrorInvalidValue;
-  const GemmPlan plan{false, tile, k_pieces, deep != 0, 0.0};
+  const GemmPlan plan{false, tile, k_pieces, deep != 0 && tile == 2 && k_pieces == 1, 0.0};
   return launch_by_plan(plan, A_q, A_s, W_q, W_s, out_bf16, M, N, d, N, fullk, false, static_cast<float *>(workspace), stream);
+}
+
+// torq_diag_gemm_ring: the form staged in a ring, whatever the planner would take
+hipError_t launch_mxfp4_gemm_ring_forced(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q, const uint8_t *W_s,
+                                         void *out_bf16, int64_t M, int64_t N, int d, int tile_m, int tile_n, int k_pieces,
+                                         int on_chip, void *workspace, size_t workspace_bytes, hipStream_t stream) {
+  if ((int64_t)d * 128 >= 0x7FFFFFFF || d % 512 != 0 || k_pieces < 1) return hipErrorInvalidValue;
+  if ((reinterpret_cast<uintptr_t>(A_s) & 15u) || (reinterpret_cast<uintptr_t>(W_s) & 15u)) return hipErrorInvalidValue;
+  if (on_chip)
+    return tile_m != 64 || tile_n != 64 || k_pieces != 2 || d % 1024 != 0
+               ? hipErrorInvalidValue
+               : launch_mxfp4_gemm_ring(64, 64, 2, A_q, A_s, W_q, W_s, out_bf16, nullptr, 1, M, N, d, N, stream);
+  if (k_pieces > 1 && ((d / 512) % k_pieces != 0 || N % 8 != 0 || !workspace ||
+                       workspace_bytes < (size_t)k_pieces * (size_t)M * (size_t)N * sizeof(float)))
+    return hipErrorInvalidValue;
+  for (int form = 3; form < HALVED; ++form)
+    if (TILE_M[form] == tile_m && TILE_N[form] == tile_n)
+      return launch_by_plan(GemmPlan{false, form, k_pieces, false, 0.0}, A_q, A_s, W_q, W_s, out_bf16, M, N, d, N, true, false,
+                            static_cast<float *>(workspace), stream);
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_mxfp4_gemm(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q,

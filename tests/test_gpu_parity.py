@@ -357,6 +357,37 @@ def test_gemm_every_plan_of_the_tiled_kernel(tq, oracle, M, N, d):
                 assert torch.equal(deep.view(torch.int16), got.view(torch.int16)), (tile, k_pieces)
 
 
+# The form staged in a ring, every tile: fewer iterations than stages, an odd number of pairs, ragged edges, tile counts
+# that are and are not multiples of 8, and cuts (k halved inside the workgroup among them).  The uncut sums are
+# mxfp4_gemm's bit for bit, a cut's are those of the other tiled forms cut alike.
+@pytest.mark.parametrize("M,N,d", [(1, 8, 512), (64, 64, 512), (65, 129, 1024), (200, 264, 1536), (128, 1024, 2048), (300, 72, 5120)])
+def test_gemm_ring_every_tile(tq, oracle, M, N, d):
+    rng = np.random.default_rng(M * 7 + N + d)
+    A_q = rng.integers(0, 256, size=(M, d // 2), dtype=np.uint8)
+    W_q = rng.integers(0, 256, size=(N, d // 2), dtype=np.uint8)
+    A_s = rng.integers(118, 136, size=(M, d // 32), dtype=np.uint8)
+    W_s = rng.integers(110, 126, size=(N, d // 32), dtype=np.uint8)
+    want = oracle.gemm(A_q, A_s, W_q, W_s)
+    dev = [torch.from_numpy(a).to(DEV) for a in (A_q, A_s, W_q, W_s)]
+    plain = tq.torq_diag_gemm_plan(*dev, tile=0)
+    torch.cuda.synchronize()
+    _assert_every_output_within_one_ulp(_bits(plain), want)
+    for k_pieces in range(1, d // 512 + 1):
+        if (d // 512) % k_pieces or (k_pieces > 1 and N % 8):
+            continue
+        ref = plain if k_pieces == 1 else tq.torq_diag_gemm_plan(*dev, tile=1, k_pieces=k_pieces)
+        for tile_m, tile_n in ((128, 128), (128, 64), (64, 128), (64, 64)):
+            out = torch.full((M + 1, N), 7.0, dtype=torch.bfloat16, device=DEV)
+            tq.torq_diag_gemm_ring(*dev, tile_m, tile_n, k_pieces, out=out[:M])
+            torch.cuda.synchronize()
+            assert torch.equal(out[:M].view(torch.int16), ref.view(torch.int16)), (tile_m, tile_n, k_pieces)
+            assert torch.all(out[M] == 7.0)
+        if k_pieces == 2 and d % 1024 == 0:
+            halved = tq.torq_diag_gemm_ring(*dev, 64, 64, 2, on_chip=True)
+            torch.cuda.synchronize()
+            assert torch.equal(halved.view(torch.int16), ref.view(torch.int16))
+
+
 def test_gemm_plan_diagnostic_rejects_what_a_form_cannot_take(tq):
     M, N, d = 64, 72, 640                                  # d is not a whole number of 512-element pieces
     z = lambda *shape: torch.zeros(shape, dtype=torch.uint8, device=DEV)

@@ -72,6 +72,35 @@ def test_ring_loop_holds_exactly_the_counted_memory_instructions(ring_kernels):
         assert waits[0] == 0 and sorted(waits[1:]) == [0, 4, 8, 12, 12, 12], (name, waits)
 
 
+# ---- mxfp4_gemm_ring_kernel: its waits count the younger requests in the same way.
+def test_gemm_ring_loop_holds_exactly_the_counted_requests():
+    with tempfile.TemporaryDirectory() as tmp:
+        text = open(build.device_asm("mxfp4_gemm_ring.hip", os.path.join(tmp, "ring.s"))).read()
+    seen = 0
+    for m in re.finditer(r"^(_ZN4torq22mxfp4_gemm_ring_kernelILi(\d)ELi(\d)ELi(\d)\w+):(.*?)^\.Lfunc_end", text, re.M | re.S):
+        name, wm, wn, groups, body = m.group(1), int(m.group(2)), int(m.group(3)), int(m.group(4)), m.group(5)
+        seen += 1
+        assert re.search(r"\.name:\s+" + name + r"\n(?:.*\n)*?\s+\.private_segment_fixed_size:\s+0\n", text), name
+        code = [line.split(";")[0].strip() for line in body.splitlines()]
+        code = [c for c in code if c]
+        barriers = [i for i, c in enumerate(code) if c == "s_barrier"]
+        codes = 2 * wm + 2 * wn                            # 128 bytes of 64 wm + 64 wn rows, 8 rows a request, 4 waves
+        is_lds = lambda c: c.startswith("buffer_load_dwordx4") and c.endswith("lds")
+        # ahead of the loop: four iterations and two pairs' scale bytes; the wait leaves all but the first of each
+        assert sum(map(is_lds, code[:barriers[0]])) == 4 * codes + 2, name
+        top = next(i for i, c in enumerate(code) if c.startswith(".LBB") and i > barriers[0] and any(x.startswith("v_mfma") for x in code[i:i + 12]))
+        end = next(i for i, c in enumerate(code) if c.startswith("s_cbranch") and i > barriers[2])
+        loop = code[top:end]
+        vmem = [c for c in loop if re.match(r"(buffer_|global_|flat_|scratch_)", c)]
+        assert len(vmem) == 2 * codes + 1 and all(map(is_lds, vmem)), (name, len(vmem))
+        first = next(i for i, c in enumerate(loop) if c == "s_barrier")
+        second = next(i for i, c in enumerate(loop) if c == "s_barrier" and i > first)
+        assert sum(map(is_lds, loop[first:second])) == codes and sum(map(is_lds, loop[second:])) == codes + 1, name
+        waits = [int(re.search(r"vmcnt\((\d+)\)", c).group(1)) for c in code if "vmcnt(" in c and c.startswith("s_waitcnt")]
+        assert waits[:4] == [3 * codes + 1, 2 * codes + 1, 2 * codes, 0], (name, waits)
+    assert seen == 10
+
+
 # ---- torq_linear_local_kernel (mxfp4_gemm_skinny.hip): not correctness but the point of the kernel.  The
 # rotation's reads are issued ahead of the workgroup's weight reads and its LDS stores must wait for them
 # alone -- s_waitcnt vmcnt(N) with N >= the number of weight loads behind them.  A load that the compiler
