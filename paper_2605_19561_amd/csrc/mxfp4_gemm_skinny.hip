@@ -113,9 +113,9 @@ template <int MT, int NS, int PT, bool PERSIST = false>
 __global__ void __launch_bounds__(64 * WAVES)
 mxfp4_gemm_skinny_kernel(const uint8_t *__restrict__ A_q, const uint8_t *__restrict__ A_s,
                          const uint8_t *__restrict__ W_q, const uint8_t *__restrict__ W_s,
-                         uint16_t *__restrict__ out, int M, int64_t N, int d) {
+                         uint16_t *__restrict__ out, int M, int64_t N, int d, int wide) {
   // dynamic LDS: scale bytes of the weight strips (16 NS rows) and of the activation rows (16 MT),
-  // d / 32 bytes each, every row padded by 4 bytes (the lanes of a k-step read one byte of 16
+  // d / 32 bytes each, every row padded by 4 or 16 bytes (the lanes of a k-step read one byte of 16
   // different rows); the waves' partial tiles are overlaid on it after the k loop
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -129,27 +129,34 @@ mxfp4_gemm_skinny_kernel(const uint8_t *__restrict__ A_q, const uint8_t *__restr
   const int c_voff = r16 * row_bytes + q * 16;     // codes: + 64 per k-step
 
   // ---- scales: copied to LDS by buffer loads with an LDS destination (no registers, nothing to
-  // wait for before the code loads go out).  Such an instruction writes lane l's dword at
-  // (base + 4 l), the global address per lane is free: LDS dword j of a region is (row j / pd,
-  // column j % pd) of the padded layout, the pad column and rows past the end load zeros.
-  const int sdw = srow_bytes / 4;                  // dwords per scale row
-  const int pd = sdw + 1;                          // padded
-  const int w_ins = (16 * NS * pd + 63) / 64;      // instructions (256 bytes each) for the weight strips
-  const int a_ins = (16 * MT * pd + 63) / 64;      // ... and for the activation rows
+  // wait for before the code loads go out).  Such an instruction writes lane l's 4 or 16 bytes at (base + 4 l or
+  // 16 l), the global address per lane is free: unit j of a region is (row j / pu, column j % pu) of the padded layout,
+  // the pad column and rows past the end load zeros.  Their addresses hold the code loads up, so units of 16 bytes (wide)
+  // take a quarter of the instructions where the rows allow it (us, by 4 and by 16, weights from HBM: [16, 28672] x 8192
+  // 29.8 -> 28.3, [16, 4096] x 14336 10.0 -> 9.5, [45, 8192] x 5120 13.9 -> 13.3, [1, 14336] x 4096 9.6 -> 9.1; issued
+  // behind the codes instead they come last and everything waits for them, [16, 8192] x 8192 10.7 -> 12.5).
+  const int unit = wide ? 16 : 4;
+  const int pu = srow_bytes / unit + 1;            // units per padded row
+  const int pd = pu * unit / 4;                    // dwords per padded row
+  const int w_ins = (16 * NS * pu + 63) / 64;      // instructions for the weight strips
+  const int a_ins = (16 * MT * pu + 63) / 64;      // ... and for the activation rows
   const int ws_off = r16 * pd * 4 + q;             // this lane's scale byte: + 4 per k-step
-  const int as_off = w_ins * 256 + r16 * pd * 4 + q;
+  const int as_off = w_ins * 64 * unit + r16 * pd * 4 + q;
   // the waves' partial tiles: over the scales (one group per workgroup), behind them (PERSIST:
   // the activations' scale bytes stay)
-  unsigned char *const red_mem = PERSIST ? smem + (w_ins + a_ins) * 256 : smem;
+  unsigned char *const red_mem = PERSIST ? smem + (w_ins + a_ins) * 64 * unit : smem;
 
+  // j / pu in float: j < 2^17 and a quotient at least 1 / (2 pu) from an integer, pu < 2^11
+  const float per_unit = __builtin_amdgcn_rcpf((float)pu);
   auto load_scales = [&](int i0, int i1, const __amdgpu_buffer_rsrc_t ws_rs) {
     for (int i = i0 + wave; i < i1; i += WAVES) {
       const bool is_w = i < w_ins;
       const int j = (is_w ? i : i - w_ins) * 64 + lane;
-      const int row = j / pd, col = j - row * pd;
-      const bool ok = col < sdw && row < (is_w ? 16 * NS : 16 * MT);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(is_w ? ws_rs : as_rsrc, LDSP(smem + i * 256), 4,
-                                               ok ? row * srow_bytes + col * 4 : OOB_VOFF, 0, 0, 0);
+      const int row = (int)(((float)j + 0.5f) * per_unit), col = j - row * pu;
+      const bool ok = col < pu - 1 && row < (is_w ? 16 * NS : 16 * MT);
+      const int voff = ok ? row * srow_bytes + col * unit : OOB_VOFF;
+      if (wide) __builtin_amdgcn_raw_ptr_buffer_load_lds(is_w ? ws_rs : as_rsrc, LDSP(smem + i * 1024), 16, voff, 0, 0, 0);
+      else __builtin_amdgcn_raw_ptr_buffer_load_lds(is_w ? ws_rs : as_rsrc, LDSP(smem + i * 256), 4, voff, 0, 0, 0);
     }
   };
   // the activation codes of the k-steps of the trip that starts at line pair p0_
@@ -645,10 +652,15 @@ torq_linear_local_kernel(const uint4 *__restrict__ x, int TG, int G, const uint4
 #undef TORQ_LOAD_W
 }
 
-static size_t skinny_lds_bytes(int MT, int NS, int d) {
-  const int pd = d / 128 + 1;                      // padded dwords per scale row
-  const size_t scale_bytes = (size_t)((16 * NS * pd + 63) / 64 + (16 * MT * pd + 63) / 64) * 256;
-  const size_t red_bytes = (size_t)WAVES * NS * MT * 4 * 64 * sizeof(float);
+// the scale bytes in LDS, copied by units of 4 or 16 bytes
+static size_t skinny_scale_bytes(int MT, int NS, int d, int unit = 4) {
+  const int pu = d / 32 / unit + 1;                // units per padded row
+  return (size_t)((16 * NS * pu + 63) / 64 + (16 * MT * pu + 63) / 64) * 64 * unit;
+}
+static size_t skinny_red_bytes(int MT, int NS) { return (size_t)WAVES * NS * MT * 4 * 64 * sizeof(float); }
+
+static size_t skinny_lds_bytes(int MT, int NS, int d, int unit = 4) {
+  const size_t scale_bytes = skinny_scale_bytes(MT, NS, d, unit), red_bytes = skinny_red_bytes(MT, NS);
   return scale_bytes > red_bytes ? scale_bytes : red_bytes;
 }
 
@@ -657,8 +669,7 @@ static hipError_t launch_cfg(const uint8_t *A_q, const uint8_t *A_s, const uint8
                              void *out, int64_t M, int64_t N, int d, hipStream_t stream, const DecodeArgs *fused) {
   const int64_t groups = (N + 16 * NS - 1) / (16 * NS);
   if (groups > 0x7FFFFFF0) return hipErrorInvalidValue;
-  const int pd = d / 128 + 1;                      // padded dwords per scale row
-  const size_t scale_bytes = (size_t)((16 * NS * pd + 63) / 64 + (16 * MT * pd + 63) / 64) * 256;
+  const size_t scale_bytes = skinny_scale_bytes(MT, NS, d);
   size_t lds_bytes = skinny_lds_bytes(MT, NS, d);
   if constexpr (NS <= 2 && PT <= (MT + NS <= 3 ? 4 : 2)) if (fused) {
     // + the "ready" word behind the scales; at least the rotation's four token-group places
@@ -686,17 +697,24 @@ static hipError_t launch_cfg(const uint8_t *A_q, const uint8_t *A_s, const uint8
   // evenly loaded: 3 or 7 groups per workgroup measured 15 - 20 % slower than 4, and half as many
   // workgroups as CUs 30 % slower than one each).
   const int KP = (d / 128 + 1) / 2;
-  const size_t p_bytes = scale_bytes + (size_t)WAVES * NS * MT * 4 * 64 * sizeof(float);
-  if constexpr (MT == 1) if (M >= 8 && KP <= PT * WAVES && (double)N * (double)d * 0.53125 >= 24e6 && p_bytes <= 64 * 1024) {
+  // the scale bytes by units of 16 where their rows allow it and the LDS has room for the wider padding
+  const bool rows16 = d % 512 == 0 && ((reinterpret_cast<uintptr_t>(A_s) | reinterpret_cast<uintptr_t>(W_s)) & 15u) == 0;
+  const size_t red_bytes = skinny_red_bytes(MT, NS);
+  if constexpr (MT == 1) if (M >= 8 && KP <= PT * WAVES && (double)N * (double)d * 0.53125 >= 24e6 && scale_bytes + red_bytes <= 64 * 1024) {
+    const size_t p_wide = skinny_scale_bytes(MT, NS, d, 16) + red_bytes;
+    const bool wide = rows16 && p_wide <= 64 * 1024;
+    const size_t p_bytes = wide ? p_wide : scale_bytes + red_bytes;
     int64_t per = 1;
     while ((groups + per - 1) / per > 256) per *= 2;
     if (per > 1) {
       const int64_t grid = (groups + per - 1) / per;
       hipLaunchKernelGGL((mxfp4_gemm_skinny_kernel<MT, NS, PT, true>), dim3((unsigned)grid), dim3(64 * WAVES), p_bytes,
-                         stream, A_q, A_s, W_q, W_s, reinterpret_cast<uint16_t *>(out), (int)M, N, d);
+                         stream, A_q, A_s, W_q, W_s, reinterpret_cast<uint16_t *>(out), (int)M, N, d, (int)wide);
       return hipGetLastError();
     }
   }
+  const bool wide = rows16 && skinny_lds_bytes(MT, NS, d, 16) <= SKINNY_MAX_LDS;
+  if (wide) lds_bytes = skinny_lds_bytes(MT, NS, d, 16);
   if (lds_bytes > SKINNY_MAX_LDS) return hipErrorInvalidValue;
   if (lds_bytes > 64 * 1024) {
     static std::atomic<uint64_t> raised{0};
@@ -705,7 +723,7 @@ static hipError_t launch_cfg(const uint8_t *A_q, const uint8_t *A_s, const uint8
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((mxfp4_gemm_skinny_kernel<MT, NS, PT>), dim3((unsigned)groups), dim3(64 * WAVES), lds_bytes,
-                     stream, A_q, A_s, W_q, W_s, reinterpret_cast<uint16_t *>(out), (int)M, N, d);
+                     stream, A_q, A_s, W_q, W_s, reinterpret_cast<uint16_t *>(out), (int)M, N, d, (int)wide);
   return hipGetLastError();
 }
 
