@@ -22,12 +22,12 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
 # The rotate kernel post-processes its MFMA results with vector ALU code, so its accumulators are
 # kept in ordinary VGPRs (no v_accvgpr_read traffic); the GEMM needs the AGPR half for its tile.
 # rotate_quant.hip writes m0 in inline assembly (the LDS address of a buffer load into LDS) and says so in the
-# clobber list (mxfp4_gemm_ring.hip the same); the compiler warns about every such statement, since it reserves m0 for itself -- nothing
+# clobber list (mxfp4_gemm_ring.hip and the whole-line kernel of mxfp4_gemm_skinny.hip the same); the compiler warns about every such statement, since it reserves m0 for itself -- nothing
 # else in that kernel uses it.
 EXTRA = {"rotate_quant.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-Wno-inline-asm"],
          "mxfp4_gemm_ring.hip": ["-Wno-inline-asm"],
          "rotate_butterfly.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
-         "mxfp4_gemm_skinny.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+         "mxfp4_gemm_skinny.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-Wno-inline-asm"]}
 
 
 def device_asm(source: str, out_path: str) -> str:

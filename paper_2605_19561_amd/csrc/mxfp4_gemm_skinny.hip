@@ -652,6 +652,11 @@ torq_linear_local_kernel(const uint4 *__restrict__ x, int TG, int G, const uint4
 #undef TORQ_LOAD_W
 }
 
+// scale rows of whole 16-byte units
+static bool rows16(const uint8_t *A_s, const uint8_t *W_s, int d) {
+  return d % 512 == 0 && ((reinterpret_cast<uintptr_t>(A_s) | reinterpret_cast<uintptr_t>(W_s)) & 15u) == 0;
+}
+
 // the scale bytes in LDS, copied by units of 4 or 16 bytes
 static size_t skinny_scale_bytes(int MT, int NS, int d, int unit = 4) {
   const int pu = d / 32 / unit + 1;                // units per padded row
@@ -662,6 +667,201 @@ static size_t skinny_red_bytes(int MT, int NS) { return (size_t)WAVES * NS * MT 
 static size_t skinny_lds_bytes(int MT, int NS, int d, int unit = 4) {
   const size_t scale_bytes = skinny_scale_bytes(MT, NS, d, unit), red_bytes = skinny_red_bytes(MT, NS);
   return scale_bytes > red_bytes ? scale_bytes : red_bytes;
+}
+
+// ---------------------------------------------------------------------------------------------
+// The same product where a CU has at most one workgroup's strips to stream (up to 256 workgroups): whole lines.
+// An operand load of the kernel above touches 16 rows of 64 bytes, half a line each, and what a CU can have on its way is
+// counted in lines (measured: a strip of 16 rows x 4 KB in 1.6 us by half lines, 1.1 by whole ones).  Here a load is 8
+// rows of 128 bytes straight into LDS, where the operand layout is picked up again; the ring of R items (a line pair of
+// the NS strips and of the MT activation tiles) is the wave's own, so nothing in the k loop waits for another wave.
+// Same k-steps, same order, same bits.
+template <int N>
+__device__ __forceinline__ void lines_wait() {
+  asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
+}
+// 16 bytes per lane from rsrc[voff + soff] to LDS byte lds_addr + 16 * lane
+__device__ __forceinline__ void lines_dma(i32x4 rsrc, uint32_t lds_addr, int voff, int soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "m0", "memory");
+}
+__device__ __forceinline__ i32x4 lines_rsrc(const uint8_t *p, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  return i32x4{(int)(uint32_t)a, (int)((uint32_t)(a >> 32) & 0xFFFFu), (int)bytes, 0x00020000};
+}
+
+template <int MT, int NS, int R>
+__global__ void __launch_bounds__(64 * WAVES)
+mxfp4_gemm_lines_kernel(const uint8_t *__restrict__ A_q, const uint8_t *__restrict__ A_s, const uint8_t *__restrict__ W_q,
+                        const uint8_t *__restrict__ W_s, uint16_t *__restrict__ out, int M, int64_t N, int d, int pad) {
+  constexpr int T = NS + MT, OPS = 2 * T, ITEM = T * 2048;          // tiles, DMA instructions and bytes of an item
+  static_assert(R * OPS <= 63, "the counter of loads in flight has six bits");
+  // LDS: [rings | scale rows of the strips, then of the activation tiles, 16 bytes of padding each (pad = 1) where there
+  // is room]; the waves' partial tiles over the rings at the end
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, q = lane >> 4;
+  const int row_bytes = d / 2, srow_bytes = d / 32, KP = d / 256;   // d is a multiple of 512
+  const int64_t n0 = (int64_t)blockIdx.x * (16 * NS);
+  const int rows_w = (N - n0 < 16 * NS) ? (int)(N - n0) : 16 * NS;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
+  const uint32_t sc0 = lds0 + WAVES * R * ITEM;
+  const unsigned char *const sc = smem + WAVES * R * ITEM;
+
+  // ---- scale rows first: unit j of 16 bytes is (row j / pu, column j % pu), the pad column loads zeros
+  const int pu = srow_bytes / 16 + pad, s_pitch = pu * 16;
+  const int w_units = 16 * NS * pu, units = w_units + 16 * MT * pu;
+  {
+    const i32x4 ws_rs = lines_rsrc(W_s + n0 * srow_bytes, (uint32_t)rows_w * srow_bytes);
+    const i32x4 as_rs = lines_rsrc(A_s, (uint32_t)M * srow_bytes);
+    const float per_unit = __builtin_amdgcn_rcpf((float)pu);        // (j / pu in float, as above)
+    for (int i = wave; i * 64 < units; i += WAVES) {
+      const int j = i * 64 + lane;
+      const int row = (int)(((float)j + 0.5f) * per_unit), col = j - row * pu;
+      const bool ok = col < srow_bytes / 16;
+      // the lanes of an instruction may straddle the strips' and the tiles' rows: one masked load from each buffer, and
+      // where only one is needed the other is an empty one
+      const bool is_w = row < 16 * NS;
+      if (i * 64 < w_units)
+        { if (is_w) lines_dma(ws_rs, sc0 + i * 1024, ok ? row * srow_bytes + col * 16 : OOB_VOFF, 0); }
+      if (i * 64 + 63 >= w_units)
+        { if (!is_w) lines_dma(as_rs, sc0 + i * 1024, ok ? (row - 16 * NS) * srow_bytes + col * 16 : OOB_VOFF, 0); }
+    }
+  }
+
+  // ---- items: line pair kp = wave, wave + 8, ...; chunks swizzled by the row, as the reads below expect
+  const i32x4 w_rs = lines_rsrc(W_q + n0 * row_bytes, (uint32_t)rows_w * row_bytes);
+  const i32x4 a_rs = lines_rsrc(A_q, (uint32_t)M * row_bytes);
+  const int l_row = lane >> 3;
+  const int v0 = l_row * row_bytes + ((lane & 7) ^ (l_row >> 1)) * 16, v1 = (l_row + 8) * row_bytes + ((lane & 7) ^ (l_row >> 1) ^ 4) * 16;
+  const uint32_t ring0 = lds0 + wave * R * ITEM;
+  const unsigned char *const ring = smem + wave * R * ITEM;
+  auto request = [&](int kp, int slot) {
+    const bool ok = kp < KP;                                        // past the k range: empty buffers, the counts hold
+    i32x4 rw = w_rs, ra = a_rs;
+    rw[2] = ok ? rw[2] : 0;
+    ra[2] = ok ? ra[2] : 0;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const int so = (t < NS ? t : t - NS) * 16 * row_bytes + kp * 128;
+      lines_dma(t < NS ? rw : ra, ring0 + slot * ITEM + t * 2048, v0, so);
+      lines_dma(t < NS ? rw : ra, ring0 + slot * ITEM + t * 2048 + 1024, v1, so);
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < R; ++i) request(wave + i * WAVES, i);
+
+  f32x4 acc[NS][MT];
+#pragma unroll
+  for (int n = 0; n < NS; ++n)
+#pragma unroll
+    for (int t = 0; t < MT; ++t) acc[n][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  lines_wait<R * OPS>();                                            // this wave's scale bytes have landed
+  asm volatile("s_barrier" ::: "memory");
+
+  const int f_off[2] = {r16 * 128 + ((q ^ ((r16 >> 1) & 7)) * 16), r16 * 128 + (((4 + q) ^ ((r16 >> 1) & 7)) * 16)};
+  int slot = 0;
+  for (int kp = wave; kp < KP; kp += WAVES) {
+    lines_wait<(R - 1) * OPS>();                                    // the oldest item has landed
+    u32x4 f[2][T];
+    int fs[2][T];
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        f[e][t] = *reinterpret_cast<const u32x4 *>(ring + slot * ITEM + t * 2048 + f_off[e]);
+        fs[e][t] = sc[(t * 16 + r16) * s_pitch + (2 * kp + e) * 4 + q];
+      }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");              // read: the slot can be filled again
+    request(kp + R * WAVES, slot);
+    slot = slot + 1 == R ? 0 : slot + 1;
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int n = 0; n < NS; ++n)
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+          acc[n][t] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
+              i32x8{(int)f[e][n][0], (int)f[e][n][1], (int)f[e][n][2], (int)f[e][n][3], 0, 0, 0, 0},
+              i32x8{(int)f[e][NS + t][0], (int)f[e][NS + t][1], (int)f[e][NS + t][2], (int)f[e][NS + t][3], 0, 0, 0, 0},
+              acc[n][t], 4, 4, 0, fs[e][n], 0, fs[e][NS + t]);
+  }
+  lines_wait<0>();                                                  // nothing is on its way into the LDS any more
+  skinny_reduce_store<MT, NS>(acc, smem, out, M, N, n0, wave, lane);
+}
+
+static size_t lines_lds_bytes(int MT, int NS, int R, int d, int pad) {
+  const size_t units = (size_t)16 * (NS + MT) * (d / 512 + pad), rings = (size_t)WAVES * R * (NS + MT) * 2048;
+  const size_t bytes = rings + (units + 63) / 64 * 1024, red = skinny_red_bytes(MT, NS);
+  return bytes > red ? bytes : red;
+}
+
+// the deepest ring with room for the scale rows: 4 items of two tiles, 3 (2) of three, 2 (1) of four, 1 of five to eight;
+// 0: none
+static int lines_ring(int MT, int NS, int d) {
+  const int T = NS + MT, most = T == 2 ? 4 : T == 3 ? 3 : T == 4 ? 2 : T <= 8 ? 1 : 0;
+  for (int R = most; R >= 1 && R >= most - 1; --R)
+    if (lines_lds_bytes(MT, NS, R, d, 0) <= SKINNY_MAX_LDS) return R;
+  return 0;
+}
+
+// Strips per workgroup of the whole-line form, 0 where it does not take the product (d a multiple of 512, 16-byte
+// aligned scale rows): as few as leave a CU at most one workgroup, which keeps every CU busy and reads the activations
+// once a CU.  It is ahead almost everywhere it fits, the more the more rows and the longer the k range; us, the other
+// form against this one, weights from HBM: [16, 8192] x 1024 6.6 / 4.6, [16, 8192] x 8192 10.1 / 9.9, [16, 28672] x 8192
+// 28.9 / 23.2, [16, 8192] x 28672 28.4 / 26.0, [45, 5120] x 8192 10.6 / 8.5, [45, 8192] x 5120 13.2 / 9.9, [64, 4096] x
+// 4096 8.0 / 5.3, [1, 14336] x 4096 9.0 / 8.4, [1, 4096] x 14336 8.7 / 8.2.  Short k ranges leave its waves idle (one
+// line pair each is 2048 elements) and have it wait for its scale bytes: up to d = 1024 it takes only many rows, or from
+// 17 rows on more than one strip a CU ([16, 1024] x 2048 0.9 times as fast, [40, 1024] x 5120 1.2, [64, 512] x 128 1.06);
+// below 8 rows the other form also keeps d = 2048 (0.94 - 1.04) and rows a multiple of 4 KB apart past 448 strips
+// ([1, 8192] x 28672 0.93, [1, 16384] x 16384 0.91: all workgroups walk the same columns, whose lines share channels).
+// Three strips of one activation tile: four measured up to 6 % ahead (two items of four tiles in the ring, one of three).
+int mxfp4_gemm_lines_strips(int64_t M, int64_t N, int d) {
+  if (M < 1 || M > 64 || d % 512 != 0) return 0;
+  const int MT = (int)((M + 15) / 16);
+  const int64_t strips = (N + 15) / 16;
+  if (strips > 7 * 256) return 0;
+  int NS = (int)((strips + 255) / 256);
+  if (MT == 1 && NS == 3) NS = 4;
+  if (NS + MT > 8 || lines_ring(MT, NS, d) == 0) return 0;
+  const bool pays = MT == 4   ? true
+                    : MT == 3 ? d >= 1024 || strips > 256
+                    : MT == 2 ? d >= 2048 || (strips > 256 && strips <= 1024)
+                    : M >= 8  ? d >= 2048
+                              : d >= 3072 && (d % 8192 != 0 || strips <= 448);
+  return pays ? NS : 0;
+}
+
+template <int MT, int NS, int R>
+static hipError_t launch_lines(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q, const uint8_t *W_s, void *out, int64_t M,
+                               int64_t N, int d, hipStream_t stream) {
+  const int pad = lines_lds_bytes(MT, NS, R, d, 1) <= SKINNY_MAX_LDS ? 1 : 0;
+  const size_t lds = lines_lds_bytes(MT, NS, R, d, pad);
+  if (lds > 64 * 1024) {
+    static std::atomic<uint64_t> raised{0};
+    const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(mxfp4_gemm_lines_kernel<MT, NS, R>), SKINNY_MAX_LDS, raised);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((mxfp4_gemm_lines_kernel<MT, NS, R>), dim3((unsigned)((N + 16 * NS - 1) / (16 * NS))), dim3(64 * WAVES), lds,
+                     stream, A_q, A_s, W_q, W_s, reinterpret_cast<uint16_t *>(out), (int)M, N, d, pad);
+  return hipGetLastError();
+}
+
+template <int MT>
+static hipError_t launch_lines_mt(int NS, const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q, const uint8_t *W_s, void *out,
+                                  int64_t M, int64_t N, int d, hipStream_t stream) {
+  const int R = lines_ring(MT, NS, d);
+#define TORQ_LINES(NS_)                                                                                                     \
+  if constexpr (NS_ + MT <= 8)                                                                                              \
+    if (NS == NS_) {                                                                                                        \
+      constexpr int T = NS_ + MT, MOST = T == 2 ? 4 : T == 3 ? 3 : T == 4 ? 2 : 1;                                          \
+      if (R == MOST) return launch_lines<MT, NS_, MOST>(A_q, A_s, W_q, W_s, out, M, N, d, stream);                          \
+      if constexpr (MOST > 1) if (R == MOST - 1) return launch_lines<MT, NS_, MOST - 1>(A_q, A_s, W_q, W_s, out, M, N, d, stream); \
+    }
+  TORQ_LINES(1) TORQ_LINES(2) TORQ_LINES(3) TORQ_LINES(4) TORQ_LINES(5) TORQ_LINES(6) TORQ_LINES(7)
+#undef TORQ_LINES
+  return hipErrorInvalidValue;
 }
 
 template <int MT, int NS, int PT>
@@ -698,11 +898,11 @@ static hipError_t launch_cfg(const uint8_t *A_q, const uint8_t *A_s, const uint8
   // workgroups as CUs 30 % slower than one each).
   const int KP = (d / 128 + 1) / 2;
   // the scale bytes by units of 16 where their rows allow it and the LDS has room for the wider padding
-  const bool rows16 = d % 512 == 0 && ((reinterpret_cast<uintptr_t>(A_s) | reinterpret_cast<uintptr_t>(W_s)) & 15u) == 0;
+  const bool by16 = rows16(A_s, W_s, d);
   const size_t red_bytes = skinny_red_bytes(MT, NS);
   if constexpr (MT == 1) if (M >= 8 && KP <= PT * WAVES && (double)N * (double)d * 0.53125 >= 24e6 && scale_bytes + red_bytes <= 64 * 1024) {
     const size_t p_wide = skinny_scale_bytes(MT, NS, d, 16) + red_bytes;
-    const bool wide = rows16 && p_wide <= 64 * 1024;
+    const bool wide = by16 && p_wide <= 64 * 1024;
     const size_t p_bytes = wide ? p_wide : scale_bytes + red_bytes;
     int64_t per = 1;
     while ((groups + per - 1) / per > 256) per *= 2;
@@ -713,7 +913,7 @@ static hipError_t launch_cfg(const uint8_t *A_q, const uint8_t *A_s, const uint8
       return hipGetLastError();
     }
   }
-  const bool wide = rows16 && skinny_lds_bytes(MT, NS, d, 16) <= SKINNY_MAX_LDS;
+  const bool wide = by16 && skinny_lds_bytes(MT, NS, d, 16) <= SKINNY_MAX_LDS;
   if (wide) lds_bytes = skinny_lds_bytes(MT, NS, d, 16);
   if (lds_bytes > SKINNY_MAX_LDS) return hipErrorInvalidValue;
   if (lds_bytes > 64 * 1024) {
@@ -777,6 +977,8 @@ static hipError_t launch_mt(const uint8_t *A_q, const uint8_t *A_s, const uint8_
       return launch_mt_ns<MT, (MT <= 2 ? 2 : 1)>(A_q, A_s, W_q, W_s, out, M, N, d, stream, fused);
     return launch_mt_ns<MT, 1>(A_q, A_s, W_q, W_s, out, M, N, d, stream, fused);
   }
+  if (const int lines = rows16(A_s, W_s, d) ? mxfp4_gemm_lines_strips(M, N, d) : 0)
+    return launch_lines_mt<MT>(lines, A_q, A_s, W_q, W_s, out, M, N, d, stream);
   const int NS = mxfp4_gemm_skinny_strips(M, N, d);
   const int pairs_per_wave = ((d / 128 + 1) / 2 + WAVES - 1) / WAVES;
   if constexpr (MT >= 2) {

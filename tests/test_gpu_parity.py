@@ -297,6 +297,32 @@ def test_gemm_weight_streaming_strips(tq, oracle, M, N, d):
     test_gemm_random_codes(tq, oracle, M, N, d)
 
 
+# The streaming kernel's whole-line form: every ring depth (two to eight tiles an item, long and short k ranges), waves
+# without a line pair, ragged rows and strips, scale rows without room for padding.  Its bits are those of the form by half
+# lines, which scale rows off the 16-byte grid still take.
+@pytest.mark.parametrize("M,N,d", [
+    (1, 16, 3072), (3, 1000, 3584), (16, 4099, 2048), (7, 4100, 28672), (16, 4112, 4096), (8, 8200, 28672), (9, 12300, 2048),
+    (16, 16400, 2048), (12, 20490, 2048), (16, 28672, 8192), (17, 40, 2048), (32, 4104, 1024), (20, 9000, 2048), (31, 14000, 2048),
+    (33, 70, 1024), (48, 5000, 2048), (40, 10000, 5120), (49, 8, 512), (64, 4100, 4096), (64, 8190, 2048)])
+def test_gemm_weight_streaming_by_whole_lines(tq, oracle, M, N, d):
+    assert tq.mxfp4_gemm_plan(M, N, d)[0], "this shape is meant to take the weight-streaming kernel"
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(M + N + d)
+    draw = lambda lo, hi, *shape: torch.randint(lo, hi, shape, dtype=torch.uint8, device=DEV, generator=gen)
+    A_q, W_q, A_s, W_s = draw(0, 256, M, d // 2), draw(0, 256, N, d // 2), draw(118, 136, M, d // 32), draw(110, 126, N, d // 32)
+    out = torch.full((M + 1, N), 7.0, dtype=torch.bfloat16, device=DEV)
+    tq.mxfp4_gemm(A_q, A_s, W_q, W_s, out=out[:M])
+    off = torch.empty(A_s.numel() + 4, dtype=torch.uint8, device=DEV)
+    off[4:] = A_s.flatten()
+    other = tq.mxfp4_gemm(A_q, off[4:].view(M, d // 32), W_q, W_s)
+    torch.cuda.synchronize()
+    assert torch.equal(out[:M].view(torch.int16), other.view(torch.int16))
+    assert torch.all(out[M] == 7.0)
+    cols = sorted({0, min(15, N - 1), N // 2, N - 1})
+    want = oracle.gemm(A_q.cpu().numpy(), A_s.cpu().numpy(), W_q[cols].cpu().numpy(), W_s[cols].cpu().numpy())
+    _assert_every_output_within_one_ulp(_bits(out[:M][:, cols].contiguous()), want)
+
+
 def _random_gemm_shapes(n, seed):
     rng = np.random.default_rng(seed)
     return [(int(rng.integers(1, 700)), int(rng.integers(1, 900)), 128 * int(rng.integers(1, 17))) for _ in range(n)]

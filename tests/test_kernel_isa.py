@@ -101,6 +101,28 @@ def test_gemm_ring_loop_holds_exactly_the_counted_requests():
     assert seen == 10
 
 
+# ---- mxfp4_gemm_lines_kernel (mxfp4_gemm_skinny.hip): "the oldest item has landed" is a count of the younger requests.
+def test_lines_loop_holds_exactly_the_counted_requests():
+    with tempfile.TemporaryDirectory() as tmp:
+        text = open(build.device_asm("mxfp4_gemm_skinny.hip", os.path.join(tmp, "skinny.s"))).read()
+    seen = 0
+    for m in re.finditer(r"^(_ZN4torq23mxfp4_gemm_lines_kernelILi(\d)ELi(\d)ELi(\d)\w+):(.*?)^\.Lfunc_end", text, re.M | re.S):
+        name, ops, ring, body = m.group(1), 2 * (int(m.group(2)) + int(m.group(3))), int(m.group(4)), m.group(5)
+        seen += 1
+        assert re.search(r"\.name:\s+" + name + r"\n(?:.*\n)*?\s+\.private_segment_fixed_size:\s+0\n", text), name
+        code = [c for c in (line.split(";")[0].strip() for line in body.splitlines()) if c]
+        waits = [(i, int(re.search(r"vmcnt\((\d+)\)", c).group(1))) for i, c in enumerate(code) if c.startswith("s_waitcnt") and "vmcnt(" in c]
+        assert [n for _, n in waits][:3] == [ring * ops, (ring - 1) * ops, 0], (name, waits)
+        is_lds = lambda c: c.startswith("buffer_load_dwordx4") and c.endswith("lds")
+        top = waits[1][0]
+        end = next(i for i, c in enumerate(code) if c.startswith("s_cbranch") and i > top)
+        vmem = [c for c in code[top:end] if re.match(r"(buffer_|global_|flat_|scratch_)", c)]
+        assert len(vmem) == ops and all(map(is_lds, vmem)), (name, len(vmem))
+        # the ring's first items lie between the scale bytes' requests (in a loop) and the first wait
+        assert sum(map(is_lds, code[:waits[0][0]])) == ring * ops + 2, name
+    assert seen == 28
+
+
 # ---- torq_linear_local_kernel (mxfp4_gemm_skinny.hip): not correctness but the point of the kernel.  The
 # rotation's reads are issued ahead of the workgroup's weight reads and its LDS stores must wait for them
 # alone -- s_waitcnt vmcnt(N) with N >= the number of weight loads behind them.  A load that the compiler
