@@ -611,6 +611,14 @@ def test_linear_is_rotate_quantize_then_gemm(tq, oracle):
 
 # --------------------------------------------------------------- graphs ------
 
+def test_calls_launch_on_the_current_stream(tq):
+    side = torch.cuda.Stream()
+    assert tq._stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert tq._stream() == side.cuda_stream
+    assert tq._stream(side) == side.cuda_stream != tq._stream()
+
+
 def test_linear_replays_from_a_hip_graph(tq):
     # Every entry point only enqueues kernels on the caller's stream and allocates nothing, so a
     # serving loop can capture it.  The graph is replayed several times, with eager work and
