@@ -71,10 +71,14 @@ rotate_kernel(const uint4 *__restrict__ x, int64_t TG, int G,
 // staging registers three waves fit a SIMD up to G = 128 (160 registers), which is worth 5 - 15 %
 // there and a few per cent beyond; at G <= 80 the register path measured faster (and fits three
 // waves per SIMD from G = 64 up as it is).
-// TB: token-groups per batch, processed together (2: every MFMA has an independent neighbour; 1 for a
-// handful of token-groups, where the shortest path through one token-group counts).
-template <int KS16, int TB, int FMT>
-__global__ void __launch_bounds__(64 * ((KS16 + 1) / 2), (KS16 >= 4 && KS16 <= 8) ? 3 : 2)   // waves per SIMD
+// TB: token-groups per batch, processed together (2: every MFMA has an independent neighbour; 1 where
+// token-groups are few and the shortest path through one counts).
+// ALONE: a workgroup is one wave and has one tile of 32 output blocks, workgroup b tile b mod NW; it stages
+// the token-group for itself, always global -> LDS directly.  For a handful of token-groups: the CU loads its
+// own slice of R_inter, 8 KB to 16 KB, not all of them (and as consecutive workgroups go to the XCDs in turn, an
+// L2 holds NW / 8 of the table rather than all of it).
+template <int KS16, int TB, bool ALONE, int FMT>
+__global__ void __launch_bounds__(ALONE ? 64 : 64 * ((KS16 + 1) / 2), (KS16 >= 4 && KS16 <= 8) ? 3 : 2)   // waves per SIMD
 rotate_kernel32(const uint4 *__restrict__ x, int64_t TG, int G,
                 const uint16_t *__restrict__ inter_hi, const uint16_t *__restrict__ inter_lo,
                 const uint4 *__restrict__ intra_hi_frag, const uint4 *__restrict__ intra_lo_frag,
@@ -87,16 +91,16 @@ rotate_kernel32(const uint4 *__restrict__ x, int64_t TG, int G,
   constexpr int NW = (KS16 + 1) / 2;
   constexpr bool ODD = (KS16 & 1) != 0;
   constexpr int TG_BYTES = KS16 * 16 * 64;           // one token-group: G rows of 64 bytes
-  constexpr int NTHR = 64 * NW;
+  constexpr int NTHR = ALONE ? 64 : 64 * NW;
   constexpr int CHUNKS = TG_BYTES / 16;
-  constexpr int CH = (CHUNKS + NTHR - 1) / NTHR;     // 16-byte chunks per thread per token-group (= 2)
-  constexpr int TG_STRIDE = CH * NTHR * 16;          // = TG_BYTES unless KS16 is odd
+  constexpr int CH = (CHUNKS + NTHR - 1) / NTHR;     // 16-byte chunks per thread per token-group (= 2; ALONE: KS16)
+  constexpr int TG_STRIDE = CH * NTHR * 16;          // = TG_BYTES unless KS16 is odd (ALONE: always)
   constexpr int STAGE_BYTES = TB * TG_STRIDE;
-  constexpr bool DMA = KS16 >= 6;
+  constexpr bool DMA = ALONE || KS16 >= 6;
   extern __shared__ __attribute__((aligned(16))) char lds[];
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = ALONE ? (int)(blockIdx.x % NW) : tid >> 6;
   const int col = lane & 31, h = lane >> 5;
 
   // ---- resident operands: R_inter from the handle's table in lane order ([tile][k-step 2 NW][lane][8],
@@ -146,7 +150,7 @@ rotate_kernel32(const uint4 *__restrict__ x, int64_t TG, int G,
   // the direct form: lane l of wave w fills LDS chunk 64 w + l (+ NTHR i) of a token-group, which is
   // the chunk of the same index in global memory; a token-group past the end reads as zeros through
   // an empty descriptor
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+  const int wave_u = ALONE ? 0 : __builtin_amdgcn_readfirstlane(wave);
   auto dma_batch = [&](int64_t b_, int buf_) {
 #pragma unroll
     for (int j = 0; j < TB; ++j) {
@@ -162,7 +166,8 @@ rotate_kernel32(const uint4 *__restrict__ x, int64_t TG, int G,
     }
   };
 
-  int64_t batch = blockIdx.x;
+  const int64_t stride = ALONE ? gridDim.x / NW : gridDim.x;
+  int64_t batch = ALONE ? blockIdx.x / NW : blockIdx.x;
   if (batch < nbatch) {
     if constexpr (DMA) {
       dma_batch(batch, 0);
@@ -174,8 +179,8 @@ rotate_kernel32(const uint4 *__restrict__ x, int64_t TG, int G,
   if constexpr (!DMA) __syncthreads();
 
   int buf = 0;
-  for (; batch < nbatch; batch += gridDim.x, buf ^= 1) {
-    const int64_t next = batch + gridDim.x;
+  for (; batch < nbatch; batch += stride, buf ^= 1) {
+    const int64_t next = batch + stride;
     const bool have_next = next < nbatch;
     if constexpr (DMA) {
       // this wave's part of the batch has landed (vmcnt(0)), then everybody's; the barrier also says
@@ -608,10 +613,11 @@ static int64_t balanced_grid(int64_t nbatch, int per_cu) {
   return (nbatch + rounds - 1) / rounds;
 }
 
-template <int KS16, int TB = 2>
+template <int KS16, int TB = 2, bool ALONE = false>
 static hipError_t launch_cfg32(const torq_rotation *r, const void *x, int64_t TG, int format, float global_scale,
                                uint8_t *codes, uint8_t *scales, float *z_out, hipStream_t stream) {
-  const int nw = (KS16 + 1) / 2;                         // = ceil(G / 32)
+  constexpr int tiles = (KS16 + 1) / 2;                  // = ceil(G / 32)
+  const int nw = ALONE ? 1 : tiles;
   const int64_t nbatch = (TG + TB - 1) / TB;
   // a token-group's place in LDS: a whole number of 16-byte chunks per thread (padded when KS16 is odd)
   const size_t tg_stride = (size_t)((KS16 * 64 + 64 * nw - 1) / (64 * nw)) * (64 * nw) * 16;
@@ -622,11 +628,11 @@ static hipError_t launch_cfg32(const torq_rotation *r, const void *x, int64_t TG
   int per_cu = (int)((160 * 1024) / lds_bytes);
   if (per_cu * nw > waves_per_cu) per_cu = waves_per_cu / nw;
   if (per_cu < 1) per_cu = 1;
-  const int64_t grid = balanced_grid(nbatch, per_cu);
+  const int64_t grid = ALONE ? tiles * nbatch : balanced_grid(nbatch, per_cu);
   const uint4 *ih = reinterpret_cast<const uint4 *>(r->intra32_hi);
   const uint4 *il = reinterpret_cast<const uint4 *>(r->intra32_lo);
   const uint16_t *ri_hi = r->inter32f_hi, *ri_lo = r->inter32f_lo;      // the table in lane order
-  TORQ_LAUNCH_FMT(rotate_kernel32, uint2, KS16, TB)
+  TORQ_LAUNCH_FMT(rotate_kernel32, uint2, KS16, TB, ALONE)
 }
 
 template <int KS16>
@@ -681,6 +687,22 @@ hipError_t launch_rotate(const torq_rotation *r, const void *x_bf16, int64_t M, 
                          uint8_t *codes, uint8_t *scales, float *z_out, hipStream_t stream) {
   const int64_t TG = M * (int64_t)(r->d / 32 / r->G);
   if (TG == 0) return hipSuccess;
+  // A handful of token-groups, G = 64 ... 128: every 32 output blocks of a token-group by a workgroup of one
+  // wave (rotate_kernel32, ALONE) while that leaves each CU no more than one of them.  The kernel is then a
+  // chain of launch, operand loads and 30 MFMAs, and a CU that holds all the waves of a token-group waits
+  // for the whole of R_inter (64 KB at G = 128) where it could wait for one tile of it.  Cold operands, HIP-graph
+  // replays, us before / now: G = 128 at 1 to 32 token-groups 3.0 / 2.6, at 64 3.0 / 2.85; G = 112 2.9 / 2.5;
+  // G = 96 at 16 3.05 / 2.5; G = 80 2.7 / 2.45; G = 64 2.9 / 2.35; the fp32 output gains 0.4 to 1.1.  With two
+  // workgroups per CU the gain is gone where the tiles are many (G = 128 at 128 token-groups 3.1 / 3.3, G = 112
+  // 3.0 / 3.0) and small elsewhere (G = 96 3.15 / 2.85); with four it is a loss (G = 128 at 256 3.3 / 4.1).
+  if (TG * ((r->G + 31) / 32) <= 256) {
+    switch (r->G) {
+#define TORQ_ALONE(K16_) \
+  case 16 * K16_: return launch_cfg32<K16_, 1, true>(r, x_bf16, TG, format, global_scale, codes, scales, z_out, stream);
+      TORQ_ALONE(4) TORQ_ALONE(5) TORQ_ALONE(6) TORQ_ALONE(7) TORQ_ALONE(8)
+#undef TORQ_ALONE
+    }
+  }
   constexpr int64_t RING_MIN_TG = 2 * 8 * 3 * 256;       // eight batches for each of the ring's 768 workgroups
   // quantising, G = 80 ... 128, large inputs: the three-buffer form of the 32x32x16 kernel.  Below eight
   // batches per workgroup the two batches requested ahead of the loop cost more than the ring saves (same

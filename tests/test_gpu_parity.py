@@ -1037,6 +1037,23 @@ def test_quantize_fmt_mxfp4_is_the_plain_entry_point(tq):
     assert torch.equal(c0, c1) and torch.equal(s0, s1)
 
 
+# the last row count that takes a wave per workgroup (rows * ceil(G / 32) <= 256) and the first that does not
+@pytest.mark.parametrize("d,G,rows", [(4096, 128, 64), (3584, 112, 64), (3072, 96, 85), (2560, 80, 85), (2048, 64, 128),
+                                      (8192, 128, 1), (5120, 80, 7)])
+@pytest.mark.parametrize("fmt", [0, 1, 2])
+def test_few_token_groups_give_the_rows_of_a_larger_call(tq, oracle, d, G, rows, fmt):
+    # every output is a function of its own token-group, computed in the same order in every launch shape
+    x = synth.activations(1024, d, nu=3.0, outliers=6, outlier_scale=50.0, seed=900 + G).to(DEV)
+    rot = tq.Rotation(d, G, *synth.rotations(G, seed=91 + G))
+    c, s = tq.torq_rotate_quantize_fmt(rot, x, fmt, 0.05)
+    z = tq.torq_rotate(rot, x)
+    for M in (rows, rows + 1):
+        guard = torch.zeros((M + 1, d // 2), dtype=torch.uint8, device=DEV)
+        few, fs = tq.torq_rotate_quantize_fmt(rot, x[:M], fmt, 0.05, codes=guard[:M])
+        assert torch.equal(few, c[:M]) and torch.equal(fs, s[:M]) and int(guard[M].sum()) == 0
+        assert torch.equal(tq.torq_rotate(rot, x[:M]).view(torch.int32), z[:M].view(torch.int32))
+
+
 @pytest.mark.parametrize("d,G", [(4096, 128), (14336, 112), (5120, 80), (2048, 64), (1024, 32), (512, 16)])
 @pytest.mark.parametrize("fmt", [1, 2])
 def test_rotate_quantize_fmt_is_rotate_then_quantize(tq, oracle, d, G, fmt):
