@@ -12,13 +12,16 @@
 // eight positions at a time with whole-dword AND / shift / ADD into nibble-packed counters (nine
 // logic operations and seven additions per dword).  The eight codeword counts follow from the
 // monomial sums and the number of blocks by inclusion-exclusion, once, in the final kernel.
-// Nibble counters hold 15, so after 15 blocks they are widened into byte-packed counters, which
-// hold 255 = 17 such chunks; then the workgroup adds its lanes' byte counters through LDS into
-// 32-bit per-thread totals.  Loads are buffer loads in groups of five with two groups in flight
+// Nibble counters hold 15: after 12 blocks the lanes of the wave are added by the matrix cores
+// (add_lanes), into 32-bit sums.  Loads are buffer loads in groups of four with two groups in flight
 // beyond the one being counted; a block past the end of the input reads as zeros (the buffer's range
-// check), and a zero nibble adds to no monomial.  Every workgroup writes its 224 totals; the final kernel adds them (integers: any order
-// gives the same result).
-// HBM bound: half a byte per element, read once.
+// check), and a zero nibble adds to no monomial.  Every workgroup writes its 224 totals; the final kernel
+// adds them (integers: any order gives the same result).
+// HBM bound: half a byte per element, read once; the counting is 64 vector operations per block and
+// wave, 3.4 us of the vector units' time at 2^21 blocks, beside 6 us of reading.  What follows the last load is
+// not hidden by anything, so it is kept short.  An earlier form widened the nibbles into byte counters after
+// 15 blocks and added the lanes through LDS: 14.7 us for the
+// call at 2^21 blocks (codes of [8192, 8192]), 7.5 us at 512; this one 11.8 us and 5.6 us.
 #include "torq_device.h"
 #include "torq_internal.h"
 
@@ -26,19 +29,19 @@ namespace torq {
 
 constexpr int HIST_THREADS = 256;
 constexpr int HIST_MAX_WG = 512;          // two resident workgroups per CU: one round
-constexpr int HIST_GROUP = 5;             // blocks per lane per group of loads
-constexpr int HIST_CHUNK = 3 * HIST_GROUP; // blocks per lane before a nibble counter could overflow
-constexpr int HIST_WIDEN_PER_PASS = 17;   // chunks before a byte counter could overflow
+constexpr int HIST_GROUP = 4;             // blocks per lane per group of loads
+constexpr int HIST_CHUNK = 3 * HIST_GROUP; // blocks per lane between two additions of the lanes
 constexpr int HIST_MONO = 7;
-constexpr int HIST_WORDS = 2 * HIST_MONO * 4;  // byte-packed counter words per lane
+constexpr int HIST_QUADS = 2 * HIST_MONO; // quadruples of byte words per lane, one matrix product each
 constexpr int HIST_PARTIAL = HIST_MONO * 32;   // per workgroup: [monomial][position]
-static_assert(HIST_CHUNK <= 15 && HIST_CHUNK * HIST_WIDEN_PER_PASS <= 255, "counter widths");
+static_assert(HIST_CHUNK <= 15, "counter width");
 
 typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
+typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4_t;
 
 __global__ void __launch_bounds__(HIST_THREADS)
 code_histogram_kernel(const uint8_t *__restrict__ codes, int64_t nblk, uint32_t *__restrict__ partial) {
-  __shared__ __attribute__((aligned(16))) uint32_t lds[HIST_WORDS][HIST_THREADS];   // byte counters of every lane
+  __shared__ uint32_t lds[HIST_THREADS / 16][HIST_PARTIAL];
 
   const int tid = threadIdx.x;
   const int64_t lanes = (int64_t)gridDim.x * HIST_THREADS;
@@ -63,7 +66,7 @@ code_histogram_kernel(const uint8_t *__restrict__ codes, int64_t nblk, uint32_t 
     for (int i = 0; i < HIST_GROUP; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, i * ROW_BYTES, 0);
   };
 
-  uint32_t nib[HIST_MONO][4], bytes[HIST_WORDS];
+  uint32_t nib[HIST_MONO][4];
   auto count_group = [&](const u32x4 (&v)[HIST_GROUP]) {
 #pragma unroll
     for (int i = 0; i < HIST_GROUP; ++i)
@@ -82,15 +85,33 @@ code_histogram_kernel(const uint8_t *__restrict__ codes, int64_t nblk, uint32_t 
       }
   };
 
-  // totals of two byte positions of one byte-counter word (see the workgroup sum below)
-  uint32_t tot_lo = 0, tot_hi = 0;
+  // Sums over lanes by v_mfma_i32_16x16x64_i8.  As A, lane l holds row l % 16 and, of the 64 k, the sixteen
+  // of its quarter l / 16: four words of byte counters, byte j of them k = 16 (l / 16) + j.  B has a one where
+  // k % 16 is the column, so D[row][j] += the byte j of the four lanes that share the row.  Quad 2 m has the even
+  // nibbles of monomial m (bytes 4 w + s: position 8 w + 2 s), 2 m + 1 the odd ones.
+  i32x4_t sum[HIST_QUADS];
 #pragma unroll
-  for (int i = 0; i < HIST_WORDS; ++i) bytes[i] = 0;
+  for (int q = 0; q < HIST_QUADS; ++q) sum[q] = i32x4_t{0, 0, 0, 0};
+  i32x4_t pick;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) pick[w] = ((tid & 15) >> 2) == w ? 1 << (8 * (tid & 3)) : 0;
+  auto add_lanes = [&]() {
+#pragma unroll
+    for (int m = 0; m < HIST_MONO; ++m) {
+      i32x4_t even, odd;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        even[w] = (int)(nib[m][w] & KB);
+        odd[w] = (int)((nib[m][w] >> 4) & KB);
+      }
+      sum[2 * m] = __builtin_amdgcn_mfma_i32_16x16x64_i8(even, pick, sum[2 * m], 0, 0, 0);
+      sum[2 * m + 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(odd, pick, sum[2 * m + 1], 0, 0, 0);
+    }
+  };
 
   u32x4 v0[HIST_GROUP], v1[HIST_GROUP], v2[HIST_GROUP];   // two groups in flight beyond the one being counted
   load_group(v0, 0);
   load_group(v1, 1);
-  int widened = 0;
   for (int g = 0; g < ngroup; g += 3) {
 #pragma unroll
     for (int m = 0; m < HIST_MONO; ++m)
@@ -102,81 +123,49 @@ code_histogram_kernel(const uint8_t *__restrict__ codes, int64_t nblk, uint32_t 
     if (g + 1 < ngroup) count_group(v1);
     load_group(v1, g + 4);
     if (g + 2 < ngroup) count_group(v2);
-    // 15 blocks at most: nibble counters -> byte counters, word 2 a = the even nibbles, 2 a + 1 the odd
-#pragma unroll
-    for (int m = 0; m < HIST_MONO; ++m)
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        bytes[2 * (m * 4 + w)] += nib[m][w] & KB;
-        bytes[2 * (m * 4 + w) + 1] += (nib[m][w] >> 4) & KB;
-      }
-    ++widened;
-    if (widened < HIST_WIDEN_PER_PASS && g + 3 < ngroup) continue;
-    widened = 0;
-
-    // workgroup sum of the byte counters, two 16-bit fields at a time (256 x 255 < 65536): thread
-    // t < 224 adds bytes (h, h + 2) of word r over the lanes 128 g .. 128 g + 127, t = 4 r + 2 h + g,
-    // and the two lane halves meet in a neighbour exchange
-#pragma unroll
-    for (int i = 0; i < HIST_WORDS; ++i) {
-      lds[i][tid] = bytes[i];
-      bytes[i] = 0;
-    }
-    __syncthreads();
-    {
-      const int r = (tid >> 2) % HIST_WORDS, shift = 8 * ((tid >> 1) & 1), l0 = 128 * (tid & 1);
-      uint32_t acc = 0;
-#pragma unroll 4
-      for (int j = 0; j < 32; ++j) {
-        // four lanes per read; staggered so that the lanes of a wave spread over the banks
-        const u32x4 q = *reinterpret_cast<const u32x4 *>(&lds[r][l0 + 4 * ((j + tid) & 31)]);
-        acc += ((q[0] >> shift) & 0x00FF00FFu) + ((q[1] >> shift) & 0x00FF00FFu) +
-               ((q[2] >> shift) & 0x00FF00FFu) + ((q[3] >> shift) & 0x00FF00FFu);
-      }
-      acc += __shfl_xor(acc, 1);
-      tot_lo += acc & 0xFFFFu;
-      tot_hi += acc >> 16;
-    }
-    __syncthreads();
+    add_lanes();
   }
 
-  if (tid < HIST_PARTIAL && (tid & 1) == 0) {
-    // word r = 2 (m * 4 + w) + odd; byte s of it counts nibble 2 s + odd of dword w: position
-    // k = 8 w + 2 s + odd.  This thread holds s = h (tot_lo) and s = h + 2 (tot_hi).  The partial
-    // sums are stored counter-major, [counter][workgroup], for the final kernel's coalesced reads.
-    const int r = tid >> 2, odd = r & 1, a = r >> 1, m = a >> 2, w = a & 3, h = (tid >> 1) & 1;
-    const int k = 8 * w + odd + 2 * h;
-    partial[(size_t)(m * 32 + k) * HIST_MAX_WG + blockIdx.x] = tot_lo;
-    partial[(size_t)(m * 32 + k + 4) * HIST_MAX_WG + blockIdx.x] = tot_hi;
+  // D: lane l holds column l % 16, rows 4 (l / 16) + r.  Sixteen partial sums per column and quad are left in the
+  // workgroup, one per quarter of a wave.
+#pragma unroll
+  for (int q = 0; q < HIST_QUADS; ++q) lds[tid >> 4][16 * q + (tid & 15)] = sum[q][0] + sum[q][1] + sum[q][2] + sum[q][3];
+  __syncthreads();
+  if (tid < HIST_PARTIAL) {
+    uint32_t total = 0;
+#pragma unroll
+    for (int i = 0; i < HIST_THREADS / 16; ++i) total += lds[i][tid];
+    // byte 4 w + s of quad 2 m + odd.  The partial sums are stored counter-major, [counter][workgroup], for the
+    // final kernel's coalesced reads.
+    const int m = tid >> 5, odd = (tid >> 4) & 1, w = (tid >> 2) & 3, s = tid & 3;
+    partial[(size_t)(m * 32 + 8 * w + 2 * s + odd) * HIST_MAX_WG + blockIdx.x] = total;
   }
 }
 
-// Workgroup k of 32, 1024 threads: thread (monomial m = t / 128, slice = t % 128) adds the partial
-// sums of the workgroups slice, slice + 128, ... (at most 8 of them, all loads in flight at once),
-// the 128 slices are added through LDS in a fixed order, and eight threads turn
+// Workgroup k of 32, a wave per monomial m (and an idle eighth): each lane adds the partial sums of eight
+// workgroups, the wave adds its lanes, and eight threads turn
 // (N, s0, s1, s2, s01, s02, s12, s012) into the eight codeword counts of position k by
-// inclusion-exclusion.
-__global__ void __launch_bounds__(1024)
+// inclusion-exclusion.  All latency: the launch, one trip to memory, the wave's six exchanges.  (With 128 slices
+// added in LDS by one thread per monomial it took 3.8 us of a call at 2^21 blocks, this takes about 2.5.)
+__global__ void __launch_bounds__(512)
 code_histogram_final_kernel(const uint32_t *__restrict__ partial, int n_partial, uint64_t nblk,
                             uint64_t *__restrict__ counts) {
-  __shared__ uint64_t part[8][128];
   __shared__ uint64_t s[8];
-  const int tid = threadIdx.x, k = blockIdx.x, m = tid >> 7, slice = tid & 127;
-  uint64_t acc = 0;
+  const int tid = threadIdx.x, k = blockIdx.x, m = tid >> 6, lane = tid & 63;
   if (m < HIST_MONO) {
-    const uint32_t *src = partial + (size_t)(m * 32 + k) * HIST_MAX_WG;
-    uint32_t v[HIST_MAX_WG / 128];
+    const u32x4 *src = reinterpret_cast<const u32x4 *>(partial + (size_t)(m * 32 + k) * HIST_MAX_WG);
+    u32x4 v[HIST_MAX_WG / 256];
 #pragma unroll
-    for (int i = 0; i < HIST_MAX_WG / 128; ++i) v[i] = (slice + 128 * i < n_partial) ? src[slice + 128 * i] : 0u;
+    for (int i = 0; i < HIST_MAX_WG / 256; ++i)
+      v[i] = (4 * lane + 256 * i < n_partial) ? src[lane + 64 * i] : u32x4{0, 0, 0, 0};
+    uint64_t acc = 0;
 #pragma unroll
-    for (int i = 0; i < HIST_MAX_WG / 128; ++i) acc += v[i];
-  }
-  part[m][slice] = acc;
-  __syncthreads();
-  if (tid < HIST_MONO) {
-    uint64_t t = 0;
-    for (int i = 0; i < 128; ++i) t += part[tid][i];
-    s[tid] = t;
+    for (int i = 0; i < HIST_MAX_WG / 256; ++i)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc += (4 * lane + 256 * i + c < n_partial) ? v[i][c] : 0u;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) acc += __shfl_xor((unsigned long long)acc, off);
+    if (lane == 0) s[m] = acc;
   }
   __syncthreads();
   if (tid < 8) {
@@ -201,15 +190,15 @@ size_t code_histogram_workspace_bytes() { return (size_t)HIST_MAX_WG * HIST_PART
 // nblk >= 0 blocks of 16 bytes (none: all counts zero); counts: 256 uint64 on the device; workspace as above
 hipError_t launch_code_histogram(const uint8_t *codes, int64_t nblk, uint64_t *counts, void *workspace,
                                  hipStream_t stream) {
-  // a workgroup per 256 * 15 blocks (one chunk per lane) while that leaves CUs free; beyond, all
+  // a workgroup per 256 * 4 blocks (one group of loads per lane) while that leaves CUs free; beyond, all
   // the workgroups that can be resident at once, each with a longer span
-  int64_t want = (nblk + (int64_t)HIST_THREADS * HIST_CHUNK - 1) / ((int64_t)HIST_THREADS * HIST_CHUNK);
+  int64_t want = (nblk + (int64_t)HIST_THREADS * HIST_GROUP - 1) / ((int64_t)HIST_THREADS * HIST_GROUP);
   const int n_wg = (int)(want < 1 ? 1 : (want > HIST_MAX_WG ? HIST_MAX_WG : want));
   uint32_t *partial = static_cast<uint32_t *>(workspace);
   hipLaunchKernelGGL(code_histogram_kernel, dim3(n_wg), dim3(HIST_THREADS), 0, stream, codes, nblk, partial);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(code_histogram_final_kernel, dim3(32), dim3(1024), 0, stream, partial, n_wg, (uint64_t)nblk,
+  hipLaunchKernelGGL(code_histogram_final_kernel, dim3(32), dim3(512), 0, stream, partial, n_wg, (uint64_t)nblk,
                      counts);
   return hipGetLastError();
 }

@@ -845,6 +845,16 @@ def test_code_histogram_against_oracle(tq, oracle, M, d):
     assert got.sum() == M * d
 
 
+# blocks: around one group of loads per lane of a workgroup (4 x 256), around all workgroups with one such group
+# (512 x 1024), and per lane one more than a whole number of chunks (12, 24), the last lanes without a block
+@pytest.mark.parametrize("nblk", [1023, 1024, 1025, 524287, 524289, 512 * 256 * 12 + 1, 512 * 256 * 24 + 1])
+def test_code_histogram_at_the_edges_of_groups_and_chunks(tq, oracle, nblk):
+    codes = torch.randint(0, 256, (nblk, 16), dtype=torch.uint8, generator=torch.Generator().manual_seed(nblk))
+    codes[nblk // 2:, 5] = 0x77         # counters that fill up unevenly
+    got = _np(tq.torq_code_histogram(codes.to(DEV), 32))
+    assert np.array_equal(got.astype(np.uint64), oracle.code_histogram(codes.numpy(), 32))
+
+
 def test_code_histogram_extremes(tq, oracle):
     d = 256
     for fill, code in ((0x00, 0), (0xFF, 7), (0x88, 0), (0x7F, 7), (0x25, None)):
