@@ -73,12 +73,18 @@ rotate_kernel(const uint4 *__restrict__ x, int64_t TG, int G,
 // waves per SIMD from G = 64 up as it is).
 // TB: token-groups per batch, processed together (2: every MFMA has an independent neighbour; 1 where
 // token-groups are few and the shortest path through one counts).
-// ALONE: a workgroup is one wave and has one tile of 32 output blocks, workgroup b tile b mod NW; it stages
-// the token-group for itself, always global -> LDS directly.  For a handful of token-groups: the CU loads its
-// own slice of R_inter, 8 KB to 16 KB, not all of them (and as consecutive workgroups go to the XCDs in turn, an
-// L2 holds NW / 8 of the table rather than all of it).
-template <int KS16, int TB, bool ALONE, int FMT>
-__global__ void __launch_bounds__(ALONE ? 64 : 64 * ((KS16 + 1) / 2), (KS16 >= 4 && KS16 <= 8) ? 3 : 2)   // waves per SIMD
+// FORM: ROT_LOOP, a workgroup takes batch after batch.
+//   ROT_ONCE, it has one: the batch is requested ahead of R_inter and staged through registers, so that the
+//   compiler counts the loads itself and the MFMAs of a k-step wait for that k-step's slice of R_inter and not for all
+//   64 KB (in a loop it waits for every operand in front of the loop, and so does the wait for loads into LDS).
+//   ROT_ALONE, as ROT_ONCE, and the workgroup is one wave with one tile of 32 output blocks, workgroup b tile
+//   b mod NW; it stages the token-group for itself.  For a handful of token-groups: the CU loads its
+//   own slice of R_inter, 8 KB to 16 KB, not all of them (and as consecutive workgroups go to the XCDs in turn, an
+//   L2 holds NW / 8 of the table rather than all of it).
+enum { ROT_LOOP = 0, ROT_ONCE = 1, ROT_ALONE = 2 };
+
+template <int KS16, int TB, int FORM, int FMT>
+__global__ void __launch_bounds__(FORM == ROT_ALONE ? 64 : 64 * ((KS16 + 1) / 2), (KS16 >= 4 && KS16 <= 8) ? 3 : 2)   // waves per SIMD
 rotate_kernel32(const uint4 *__restrict__ x, int64_t TG, int G,
                 const uint16_t *__restrict__ inter_hi, const uint16_t *__restrict__ inter_lo,
                 const uint4 *__restrict__ intra_hi_frag, const uint4 *__restrict__ intra_lo_frag,
@@ -89,6 +95,7 @@ rotate_kernel32(const uint4 *__restrict__ x, int64_t TG, int G,
   // is not a whole number of 16-byte chunks per thread, so its LDS place is padded to one
   // (TG_STRIDE); the chunks past its end load as zeros into the pad.
   constexpr int NW = (KS16 + 1) / 2;
+  constexpr bool ALONE = FORM == ROT_ALONE, ONCE = FORM != ROT_LOOP;
   constexpr bool ODD = (KS16 & 1) != 0;
   constexpr int TG_BYTES = KS16 * 16 * 64;           // one token-group: G rows of 64 bytes
   constexpr int NTHR = ALONE ? 64 : 64 * NW;
@@ -96,12 +103,71 @@ rotate_kernel32(const uint4 *__restrict__ x, int64_t TG, int G,
   constexpr int CH = (CHUNKS + NTHR - 1) / NTHR;     // 16-byte chunks per thread per token-group (= 2; ALONE: KS16)
   constexpr int TG_STRIDE = CH * NTHR * 16;          // = TG_BYTES unless KS16 is odd (ALONE: always)
   constexpr int STAGE_BYTES = TB * TG_STRIDE;
-  constexpr bool DMA = ALONE || KS16 >= 6;
+  constexpr bool DMA = KS16 >= 6;
   extern __shared__ __attribute__((aligned(16))) char lds[];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = ALONE ? (int)(blockIdx.x % NW) : tid >> 6;
   const int col = lane & 31, h = lane >> 5;
+
+  const int64_t nbatch = (TG + TB - 1) / TB;
+  // a token-group past the end reads as zeros through an empty descriptor, and so do the chunks past its own
+  auto rsrc_of = [&](int64_t tg) {
+    return __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char *>(reinterpret_cast<const char *>(x) + (tg < TG ? tg : 0) * (int64_t)TG_BYTES), 0,
+        tg < TG ? TG_BYTES : 0, 0x00020000);
+  };
+  i32x4 stage_regs[TB][CH];
+  auto load_batch = [&](int64_t batch) {
+#pragma unroll
+    for (int j = 0; j < TB; ++j) {
+      const __amdgpu_buffer_rsrc_t rs = rsrc_of(batch * TB + j);
+#pragma unroll
+      for (int i = 0; i < CH; ++i)
+        stage_regs[j][i] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (tid + i * NTHR) * 16, 0, 0));
+    }
+  };
+  auto store_batch = [&](int buf) {
+    char *base = lds + buf * STAGE_BYTES;
+#pragma unroll
+    for (int j = 0; j < TB; ++j)
+#pragma unroll
+      for (int i = 0; i < CH; ++i)
+        *reinterpret_cast<i32x4 *>(base + j * TG_STRIDE + (tid + i * NTHR) * 16) = stage_regs[j][i];
+  };
+
+  // the direct form: lane l of wave w fills LDS chunk 64 w + l (+ NTHR i) of a token-group, which is
+  // the chunk of the same index in global memory
+  const int wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);
+  auto dma_batch = [&](int64_t b_, int buf_) {
+#pragma unroll
+    for (int j = 0; j < TB; ++j) {
+      const __amdgpu_buffer_rsrc_t rs = rsrc_of(b_ * TB + j);
+#pragma unroll
+      for (int i = 0; i < CH; ++i)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            rs, (__attribute__((address_space(3))) void *)(lds + buf_ * STAGE_BYTES + j * TG_STRIDE + (wave_u * 64 + i * NTHR) * 16),
+            16, tid * 16, i * NTHR * 16, 0, 0);
+    }
+  };
+
+  const int64_t stride = ALONE ? gridDim.x / NW : gridDim.x;
+  int64_t batch = ALONE ? blockIdx.x / NW : blockIdx.x;
+  if (batch >= nbatch) return;                               // uniform over the workgroup
+  bf16x8 Ah[2], Al[2];
+  auto load_intra = [&]() {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      Ah[t] = __builtin_bit_cast(bf16x8, intra_hi_frag[t * 64 + lane]);
+      Al[t] = __builtin_bit_cast(bf16x8, intra_lo_frag[t * 64 + lane]);
+    }
+  };
+  if constexpr (ONCE) {
+    load_batch(batch);
+    __builtin_amdgcn_sched_barrier(0);
+    load_intra();
+    __builtin_amdgcn_sched_barrier(0);
+  }
 
   // ---- resident operands: R_inter from the handle's table in lane order ([tile][k-step 2 NW][lane][8],
   // zeros for the block rows and columns past G), one load of a wave = 1 KiB of consecutive bytes
@@ -114,75 +180,28 @@ rotate_kernel32(const uint4 *__restrict__ x, int64_t TG, int G,
       Bl[ks] = __builtin_bit_cast(bf16x8, fl[(wave * 2 * NW + ks) * 64 + lane]);
     }
   }
-  bf16x8 Ah[2], Al[2];
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    Ah[t] = __builtin_bit_cast(bf16x8, intra_hi_frag[t * 64 + lane]);
-    Al[t] = __builtin_bit_cast(bf16x8, intra_lo_frag[t * 64 + lane]);
-  }
 
   // transposing-read address of this lane inside a token-group (k-step 0, first half)
   const int blk = lane >> 4, s16 = lane & 15;
   const int tr_off = ((8 * (blk >> 1) + (s16 >> 2)) * 32 + 16 * (blk & 1) + 4 * (s16 & 3)) * 2;
 
-  const int64_t nbatch = (TG + TB - 1) / TB;
-  uint4 stage_regs[TB][CH];
-  auto load_batch = [&](int64_t batch) {
-#pragma unroll
-    for (int j = 0; j < TB; ++j) {
-      const int64_t tg = batch * TB + j;
-#pragma unroll
-      for (int i = 0; i < CH; ++i) {
-        if (tg < TG && (!ODD || tid + i * NTHR < CHUNKS)) stage_regs[j][i] = x[tg * (TG_BYTES / 16) + tid + i * NTHR];
-        else stage_regs[j][i] = make_uint4(0, 0, 0, 0);
-      }
-    }
-  };
-  auto store_batch = [&](int buf) {
-    char *base = lds + buf * STAGE_BYTES;
-#pragma unroll
-    for (int j = 0; j < TB; ++j)
-#pragma unroll
-      for (int i = 0; i < CH; ++i)
-        *reinterpret_cast<uint4 *>(base + j * TG_STRIDE + (tid + i * NTHR) * 16) = stage_regs[j][i];
-  };
-
-  // the direct form: lane l of wave w fills LDS chunk 64 w + l (+ NTHR i) of a token-group, which is
-  // the chunk of the same index in global memory; a token-group past the end reads as zeros through
-  // an empty descriptor
-  const int wave_u = ALONE ? 0 : __builtin_amdgcn_readfirstlane(wave);
-  auto dma_batch = [&](int64_t b_, int buf_) {
-#pragma unroll
-    for (int j = 0; j < TB; ++j) {
-      const int64_t tg = b_ * TB + j;
-      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<char *>(reinterpret_cast<const char *>(x) + (tg < TG ? tg : 0) * (int64_t)TG_BYTES), 0,
-          tg < TG ? TG_BYTES : 0, 0x00020000);
-#pragma unroll
-      for (int i = 0; i < CH; ++i)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            rs, (__attribute__((address_space(3))) void *)(lds + buf_ * STAGE_BYTES + j * TG_STRIDE + (wave_u * 64 + i * NTHR) * 16),
-            16, tid * 16, i * NTHR * 16, 0, 0);
-    }
-  };
-
-  const int64_t stride = ALONE ? gridDim.x / NW : gridDim.x;
-  int64_t batch = ALONE ? blockIdx.x / NW : blockIdx.x;
-  if (batch < nbatch) {
-    if constexpr (DMA) {
-      dma_batch(batch, 0);
-    } else {
-      load_batch(batch);
-      store_batch(0);
-    }
+  if constexpr (ONCE) {
+    __builtin_amdgcn_sched_barrier(0);                       // everything is requested before anything is waited for
+  } else {
+    load_intra();
+    if constexpr (DMA) dma_batch(batch, 0);
+    else load_batch(batch);
   }
-  if constexpr (!DMA) __syncthreads();
+  if constexpr (!DMA || ONCE) {
+    store_batch(0);
+    __syncthreads();
+  }
 
   int buf = 0;
-  for (; batch < nbatch; batch += stride, buf ^= 1) {
+  for (;; batch += stride, buf ^= 1) {
     const int64_t next = batch + stride;
-    const bool have_next = next < nbatch;
-    if constexpr (DMA) {
+    const bool have_next = !ONCE && next < nbatch;
+    if constexpr (DMA && !ONCE) {
       // this wave's part of the batch has landed (vmcnt(0)), then everybody's; the barrier also says
       // that every wave is done reading the other buffer
       __builtin_amdgcn_s_waitcnt(0x0F70);
@@ -298,8 +317,9 @@ rotate_kernel32(const uint4 *__restrict__ x, int64_t TG, int G,
       }
     }
 
+    if (!have_next) break;                                     // uniform over the workgroup
     if constexpr (!DMA) {
-      if (have_next) store_batch(buf ^ 1);
+      store_batch(buf ^ 1);
       __syncthreads();
     }
   }
@@ -613,12 +633,21 @@ static int64_t balanced_grid(int64_t nbatch, int per_cu) {
   return (nbatch + rounds - 1) / rounds;
 }
 
-template <int KS16, int TB = 2, bool ALONE = false>
+template <int KS16, int TB = 2, int FORM = ROT_LOOP>
 static hipError_t launch_cfg32(const torq_rotation *r, const void *x, int64_t TG, int format, float global_scale,
                                uint8_t *codes, uint8_t *scales, float *z_out, hipStream_t stream) {
   constexpr int tiles = (KS16 + 1) / 2;                  // = ceil(G / 32)
-  const int nw = ALONE ? 1 : tiles;
+  const int nw = FORM == ROT_ALONE ? 1 : tiles;
   const int64_t nbatch = (TG + TB - 1) / TB;
+  // One batch for each CU: ROT_ONCE.  HIP-graph replays over rotating inputs, us before / now: X [128, 14336] 4.4 /
+  // 4.1, [256, 4096] 3.7 / 3.45, [512, 4096] 4.65 / 4.5, [64, 8192] 3.1 / 2.95.  With two workgroups per CU or more
+  // they hide each other's loads and the register staging costs more than it gains: [1024, 4096] 5.8 / 6.1,
+  // [333, 14336] 6.6 / 6.85.  (Elsewhere the buffer loads of the register staging are what is new: G = 80
+  // [600, 5120] 5.7 / 5.2, G = 64 [1024, 2048] 4.35 / 4.1.)
+  if constexpr (FORM == ROT_LOOP && KS16 >= 4 && KS16 <= 8) {
+    if (nbatch <= 256)
+      return launch_cfg32<KS16, TB, ROT_ONCE>(r, x, TG, format, global_scale, codes, scales, z_out, stream);
+  }
   // a token-group's place in LDS: a whole number of 16-byte chunks per thread (padded when KS16 is odd)
   const size_t tg_stride = (size_t)((KS16 * 64 + 64 * nw - 1) / (64 * nw)) * (64 * nw) * 16;
   const size_t lds_bytes = 2 * (size_t)TB * tg_stride;
@@ -628,11 +657,11 @@ static hipError_t launch_cfg32(const torq_rotation *r, const void *x, int64_t TG
   int per_cu = (int)((160 * 1024) / lds_bytes);
   if (per_cu * nw > waves_per_cu) per_cu = waves_per_cu / nw;
   if (per_cu < 1) per_cu = 1;
-  const int64_t grid = ALONE ? tiles * nbatch : balanced_grid(nbatch, per_cu);
+  const int64_t grid = FORM == ROT_ALONE ? tiles * nbatch : FORM == ROT_ONCE ? nbatch : balanced_grid(nbatch, per_cu);
   const uint4 *ih = reinterpret_cast<const uint4 *>(r->intra32_hi);
   const uint4 *il = reinterpret_cast<const uint4 *>(r->intra32_lo);
   const uint16_t *ri_hi = r->inter32f_hi, *ri_lo = r->inter32f_lo;      // the table in lane order
-  TORQ_LAUNCH_FMT(rotate_kernel32, uint2, KS16, TB, ALONE)
+  TORQ_LAUNCH_FMT(rotate_kernel32, uint2, KS16, TB, FORM)
 }
 
 template <int KS16>
@@ -688,7 +717,7 @@ hipError_t launch_rotate(const torq_rotation *r, const void *x_bf16, int64_t M, 
   const int64_t TG = M * (int64_t)(r->d / 32 / r->G);
   if (TG == 0) return hipSuccess;
   // A handful of token-groups, G = 64 ... 128: every 32 output blocks of a token-group by a workgroup of one
-  // wave (rotate_kernel32, ALONE) while that leaves each CU no more than one of them.  The kernel is then a
+  // wave (rotate_kernel32, ROT_ALONE) while that leaves each CU no more than one of them.  The kernel is then a
   // chain of launch, operand loads and 30 MFMAs, and a CU that holds all the waves of a token-group waits
   // for the whole of R_inter (64 KB at G = 128) where it could wait for one tile of it.  Cold operands, HIP-graph
   // replays, us before / now: G = 128 at 1 to 32 token-groups 3.0 / 2.6, at 64 3.0 / 2.85; G = 112 2.9 / 2.5;
@@ -698,7 +727,7 @@ hipError_t launch_rotate(const torq_rotation *r, const void *x_bf16, int64_t M, 
   if (TG * ((r->G + 31) / 32) <= 256) {
     switch (r->G) {
 #define TORQ_ALONE(K16_) \
-  case 16 * K16_: return launch_cfg32<K16_, 1, true>(r, x_bf16, TG, format, global_scale, codes, scales, z_out, stream);
+  case 16 * K16_: return launch_cfg32<K16_, 1, ROT_ALONE>(r, x_bf16, TG, format, global_scale, codes, scales, z_out, stream);
       TORQ_ALONE(4) TORQ_ALONE(5) TORQ_ALONE(6) TORQ_ALONE(7) TORQ_ALONE(8)
 #undef TORQ_ALONE
     }

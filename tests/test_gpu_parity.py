@@ -1047,9 +1047,12 @@ def test_quantize_fmt_mxfp4_is_the_plain_entry_point(tq):
     assert torch.equal(c0, c1) and torch.equal(s0, s1)
 
 
-# the last row count that takes a wave per workgroup (rows * ceil(G / 32) <= 256) and the first that does not
+# the last row count that takes a wave per workgroup (rows * ceil(G / 32) <= 256) and the first that does not; the last
+# that has one batch per workgroup (256 batches, of one or two token-groups, an odd last one) and the first that has more
 @pytest.mark.parametrize("d,G,rows", [(4096, 128, 64), (3584, 112, 64), (3072, 96, 85), (2560, 80, 85), (2048, 64, 128),
-                                      (8192, 128, 1), (5120, 80, 7)])
+                                      (8192, 128, 1), (5120, 80, 7), (4096, 128, 256), (4096, 128, 511),
+                                      (4096, 128, 512), (3584, 112, 512), (3072, 96, 511), (2560, 80, 512),
+                                      (2048, 64, 511), (2048, 64, 512)])
 @pytest.mark.parametrize("fmt", [0, 1, 2])
 def test_few_token_groups_give_the_rows_of_a_larger_call(tq, oracle, d, G, rows, fmt):
     # every output is a function of its own token-group, computed in the same order in every launch shape
