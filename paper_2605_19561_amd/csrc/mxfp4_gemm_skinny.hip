@@ -810,12 +810,15 @@ static int lines_ring(int MT, int NS, int d) {
 // aligned scale rows): as few as leave a CU at most one workgroup, which keeps every CU busy and reads the activations
 // once a CU.  It is ahead almost everywhere it fits, the more the more rows and the longer the k range; us, the other
 // form against this one, weights from HBM: [16, 8192] x 1024 6.6 / 4.6, [16, 8192] x 8192 10.1 / 9.9, [16, 28672] x 8192
-// 28.9 / 23.2, [16, 8192] x 28672 28.4 / 26.0, [45, 5120] x 8192 10.6 / 8.5, [45, 8192] x 5120 13.2 / 9.9, [64, 4096] x
+// 28.9 / 23.2, [45, 5120] x 8192 10.6 / 8.5, [45, 8192] x 5120 13.2 / 9.9, [64, 4096] x
 // 4096 8.0 / 5.3, [1, 14336] x 4096 9.0 / 8.4, [1, 4096] x 14336 8.7 / 8.2.  Short k ranges leave its waves idle (one
 // line pair each is 2048 elements) and have it wait for its scale bytes: up to d = 1024 it takes only many rows, or from
 // 17 rows on more than one strip a CU ([16, 1024] x 2048 0.9 times as fast, [40, 1024] x 5120 1.2, [64, 512] x 128 1.06);
 // below 8 rows the other form also keeps d = 2048 (0.94 - 1.04) and rows a multiple of 4 KB apart past 448 strips
 // ([1, 8192] x 28672 0.93, [1, 16384] x 16384 0.91: all workgroups walk the same columns, whose lines share channels).
+// From 8 rows on the same holds past 1600 strips, where the persistent form fills the CUs: [16, 8192] x 28672 in a
+// decoder block 29.4 / 27.5 (this form / the other), whole calls [8, 8192] x 26624 30.5 / 28.4, [12, 8192] x 28672 31.8 / 30.3,
+// [16, 8192] x 26624 30.7 / 29.8, but x 25600 28.2 / 29.4, x 24576 27.6 / 28.8, x 20480 22.7 / 28.7.
 // Three strips of one activation tile: four measured up to 6 % ahead (two items of four tiles in the ring, one of three).
 int mxfp4_gemm_lines_strips(int64_t M, int64_t N, int d) {
   if (M < 1 || M > 64 || d % 512 != 0) return 0;
@@ -828,7 +831,7 @@ int mxfp4_gemm_lines_strips(int64_t M, int64_t N, int d) {
   const bool pays = MT == 4   ? true
                     : MT == 3 ? d >= 1024 || strips > 256
                     : MT == 2 ? d >= 2048 || (strips > 256 && strips <= 1024)
-                    : M >= 8  ? d >= 2048
+                    : M >= 8  ? d >= 2048 && (d % 8192 != 0 || strips <= 1600)
                               : d >= 3072 && (d % 8192 != 0 || strips <= 448);
   return pays ? NS : 0;
 }
@@ -1067,14 +1070,14 @@ bool torq_linear_local_fits(const torq_rotation *r, int64_t M) {
   return (r->d / 128 + 1) / 2 <= 8 * WAVES * 4 && local_lds_bytes(M, r->d, 1) <= 64 * 1024;
 }
 
-// Where the one-launch form is the faster way through torq_linear, measured against rotate + quantise
-// followed by the GEMM as HIP-graph replays over weight copies of 600 MB in all (weights from HBM, as in a
-// model; with six copies of a 31 MB layer the 256 MB Infinity Cache held them, and the form seemed to pay up
-// to 48 MB): one or two token-groups up to 20 MB of packed weights, three or four up to 16 MB.  One launch
-// against two, us: [1, 4096] x 1024 5.9 / 7.3, x 4096 6.2 / 7.7, x 8192 8.3 / 9.0, x 11008 11.2 / 10.2,
-// x 14336 11.4 / 11.6; [1, 8192] x 4096 8.6 / 9.6, x 8192 12.1 / 12.1; [4, 4096] x 4096 7.9 / 8.0, x 6144
-// 9.1 / 9.3, x 8192 10.0 / 9.4, x 14336 12.8 / 12.2; [2, 8192] x 2048 8.7 / 9.1, x 4096 10.1 / 9.7;
-// [1, 14336] x 2048 (G = 112) 10.7 / 11.9, x 4096 12.4 / 12.6; [1, 8192] x 28672 (125 MB): 30.1 / 28.7.
+// Where the one-launch form is the faster way through torq_linear: one or two token-groups up to 20 MB of packed
+// weights, three or four up to 16 MB.  Measured against rotate + quantise followed by the GEMM with weights from HBM (copies
+// of 600 MB in all; with six copies of a 31 MB layer the 256 MB Infinity Cache held them, and the form seemed to
+// pay up to 48 MB).  One launch against two, us, HIP-graph replays: [1, 4096] x 1024 5.9 / 6.9, x 4096 6.3 / 7.4, x 8192
+// 8.3 / 9.0, x 11008 11.2 / 9.9, x 14336 11.4 / 10.7; [1, 8192] x 4096 8.9 / 9.2, x 8192 12.2 / 11.6.  Three or four token-groups are within a launch's gap of each other, and which is ahead depends on who waits:
+// replayed, [4, 4096] x 1024 7.1 / 7.2, x 4096 8.4 / 7.6, [2, 8192] x 2048 8.7 / 8.1, [1, 14336] x 2048 (G = 112)
+// 10.7 / 9.5; called one after the other from Python, where a launch more is 3 us of the host, 7.0 / 10.0, 7.0 / 10.0,
+// 7.7 / 8.6 and 10.6 / 9.1 with buffers kept by the caller, 10.3 / 13.4, 10.3 / 13.3, 9.6 / 12.3 and 10.6 / 12.1 without.
 bool torq_linear_local_pays(const torq_rotation *r, int64_t M, int64_t N) {
   if (!torq_linear_local_fits(r, M) || N <= 0) return false;
   const int64_t token_groups = M * (int64_t)(r->d / 32 / r->G);

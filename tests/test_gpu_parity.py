@@ -302,7 +302,7 @@ def test_gemm_weight_streaming_strips(tq, oracle, M, N, d):
 # lines, which scale rows off the 16-byte grid still take.
 @pytest.mark.parametrize("M,N,d", [
     (1, 16, 3072), (3, 1000, 3584), (16, 4099, 2048), (7, 4100, 28672), (16, 4112, 4096), (8, 8200, 28672), (9, 12300, 2048),
-    (16, 16400, 2048), (12, 20490, 2048), (16, 28672, 8192), (17, 40, 2048), (32, 4104, 1024), (20, 9000, 2048), (31, 14000, 2048),
+    (16, 16400, 2048), (12, 20490, 2048), (16, 28672, 7168), (16, 28672, 8192), (17, 40, 2048), (32, 4104, 1024), (20, 9000, 2048), (31, 14000, 2048),
     (33, 70, 1024), (48, 5000, 2048), (40, 10000, 5120), (49, 8, 512), (64, 4100, 4096), (64, 8190, 2048)])
 def test_gemm_weight_streaming_by_whole_lines(tq, oracle, M, N, d):
     assert tq.mxfp4_gemm_plan(M, N, d)[0], "this shape is meant to take the weight-streaming kernel"
