@@ -755,7 +755,13 @@ def gemm_kernel_name(tq, M, N, d, workspace_bytes):
     """Which kernel(s) mxfp4_gemm_ws runs a product on, for the lines' labels."""
     def one(n):
         streaming, tile_m, tile_n, pieces = tq.mxfp4_gemm_plan(M, n, d, workspace_bytes)
-        return "weight-streaming" if streaming else f"tiled {tile_m}x{tile_n}" + (f", k cut in {pieces}" if pieces > 1 else "")
+        staging = tq.torq_diag_gemm_form(M, n, d, workspace_bytes)[0]
+        if streaming:
+            return f"weight-streaming, {staging}"
+        tile = f"tiled {tile_m}x{tile_n}" + (" in a ring" if staging.startswith("ring") else "")
+        if staging == "ring, halved":
+            return tile + ", k halved in the workgroup"
+        return tile + (f", k cut in {pieces}" if pieces > 1 else "")
     main = tq.mxfp4_gemm_main_columns(M, N, d, workspace_bytes)
     if main < N:
         return f"{one(N)} on {main} columns (whole rounds), then {one(N - main)} on {N - main}"

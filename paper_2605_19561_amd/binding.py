@@ -21,7 +21,7 @@ EXPORTS = [
     "torq_linear_workspace_bytes_n", "torq_block_gram_workspace_bytes", "torq_block_gram", "torq_block_gram_positions",
     "torq_equalize_inter", "torq_code_histogram_workspace_bytes", "torq_code_histogram", "torq_intra_pair_scores",
     "torq_intra_best_angle", "torq_calibrate_intra", "torq_diag_mfma_burn", "torq_linear_static",
-    "torq_diag_copy", "torq_diag_gemm_ablation", "torq_diag_gemm_persistent", "torq_diag_gemm_plan", "torq_diag_gemm_ring", "torq_diag_rotate_ablation", "torq_linear_single_launch_reset", "torq_linear_single_launch_gave_up", "torq_linear_single_launch_probe",
+    "torq_diag_copy", "torq_diag_gemm_ablation", "torq_diag_gemm_persistent", "torq_diag_gemm_plan", "torq_diag_gemm_ring", "torq_diag_gemm_form", "torq_diag_rotate_ablation", "torq_linear_single_launch_reset", "torq_linear_single_launch_gave_up", "torq_linear_single_launch_probe",
 ]
 
 TORQ_OK, TORQ_EINVAL, TORQ_EALIGN, TORQ_EWORKSPACE, TORQ_EHIP, TORQ_ENODEVICE, TORQ_ECONVERGE = 0, -1, -2, -3, -4, -5, -6
@@ -128,6 +128,8 @@ def lib():
         L.torq_diag_gemm_plan.argtypes = [vp, vp, vp, vp, vp, i64, i64, i32, i32, i32, i32, vp, sz, vp]
         L.torq_diag_gemm_ring.restype = i32
         L.torq_diag_gemm_ring.argtypes = [vp, vp, vp, vp, vp, i64, i64, i32, i32, i32, i32, i32, vp, sz, vp]
+        L.torq_diag_gemm_form.restype = i32
+        L.torq_diag_gemm_form.argtypes = [i64, i64, i32, sz] + [C.POINTER(i32)] * 4
         L.torq_diag_rotate_ablation.restype = i32
         L.torq_diag_rotate_ablation.argtypes = [vp, vp, i64, vp, vp, i32, vp]
         L.torq_diag_copy.restype = i32
@@ -480,6 +482,17 @@ def torq_diag_gemm_ring(A_q, A_s, W_q, W_s, tile_m: int, tile_n: int, k_pieces: 
                                      ws_ptr, workspace.numel() if workspace is not None else 0, _stream(stream)),
            "torq_diag_gemm_ring")
     return out
+
+
+GEMM_STAGING = ("registers", "ring", "ring, halved", "strips", "whole lines")
+
+
+def torq_diag_gemm_form(M: int, N: int, d: int, workspace_bytes: int = 0):
+    """Returns (staging, strips, items, padded) of the form behind mxfp4_gemm_plan's answer (see include/torq.h); staging is
+    one of GEMM_STAGING."""
+    v = [C.c_int() for _ in range(4)]
+    _check(lib().torq_diag_gemm_form(M, N, d, workspace_bytes, *(C.byref(x) for x in v)), "torq_diag_gemm_form")
+    return GEMM_STAGING[v[0].value], v[1].value, v[2].value, bool(v[3].value)
 
 
 def torq_diag_rotate_ablation(rot, x_bf16, codes, scales, skip: int, stream=None):

@@ -454,6 +454,14 @@ int mxfp4_gemm_plan(int64_t M, int64_t N, int d, size_t workspace_bytes, int *we
   return TORQ_OK;
 }
 
+int torq_diag_gemm_form(int64_t M, int64_t N, int d, size_t workspace_bytes, int *staging, int *strips, int *items,
+                        int *padded) {
+  if (M <= 0 || N <= 0 || d <= 0 || d % 128 != 0) return TORQ_EINVAL;
+  if (!staging || !strips || !items || !padded) return TORQ_EINVAL;
+  torq::mxfp4_gemm_form(M, N, d, workspace_bytes, staging, strips, items, padded);
+  return TORQ_OK;
+}
+
 int64_t mxfp4_gemm_main_columns(int64_t M, int64_t N, int d, size_t workspace_bytes) {
   if (M <= 0 || N <= 0 || d <= 0 || d % 128 != 0) return 0;
   return torq::mxfp4_gemm_main_columns(M, N, d, workspace_bytes);

@@ -824,15 +824,33 @@ int64_t mxfp4_gemm_main_columns(int64_t M, int64_t N, int d, size_t workspace_by
   return choose_main_columns(M, N, d, allow, workspace_bytes, plan_with(M, N, d, allow, workspace_bytes));
 }
 
+// the product's only launch, or its first
+static GemmPlan first_plan(int64_t M, int64_t N, int d, size_t workspace_bytes) {
+  if (mxfp4_gemm_main_columns(M, N, d, workspace_bytes) < N) return GemmPlan{false, 0, 1, false, 0.0};
+  return plan_with(M, N, d, d % 512 == 0, workspace_bytes);
+}
+
 void mxfp4_gemm_plan(int64_t M, int64_t N, int d, size_t workspace_bytes, int *skinny, int *tile_m, int *tile_n,
                      int *splits) {
-  GemmPlan plan = plan_with(M, N, d, d % 512 == 0, workspace_bytes);
-  if (mxfp4_gemm_main_columns(M, N, d, workspace_bytes) < N) plan = GemmPlan{false, 0, 1, false, 0.0};   // the first launch
+  const GemmPlan plan = first_plan(M, N, d, workspace_bytes);
   *skinny = plan.skinny;
-  // a tile of 64 rows is half of one of 128 that two workgroups share
-  *tile_m = plan.skinny ? 0 : TILE_M[plan.cfg] < 128 ? 128 : TILE_M[plan.cfg];
+  *tile_m = plan.skinny ? 0 : TILE_M[plan.cfg];
   *tile_n = plan.skinny ? 16 : TILE_N[plan.cfg];
   *splits = plan.splits;
+}
+
+void mxfp4_gemm_form(int64_t M, int64_t N, int d, size_t workspace_bytes, int *staging, int *strips, int *items, int *padded) {
+  const GemmPlan plan = first_plan(M, N, d, workspace_bytes);
+  *strips = *items = *padded = 0;
+  if (!plan.skinny) {
+    *staging = plan.cfg == HALVED                                     ? TORQ_GEMM_RING_HALVED
+               : plan.cfg > 2 || (plan.cfg == 2 && plan.splits > 1)   ? TORQ_GEMM_RING
+                                                                      : TORQ_GEMM_REGISTERS;
+    return;
+  }
+  const bool lines = mxfp4_gemm_lines_form(M, N, d, strips, items, padded);
+  *staging = lines ? TORQ_GEMM_WHOLE_LINES : TORQ_GEMM_STRIPS;
+  if (!lines) *strips = mxfp4_gemm_skinny_strips(M, N, d);
 }
 
 size_t mxfp4_gemm_workspace_bytes(int64_t M, int64_t N, int d) {

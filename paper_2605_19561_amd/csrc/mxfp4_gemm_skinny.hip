@@ -797,6 +797,8 @@ static size_t lines_lds_bytes(int MT, int NS, int R, int d, int pad) {
   return bytes > red ? bytes : red;
 }
 
+static int lines_pad(int MT, int NS, int R, int d) { return lines_lds_bytes(MT, NS, R, d, 1) <= SKINNY_MAX_LDS ? 1 : 0; }
+
 // the deepest ring with room for the scale rows: 4 items of two tiles, 3 (2) of three, 2 (1) of four, 1 of five to eight;
 // 0: none
 static int lines_ring(int MT, int NS, int d) {
@@ -836,10 +838,22 @@ int mxfp4_gemm_lines_strips(int64_t M, int64_t N, int d) {
   return pays ? NS : 0;
 }
 
+// whether the product (16-byte aligned scale rows) takes the whole-line form, and which: strips per workgroup, items in a
+// wave's ring, padding of the scale rows
+bool mxfp4_gemm_lines_form(int64_t M, int64_t N, int d, int *strips, int *items, int *padded) {
+  const int NS = mxfp4_gemm_lines_strips(M, N, d);
+  if (NS == 0) return false;
+  const int MT = (int)((M + 15) / 16);
+  *strips = NS;
+  *items = lines_ring(MT, NS, d);
+  *padded = lines_pad(MT, NS, *items, d);
+  return true;
+}
+
 template <int MT, int NS, int R>
 static hipError_t launch_lines(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q, const uint8_t *W_s, void *out, int64_t M,
                                int64_t N, int d, hipStream_t stream) {
-  const int pad = lines_lds_bytes(MT, NS, R, d, 1) <= SKINNY_MAX_LDS ? 1 : 0;
+  const int pad = lines_pad(MT, NS, R, d);
   const size_t lds = lines_lds_bytes(MT, NS, R, d, pad);
   if (lds > 64 * 1024) {
     static std::atomic<uint64_t> raised{0};

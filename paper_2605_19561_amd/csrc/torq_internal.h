@@ -71,6 +71,8 @@ size_t mxfp4_gemm_workspace_bytes(int64_t M, int64_t N, int d);
 // what launch_mxfp4_gemm would do with a workspace of that size (operands assumed 16-byte aligned)
 void mxfp4_gemm_plan(int64_t M, int64_t N, int d, size_t workspace_bytes, int *skinny, int *tile_m, int *tile_n,
                      int *splits);
+// torq_diag_gemm_form: the form behind the plan
+void mxfp4_gemm_form(int64_t M, int64_t N, int d, size_t workspace_bytes, int *staging, int *strips, int *items, int *padded);
 // The tiled kernel with its operands staged in a ring (mxfp4_gemm_ring.hip): tiles 128x128, 128x64, 64x128 and 64x64,
 // d a multiple of 512, scale arrays 16-byte aligned.  groups = 2 (64x64 only): the workgroup's two halves take half of the
 // k range each and add up on the chip.  splits > 1: the pieces' fp32 sums go to partial[splits][M][N] and out is not
@@ -97,6 +99,7 @@ hipError_t launch_mxfp4_gemm(const uint8_t *A_q, const uint8_t *A_s, const uint8
 // mxfp4_gemm_skinny_fits (the scale rows it stages fit the LDS).
 int mxfp4_gemm_skinny_strips(int64_t M, int64_t N, int d);   // 16-row weight strips per workgroup
 int mxfp4_gemm_lines_strips(int64_t M, int64_t N, int d);    // the same of its whole-line form, 0: not taken
+bool mxfp4_gemm_lines_form(int64_t M, int64_t N, int d, int *strips, int *items, int *padded);
 bool mxfp4_gemm_skinny_fits(int64_t M, int d);
 hipError_t launch_mxfp4_gemm_skinny(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q,
                                     const uint8_t *W_s, void *out_bf16, int64_t M, int64_t N, int d,

@@ -170,6 +170,26 @@ def test_gemm_planner_between_streaming_and_a_cut_k_range(M, N, d, streaming):
     assert binding.mxfp4_gemm_plan(M, N, d, 1 << 40)[0] is streaming
 
 
+def test_gemm_plan_names_the_tile_and_the_form_that_run():
+    # a batch of 45 against a wide layer: one row of 64-row tiles, two workgroups share nothing
+    assert binding.mxfp4_gemm_plan(45, 25600, 5120) == (False, 64, 128, 1)
+    assert binding.torq_diag_gemm_form(45, 25600, 5120) == ("ring", 0, 0, False)
+    # a last tile row of one output row, a long k range: the halves meet inside the workgroup
+    need = binding.mxfp4_gemm_workspace_bytes(257, 2048, 7168)
+    assert binding.mxfp4_gemm_plan(257, 2048, 7168, need) == (False, 64, 64, 2)
+    assert binding.torq_diag_gemm_form(257, 2048, 7168, need)[0] == "ring, halved"
+    assert binding.torq_diag_gemm_form(257, 2048, 7168)[0] == "ring"
+    assert binding.torq_diag_gemm_form(8192, 28672, 8192)[0] == "registers"
+    assert binding.torq_diag_gemm_form(4096, 5120, 5120)[0] == "registers"       # the first launch of two
+    assert binding.torq_diag_gemm_form(16, 8192, 28672) == ("whole lines", 2, 2, True)
+    assert binding.torq_diag_gemm_form(16, 28672, 8192)[:2] == ("strips", 2)
+    L = binding.lib()
+    v = [C.c_int() for _ in range(4)]
+    assert L.torq_diag_gemm_form(0, 4, 128, 0, *(C.byref(x) for x in v)) == binding.TORQ_EINVAL
+    assert L.torq_diag_gemm_form(4, 4, 100, 0, *(C.byref(x) for x in v)) == binding.TORQ_EINVAL
+    assert L.torq_diag_gemm_form(4, 4, 128, 0, None, *(C.byref(x) for x in v[1:])) == binding.TORQ_EINVAL
+
+
 def test_gemm_planner_invariants_over_random_shapes():
     # whatever the cost model prefers, a plan has to be one the kernels can run: pieces that divide the k range
     # into whole pairs of iterations, fp32 rows that are 16-byte aligned, a workspace that holds them, a first
@@ -185,12 +205,18 @@ def test_gemm_planner_invariants_over_random_shapes():
             assert main == N or (0 < main < N and main % 256 == 0 and d % 512 == 0 and N % 8 == 0), (M, N, d, main)
             for n in ((N,) if main == N else (N, N - main)):
                 streaming, tm, tn, pieces = binding.mxfp4_gemm_plan(M, n, d, ws)
+                staging, strips, items, _ = binding.torq_diag_gemm_form(M, n, d, ws)
+                assert (strips > 0) == streaming and (items > 0) == (staging == "whole lines"), (M, n, d, staging)
                 if streaming:
-                    assert M <= 64 and pieces == 1
+                    assert M <= 64 and pieces == 1 and staging in ("strips", "whole lines")
+                    assert staging == "strips" or d % 512 == 0
                     continue
-                assert (tm, tn) in ((256, 256), (256, 128), (128, 128), (128, 64)), (M, n, d, tm, tn)
-                if (tm, tn) == (128, 64):
-                    assert d % 512 == 0
+                if staging == "registers":
+                    assert (tm, tn) in ((256, 256), (256, 128), (128, 128)), (M, n, d, tm, tn)
+                    assert pieces == 1 or (tm, tn) == (256, 128)
+                else:
+                    assert (tm, tn) in ((128, 128), (128, 64), (64, 128), (64, 64)) and d % 512 == 0, (M, n, d, tm, tn)
+                    assert staging == "ring" or (tm, tn, pieces) == (64, 64, 2)
                 if pieces > 1:
                     assert d % 512 == 0 and (d // 512) % pieces == 0 and n % 8 == 0 and (tm, tn) != (256, 256)
                     assert ws >= pieces * M * n * 4, (M, n, d, pieces, ws)
