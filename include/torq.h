@@ -152,7 +152,8 @@ int torq_quantize_f32_fmt(const float *z_f32, int64_t M, int d, int format, floa
  * is cut into pieces that run as separate workgroups; their fp32 tiles go through `workspace` and a
  * second kernel adds them in a fixed order (deterministic) and rounds once to bf16.
  *   workspace  device, 16-byte aligned, at least mxfp4_gemm_workspace_bytes(M, N, d) bytes (0 for
- *              shapes that are not cut); NULL or too small: exactly mxfp4_gemm. */
+ *              shapes that are not cut, 16 where the halves of the k range meet on the chip); NULL or
+ *              too small: exactly mxfp4_gemm. */
 size_t mxfp4_gemm_workspace_bytes(int64_t M, int64_t N, int d);
 /* Which kernel the product of that shape runs on, given a workspace of that many bytes (0: as
  * mxfp4_gemm) and 16-byte aligned scale arrays: *weight_streaming = 1 for the kernel that streams

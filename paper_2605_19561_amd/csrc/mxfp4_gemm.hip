@@ -711,6 +711,12 @@ static double skinny_several_us(int ns, int64_t M, int64_t N, int d) {
   return work > read ? work : read;
 }
 
+// The workspace that a plan needs.  Form 7 writes nothing there: 16 bytes are the caller's word that the sum may be cut.
+static size_t plan_bytes(const GemmPlan &plan, int64_t M, int64_t N) {
+  if (plan.splits == 1) return 0;
+  return plan.cfg == HALVED ? 16 : (size_t)plan.splits * (size_t)M * (size_t)N * sizeof(float);
+}
+
 static GemmPlan choose_plan(int64_t M, int64_t N, int d, bool allow_split) {
   const bool can_skinny = mxfp4_gemm_skinny_fits(M, d);
   const double KT = (d + 255) / 256;
@@ -747,8 +753,8 @@ static GemmPlan choose_plan(int64_t M, int64_t N, int d, bool allow_split) {
           offer(form, s, tiled_us(form, s, M, N, d));
         }
       }
-      // Form 7, a cut in two that stays on the chip (it asks for the scratch of two pieces like any cut, so that a call
-      // without scratch keeps the uncut sum).  As a rule form 5's two workgroups a CU do the same (form 7 2 - 14 % slower
+      // Form 7, a cut in two that stays on the chip (offered with a workspace like any cut, so that a call without one keeps
+      // the uncut sum).  As a rule form 5's two workgroups a CU do the same (form 7 2 - 14 % slower
       // on 500 shapes); where the last tile row is nearly empty and the k range long it is ahead: us, form 5 / 7, [257,
       // 7168] x 2048 9.6 / 9.1, [129, 11264] x 1536 13.0 / 12.0, [130, 16384] x 512 17.4 / 15.3, [193, 9216] x 1024 11.1 / 10.5.
       if (may_split && d % 1024 == 0 && d >= 24 * 256 && tiles_of(HALVED) <= 256 && (M - 1) % 64 < 8)
@@ -814,8 +820,7 @@ static int64_t choose_main_columns(int64_t M, int64_t N, int d, bool allow_split
 // the plan of a product given the workspace it may use (a cut k range needs its pieces' fp32 tiles there)
 static GemmPlan plan_with(int64_t M, int64_t N, int d, bool allow_split, size_t workspace_bytes) {
   GemmPlan plan = choose_plan(M, N, d, allow_split);
-  if (plan.splits > 1 && workspace_bytes < (size_t)plan.splits * (size_t)M * (size_t)N * sizeof(float))
-    plan = choose_plan(M, N, d, false);
+  if (workspace_bytes < plan_bytes(plan, M, N)) plan = choose_plan(M, N, d, false);
   return plan;
 }
 
@@ -856,11 +861,8 @@ void mxfp4_gemm_form(int64_t M, int64_t N, int d, size_t workspace_bytes, int *s
 size_t mxfp4_gemm_workspace_bytes(int64_t M, int64_t N, int d) {
   const GemmPlan plan = choose_plan(M, N, d, true);
   const int64_t main_n = choose_main_columns(M, N, d, true, ~(size_t)0, plan);
-  if (main_n < N) {
-    const GemmPlan tail = choose_plan(M, N - main_n, d, true);
-    return tail.splits > 1 ? (size_t)tail.splits * (size_t)M * (size_t)(N - main_n) * sizeof(float) : 0;
-  }
-  return plan.splits > 1 ? (size_t)plan.splits * (size_t)M * (size_t)N * sizeof(float) : 0;
+  if (main_n < N) return plan_bytes(choose_plan(M, N - main_n, d, true), M, N - main_n);
+  return plan_bytes(plan, M, N);
 }
 
 // one product by a given plan of the tiled kernel: out's rows are ldc elements apart.  fullk: d is a whole

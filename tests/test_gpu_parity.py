@@ -414,6 +414,22 @@ def test_gemm_ring_every_tile(tq, oracle, M, N, d):
             assert torch.equal(halved.view(torch.int16), ref.view(torch.int16))
 
 
+# The k range halved inside a workgroup: the planner's own call, with the 16 bytes of workspace that it asks for
+@pytest.mark.parametrize("M,N,d", [(257, 2048, 7168), (129, 4096, 14336), (321, 1024, 7168)])
+def test_gemm_halved_on_the_chip_leaves_the_workspace_alone(tq, M, N, d):
+    need = tq.mxfp4_gemm_workspace_bytes(M, N, d)
+    assert need == 16 and tq.torq_diag_gemm_form(M, N, d, need)[0] == "ring, halved"
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(M + N + d)
+    draw = lambda lo, hi, *shape: torch.randint(lo, hi, shape, dtype=torch.uint8, device=DEV, generator=gen)
+    ops = draw(0, 256, M, d // 2), draw(118, 136, M, d // 32), draw(0, 256, N, d // 2), draw(110, 126, N, d // 32)
+    ws = torch.full((16,), 77, dtype=torch.uint8, device=DEV)
+    got = tq.mxfp4_gemm_ws(*ops, workspace=ws)
+    want = tq.torq_diag_gemm_ring(*ops, 64, 64, 2)          # the same two pieces through a workspace
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16)) and torch.all(ws == 77)
+
+
 def test_gemm_plan_diagnostic_rejects_what_a_form_cannot_take(tq):
     M, N, d = 64, 72, 640                                  # d is not a whole number of 512-element pieces
     z = lambda *shape: torch.zeros(shape, dtype=torch.uint8, device=DEV)
