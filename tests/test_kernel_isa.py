@@ -101,6 +101,15 @@ def test_gemm_ring_loop_holds_exactly_the_counted_requests():
     assert seen == 10
 
 
+# ---- mxfp4_gemm_skinny_kernel: its prologue stands ahead of every load, so it holds the one reciprocal of the scale rows'
+# pitch and no integer division (which would hold another).
+def test_strip_kernel_prologue_divides_by_nothing_that_varies():
+    with tempfile.TemporaryDirectory() as tmp:
+        text = open(build.device_asm("mxfp4_gemm_skinny.hip", os.path.join(tmp, "skinny.s"))).read()
+    bodies = re.findall(r"^_ZN4torq24mxfp4_gemm_skinny_kernel\S+:(.*?)^\.Lfunc_end", text, re.M | re.S)
+    assert len(bodies) == 30 and all(len(re.findall(r"^\s+v_rcp_", b, re.M)) == 1 for b in bodies)
+
+
 # ---- mxfp4_gemm_lines_kernel (mxfp4_gemm_skinny.hip): "the oldest item has landed" is a count of the younger requests.
 def test_lines_loop_holds_exactly_the_counted_requests():
     with tempfile.TemporaryDirectory() as tmp:
