@@ -820,10 +820,11 @@ static int lines_ring(int MT, int NS, int d) {
 // 17 rows on more than one strip a CU ([16, 1024] x 2048 0.9 times as fast, [40, 1024] x 5120 1.2, [64, 512] x 128 1.06);
 // below 8 rows the other form also keeps d = 2048 (0.94 - 1.04) and rows a multiple of 4 KB apart past 448 strips
 // ([1, 8192] x 28672 0.93, [1, 16384] x 16384 0.91: all workgroups walk the same columns, whose lines share channels).
-// From 8 rows on the same holds past 1600 strips, where the persistent form fills the CUs: [16, 8192] x 28672 in a
-// decoder block 29.4 / 27.5 (this form / the other), whole calls [8, 8192] x 26624 30.5 / 28.4, [12, 8192] x 28672 31.8 / 30.3,
+// From 8 rows on past 1600 strips: seven strips a CU leave a ring of one item, and beside it the scale rows of d = 8192 at
+// most.  At that length (rows 4 KB apart again) the persistent form is ahead: [16, 8192] x 28672 in a decoder block 29.4 /
+// 27.5 (this form / the other), alone 31.0 / 31.0, whole calls [8, 8192] x 26624 30.5 / 28.4, [12, 8192] x 28672 31.8 / 30.3,
 // [16, 8192] x 26624 30.7 / 29.8, but x 25600 28.2 / 29.4, x 24576 27.6 / 28.8, x 20480 22.7 / 28.7.
-// Three strips of one activation tile: four measured up to 6 % ahead (two items of four tiles in the ring, one of three).
+// Three strips of one activation tile: four measured up to 6 % ahead.
 int mxfp4_gemm_lines_strips(int64_t M, int64_t N, int d) {
   if (M < 1 || M > 64 || d % 512 != 0) return 0;
   const int MT = (int)((M + 15) / 16);
@@ -835,7 +836,7 @@ int mxfp4_gemm_lines_strips(int64_t M, int64_t N, int d) {
   const bool pays = MT == 4   ? true
                     : MT == 3 ? d >= 1024 || strips > 256
                     : MT == 2 ? d >= 2048 || (strips > 256 && strips <= 1024)
-                    : M >= 8  ? d >= 2048 && (d % 8192 != 0 || strips <= 1600)
+                    : M >= 8  ? d >= 2048 && (d < 8192 || strips <= 1600)
                               : d >= 3072 && (d % 8192 != 0 || strips <= 448);
   return pays ? NS : 0;
 }
@@ -872,7 +873,7 @@ static hipError_t launch_lines_mt(int NS, const uint8_t *A_q, const uint8_t *A_s
                                   int64_t M, int64_t N, int d, hipStream_t stream) {
   const int R = lines_ring(MT, NS, d);
 #define TORQ_LINES(NS_)                                                                                                     \
-  if constexpr (NS_ + MT <= 8)                                                                                              \
+  if constexpr (NS_ + MT <= 8 && !(MT == 1 && NS_ == 3))                                                                    \
     if (NS == NS_) {                                                                                                        \
       constexpr int T = NS_ + MT, MOST = T == 2 ? 4 : T == 3 ? 3 : T == 4 ? 2 : 1;                                          \
       if (R == MOST) return launch_lines<MT, NS_, MOST>(A_q, A_s, W_q, W_s, out, M, N, d, stream);                          \

@@ -225,6 +225,20 @@ def test_gemm_planner_invariants_over_random_shapes():
                 assert binding.mxfp4_gemm_plan(M, N, d, ws)[:3] == (False, 256, 256)
 
 
+def test_every_whole_line_form_that_the_rule_takes_has_its_gpu_case():
+    # a border that moves brings forms that no test runs, or leaves a case on another form
+    from test_gpu_parity import WHOLE_LINES
+    for (M, N, d), form in WHOLE_LINES.items():
+        assert binding.torq_diag_gemm_form(M, N, d) == ("whole lines", *form), (M, N, d)
+    tested = {((M + 15) // 16, *form) for (M, _, _), form in WHOLE_LINES.items()}
+    for M in (1, 7, 8, 16, 17, 32, 33, 48, 49, 64):
+        for d in range(512, 28673, 512):
+            for strips in sorted({*range(1, 1793, 16), *(256 * i + j for i in range(1, 7) for j in (0, 1)), 1600, 1601, 1792}):
+                for workspace in (0, 1 << 40):
+                    staging, *form = binding.torq_diag_gemm_form(M, 16 * strips, d, workspace)
+                    assert staging != "whole lines" or ((M + 15) // 16, *form) in tested, (M, 16 * strips, d, form)
+
+
 def test_format_entry_points_reject_unknown_formats_and_bad_scales():
     L = binding.lib()
     good = C.c_void_p(0x1000)

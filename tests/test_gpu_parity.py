@@ -297,15 +297,31 @@ def test_gemm_weight_streaming_strips(tq, oracle, M, N, d):
     test_gemm_random_codes(tq, oracle, M, N, d)
 
 
-# The streaming kernel's whole-line form: every ring depth (two to eight tiles an item, long and short k ranges), waves
-# without a line pair, ragged rows and strips, scale rows without room for padding.  Its bits are those of the form by half
-# lines, which scale rows off the 16-byte grid still take.
-@pytest.mark.parametrize("M,N,d", [
-    (1, 16, 3072), (3, 1000, 3584), (16, 4099, 2048), (7, 4100, 28672), (16, 4112, 4096), (8, 8200, 28672), (9, 12300, 2048),
-    (16, 16400, 2048), (12, 20490, 2048), (16, 28672, 7168), (16, 28672, 8192), (17, 40, 2048), (32, 4104, 1024), (20, 9000, 2048), (31, 14000, 2048),
-    (33, 70, 1024), (48, 5000, 2048), (40, 10000, 5120), (49, 8, 512), (64, 4100, 4096), (64, 8190, 2048)])
+# The streaming kernel's whole-line form, each that the rule takes: (M, N, d) -> strips per workgroup, items in a wave's
+# ring, scale rows padded or not (tests/test_abi.py walks the rule and finds no other); among them waves without a line pair,
+# ragged rows and strips.  Its bits are those of the form by half lines, which scale rows off the 16-byte grid still take.
+WHOLE_LINES = {
+    (1, 16, 3072): (1, 4, True), (3, 1000, 3584): (1, 4, True),
+    (16, 4099, 2048): (2, 3, True), (16, 4112, 4096): (2, 3, True), (1, 4352, 10752): (2, 3, False), (7, 4100, 28672): (2, 2, True),
+    (8, 8200, 28672): (4, 1, True), (9, 12300, 2048): (4, 1, True),
+    (16, 16400, 2048): (5, 1, True), (1, 16400, 21504): (5, 1, False),
+    (12, 20490, 2048): (6, 1, True), (1, 20496, 13824): (6, 1, False),
+    (16, 28672, 7168): (7, 1, True), (16, 25600, 8192): (7, 1, False),
+    (17, 40, 2048): (1, 3, True), (17, 256, 10752): (1, 3, False), (17, 256, 11264): (1, 2, True),
+    (32, 4104, 1024): (2, 2, True), (32, 7440, 16384): (2, 2, False), (17, 6144, 16896): (2, 1, True),
+    (20, 9000, 2048): (3, 1, True), (31, 14000, 2048): (4, 1, True), (17, 12304, 21504): (4, 1, False),
+    (17, 16640, 2048): (5, 1, True), (32, 16400, 13824): (5, 1, False),
+    (17, 20736, 2048): (6, 1, True), (17, 20496, 8192): (6, 1, False),
+    (33, 70, 1024): (1, 2, True), (33, 16, 16384): (1, 2, False), (33, 256, 17408): (1, 1, True), (48, 5000, 2048): (2, 1, True),
+    (40, 10000, 5120): (3, 1, True), (33, 8208, 21504): (3, 1, False), (48, 13824, 5120): (4, 1, True), (48, 12304, 13824): (4, 1, False),
+    (49, 8, 512): (1, 1, True), (64, 4100, 4096): (2, 1, True), (64, 8190, 2048): (2, 1, True), (49, 4112, 21504): (2, 1, False),
+    (49, 8448, 4096): (3, 1, True)}
+
+
+@pytest.mark.parametrize("M,N,d", list(WHOLE_LINES) + [(16, 28672, 8192)])     # (the last: strips, by 16 bytes of scales and by 4)
 def test_gemm_weight_streaming_by_whole_lines(tq, oracle, M, N, d):
-    assert tq.mxfp4_gemm_plan(M, N, d)[0], "this shape is meant to take the weight-streaming kernel"
+    form = tq.torq_diag_gemm_form(M, N, d)
+    assert form == ("whole lines", *WHOLE_LINES[M, N, d]) if (M, N, d) in WHOLE_LINES else form[0] == "strips"
     gen = torch.Generator(device=DEV)
     gen.manual_seed(M + N + d)
     draw = lambda lo, hi, *shape: torch.randint(lo, hi, shape, dtype=torch.uint8, device=DEV, generator=gen)

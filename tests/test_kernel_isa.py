@@ -129,7 +129,7 @@ def test_lines_loop_holds_exactly_the_counted_requests():
         assert len(vmem) == ops and all(map(is_lds, vmem)), (name, len(vmem))
         # the ring's first items lie between the scale bytes' requests (in a loop) and the first wait
         assert sum(map(is_lds, code[:waits[0][0]])) == ring * ops + 2, name
-    assert seen == 28
+    assert seen == 26
 
 
 # ---- torq_linear_local_kernel (mxfp4_gemm_skinny.hip): not correctness but the point of the kernel.  The
