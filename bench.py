@@ -758,10 +758,7 @@ def gemm_kernel_name(tq, M, N, d, workspace_bytes):
         staging = tq.torq_diag_gemm_form(M, n, d, workspace_bytes)[0]
         if streaming:
             return f"weight-streaming, {staging}"
-        tile = f"tiled {tile_m}x{tile_n}" + (" in a ring" if staging.startswith("ring") else "")
-        if staging == "ring, halved":
-            return tile + ", k halved in the workgroup"
-        return tile + (f", k cut in {pieces}" if pieces > 1 else "")
+        return f"tiled {tile_m}x{tile_n}" + (" in a ring" if staging == "ring" else "") + (f", k cut in {pieces}" if pieces > 1 else "")
     main = tq.mxfp4_gemm_main_columns(M, N, d, workspace_bytes)
     if main < N:
         return f"{one(N)} on {main} columns (whole rounds), then {one(N - main)} on {N - main}"

@@ -152,14 +152,12 @@ int torq_quantize_f32_fmt(const float *z_f32, int64_t M, int d, int format, floa
  * is cut into pieces that run as separate workgroups; their fp32 tiles go through `workspace` and a
  * second kernel adds them in a fixed order (deterministic) and rounds once to bf16.
  *   workspace  device, 16-byte aligned, at least mxfp4_gemm_workspace_bytes(M, N, d) bytes (0 for
- *              shapes that are not cut, 16 where the halves of the k range meet on the chip); NULL or
- *              too small: exactly mxfp4_gemm. */
+ *              shapes that are not cut); NULL or too small: exactly mxfp4_gemm. */
 size_t mxfp4_gemm_workspace_bytes(int64_t M, int64_t N, int d);
 /* Which kernel the product of that shape runs on, given a workspace of that many bytes (0: as
  * mxfp4_gemm) and 16-byte aligned scale arrays: *weight_streaming = 1 for the kernel that streams
  * 16-row weight strips (at most 64 activation rows; *tile_m = 0, *tile_n = 16), else 0 and
- * *tile_m x *tile_n is the output tile; *k_pieces > 1 if the k range is cut, 2 also where the two
- * halves meet inside a workgroup (torq_diag_gemm_form tells these apart).  Host only, launches
+ * *tile_m x *tile_n is the output tile; *k_pieces > 1 if the k range is cut.  Host only, launches
  * nothing; for logs and tests. */
 int mxfp4_gemm_plan(int64_t M, int64_t N, int d, size_t workspace_bytes, int *weight_streaming, int *tile_m,
                     int *tile_n, int *k_pieces);
@@ -451,17 +449,14 @@ int torq_diag_gemm_plan(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W
                         void *workspace, size_t workspace_bytes, void *stream);
 /* The same for the form of the tiled kernel that stages its operands in a ring: tile_m x tile_n is 128 x 128, 128 x 64,
  * 64 x 128 or 64 x 64, d a multiple of 512, all pointers 16-byte aligned; k_pieces and workspace as above.
- *   on_chip     != 0: the k range halved inside a workgroup (64 x 64, k_pieces = 2, d a multiple of 1024; no workspace):
- *               the bits of k_pieces = 2
  * Anything else: TORQ_EINVAL / TORQ_EALIGN. */
 int torq_diag_gemm_ring(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q, const uint8_t *W_s,
                         void *out_bf16, int64_t M, int64_t N, int d, int tile_m, int tile_n, int k_pieces,
-                        int on_chip, void *workspace, size_t workspace_bytes, void *stream);
+                        void *workspace, size_t workspace_bytes, void *stream);
 /* The form behind mxfp4_gemm_plan's answer, for the same arguments (16-byte aligned scale arrays; the first launch where
  * there are two):
  *   staging   TORQ_GEMM_REGISTERS    tiled, operands staged through registers
  *             TORQ_GEMM_RING         tiled, operands staged in a ring
- *             TORQ_GEMM_RING_HALVED  the same, the k range halved inside a workgroup
  *             TORQ_GEMM_STRIPS       weight-streaming, strips straight to registers
  *             TORQ_GEMM_WHOLE_LINES  weight-streaming, by whole lines through a ring of each wave
  *   strips    16-row weight strips per workgroup of the two weight-streaming forms, else 0
@@ -469,9 +464,8 @@ int torq_diag_gemm_ring(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W
  * Host only, launches nothing.  TORQ_EINVAL for arguments that mxfp4_gemm_plan rejects. */
 #define TORQ_GEMM_REGISTERS   0
 #define TORQ_GEMM_RING        1
-#define TORQ_GEMM_RING_HALVED 2
-#define TORQ_GEMM_STRIPS      3
-#define TORQ_GEMM_WHOLE_LINES 4
+#define TORQ_GEMM_STRIPS      2
+#define TORQ_GEMM_WHOLE_LINES 3
 int torq_diag_gemm_form(int64_t M, int64_t N, int d, size_t workspace_bytes, int *staging, int *strips, int *items,
                         int *padded);
 /* A plain device-to-device copy of n_bytes (a multiple of 16; src and dst 16-byte aligned, not

@@ -127,7 +127,7 @@ def lib():
         L.torq_diag_gemm_plan.restype = i32
         L.torq_diag_gemm_plan.argtypes = [vp, vp, vp, vp, vp, i64, i64, i32, i32, i32, i32, vp, sz, vp]
         L.torq_diag_gemm_ring.restype = i32
-        L.torq_diag_gemm_ring.argtypes = [vp, vp, vp, vp, vp, i64, i64, i32, i32, i32, i32, i32, vp, sz, vp]
+        L.torq_diag_gemm_ring.argtypes = [vp, vp, vp, vp, vp, i64, i64, i32, i32, i32, i32, vp, sz, vp]
         L.torq_diag_gemm_form.restype = i32
         L.torq_diag_gemm_form.argtypes = [i64, i64, i32, sz] + [C.POINTER(i32)] * 4
         L.torq_diag_rotate_ablation.restype = i32
@@ -467,24 +467,24 @@ def torq_diag_gemm_plan(A_q, A_s, W_q, W_s, tile: int, k_pieces: int = 1, deep: 
     return out
 
 
-def torq_diag_gemm_ring(A_q, A_s, W_q, W_s, tile_m: int, tile_n: int, k_pieces: int = 1, on_chip: bool = False, out=None,
+def torq_diag_gemm_ring(A_q, A_s, W_q, W_s, tile_m: int, tile_n: int, k_pieces: int = 1, out=None,
                         workspace=None, stream=None):
     """mxfp4_gemm's tiled kernel staged in a ring, on a chosen tile shape and number of k pieces (see include/torq.h)."""
     M, N, d = A_q.shape[0], W_q.shape[0], A_q.shape[1] * 2
     if out is None:
         out = torch.empty((M, N), dtype=torch.bfloat16, device=A_q.device)
-    if workspace is None and k_pieces > 1 and not on_chip:
+    if workspace is None and k_pieces > 1:
         workspace = torch.empty((k_pieces * M * N * 4,), dtype=torch.uint8, device=A_q.device)
     ws_ptr = _dev(workspace, torch.uint8, "workspace") if workspace is not None else None
     _check(lib().torq_diag_gemm_ring(_dev(A_q, torch.uint8, "A_q"), _dev(A_s, torch.uint8, "A_s"),
                                      _dev(W_q, torch.uint8, "W_q"), _dev(W_s, torch.uint8, "W_s"),
-                                     _dev(out, torch.bfloat16, "out"), M, N, d, int(tile_m), int(tile_n), int(k_pieces), int(on_chip),
+                                     _dev(out, torch.bfloat16, "out"), M, N, d, int(tile_m), int(tile_n), int(k_pieces),
                                      ws_ptr, workspace.numel() if workspace is not None else 0, _stream(stream)),
            "torq_diag_gemm_ring")
     return out
 
 
-GEMM_STAGING = ("registers", "ring", "ring, halved", "strips", "whole lines")
+GEMM_STAGING = ("registers", "ring", "strips", "whole lines")
 
 
 def torq_diag_gemm_form(M: int, N: int, d: int, workspace_bytes: int = 0):

@@ -778,12 +778,12 @@ int torq_diag_gemm_plan(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W
 
 int torq_diag_gemm_ring(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q, const uint8_t *W_s,
                         void *out_bf16, int64_t M, int64_t N, int d, int tile_m, int tile_n, int k_pieces,
-                        int on_chip, void *workspace, size_t workspace_bytes, void *stream) {
+                        void *workspace, size_t workspace_bytes, void *stream) {
   if (M <= 0 || N <= 0 || d <= 0 || d % 512 != 0 || k_pieces < 1 || k_pieces > 64) return TORQ_EINVAL;
   if (!A_q || !A_s || !W_q || !W_s || !out_bf16) return TORQ_EINVAL;
   if (misaligned(A_q) || misaligned(W_q) || misaligned(out_bf16) || misaligned(A_s) || misaligned(W_s) || misaligned(workspace))
     return TORQ_EALIGN;
-  hipError_t e = torq::launch_mxfp4_gemm_ring_forced(A_q, A_s, W_q, W_s, out_bf16, M, N, d, tile_m, tile_n, k_pieces, on_chip, workspace,
+  hipError_t e = torq::launch_mxfp4_gemm_ring_forced(A_q, A_s, W_q, W_s, out_bf16, M, N, d, tile_m, tile_n, k_pieces, workspace,
                                                      workspace_bytes, (hipStream_t)stream);
   if (e == hipErrorInvalidValue) return TORQ_EINVAL;
   return e == hipSuccess ? TORQ_OK : hip_fail(e);

@@ -591,10 +591,9 @@ static int choose_tile(int64_t M, int64_t N) {
 }
 
 // the tiled forms: 0 = 256 x 256, 1 = 256 x 128, 2 = 128 x 128 staged through registers (above); 3 = 128 x 64,
-// 4 = 64 x 128, 5 = 64 x 64, 6 = 128 x 128 staged in a ring (mxfp4_gemm_ring.hip); 7 = 5 with the k range halved inside
-// the workgroup
-constexpr int FORMS = 8, HALVED = 7;
-static const int TILE_M[FORMS] = {256, 256, 128, 128, 64, 64, 128, 64}, TILE_N[FORMS] = {256, 128, 128, 64, 128, 64, 128, 64};
+// 4 = 64 x 128, 5 = 64 x 64, 6 = 128 x 128 staged in a ring (mxfp4_gemm_ring.hip)
+constexpr int FORMS = 7;
+static const int TILE_M[FORMS] = {256, 256, 128, 128, 64, 64, 128}, TILE_N[FORMS] = {256, 128, 128, 64, 128, 64, 128};
 
 // How a product is run: the weight-streaming kernel (mxfp4_gemm_skinny.hip), or the tiled kernel
 // in form `cfg` with its k range cut into `splits` pieces (1 = not cut).
@@ -636,7 +635,7 @@ static double rounds_us(int cfg, double tiles, double KT, int64_t N, int d) {
 // On 200 shapes that the fit had not seen the choice is 1.3 % off the best candidate on average, 3 % at the 90th percentile,
 // 28 % at worst; against the planner before, which had no ring, 1.19 times faster on average over 320.
 struct TileCost { double a, b, q, al, a2, stream, rows, cut, cut_mn, cut_s; };
-static const TileCost TILE_COST[HALVED] = {
+static const TileCost TILE_COST[FORMS] = {
     {12, 0.864, 1.067, 0.238, 3.631, 0.143, 0.02, 0, 0, 0},
     {5.699, 0.062, 1.158, 0.641, 4.019, 0.227, 0.065, 1.689, 1.24, 0.127},
     {3.973, 0, 0.836, 0.548, 2.895, 0.211, 0.057, 0, 0, 0},
@@ -644,7 +643,7 @@ static const TileCost TILE_COST[HALVED] = {
     {3.152, 0, 0.555, 0.629, 2.255, 0.126, 0.127, 2.393, 1.294, 0.146},
     {2.823, 0.015, 0.298, 0.749, 1.208, 0.134, 0.144, 1.848, 1.847, 0.136},
     {4.053, 0.053, 0.763, 0.573, 3.755, 0.195, 0.061, 2.248, 1.298, 0.172}};
-static const int TILE_SHARE[HALVED] = {1, 1, 2, 1, 1, 2, 1};      // workgroups that share a CU (by their LDS)
+static const int TILE_SHARE[FORMS] = {1, 1, 2, 1, 1, 2, 1};      // workgroups that share a CU (by their LDS)
 
 static double tiled_us(int form, int s, int64_t M, int64_t N, int d) {
   const double tiles_m = (double)((M + TILE_M[form] - 1) / TILE_M[form]), tiles_n = (double)((N + TILE_N[form] - 1) / TILE_N[form]);
@@ -711,10 +710,9 @@ static double skinny_several_us(int ns, int64_t M, int64_t N, int d) {
   return work > read ? work : read;
 }
 
-// The workspace that a plan needs.  Form 7 writes nothing there: 16 bytes are the caller's word that the sum may be cut.
+// the workspace that a plan needs
 static size_t plan_bytes(const GemmPlan &plan, int64_t M, int64_t N) {
-  if (plan.splits == 1) return 0;
-  return plan.cfg == HALVED ? 16 : (size_t)plan.splits * (size_t)M * (size_t)N * sizeof(float);
+  return plan.splits > 1 ? (size_t)plan.splits * (size_t)M * (size_t)N * sizeof(float) : 0;
 }
 
 static GemmPlan choose_plan(int64_t M, int64_t N, int d, bool allow_split) {
@@ -744,7 +742,7 @@ static GemmPlan choose_plan(int64_t M, int64_t N, int d, bool allow_split) {
           offer(!whole ? 2 : wide ? 4 : 5, s, few_rows_us(wide, s, N, d) + cut);
         }
     } else {
-      for (int form = 0; form < HALVED; ++form) {
+      for (int form = 0; form < FORMS; ++form) {
         if (form > 2 && !whole) continue;                            // the ring only takes whole pieces
         const bool cut = may_split && form != 0 && form != 2;        // the largest tile and form 2 are never cut
         for (int s = 1; s <= 16 && s <= (cut ? pairs : 1); ++s) {
@@ -753,12 +751,6 @@ static GemmPlan choose_plan(int64_t M, int64_t N, int d, bool allow_split) {
           offer(form, s, tiled_us(form, s, M, N, d));
         }
       }
-      // Form 7, a cut in two that stays on the chip (offered with a workspace like any cut, so that a call without one keeps
-      // the uncut sum).  As a rule form 5's two workgroups a CU do the same (form 7 2 - 14 % slower
-      // on 500 shapes); where the last tile row is nearly empty and the k range long it is ahead: us, form 5 / 7, [257,
-      // 7168] x 2048 9.6 / 9.1, [129, 11264] x 1536 13.0 / 12.0, [130, 16384] x 512 17.4 / 15.3, [193, 9216] x 1024 11.1 / 10.5.
-      if (may_split && d % 1024 == 0 && d >= 24 * 256 && tiles_of(HALVED) <= 256 && (M - 1) % 64 < 8)
-        offer(HALVED, 2, 0.94 * tiled_us(5, 1, M, N, d));
     }
   }
   // The streaming kernel's whole-line form against the tiles, weights from HBM: up to 16 rows it is ahead wherever it is
@@ -848,9 +840,7 @@ void mxfp4_gemm_form(int64_t M, int64_t N, int d, size_t workspace_bytes, int *s
   const GemmPlan plan = first_plan(M, N, d, workspace_bytes);
   *strips = *items = *padded = 0;
   if (!plan.skinny) {
-    *staging = plan.cfg == HALVED                                     ? TORQ_GEMM_RING_HALVED
-               : plan.cfg > 2 || (plan.cfg == 2 && plan.splits > 1)   ? TORQ_GEMM_RING
-                                                                      : TORQ_GEMM_REGISTERS;
+    *staging = plan.cfg > 2 || (plan.cfg == 2 && plan.splits > 1) ? TORQ_GEMM_RING : TORQ_GEMM_REGISTERS;
     return;
   }
   const bool lines = mxfp4_gemm_lines_form(M, N, d, strips, items, padded);
@@ -874,10 +864,8 @@ static hipError_t launch_by_plan(const GemmPlan &plan, const uint8_t *A_q, const
   const int splits = plan.splits;
   if ((splits > 1 || plan.deep || plan.cfg > 2) && !fullk) return hipErrorInvalidValue;
   if (splits > 1 && !partial) return hipErrorInvalidValue;
-  if (plan.cfg == HALVED)
-    return launch_mxfp4_gemm_ring(64, 64, 2, A_q, A_s, W_q, W_s, out_bf16, nullptr, 1, M, N, d, ldc, stream);
   if (plan.cfg > 2 || (plan.cfg == 2 && splits > 1)) {
-    const hipError_t e = launch_mxfp4_gemm_ring(TILE_M[plan.cfg], TILE_N[plan.cfg], 1, A_q, A_s, W_q, W_s, out_bf16, partial, splits,
+    const hipError_t e = launch_mxfp4_gemm_ring(TILE_M[plan.cfg], TILE_N[plan.cfg], A_q, A_s, W_q, W_s, out_bf16, partial, splits,
                                                 M, N, d, ldc, stream);
     return splits > 1 && e == hipSuccess ? launch_splitk_reduce(partial, splits, M, N, ldc, out_bf16, stream) : e;
   }
@@ -935,17 +923,13 @@ hipError_t launch_mxfp4_gemm_forced(const uint8_t *A_q, const uint8_t *A_s, cons
 // torq_diag_gemm_ring: the form staged in a ring, whatever the planner would take
 hipError_t launch_mxfp4_gemm_ring_forced(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q, const uint8_t *W_s,
                                          void *out_bf16, int64_t M, int64_t N, int d, int tile_m, int tile_n, int k_pieces,
-                                         int on_chip, void *workspace, size_t workspace_bytes, hipStream_t stream) {
+                                         void *workspace, size_t workspace_bytes, hipStream_t stream) {
   if ((int64_t)d * 128 >= 0x7FFFFFFF || d % 512 != 0 || k_pieces < 1) return hipErrorInvalidValue;
   if ((reinterpret_cast<uintptr_t>(A_s) & 15u) || (reinterpret_cast<uintptr_t>(W_s) & 15u)) return hipErrorInvalidValue;
-  if (on_chip)
-    return tile_m != 64 || tile_n != 64 || k_pieces != 2 || d % 1024 != 0
-               ? hipErrorInvalidValue
-               : launch_mxfp4_gemm_ring(64, 64, 2, A_q, A_s, W_q, W_s, out_bf16, nullptr, 1, M, N, d, N, stream);
   if (k_pieces > 1 && ((d / 512) % k_pieces != 0 || N % 8 != 0 || !workspace ||
                        workspace_bytes < (size_t)k_pieces * (size_t)M * (size_t)N * sizeof(float)))
     return hipErrorInvalidValue;
-  for (int form = 3; form < HALVED; ++form)
+  for (int form = 3; form < FORMS; ++form)
     if (TILE_M[form] == tile_m && TILE_N[form] == tile_n)
       return launch_by_plan(GemmPlan{false, form, k_pieces, false, 0.0}, A_q, A_s, W_q, W_s, out_bf16, M, N, d, N, true, false,
                             static_cast<float *>(workspace), stream);

@@ -50,10 +50,8 @@ constexpr int NST = 4, NSB = 2;       // stages of codes, buffers of scale bytes
 // assembly, which keeps the compiler from waiting for all of them in front of every LDS read; past the end the
 // requests go to empty buffers, so that the count holds.
 // SPLIT: blockIdx.y is the piece of the k range, its fp32 sums go to partial[blockIdx.y][M][N].
-// KG = 2: eight waves, two such groups with a ring each; group kg multiplies every second piece of the k range and the
-// groups' sums meet in LDS (a product of few tiles otherwise has room for twice the waves).
-template <int WM, int WN, int KG, bool SPLIT>
-__global__ void __launch_bounds__(256 * KG)
+template <int WM, int WN, bool SPLIT>
+__global__ void __launch_bounds__(256)
 mxfp4_gemm_ring_kernel(const uint8_t *__restrict__ A_q, const uint8_t *__restrict__ A_s, const uint8_t *__restrict__ W_q,
                        const uint8_t *__restrict__ W_s, uint16_t *__restrict__ out, float *__restrict__ partial, int64_t M,
                        int64_t N, int d, int tiles_m, int tiles_n, int64_t ldc) {
@@ -61,8 +59,7 @@ mxfp4_gemm_ring_kernel(const uint8_t *__restrict__ A_q, const uint8_t *__restric
   constexpr int A_CH = BM / 32, W_CH = BN / 32, C = A_CH + W_CH;   // DMA instructions of a wave per iteration
   constexpr int ROWS = (BM + BN + 255) / 256 * 256, S = ROWS / 256;  // scale rows (padded), DMA instructions per pair
   constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128, SBUF = ROWS * 16, S_BASE = NST * STAGE;
-  constexpr int GROUP = S_BASE + NSB * SBUF;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
+  extern __shared__ __attribute__((aligned(16))) char lds[];
 
   const int total = tiles_m * tiles_n;
   int lid = blockIdx.x;
@@ -71,15 +68,13 @@ mxfp4_gemm_ring_kernel(const uint8_t *__restrict__ A_q, const uint8_t *__restric
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
   const int rows_a = (M - m0 < BM) ? (int)(M - m0) : BM, rows_w = (N - n0 < BN) ? (int)(N - n0) : BN;
 
-  const int tid = threadIdx.x & 255, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int kg = KG > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
-  char *const lds = smem + kg * GROUP;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wy = wave >> 1, wx = wave & 1;
   const int lrow = lane & 31, g = lane >> 5;
   const int row_bytes = d / 2, srow_bytes = d / 32;
   const int KT = d / 256;
-  const int pieces = KG * (SPLIT ? (int)gridDim.y : 1), count = KT / pieces;      // even
-  const int kt0 = (KG * (SPLIT ? (int)blockIdx.y : 0) + kg) * count;
+  const int count = SPLIT ? KT / (int)gridDim.y : KT;      // even
+  const int kt0 = SPLIT ? (int)blockIdx.y * count : 0;
 
   const i32x4 a_rs = ring_rsrc(A_q + m0 * row_bytes, (uint32_t)rows_a * row_bytes);
   const i32x4 w_rs = ring_rsrc(W_q + n0 * row_bytes, (uint32_t)rows_w * row_bytes);
@@ -211,24 +206,6 @@ mxfp4_gemm_ring_kernel(const uint8_t *__restrict__ A_q, const uint8_t *__restric
 #undef SGB
   ring_meet<0>();                                  // (what follows reuses the stages) nothing is on its way into the LDS any more
 
-  if constexpr (KG > 1) {
-    // group 1's sums to LDS, group 0 adds them (the order in which a cut's pieces are added) and goes on alone
-    f32x4 *const sums = reinterpret_cast<f32x4 *>(smem) + wave * (WM * WN * 256) + lane;
-    if (kg == 1)
-#pragma unroll
-      for (int t = 0; t < WM * WN * 4; ++t) {
-        const f32x16 &a = acc[t / 4 / WM][t / 4 % WM];
-        sums[t * 64] = f32x4{a[t % 4 * 4], a[t % 4 * 4 + 1], a[t % 4 * 4 + 2], a[t % 4 * 4 + 3]};
-      }
-    __syncthreads();
-    if (kg == 1) return;
-#pragma unroll
-    for (int t = 0; t < WM * WN * 4; ++t) {
-      const f32x4 v = sums[t * 64];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[t / 4 / WM][t / 4 % WM][t % 4 * 4 + e] += v[e];
-    }
-  }
   if constexpr (SPLIT) {
     float *const dstp = partial + (size_t)blockIdx.y * (size_t)M * (size_t)N;
 #pragma unroll
@@ -246,7 +223,7 @@ mxfp4_gemm_ring_kernel(const uint8_t *__restrict__ A_q, const uint8_t *__restric
     }
   } else {
     constexpr int ROW_E = 64 * WN, PITCH_E = ROW_E + 16, CH_ROW = ROW_E / 16;
-    char *const ep = smem + (KG > 1 ? 4 * WM * WN * 4096 : 0) + wave * (32 * WM) * PITCH_E;
+    char *const ep = lds + wave * (32 * WM) * PITCH_E;
 #pragma unroll
     for (int i = 0; i < WM; ++i)
 #pragma unroll
@@ -280,32 +257,32 @@ mxfp4_gemm_ring_kernel(const uint8_t *__restrict__ A_q, const uint8_t *__restric
   }
 }
 
-template <int WM, int WN, int KG>
+template <int WM, int WN>
 static hipError_t launch_ring(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q, const uint8_t *W_s, void *out,
                               float *partial, int splits, int64_t M, int64_t N, int d, int64_t ldc, hipStream_t stream) {
   constexpr int BM = 64 * WM, BN = 64 * WN, ROWS = (BM + BN + 255) / 256 * 256;
-  constexpr size_t lds = KG * ((size_t)NST * (BM + BN) * 128 + (size_t)NSB * ROWS * 16);
+  constexpr size_t lds = (size_t)NST * (BM + BN) * 128 + (size_t)NSB * ROWS * 16;
   static_assert(lds <= 160 * 1024, "LDS of a CU");
   const int64_t tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   if (tiles_m * tiles_n > 0x7FFFFFFF) return hipErrorInvalidValue;
   auto go = [&](auto kern, std::atomic<uint64_t> &raised) {
     const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(kern), lds, raised);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n), splits), dim3(256 * KG), lds, stream, A_q, A_s, W_q, W_s,
+    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n), splits), dim3(256), lds, stream, A_q, A_s, W_q, W_s,
                        reinterpret_cast<uint16_t *>(out), partial, M, N, d, (int)tiles_m, (int)tiles_n, ldc);
     return hipGetLastError();
   };
   static std::atomic<uint64_t> raised[2];
-  return splits > 1 ? go(mxfp4_gemm_ring_kernel<WM, WN, KG, true>, raised[1]) : go(mxfp4_gemm_ring_kernel<WM, WN, KG, false>, raised[0]);
+  return splits > 1 ? go(mxfp4_gemm_ring_kernel<WM, WN, true>, raised[1]) : go(mxfp4_gemm_ring_kernel<WM, WN, false>, raised[0]);
 }
 
-hipError_t launch_mxfp4_gemm_ring(int tile_m, int tile_n, int groups, const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q,
+hipError_t launch_mxfp4_gemm_ring(int tile_m, int tile_n, const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q,
                                   const uint8_t *W_s, void *out, float *partial, int splits, int64_t M, int64_t N, int d,
                                   int64_t ldc, hipStream_t stream) {
-#define TORQ_RING(WM_, WN_, KG_)                                 \
-  if (tile_m == 64 * WM_ && tile_n == 64 * WN_ && groups == KG_) \
-    return launch_ring<WM_, WN_, KG_>(A_q, A_s, W_q, W_s, out, partial, splits, M, N, d, ldc, stream);
-  TORQ_RING(2, 2, 1) TORQ_RING(2, 1, 1) TORQ_RING(1, 2, 1) TORQ_RING(1, 1, 1) TORQ_RING(1, 1, 2)
+#define TORQ_RING(WM_, WN_)                      \
+  if (tile_m == 64 * WM_ && tile_n == 64 * WN_)  \
+    return launch_ring<WM_, WN_>(A_q, A_s, W_q, W_s, out, partial, splits, M, N, d, ldc, stream);
+  TORQ_RING(2, 2) TORQ_RING(2, 1) TORQ_RING(1, 2) TORQ_RING(1, 1)
 #undef TORQ_RING
   return hipErrorInvalidValue;
 }

@@ -74,15 +74,14 @@ void mxfp4_gemm_plan(int64_t M, int64_t N, int d, size_t workspace_bytes, int *s
 // torq_diag_gemm_form: the form behind the plan
 void mxfp4_gemm_form(int64_t M, int64_t N, int d, size_t workspace_bytes, int *staging, int *strips, int *items, int *padded);
 // The tiled kernel with its operands staged in a ring (mxfp4_gemm_ring.hip): tiles 128x128, 128x64, 64x128 and 64x64,
-// d a multiple of 512, scale arrays 16-byte aligned.  groups = 2 (64x64 only): the workgroup's two halves take half of the
-// k range each and add up on the chip.  splits > 1: the pieces' fp32 sums go to partial[splits][M][N] and out is not
-// written.  d / 512 divisible by groups * splits.
-hipError_t launch_mxfp4_gemm_ring(int tile_m, int tile_n, int groups, const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q,
+// d a multiple of 512, scale arrays 16-byte aligned.  splits > 1: the pieces' fp32 sums go to partial[splits][M][N] and out is not
+// written.  d / 512 divisible by splits.
+hipError_t launch_mxfp4_gemm_ring(int tile_m, int tile_n, const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q,
                                   const uint8_t *W_s, void *out, float *partial, int splits, int64_t M, int64_t N, int d,
                                   int64_t ldc, hipStream_t stream);
 hipError_t launch_mxfp4_gemm_ring_forced(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q, const uint8_t *W_s,
                                          void *out_bf16, int64_t M, int64_t N, int d, int tile_m, int tile_n, int k_pieces,
-                                         int on_chip, void *workspace, size_t workspace_bytes, hipStream_t stream);
+                                         void *workspace, size_t workspace_bytes, hipStream_t stream);
 // the tiled kernel on a given plan: tile 0 ... 3 = 256x256, 256x128, 128x128, 128x64 (always in a ring); k_pieces > 1 needs the workspace (k_pieces * M * N floats) and d / 512 divisible by it; deep: tile 2's deeper load
 // pipeline where it is not cut
 hipError_t launch_mxfp4_gemm_forced(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q, const uint8_t *W_s,

@@ -400,8 +400,8 @@ def test_gemm_every_plan_of_the_tiled_kernel(tq, oracle, M, N, d):
 
 
 # The form staged in a ring, every tile: fewer iterations than stages, an odd number of pairs, ragged edges, tile counts
-# that are and are not multiples of 8, and cuts (k halved inside the workgroup among them).  The uncut sums are
-# mxfp4_gemm's bit for bit, a cut's are those of the other tiled forms cut alike.
+# that are and are not multiples of 8, and cuts.  The uncut sums are mxfp4_gemm's bit for bit, a cut's are those of the
+# other tiled forms cut alike.
 @pytest.mark.parametrize("M,N,d", [(1, 8, 512), (64, 64, 512), (65, 129, 1024), (200, 264, 1536), (128, 1024, 2048), (300, 72, 5120)])
 def test_gemm_ring_every_tile(tq, oracle, M, N, d):
     rng = np.random.default_rng(M * 7 + N + d)
@@ -424,26 +424,6 @@ def test_gemm_ring_every_tile(tq, oracle, M, N, d):
             torch.cuda.synchronize()
             assert torch.equal(out[:M].view(torch.int16), ref.view(torch.int16)), (tile_m, tile_n, k_pieces)
             assert torch.all(out[M] == 7.0)
-        if k_pieces == 2 and d % 1024 == 0:
-            halved = tq.torq_diag_gemm_ring(*dev, 64, 64, 2, on_chip=True)
-            torch.cuda.synchronize()
-            assert torch.equal(halved.view(torch.int16), ref.view(torch.int16))
-
-
-# The k range halved inside a workgroup: the planner's own call, with the 16 bytes of workspace that it asks for
-@pytest.mark.parametrize("M,N,d", [(257, 2048, 7168), (129, 4096, 14336), (321, 1024, 7168)])
-def test_gemm_halved_on_the_chip_leaves_the_workspace_alone(tq, M, N, d):
-    need = tq.mxfp4_gemm_workspace_bytes(M, N, d)
-    assert need == 16 and tq.torq_diag_gemm_form(M, N, d, need)[0] == "ring, halved"
-    gen = torch.Generator(device=DEV)
-    gen.manual_seed(M + N + d)
-    draw = lambda lo, hi, *shape: torch.randint(lo, hi, shape, dtype=torch.uint8, device=DEV, generator=gen)
-    ops = draw(0, 256, M, d // 2), draw(118, 136, M, d // 32), draw(0, 256, N, d // 2), draw(110, 126, N, d // 32)
-    ws = torch.full((16,), 77, dtype=torch.uint8, device=DEV)
-    got = tq.mxfp4_gemm_ws(*ops, workspace=ws)
-    want = tq.torq_diag_gemm_ring(*ops, 64, 64, 2)          # the same two pieces through a workspace
-    torch.cuda.synchronize()
-    assert torch.equal(got.view(torch.int16), want.view(torch.int16)) and torch.all(ws == 77)
 
 
 def test_gemm_plan_diagnostic_rejects_what_a_form_cannot_take(tq):
