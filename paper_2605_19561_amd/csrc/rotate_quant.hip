@@ -80,7 +80,7 @@ rotate_kernel(const uint4 *__restrict__ x, int64_t TG, int G,
 //   ROT_ALONE, as ROT_ONCE, and the workgroup is one wave with one tile of 32 output blocks, workgroup b tile
 //   b mod NW; it stages the token-group for itself.  For a handful of token-groups: the CU loads its
 //   own slice of R_inter, 8 KB to 16 KB, not all of them (and as consecutive workgroups go to the XCDs in turn, an
-//   L2 holds NW / 8 of the table rather than all of it).
+//   L2 holds one tile of the table for NW = 2 or 4; all of it for NW = 3).
 enum { ROT_LOOP = 0, ROT_ONCE = 1, ROT_ALONE = 2 };
 
 template <int KS16, int TB, int FORM, int FMT>
@@ -718,7 +718,7 @@ hipError_t launch_rotate(const torq_rotation *r, const void *x_bf16, int64_t M, 
   if (TG == 0) return hipSuccess;
   // A handful of token-groups, G = 64 ... 128: every 32 output blocks of a token-group by a workgroup of one
   // wave (rotate_kernel32, ROT_ALONE) while that leaves each CU no more than one of them.  The kernel is then a
-  // chain of launch, operand loads and 30 MFMAs, and a CU that holds all the waves of a token-group waits
+  // chain of launch, operand loads and 14 to 22 MFMAs, and a CU that holds all the waves of a token-group waits
   // for the whole of R_inter (64 KB at G = 128) where it could wait for one tile of it.  Cold operands, HIP-graph
   // replays, us before / now: G = 128 at 1 to 32 token-groups 3.0 / 2.6, at 64 3.0 / 2.85; G = 112 2.9 / 2.5;
   // G = 96 at 16 3.05 / 2.5; G = 80 2.7 / 2.45; G = 64 2.9 / 2.35; the fp32 output gains 0.4 to 1.1.  With two
