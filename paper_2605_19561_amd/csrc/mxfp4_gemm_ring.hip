@@ -20,17 +20,6 @@ namespace {
 
 typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
 
-// 16 bytes per lane from rsrc[voff + soff] to LDS byte lds_addr + 16 * lane
-__device__ __forceinline__ void ring_dma16(i32x4 rsrc, uint32_t lds_addr, int voff, int soff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "m0");
-}
-
-__device__ __forceinline__ i32x4 ring_rsrc(const uint8_t *p, uint32_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(p);
-  return i32x4{(int)(uint32_t)a, (int)((uint32_t)(a >> 32) & 0xFFFFu), (int)bytes, 0x00020000};
-}
-
 // every DMA but the youngest N of this wave has landed, every LDS read of it has returned; then the workgroup meets
 template <int N>
 __device__ __forceinline__ void ring_meet() {
@@ -76,10 +65,10 @@ mxfp4_gemm_ring_kernel(const uint8_t *__restrict__ A_q, const uint8_t *__restric
   const int count = SPLIT ? KT / (int)gridDim.y : KT;      // even
   const int kt0 = SPLIT ? (int)blockIdx.y * count : 0;
 
-  const i32x4 a_rs = ring_rsrc(A_q + m0 * row_bytes, (uint32_t)rows_a * row_bytes);
-  const i32x4 w_rs = ring_rsrc(W_q + n0 * row_bytes, (uint32_t)rows_w * row_bytes);
-  const i32x4 as_rs = ring_rsrc(A_s + m0 * srow_bytes, (uint32_t)rows_a * srow_bytes);
-  const i32x4 ws_rs = ring_rsrc(W_s + n0 * srow_bytes, (uint32_t)rows_w * srow_bytes);
+  const i32x4 a_rs = raw_buffer(A_q + m0 * row_bytes, (uint32_t)rows_a * row_bytes);
+  const i32x4 w_rs = raw_buffer(W_q + n0 * row_bytes, (uint32_t)rows_w * row_bytes);
+  const i32x4 as_rs = raw_buffer(A_s + m0 * srow_bytes, (uint32_t)rows_a * srow_bytes);
+  const i32x4 ws_rs = raw_buffer(W_s + n0 * srow_bytes, (uint32_t)rows_w * srow_bytes);
   const int c_row = tid >> 3;
   const int c_voff = c_row * row_bytes + (((tid & 7) ^ ((c_row >> 1) & 7)) * 16);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
@@ -88,7 +77,7 @@ mxfp4_gemm_ring_kernel(const uint8_t *__restrict__ A_q, const uint8_t *__restric
   // chunk c (32 rows of a wave's DMA each) of an iteration's codes into stage slot: the weights first
   auto code_chunk = [&](int c, i32x4 ra, i32x4 rw, int ko, int slot) {
     const int i = c < W_CH ? c : c - W_CH;
-    ring_dma16(c < W_CH ? rw : ra, lds0 + slot * STAGE + (c < W_CH ? A_BYTES : 0) + i * 4096 + wave * 1024, c_voff, ko + i * 32 * row_bytes);
+    load_to_lds16<false>(c < W_CH ? rw : ra, lds0 + slot * STAGE + (c < W_CH ? A_BYTES : 0) + i * 4096 + wave * 1024, c_voff, ko + i * 32 * row_bytes);
   };
   auto load_codes = [&](int k, int slot) {
     const bool ok = k < count;
@@ -104,7 +93,7 @@ mxfp4_gemm_ring_kernel(const uint8_t *__restrict__ A_q, const uint8_t *__restric
       const int r0 = i * 256 + wave * 64;                          // BM is a multiple of 64
       const bool is_a = r0 < BM;
       const i32x4 rs = empty(is_a ? as_rs : ws_rs, ok && r0 < BM + BN);
-      ring_dma16(rs, lds0 + S_BASE + sb * SBUF + r0 * 16, lane * srow_bytes, (is_a ? r0 : r0 - BM) * srow_bytes + (kt0 / 2 + q) * 16);
+      load_to_lds16<false>(rs, lds0 + S_BASE + sb * SBUF + r0 * 16, lane * srow_bytes, (is_a ? r0 : r0 - BM) * srow_bytes + (kt0 / 2 + q) * 16);
     }
   };
 

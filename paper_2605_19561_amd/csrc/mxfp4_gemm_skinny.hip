@@ -682,15 +682,6 @@ template <int N>
 __device__ __forceinline__ void lines_wait() {
   asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
 }
-// 16 bytes per lane from rsrc[voff + soff] to LDS byte lds_addr + 16 * lane
-__device__ __forceinline__ void lines_dma(i32x4 rsrc, uint32_t lds_addr, int voff, int soff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "m0", "memory");
-}
-__device__ __forceinline__ i32x4 lines_rsrc(const uint8_t *p, uint32_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(p);
-  return i32x4{(int)(uint32_t)a, (int)((uint32_t)(a >> 32) & 0xFFFFu), (int)bytes, 0x00020000};
-}
 
 template <int MT, int NS, int R>
 __global__ void __launch_bounds__(64 * WAVES)
@@ -715,8 +706,8 @@ mxfp4_gemm_lines_kernel(const uint8_t *__restrict__ A_q, const uint8_t *__restri
   const int pu = srow_bytes / 16 + pad, s_pitch = pu * 16;
   const int w_units = 16 * NS * pu, units = w_units + 16 * MT * pu;
   {
-    const i32x4 ws_rs = lines_rsrc(W_s + n0 * srow_bytes, (uint32_t)rows_w * srow_bytes);
-    const i32x4 as_rs = lines_rsrc(A_s, (uint32_t)M * srow_bytes);
+    const i32x4 ws_rs = raw_buffer(W_s + n0 * srow_bytes, (uint32_t)rows_w * srow_bytes);
+    const i32x4 as_rs = raw_buffer(A_s, (uint32_t)M * srow_bytes);
     const float per_unit = __builtin_amdgcn_rcpf((float)pu);        // (j / pu in float, as above)
     for (int i = wave; i * 64 < units; i += WAVES) {
       const int j = i * 64 + lane;
@@ -726,15 +717,15 @@ mxfp4_gemm_lines_kernel(const uint8_t *__restrict__ A_q, const uint8_t *__restri
       // where only one is needed the other is an empty one
       const bool is_w = row < 16 * NS;
       if (i * 64 < w_units)
-        { if (is_w) lines_dma(ws_rs, sc0 + i * 1024, ok ? row * srow_bytes + col * 16 : OOB_VOFF, 0); }
+        { if (is_w) load_to_lds16(ws_rs, sc0 + i * 1024, ok ? row * srow_bytes + col * 16 : OOB_VOFF, 0); }
       if (i * 64 + 63 >= w_units)
-        { if (!is_w) lines_dma(as_rs, sc0 + i * 1024, ok ? (row - 16 * NS) * srow_bytes + col * 16 : OOB_VOFF, 0); }
+        { if (!is_w) load_to_lds16(as_rs, sc0 + i * 1024, ok ? (row - 16 * NS) * srow_bytes + col * 16 : OOB_VOFF, 0); }
     }
   }
 
   // ---- items: line pair kp = wave, wave + 8, ...; chunks swizzled by the row, as the reads below expect
-  const i32x4 w_rs = lines_rsrc(W_q + n0 * row_bytes, (uint32_t)rows_w * row_bytes);
-  const i32x4 a_rs = lines_rsrc(A_q, (uint32_t)M * row_bytes);
+  const i32x4 w_rs = raw_buffer(W_q + n0 * row_bytes, (uint32_t)rows_w * row_bytes);
+  const i32x4 a_rs = raw_buffer(A_q, (uint32_t)M * row_bytes);
   const int l_row = lane >> 3;
   const int v0 = l_row * row_bytes + ((lane & 7) ^ (l_row >> 1)) * 16, v1 = (l_row + 8) * row_bytes + ((lane & 7) ^ (l_row >> 1) ^ 4) * 16;
   const uint32_t ring0 = lds0 + wave * R * ITEM;
@@ -747,8 +738,8 @@ mxfp4_gemm_lines_kernel(const uint8_t *__restrict__ A_q, const uint8_t *__restri
 #pragma unroll
     for (int t = 0; t < T; ++t) {
       const int so = (t < NS ? t : t - NS) * 16 * row_bytes + kp * 128;
-      lines_dma(t < NS ? rw : ra, ring0 + slot * ITEM + t * 2048, v0, so);
-      lines_dma(t < NS ? rw : ra, ring0 + slot * ITEM + t * 2048 + 1024, v1, so);
+      load_to_lds16(t < NS ? rw : ra, ring0 + slot * ITEM + t * 2048, v0, so);
+      load_to_lds16(t < NS ? rw : ra, ring0 + slot * ITEM + t * 2048 + 1024, v1, so);
     }
   };
 #pragma unroll

@@ -336,7 +336,7 @@ rotate_kernel32(const uint4 *__restrict__ x, int64_t TG, int G,
 //
 // Two things are issued from assembly because of how the compiler orders LDS traffic: it places every LDS
 // read it recognises behind ALL outstanding loads into LDS (vmcnt(0)), which would undo the ring.  So
-// the loads into LDS (dma16) and the transposing reads (lds_tr_read) are invisible to it, and the waits
+// the loads into LDS (load_to_lds16) and the transposing reads (lds_tr_read) are invisible to it, and the waits
 // are written by hand:
 //   * LDS reads: lds_wait4 (lgkmcnt(0)) in front of the MFMAs that consume them; the next k-step's four
 //     reads are issued right after it and have the MFMAs of this k-step to land.
@@ -368,11 +368,6 @@ __device__ __forceinline__ i16x4 lds_tr_read(uint32_t addr) {
 }
 __device__ __forceinline__ void lds_wait4(i16x4 &a, i16x4 &b, i16x4 &c, i16x4 &d) {
   asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
-}
-// 16 bytes per lane from a buffer straight into LDS at lds_addr + 16 * lane (lds_addr wave-uniform)
-__device__ __forceinline__ void dma16(i32x4 rsrc, uint32_t lds_addr, uint32_t voff, uint32_t soff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
 }
 typedef __attribute__((__vector_size__(2 * sizeof(unsigned)))) unsigned u32x2;
 
@@ -438,7 +433,7 @@ rotate_ring_kernel32(const uint4 *__restrict__ x, int64_t TG, int G,
       const i32x4 rs = i32x4{(int)(uint32_t)base, (int)((uint32_t)(base >> 32) & 0xFFFFu), ok ? TG_BYTES : 0, 0x00020000};
       const uint32_t la = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)(dst) + j * TG_STRIDE + wave_u * 64 * 16;
 #pragma unroll
-      for (int i = 0; i < CH; ++i) dma16(rs, la + i * NTHR * 16, tid * 16, i * NTHR * 16);
+      for (int i = 0; i < CH; ++i) load_to_lds16(rs, la + i * NTHR * 16, tid * 16, i * NTHR * 16);
     }
   };
 

@@ -15,6 +15,22 @@ typedef __attribute__((__vector_size__(8 * sizeof(int)))) int i32x8;
 typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short i16x4;
 
+// A raw buffer of `bytes` bytes as four words, and a load of 16 bytes per lane from it, at voff + soff, straight into LDS at
+// lds_addr + 16 * lane (lds_addr uniform over the wave).  Inline assembly: the compiler neither waits for it nor knows that
+// it writes, so a kernel counts these loads in its own waits.  FENCE: the compiler's own memory accesses stay on their
+// side of it (a kernel that places its LDS reads itself does without, and its products may move past).
+__device__ __forceinline__ i32x4 raw_buffer(const void *p, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  return i32x4{(int)(uint32_t)a, (int)((uint32_t)(a >> 32) & 0xFFFFu), (int)bytes, 0x00020000};
+}
+#define TORQ_LOAD_TO_LDS16 "s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+template <bool FENCE = true>
+__device__ __forceinline__ void load_to_lds16(i32x4 rsrc, uint32_t lds_addr, int voff, int soff) {
+  if constexpr (FENCE) asm volatile(TORQ_LOAD_TO_LDS16 :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "m0", "memory");
+  else asm volatile(TORQ_LOAD_TO_LDS16 :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "m0");
+}
+#undef TORQ_LOAD_TO_LDS16
+
 // ---------------------------------------------------------------------------
 // MXFP4 quantiser for one microscaling block (Section 4, Eq. 1; Algorithm 3,
 // step 4).  The shared scale is the E8M0 byte with 2^(byte-127) =
