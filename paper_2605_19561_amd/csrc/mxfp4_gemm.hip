@@ -627,33 +627,81 @@ static double rounds_us(int cfg, double tiles, double KT, int64_t N, int d) {
 // planner prices every candidate with a model fitted to measurements and takes the cheapest.  All measurements: HIP-graph
 // replays over weight copies of up to 600 MB in all (weights from HBM, as in a model; activations from the caches).
 //
-// More than 64 rows: 900 random shapes (M = 65 ... 2048, N = 256 ... 28672, d = 1024 ... 28672), every candidate of each.
-// Microseconds, for w workgroups a CU, rounds = ceil(w / those that share a CU), e = al ceil(w) + (1 - al) w:
-//   a + a2 (rounds - 1) + iterations of one workgroup * (b + q e)   (a CU's workgroups share its path from the L2, and a
-//   full chip the path behind it), never less than a + the weights' bytes * (stream + rows * tile rows); a cut adds the
-//   second launch, the pieces' traffic and a little per piece.
-// On 200 shapes that the fit had not seen the choice is 1.3 % off the best candidate on average, 3 % at the 90th percentile,
-// 28 % at worst; against the planner before, which had no ring, 1.19 times faster on average over 320.
-struct TileCost { double a, b, q, al, a2, stream, rows, cut, cut_mn, cut_s; };
-static const TileCost TILE_COST[FORMS] = {
-    {12, 0.864, 1.067, 0.238, 3.631, 0.143, 0.02, 0, 0, 0},
-    {5.699, 0.062, 1.158, 0.641, 4.019, 0.227, 0.065, 1.689, 1.24, 0.127},
-    {3.973, 0, 0.836, 0.548, 2.895, 0.211, 0.057, 0, 0, 0},
-    {3.119, 0.018, 0.483, 0.682, 1.998, 0.251, 0.075, 2.134, 1.675, 0.127},
-    {3.152, 0, 0.555, 0.629, 2.255, 0.126, 0.127, 2.393, 1.294, 0.146},
-    {2.823, 0.015, 0.298, 0.749, 1.208, 0.134, 0.144, 1.848, 1.847, 0.136},
-    {4.053, 0.053, 0.763, 0.573, 3.755, 0.195, 0.061, 2.248, 1.298, 0.172}};
+// More than 64 rows: 20800 random shapes (M = 65 ... 65000, N = 8 ... 28672, d = 256 ... 28672), every candidate of each.
+// Microseconds, linear in what a launch does, for `iters` iterations of each of w workgroups a CU (full = ceil(w)):
+//   the launch, each further round of workgroups, iters * full and iters * w (a CU's workgroups share its path from the L2,
+//   and a full chip the path behind it), iters * w again times iters / 32 (a long launch meets the power limit) and times
+//   the part of the tiles that is padding, the MB that the XCDs' L2s fetch (fetched_mb), the weights' MB, the output's 10^6
+//   elements, these again where rows are not whole 16-byte pieces or the last tile column is ragged, and for a cut the
+//   second launch, the pieces' 10^6 elements and a little per piece.
+// The coefficients are those whose choices cost least on four fifths of the shapes (not those that fit the times best).  On the
+// others the choice is 0.3 % off the best candidate on average, 1 % at the 90th percentile, 6 % at the 99th, 33 % at worst.
+// Prices fitted to 65 ... 2048 rows that knew of the weights' traffic alone came before: 1.3 %, 4 %, 22 % and 45 % up to 2048
+// rows, 3.5 %, 13 %, 32 % and 43 % beyond ([4096, 5120] x 1024 20.1 -> 18.3 us, [9472, 2048] x 1152 29.0 -> 20.7,
+// [4919, 11264] x 384 31.1 -> 22.4).
+struct TileCost { double a, round, full, part, deep, pad, fetched, weights, out, odd, edge, cut, cut_mn, cut_s; };
+// (the last three: the plain forms of the first three, which take any d)
+static const TileCost TILE_COST[FORMS + 3] = {
+    {11, 0, 1.02, 0.493, 0.0572, 0.169, 0.00756, 0.0229, 0, 1.49, 0.373, 0, 0, 0},
+    {3.96, 2.47, 0.768, 0.0856, 0.02, -0.151, 0.031, 0.0496, 0.371, 1.67, 0.449, 2.04, 1.46, 0.108},
+    {3.72, 1.03, 0.466, 0.0158, 0.0344, -0.223, 0.0462, 0.094, 0.309, 1.47, 0.0831, 0, 0, 0},
+    {3.43, 2.01, 0.314, 0, 0.0202, -0.198, 0.0503, 0.0999, 0.00635, 2.15, 0.431, 2.12, 1.45, 0.0958},
+    {3.51, 1.94, 0.314, 0, 0.0286, -0.124, 0.0414, 0.139, -0.0568, 1.51, 0.372, 1.85, 1.55, 0.147},
+    {3.03, 0.71, 0.224, 0, 0.0212, -0.108, 0.0234, 0.128, 0.289, 1.82, 0.228, 1.73, 1.88, 0.13},
+    {4.34, 2.13, 0.46, 0.00694, 0.0271, -0.136, 0.0409, 0.0673, 0.278, 1.65, 0.16, 1.05, 1.51, 0.207},
+    {11.8, 0, 1.92, -0.0477, 0.254, -0.488, 0.00869, 0.23, 0.0024, 1.45, 0.546, 0, 0, 0},
+    {5.42, 0.23, 1.52, 0, 0.105, -0.219, 0.0212, 0.0236, 0.438, 1.78, 0.219, 0, 0, 0},
+    {5.16, 2.56, 0.849, -0.00299, 0, -0.442, 0.0609, 0.159, -0.0351, 1.26, 0.17, 0, 0, 0}};
 static const int TILE_SHARE[FORMS] = {1, 1, 2, 1, 1, 2, 1};      // workgroups that share a CU (by their LDS)
 
-static double tiled_us(int form, int s, int64_t M, int64_t N, int d) {
-  const double tiles_m = (double)((M + TILE_M[form] - 1) / TILE_M[form]), tiles_n = (double)((N + TILE_N[form] - 1) / TILE_N[form]);
-  const double w = tiles_m * tiles_n * s / 256.0, iters = (double)((d + 255) / 256) / s;
-  const TileCost &c = TILE_COST[form];
-  const double rounds = std::ceil(w / TILE_SHARE[form]);
-  double t = c.a + c.a2 * (rounds - 1.0) + iters * (c.b + c.q * (c.al * std::ceil(w) + (1.0 - c.al) * w));
-  const double stream = c.a + (double)N * (double)d * 0.53125 / 1e6 * (c.stream + c.rows * tiles_m);
-  if (t < stream) t = stream;
-  if (s > 1) t += c.cut + c.cut_mn * (double)s * (double)M * (double)N / 1e6 + c.cut_s * s;
+// MB of operands that the L2s of the eight XCDs fetch: an XCD runs n tiles at a time and fetches their rows of A and of W
+// once.  Tile order as in the kernels: a tile count that is a multiple of 8 is dealt out in contiguous runs, any other
+// in turn, down the tile rows first (the forms staged through registers: of eight rows at a time).
+static double fetched_mb(int form, int64_t tiles_m, int64_t tiles_n, int d) {
+  const double run = std::fmax(1.0, (double)(tiles_m * tiles_n) / 8.0), n = std::fmin(run, 32.0 * TILE_SHARE[form]);
+  const int64_t rows = form > 2 || tiles_m < 8 ? tiles_m : 8;
+  const double tm = (double)tiles_m, tn = (double)tiles_n, r = (double)rows;
+  double a, w;                                                   // tile rows and columns among the n
+  if (tiles_m * tiles_n % 8 == 0) {
+    a = n <= r * tn ? std::fmin(n, r) : std::fmin(tm, n / tn);
+    w = std::fmin(tn, 1.0 + (n - 1.0) / r);
+  } else if (form <= 2 && tiles_m >= 8) {
+    a = std::fmax(1.0, n / tn);
+    w = std::fmin(tn, n);
+  } else {
+    const int64_t low = rows & -rows;                            // the power of two in it: every 8 / low-th column meets the
+    const double cols = std::fmin(tn, std::fmax(1.0, 8.0 * n / r));   // same rows again
+    a = std::fmin(std::fmin(n, r), (double)((rows + 7) / 8) * std::fmin(cols, low < 8 ? (double)(8 / low) : 1.0));
+    w = std::fmin(n, cols);
+  }
+  return 8.0 * (run / n) * (a * TILE_M[form] + w * TILE_N[form]) * (double)d * 0.53125 / 1e6;
+}
+
+// the price of a form: `base` whatever the number of pieces
+struct TiledPrice {
+  const TileCost *c;
+  int share;
+  double base, w, iters, mn;
+};
+
+static TiledPrice tiled_price(int form, int64_t M, int64_t N, int d) {
+  const int64_t tiles_m = (M + TILE_M[form] - 1) / TILE_M[form], tiles_n = (N + TILE_N[form] - 1) / TILE_N[form];
+  const TileCost &c = TILE_COST[d % 512 == 0 ? form : FORMS + form];
+  const double mn = (double)M * (double)N / 1e6, w = (double)(tiles_m * tiles_n) / 256.0, iters = (double)((d + 255) / 256);
+  const double padding = 1.0 - (double)M * (double)N / ((double)(tiles_m * TILE_M[form]) * (double)(tiles_n * TILE_N[form]));
+  const double edge = N % 8 != 0 ? c.odd : N % TILE_N[form] != 0 ? c.edge : 0.0;
+  return TiledPrice{&c, TILE_SHARE[form],
+                    c.a + c.fetched * fetched_mb(form, tiles_m, tiles_n, d) + c.weights * (double)N * (double)d * 0.53125 / 1e6 +
+                        mn * (c.out + edge) + w * iters * (c.part + c.pad * padding),
+                    w, iters, mn};
+}
+
+static double tiled_us(const TiledPrice &p, int s) {
+  const TileCost &c = *p.c;
+  const double w = p.w * s, iters = p.iters / s;                 // (w * iters is the same for every s)
+  double t = p.base + c.round * (std::ceil(w / p.share) - 1.0) + iters * std::ceil(w) * c.full +
+             p.w * p.iters * c.deep * std::fmin(iters, 112.0) / 32.0;
+  if (s > 1) t += c.cut + (double)s * (c.cut_mn * p.mn + c.cut_s);
   return t;
 }
 
@@ -745,10 +793,11 @@ static GemmPlan choose_plan(int64_t M, int64_t N, int d, bool allow_split) {
       for (int form = 0; form < FORMS; ++form) {
         if (form > 2 && !whole) continue;                            // the ring only takes whole pieces
         const bool cut = may_split && form != 0 && form != 2;        // the largest tile and form 2 are never cut
+        const TiledPrice price = tiled_price(form, M, N, d);
         for (int s = 1; s <= 16 && s <= (cut ? pairs : 1); ++s) {
           if (s > 1 && (pairs % s != 0 || tiles_of(form) * s > 640)) continue;
           if (s == 1 && form != 0 && tiles_of(form) > 2048) continue;
-          offer(form, s, tiled_us(form, s, M, N, d));
+          offer(form, s, tiled_us(price, s));
         }
       }
     }

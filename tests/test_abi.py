@@ -170,6 +170,20 @@ def test_gemm_planner_between_streaming_and_a_cut_k_range(M, N, d, streaming):
     assert binding.mxfp4_gemm_plan(M, N, d, 1 << 40)[0] is streaming
 
 
+# More than 64 rows, one round of the largest tile: shapes where the expected form measured 10 % or more ahead of every other,
+# weights from HBM, tall ones (the activations are most of the traffic), short k ranges, ragged tile counts among them
+@pytest.mark.parametrize("M,N,d,plan,staging", [
+    (4096, 1024, 5120, (128, 128, 1), "registers"), (7552, 1408, 2048, (128, 128, 1), "registers"),
+    (3007, 3200, 2048, (128, 128, 1), "registers"), (6424, 1187, 6144, (128, 128, 1), "registers"),
+    (3456, 4352, 8192, (256, 256, 1), "registers"), (386, 28530, 3072, (256, 256, 1), "registers"),
+    (4992, 384, 17408, (64, 128, 1), "ring"), (4052, 512, 11264, (64, 128, 1), "ring"), (7548, 225, 16384, (64, 128, 1), "ring"),
+    (15803, 67, 9216, (64, 128, 1), "ring"), (128, 8192, 5120, (64, 64, 1), "ring"), (65, 7882, 8192, (64, 64, 1), "ring"),
+    (128, 4086, 4096, (64, 64, 1), "ring"), (65, 8826, 2048, (128, 64, 1), "ring"), (1743, 1152, 26624, (128, 128, 2), "ring")])
+def test_gemm_planner_takes_the_form_that_is_far_ahead(M, N, d, plan, staging):
+    assert binding.mxfp4_gemm_plan(M, N, d, 1 << 40) == (False, *plan)
+    assert binding.torq_diag_gemm_form(M, N, d, 1 << 40)[0] == staging
+
+
 def test_gemm_plan_names_the_tile_and_the_form_that_run():
     # a batch of 45 against a wide layer: one row of 64-row tiles, two workgroups share nothing
     assert binding.mxfp4_gemm_plan(45, 25600, 5120) == (False, 64, 128, 1)

@@ -181,7 +181,7 @@ def test_gemm_full_size_sampled_outputs(tq, oracle, M, N, d):
 # of the two launches is compared with the same columns computed as products of their own, bit for bit, and
 # with the whole product on another tile shape.
 @pytest.mark.parametrize("M,N,d", [(4096, 5120, 5120), (4000, 5000, 5120), (4096, 25600, 5120), (4096, 5120, 25600),
-                                   (8192, 5120, 8192)])
+                                   (8192, 5120, 8192), (1024, 17408, 28672)])
 def test_gemm_whole_rounds_first_then_the_remaining_columns(tq, M, N, d):
     g = torch.Generator(device=DEV)
     g.manual_seed(synth.SEED_BASE + 7 * M + N + d)
