@@ -627,7 +627,7 @@ static double rounds_us(int cfg, double tiles, double KT, int64_t N, int d) {
 // planner prices every candidate with a model fitted to measurements and takes the cheapest.  All measurements: HIP-graph
 // replays over weight copies of up to 600 MB in all (weights from HBM, as in a model; activations from the caches).
 //
-// More than 64 rows: 20800 random shapes (M = 65 ... 65000, N = 8 ... 28672, d = 256 ... 28672), every candidate of each.
+// More than 64 rows: 20900 random shapes (M = 65 ... 65000, N = 8 ... 28672, d = 256 ... 28672), every candidate of each.
 // Microseconds, linear in what a launch does, for `iters` iterations of each of w workgroups a CU (full = ceil(w)):
 //   the launch, each further round of workgroups, iters * full and iters * w (a CU's workgroups share its path from the L2,
 //   and a full chip the path behind it), iters * w again times iters / 32 (a long launch meets the power limit) and times
@@ -635,43 +635,43 @@ static double rounds_us(int cfg, double tiles, double KT, int64_t N, int d) {
 //   elements, these again where rows are not whole 16-byte pieces or the last tile column is ragged, and for a cut the
 //   second launch, the pieces' 10^6 elements and a little per piece.
 // The coefficients are those whose choices cost least on four fifths of the shapes (not those that fit the times best).  On the
-// others the choice is 0.3 % off the best candidate on average, 1 % at the 90th percentile, 6 % at the 99th, 33 % at worst.
+// others the choice is 0.3 % off the best candidate on average, 1 % at the 90th percentile, 7 % at the 99th, 23 % at worst.
 // Prices fitted to 65 ... 2048 rows that knew of the weights' traffic alone came before: 1.3 %, 4 %, 22 % and 45 % up to 2048
 // rows, 3.5 %, 13 %, 32 % and 43 % beyond ([4096, 5120] x 1024 20.1 -> 18.3 us, [9472, 2048] x 1152 29.0 -> 20.7,
 // [4919, 11264] x 384 31.1 -> 22.4).
 struct TileCost { double a, round, full, part, deep, pad, fetched, weights, out, odd, edge, cut, cut_mn, cut_s; };
 // (the last three: the plain forms of the first three, which take any d)
 static const TileCost TILE_COST[FORMS + 3] = {
-    {11, 0, 1.02, 0.493, 0.0572, 0.169, 0.00756, 0.0229, 0, 1.49, 0.373, 0, 0, 0},
-    {3.96, 2.47, 0.768, 0.0856, 0.02, -0.151, 0.031, 0.0496, 0.371, 1.67, 0.449, 2.04, 1.46, 0.108},
-    {3.72, 1.03, 0.466, 0.0158, 0.0344, -0.223, 0.0462, 0.094, 0.309, 1.47, 0.0831, 0, 0, 0},
-    {3.43, 2.01, 0.314, 0, 0.0202, -0.198, 0.0503, 0.0999, 0.00635, 2.15, 0.431, 2.12, 1.45, 0.0958},
-    {3.51, 1.94, 0.314, 0, 0.0286, -0.124, 0.0414, 0.139, -0.0568, 1.51, 0.372, 1.85, 1.55, 0.147},
-    {3.03, 0.71, 0.224, 0, 0.0212, -0.108, 0.0234, 0.128, 0.289, 1.82, 0.228, 1.73, 1.88, 0.13},
-    {4.34, 2.13, 0.46, 0.00694, 0.0271, -0.136, 0.0409, 0.0673, 0.278, 1.65, 0.16, 1.05, 1.51, 0.207},
-    {11.8, 0, 1.92, -0.0477, 0.254, -0.488, 0.00869, 0.23, 0.0024, 1.45, 0.546, 0, 0, 0},
-    {5.42, 0.23, 1.52, 0, 0.105, -0.219, 0.0212, 0.0236, 0.438, 1.78, 0.219, 0, 0, 0},
-    {5.16, 2.56, 0.849, -0.00299, 0, -0.442, 0.0609, 0.159, -0.0351, 1.26, 0.17, 0, 0, 0}};
+    {10.1, 0, 1.09, 0.493, 0.0102, 0.189, 0.0125, 0.0144, 0, 1.55, 0.417, 0, 0, 0},
+    {3.63, 2.25, 0.846, 0.0387, 0.00581, -0.129, 0.0255, 0.0457, 0.414, 1.74, 0.517, 2.46, 1.44, 0.11},
+    {3.36, 0.674, 0.527, -0.0493, 0.0318, -0.167, 0.0466, 0.0956, 0.358, 1.52, 0.157, 0, 0, 0},
+    {3.21, 1.74, 0.365, 0, 0.0184, -0.187, 0.0314, 0.0829, 0.205, 2.19, 0.325, 2.13, 1.69, 0.108},
+    {3.48, 2.32, 0.324, 0.0136, 0.0296, -0.228, 0.0384, 0.141, 0.0152, 1.38, 0.317, 2, 1.59, 0.13},
+    {3.02, 0.632, 0.226, 0, 0.0183, -0.135, 0.0268, 0.126, 0.335, 1.63, 0.058, 1.74, 1.9, 0.128},
+    {4.17, 1.98, 0.516, 0, 0.0155, -0.0899, 0.036, 0.0573, 0.312, 1.67, 0.155, 1.46, 1.28, 0.208},
+    {11.2, 0, 1.92, -0.128, 0.253, -0.162, 0.0308, 0.137, 0, 1.59, 0.617, 0, 0, 0},
+    {5.07, 0.565, 1.48, 0, 0.0141, 0.0465, 0.0769, -0.0352, 0.451, 1.33, 0.364, 0, 0, 0},
+    {5.02, 1.59, 0.873, -0.00314, 0.0298, -0.196, 0.0393, 0.166, 0, 1.48, 0.28, 0, 0, 0}};
 static const int TILE_SHARE[FORMS] = {1, 1, 2, 1, 1, 2, 1};      // workgroups that share a CU (by their LDS)
 
 // MB of operands that the L2s of the eight XCDs fetch: an XCD runs n tiles at a time and fetches their rows of A and of W
 // once.  Tile order as in the kernels: a tile count that is a multiple of 8 is dealt out in contiguous runs, any other
-// in turn, down the tile rows first (the forms staged through registers: of eight rows at a time).
+// in turn, down eight tile rows first.
 static double fetched_mb(int form, int64_t tiles_m, int64_t tiles_n, int d) {
   const double run = std::fmax(1.0, (double)(tiles_m * tiles_n) / 8.0), n = std::fmin(run, 32.0 * TILE_SHARE[form]);
-  const int64_t rows = form > 2 || tiles_m < 8 ? tiles_m : 8;
+  const int64_t rows = tiles_m < 8 ? tiles_m : 8;
   const double tm = (double)tiles_m, tn = (double)tiles_n, r = (double)rows;
   double a, w;                                                   // tile rows and columns among the n
   if (tiles_m * tiles_n % 8 == 0) {
     a = n <= r * tn ? std::fmin(n, r) : std::fmin(tm, n / tn);
     w = std::fmin(tn, 1.0 + (n - 1.0) / r);
-  } else if (form <= 2 && tiles_m >= 8) {
+  } else if (rows == 8) {                                        // every eighth tile: the same row of each eight
     a = std::fmax(1.0, n / tn);
     w = std::fmin(tn, n);
-  } else {
-    const int64_t low = rows & -rows;                            // the power of two in it: every 8 / low-th column meets the
-    const double cols = std::fmin(tn, std::fmax(1.0, 8.0 * n / r));   // same rows again
-    a = std::fmin(std::fmin(n, r), (double)((rows + 7) / 8) * std::fmin(cols, low < 8 ? (double)(8 / low) : 1.0));
+  } else {                                                       // `low` the power of two in rows: every 8 / low-th column
+    const int64_t low = rows & -rows;                            // meets the same row again
+    const double cols = std::fmin(tn, std::fmax(1.0, 8.0 * n / r));
+    a = std::fmin(std::fmin(n, r), std::fmin(cols, (double)(8 / low)));
     w = std::fmin(n, cols);
   }
   return 8.0 * (run / n) * (a * TILE_M[form] + w * TILE_N[form]) * (double)d * 0.53125 / 1e6;

@@ -145,10 +145,10 @@ def test_gemm_workspace_entry_points_validate_and_plan_on_the_host():
     assert binding.mxfp4_gemm_main_columns(4096, 5120, 5120) == 4096
     assert binding.mxfp4_gemm_plan(4096, 5120, 5120) == (False, 256, 256, 1)
     assert binding.mxfp4_gemm_main_columns(4096, 25600, 5120) == 24576          # six rounds and a quarter
-    need = binding.mxfp4_gemm_workspace_bytes(4096, 5120, 25600)                # the remainder's k range is cut
-    assert binding.mxfp4_gemm_main_columns(4096, 5120, 25600, need) == 4096
-    pieces = binding.mxfp4_gemm_plan(4096, 1024, 25600, need)[3]
-    assert pieces > 1 and need == pieces * 4096 * 1024 * 4
+    need = binding.mxfp4_gemm_workspace_bytes(1024, 17408, 28672)               # the remainder's k range is cut
+    assert binding.mxfp4_gemm_main_columns(1024, 17408, 28672, need) == 16384
+    pieces = binding.mxfp4_gemm_plan(1024, 1024, 28672, need)[3]
+    assert pieces > 1 and need == pieces * 1024 * 1024 * 4
     for M, N, d in [(8192, 28672, 8192), (8192, 8192, 28672), (2048, 14336, 4096), (4096, 5124, 5120), (64, 70000, 4096)]:
         assert binding.mxfp4_gemm_main_columns(M, N, d) == N                    # whole rounds, a last round more than
     assert binding.mxfp4_gemm_main_columns(0, 4, 128) == 0                      # half full, N % 8 != 0, few rows; invalid
@@ -173,12 +173,14 @@ def test_gemm_planner_between_streaming_and_a_cut_k_range(M, N, d, streaming):
 # More than 64 rows, one round of the largest tile: shapes where the expected form measured 10 % or more ahead of every other,
 # weights from HBM, tall ones (the activations are most of the traffic), short k ranges, ragged tile counts among them
 @pytest.mark.parametrize("M,N,d,plan,staging", [
-    (4096, 1024, 5120, (128, 128, 1), "registers"), (7552, 1408, 2048, (128, 128, 1), "registers"),
-    (3007, 3200, 2048, (128, 128, 1), "registers"), (6424, 1187, 6144, (128, 128, 1), "registers"),
-    (3456, 4352, 8192, (256, 256, 1), "registers"), (386, 28530, 3072, (256, 256, 1), "registers"),
-    (4992, 384, 17408, (64, 128, 1), "ring"), (4052, 512, 11264, (64, 128, 1), "ring"), (7548, 225, 16384, (64, 128, 1), "ring"),
-    (15803, 67, 9216, (64, 128, 1), "ring"), (128, 8192, 5120, (64, 64, 1), "ring"), (65, 7882, 8192, (64, 64, 1), "ring"),
-    (128, 4086, 4096, (64, 64, 1), "ring"), (65, 8826, 2048, (128, 64, 1), "ring"), (1743, 1152, 26624, (128, 128, 2), "ring")])
+    (3072, 3328, 1024, (128, 128, 1), "registers"), (2239, 4224, 2048, (128, 128, 1), "registers"),
+    (14469, 640, 1024, (128, 128, 1), "registers"), (881, 8273, 2048, (128, 128, 1), "registers"),
+    (16267, 1024, 3072, (256, 256, 1), "registers"), (1769, 8192, 7680, (256, 256, 1), "registers"),
+    (5203, 1024, 17408, (256, 128, 1), "registers"), (219, 23936, 11264, (256, 128, 1), "registers"),
+    (3200, 768, 21504, (256, 128, 3), "registers"), (6912, 233, 5120, (64, 128, 1), "ring"),
+    (131, 9216, 5120, (64, 128, 1), "ring"), (19968, 48, 13312, (128, 64, 1), "ring"), (106, 14208, 1024, (128, 64, 1), "ring"),
+    (2675, 384, 11264, (64, 64, 1), "ring"), (292, 236, 2048, (64, 64, 1), "ring"), (228, 768, 19456, (64, 64, 2), "ring"),
+    (4992, 640, 18432, (128, 128, 1), "ring"), (4921, 256, 24576, (128, 128, 3), "ring"), (65, 5632, 16384, (128, 128, 4), "ring")])
 def test_gemm_planner_takes_the_form_that_is_far_ahead(M, N, d, plan, staging):
     assert binding.mxfp4_gemm_plan(M, N, d, 1 << 40) == (False, *plan)
     assert binding.torq_diag_gemm_form(M, N, d, 1 << 40)[0] == staging

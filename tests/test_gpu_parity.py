@@ -401,9 +401,10 @@ def test_gemm_every_plan_of_the_tiled_kernel(tq, oracle, M, N, d):
 
 
 # The form staged in a ring, every tile: fewer iterations than stages, an odd number of pairs, ragged edges, tile counts
-# that are and are not multiples of 8, and cuts.  The uncut sums are mxfp4_gemm's bit for bit, a cut's are those of the
-# other tiled forms cut alike.
-@pytest.mark.parametrize("M,N,d", [(1, 8, 512), (64, 64, 512), (65, 129, 1024), (200, 264, 1536), (128, 1024, 2048), (300, 72, 5120)])
+# that are and are not multiples of 8, more than eight tile rows with and without a shorter last group, and cuts.  The
+# uncut sums are mxfp4_gemm's bit for bit, a cut's are those of the other tiled forms cut alike.
+@pytest.mark.parametrize("M,N,d", [(1, 8, 512), (64, 64, 512), (65, 129, 1024), (200, 264, 1536), (128, 1024, 2048), (300, 72, 5120),
+                                   (1090, 200, 1024), (1024, 136, 512), (2100, 80, 512)])
 def test_gemm_ring_every_tile(tq, oracle, M, N, d):
     rng = np.random.default_rng(M * 7 + N + d)
     A_q = rng.integers(0, 256, size=(M, d // 2), dtype=np.uint8)
