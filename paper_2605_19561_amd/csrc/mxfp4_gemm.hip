@@ -36,7 +36,6 @@ namespace torq {
 
 constexpr int GEMM_GROUP_M = 8;       // tile rows per scheduling group
 
-typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
@@ -393,66 +392,13 @@ mxfp4_gemm_kernel(const uint8_t *__restrict__ A_q, const uint8_t *__restrict__ A
 #undef ITER
 #undef SGB
 
-  // ---- epilogue.  acc[j][i][r] = out[m = .. + lane%32][n = .. + 8*(r/4) + 4*(lane/32) + r%4]:
-  // a lane holds 8-byte pieces of one output row.  Storing those directly makes every 128-byte
-  // line of the output arrive in 16 separate partial writes, so the wave first transposes its
-  // piece through LDS (free after the last barrier of the k loop; each wave uses a private
-  // region) and then stores 16 bytes per lane with 8 adjacent lanes covering one full line.
+  // ---- epilogue (the LDS is free after the last barrier of the k loop; each wave uses a private region)
   if constexpr (PERSIST) {
     // (stored tile by tile above)
   } else if (SPLIT) {
-    // fp32 sums of this k piece: 16 bytes per lane and register quad, straight from the accumulators
-    float *const dstp = partial + (size_t)blockIdx.y * (size_t)M * (size_t)N;
-#pragma unroll
-    for (int i = 0; i < WM; ++i) {
-      const int64_t m = m0 + (wy * WM + i) * 32 + lrow;
-#pragma unroll
-      for (int j = 0; j < WN; ++j)
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-          const int64_t n = n0 + (wx * WN + j) * 32 + 8 * rr + 4 * g;
-          if (m < M && n + 4 <= N)
-            *reinterpret_cast<f32x4 *>(dstp + m * N + n) =
-                f32x4{acc[j][i][4 * rr], acc[j][i][4 * rr + 1], acc[j][i][4 * rr + 2], acc[j][i][4 * rr + 3]};
-        }
-    }
+    store_sums<WM, WN>(acc, partial + (size_t)blockIdx.y * (size_t)M * (size_t)N, m0, n0, wy, wx, M, N, lrow, g);
   } else {
-    constexpr int ROW_E = 64 * WN;               // bytes of one output row of this wave's piece
-    constexpr int PITCH_E = ROW_E + 16;
-    constexpr int CH_ROW = ROW_E / 16;           // 16-byte chunks per row
-    char *const ep = lds + wave * (32 * WM) * PITCH_E;
-#pragma unroll
-    for (int i = 0; i < WM; ++i)
-#pragma unroll
-      for (int j = 0; j < WN; ++j)
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-          bf16x4 v;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = (__bf16)acc[j][i][4 * rr + e];
-          *reinterpret_cast<bf16x4 *>(ep + (i * 32 + lrow) * PITCH_E + (32 * j + 8 * rr + 4 * g) * 2) = v;
-        }
-    const bool vec_ok = (ldc & 7) == 0;           // (out itself is 16-byte aligned: checked by the host)
-#pragma unroll
-    for (int i = 0; i < WM; ++i)
-#pragma unroll
-      for (int t = 0; t < 32 * CH_ROW / 64; ++t) {
-        const int idx = t * 64 + lane;
-        const int row = idx / CH_ROW, ch = idx % CH_ROW;
-        const u32x4 v = *reinterpret_cast<const u32x4 *>(ep + (i * 32 + row) * PITCH_E + ch * 16);
-        const int64_t m = m0 + (wy * WM + i) * 32 + row;
-        const int64_t n = n0 + wx * WN * 32 + ch * 8;
-        if (m < M) {
-          uint16_t *dst = out + m * ldc + n;
-          if (vec_ok && n + 8 <= N) {
-            *reinterpret_cast<u32x4 *>(dst) = v;
-          } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              if (n + e < N) dst[e] = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
-          }
-        }
-      }
+    store_bf16<WM, WN>(acc, lds + wave * (32 * WM) * (64 * WN + 16), out, m0, n0, wy, wx, M, N, ldc, lane, lrow, g);
   }
 #undef G_LOAD
 #undef G_LOAD_Q

@@ -18,8 +18,6 @@ namespace torq {
 
 namespace {
 
-typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
-
 // every DMA but the youngest N of this wave has landed, every LDS read of it has returned; then the workgroup meets
 template <int N>
 __device__ __forceinline__ void ring_meet() {
@@ -214,55 +212,10 @@ mxfp4_gemm_ring_kernel(const uint8_t *__restrict__ A_q, const uint8_t *__restric
 #undef SGB
   ring_meet<0>();                                  // (what follows reuses the stages) nothing is on its way into the LDS any more
 
-  if constexpr (SPLIT) {
-    float *const dstp = partial + (size_t)blockIdx.y * (size_t)M * (size_t)N;
-#pragma unroll
-    for (int i = 0; i < WM; ++i) {
-      const int64_t m = m0 + (wy * WM + i) * 32 + lrow;
-#pragma unroll
-      for (int j = 0; j < WN; ++j)
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-          const int64_t n = n0 + (wx * WN + j) * 32 + 8 * rr + 4 * g;
-          if (m < M && n + 4 <= N)
-            *reinterpret_cast<f32x4 *>(dstp + m * N + n) =
-                f32x4{acc[j][i][4 * rr], acc[j][i][4 * rr + 1], acc[j][i][4 * rr + 2], acc[j][i][4 * rr + 3]};
-        }
-    }
-  } else {
-    constexpr int ROW_E = 64 * WN, PITCH_E = ROW_E + 16, CH_ROW = ROW_E / 16;
-    char *const ep = lds + wave * (32 * WM) * PITCH_E;
-#pragma unroll
-    for (int i = 0; i < WM; ++i)
-#pragma unroll
-      for (int j = 0; j < WN; ++j)
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-          bf16x4 v;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = (__bf16)acc[j][i][4 * rr + e];
-          *reinterpret_cast<bf16x4 *>(ep + (i * 32 + lrow) * PITCH_E + (32 * j + 8 * rr + 4 * g) * 2) = v;
-        }
-    const bool vec_ok = (ldc & 7) == 0;
-#pragma unroll
-    for (int i = 0; i < WM; ++i)
-#pragma unroll
-      for (int t = 0; t < 32 * CH_ROW / 64; ++t) {
-        const int idx = t * 64 + lane, row = idx / CH_ROW, ch = idx % CH_ROW;
-        const u32x4 v = *reinterpret_cast<const u32x4 *>(ep + (i * 32 + row) * PITCH_E + ch * 16);
-        const int64_t m = m0 + (wy * WM + i) * 32 + row, n = n0 + wx * WN * 32 + ch * 8;
-        if (m < M) {
-          uint16_t *dst = out + m * ldc + n;
-          if (vec_ok && n + 8 <= N) {
-            *reinterpret_cast<u32x4 *>(dst) = v;
-          } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              if (n + e < N) dst[e] = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
-          }
-        }
-      }
-  }
+  if constexpr (SPLIT)
+    store_sums<WM, WN>(acc, partial + (size_t)blockIdx.y * (size_t)M * (size_t)N, m0, n0, wy, wx, M, N, lrow, g);
+  else
+    store_bf16<WM, WN>(acc, lds + wave * (32 * WM) * (64 * WN + 16), out, m0, n0, wy, wx, M, N, ldc, lane, lrow, g);
 }
 
 template <int WM, int WN>

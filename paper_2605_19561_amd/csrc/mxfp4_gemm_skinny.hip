@@ -28,7 +28,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint3
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
 }
 
-typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
 #define LDSP(x) ((__attribute__((address_space(3))) void *)(x))
 
 constexpr int WAVES = 8;              // waves per workgroup = ways the k range is split

@@ -13,6 +13,7 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(8 * sizeof(int)))) int i32x8;
 typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4;
+typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short i16x4;
 
 // A raw buffer of `bytes` bytes as four words, and a load of 16 bytes per lane from it, at voff + soff, straight into LDS at
@@ -30,6 +31,67 @@ __device__ __forceinline__ void load_to_lds16(i32x4 rsrc, uint32_t lds_addr, int
   else asm volatile(TORQ_LOAD_TO_LDS16 :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "m0");
 }
 #undef TORQ_LOAD_TO_LDS16
+
+// The output tile of a GEMM workgroup whose wave holds acc[j][i][r] = out[m0 + 32 (wy WM + i) + lane % 32][n0 + 32 (wx WN
+// + j) + 8 (r / 4) + 4 (lane / 32) + r % 4] (m0, n0: the tile's corner; wy, wx: the wave's place in it).
+// The fp32 sums of a k piece: 16 bytes per lane and register quad, straight from the accumulators (N a multiple of 8).
+template <int WM, int WN>
+__device__ __forceinline__ void store_sums(const f32x16 (&acc)[WN][WM], float *piece, int64_t m0, int64_t n0, int wy,
+                                           int wx, int64_t M, int64_t N, int lrow, int g) {
+#pragma unroll
+  for (int i = 0; i < WM; ++i) {
+    const int64_t m = m0 + (wy * WM + i) * 32 + lrow;
+#pragma unroll
+    for (int j = 0; j < WN; ++j)
+#pragma unroll
+      for (int rr = 0; rr < 4; ++rr) {
+        const int64_t n = n0 + (wx * WN + j) * 32 + 8 * rr + 4 * g;
+        if (m < M && n + 4 <= N)
+          *reinterpret_cast<f32x4 *>(piece + m * N + n) =
+              f32x4{acc[j][i][4 * rr], acc[j][i][4 * rr + 1], acc[j][i][4 * rr + 2], acc[j][i][4 * rr + 3]};
+      }
+  }
+}
+// bf16 outputs.  A lane holds 8-byte pieces of one output row; stored directly, every 128-byte line of the output arrives
+// in 16 separate partial writes, so the wave first transposes its piece through its own LDS at ep (32 WM rows of 64 WN + 16
+// bytes, free by now) and then stores 16 bytes per lane, with 8 adjacent lanes covering one full line.
+template <int WM, int WN>
+__device__ __forceinline__ void store_bf16(const f32x16 (&acc)[WN][WM], char *ep, uint16_t *out, int64_t m0, int64_t n0,
+                                           int wy, int wx, int64_t M, int64_t N, int64_t ldc, int lane, int lrow, int g) {
+  constexpr int ROW_E = 64 * WN;               // bytes of one output row of this wave's piece
+  constexpr int PITCH_E = ROW_E + 16;
+  constexpr int CH_ROW = ROW_E / 16;           // 16-byte chunks per row
+#pragma unroll
+  for (int i = 0; i < WM; ++i)
+#pragma unroll
+    for (int j = 0; j < WN; ++j)
+#pragma unroll
+      for (int rr = 0; rr < 4; ++rr) {
+        bf16x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = (__bf16)acc[j][i][4 * rr + e];
+        *reinterpret_cast<bf16x4 *>(ep + (i * 32 + lrow) * PITCH_E + (32 * j + 8 * rr + 4 * g) * 2) = v;
+      }
+  const bool vec_ok = (ldc & 7) == 0;           // (out itself is 16-byte aligned: checked by the host)
+#pragma unroll
+  for (int i = 0; i < WM; ++i)
+#pragma unroll
+    for (int t = 0; t < 32 * CH_ROW / 64; ++t) {
+      const int idx = t * 64 + lane, row = idx / CH_ROW, ch = idx % CH_ROW;
+      const u32x4 v = *reinterpret_cast<const u32x4 *>(ep + (i * 32 + row) * PITCH_E + ch * 16);
+      const int64_t m = m0 + (wy * WM + i) * 32 + row, n = n0 + wx * WN * 32 + ch * 8;
+      if (m < M) {
+        uint16_t *dst = out + m * ldc + n;
+        if (vec_ok && n + 8 <= N) {
+          *reinterpret_cast<u32x4 *>(dst) = v;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (n + e < N) dst[e] = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
+        }
+      }
+    }
+}
 
 // ---------------------------------------------------------------------------
 // MXFP4 quantiser for one microscaling block (Section 4, Eq. 1; Algorithm 3,
