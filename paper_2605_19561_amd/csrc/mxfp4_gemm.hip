@@ -751,8 +751,11 @@ static GemmPlan choose_plan(int64_t M, int64_t N, int d, bool allow_split) {
   // The streaming kernel's whole-line form against the tiles, weights from HBM: up to 16 rows it is ahead wherever it is
   // taken ([1, 28672] x 2048 1.25 times as fast, 0.97 at worst); up to 32 rows and d = 12288 too (1.1 - 1.5); beyond 32
   // rows up to d = 12288 and 640 strips ([64, 8192] x 1024 1.19, [48, 8192] x 10240 1.30; past 640 strips [48, 4096] x
-  // 14336 0.96, [64, 8192] x 16384 0.90).  Longer k ranges from 17 rows on stay with the rule below, whose cuts win where
-  // there are few strips ([32, 28672] x 1024 0.68) and lose where there are many ([32, 28672] x 8192 1.12).
+  // 14336 0.96, [64, 8192] x 16384 0.90).  Longer k ranges from 17 rows on stay with the rule below, which is
+  // ahead of whole lines where there are few strips ([32, 28672] x 1024 10.2 us against 15.3, [64, 25600] x 2560 15.9 / 21.1)
+  // and behind them where there are many ([32, 14336] x 10240 29.7 / 18.5, [17, 28672] x
+  // 5120 28.6 / 20.4, [32, 28672] x 10240 44.8 / 33.7, [32, 28672] x 8192 29.6 / 26.9): the form has no price of its own here
+  // that would tell the two apart.
   if (can_skinny && d >= 2048 && mxfp4_gemm_lines_strips(M, N, d) > 0 &&
       (M <= 16 || (d <= 12288 && (M <= 32 || (d >= 4096 && (N + 15) / 16 <= 640)))))
     return GemmPlan{true, 0, 1, false, skinny_one_us(M, N, d)};
