@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtorq.so")
 SOURCES = ["api.hip", "quantize.hip", "rotate_quant.hip", "rotate_butterfly.hip", "mxfp4_gemm.hip", "mxfp4_gemm_ring.hip",
-           "mxfp4_gemm_skinny.hip", "block_gram.hip", "code_histogram.hip",
+           "mxfp4_gemm_skinny.hip", "mxfp4_gemm_stream.hip", "block_gram.hip", "code_histogram.hip",
            "intra_calib.hip", "diag.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
@@ -27,7 +27,8 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
 EXTRA = {"rotate_quant.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-Wno-inline-asm"],
          "mxfp4_gemm_ring.hip": ["-Wno-inline-asm"],
          "rotate_butterfly.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
-         "mxfp4_gemm_skinny.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-Wno-inline-asm"]}
+         "mxfp4_gemm_skinny.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-Wno-inline-asm"],
+         "mxfp4_gemm_stream.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-Wno-inline-asm"]}
 
 
 def device_asm(source: str, out_path: str) -> str:

@@ -541,14 +541,15 @@ static int choose_tile(int64_t M, int64_t N) {
 constexpr int FORMS = 7;
 static const int TILE_M[FORMS] = {256, 256, 128, 128, 64, 64, 128}, TILE_N[FORMS] = {256, 128, 128, 64, 128, 64, 128};
 
-// How a product is run: the weight-streaming kernel (mxfp4_gemm_skinny.hip), or the tiled kernel
-// in form `cfg` with its k range cut into `splits` pieces (1 = not cut).
+// How a product is run: the weight-streaming kernels (mxfp4_gemm_skinny.hip, or with `stream` mxfp4_gemm_stream.hip), or the
+// tiled kernel in form `cfg` with its k range cut into `splits` pieces (1 = not cut).
 struct GemmPlan {
   bool skinny;
   int cfg;
   int splits;
   bool deep;      // form 2's deeper load pipeline (up to a round of 256 x 256 tiles)
   double us;      // the model's estimate of the launch time
+  bool stream = false;
 };
 
 // Several rounds of tiles: microseconds of a launch of `tiles` tiles of shape cfg over KT iterations.
@@ -709,7 +710,8 @@ static size_t plan_bytes(const GemmPlan &plan, int64_t M, int64_t N) {
   return plan.splits > 1 ? (size_t)plan.splits * (size_t)M * (size_t)N * sizeof(float) : 0;
 }
 
-static GemmPlan choose_plan(int64_t M, int64_t N, int d, bool allow_split) {
+// aligned: the scale arrays lie on 16 bytes
+static GemmPlan choose_plan(int64_t M, int64_t N, int d, bool allow_split, bool aligned) {
   const bool can_skinny = mxfp4_gemm_skinny_fits(M, d);
   const double KT = (d + 255) / 256;
   auto tiles_of = [&](int form) { return ((M + TILE_M[form] - 1) / TILE_M[form]) * ((N + TILE_N[form] - 1) / TILE_N[form]); };
@@ -777,6 +779,9 @@ static GemmPlan choose_plan(int64_t M, int64_t N, int d, bool allow_split) {
     }
     if (factor * t <= plan.us) plan = GemmPlan{true, 0, 1, false, t};
   }
+  // (where the streaming kernel is the choice and takes the product by whole lines, it keeps it)
+  if (aligned && mxfp4_gemm_stream_takes(M, N, d) && !(plan.skinny && mxfp4_gemm_lines_strips(M, N, d) > 0))
+    plan = GemmPlan{true, 0, 1, false, plan.us, true};
   return plan;
 }
 
@@ -790,7 +795,7 @@ static GemmPlan choose_plan(int64_t M, int64_t N, int d, bool allow_split) {
 // [4096, 5120, 5120] 71.5 -> 66.3, [4096, 25600, 5120] 291 -> 279; every output is the sum it was before
 // (same k order in every tile shape; where the remainder's k range is cut, up to the order of its fp32 sums,
 // as for any product that mxfp4_gemm_ws cuts).
-static GemmPlan plan_with(int64_t M, int64_t N, int d, bool allow_split, size_t workspace_bytes);
+static GemmPlan plan_with(int64_t M, int64_t N, int d, bool allow_split, size_t workspace_bytes, bool aligned = true);
 static int64_t choose_main_columns(int64_t M, int64_t N, int d, bool allow_split, size_t workspace_bytes, const GemmPlan &whole) {
   if (whole.skinny || whole.splits > 1 || whole.cfg > 2 || d % 512 != 0 || N % 8 != 0 || M <= 64) return N;
   const int64_t tiles_m = (M + 255) / 256, tiles_n = (N + 255) / 256, tiles = tiles_m * tiles_n;
@@ -808,9 +813,9 @@ static int64_t choose_main_columns(int64_t M, int64_t N, int d, bool allow_split
   return two < 0.985 * one ? 256 * cols : N;
 }
 // the plan of a product given the workspace it may use (a cut k range needs its pieces' fp32 tiles there)
-static GemmPlan plan_with(int64_t M, int64_t N, int d, bool allow_split, size_t workspace_bytes) {
-  GemmPlan plan = choose_plan(M, N, d, allow_split);
-  if (workspace_bytes < plan_bytes(plan, M, N)) plan = choose_plan(M, N, d, false);
+static GemmPlan plan_with(int64_t M, int64_t N, int d, bool allow_split, size_t workspace_bytes, bool aligned) {
+  GemmPlan plan = choose_plan(M, N, d, allow_split, aligned);
+  if (workspace_bytes < plan_bytes(plan, M, N)) plan = choose_plan(M, N, d, false, aligned);
   return plan;
 }
 
@@ -841,15 +846,21 @@ void mxfp4_gemm_form(int64_t M, int64_t N, int d, size_t workspace_bytes, int *s
     *staging = plan.cfg > 2 || (plan.cfg == 2 && plan.splits > 1) ? TORQ_GEMM_RING : TORQ_GEMM_REGISTERS;
     return;
   }
+  if (plan.stream) {
+    *staging = TORQ_GEMM_STRIPS;
+    *strips = mxfp4_gemm_stream_strips(d);
+    *padded = 1;
+    return;
+  }
   const bool lines = mxfp4_gemm_lines_form(M, N, d, strips, items, padded);
   *staging = lines ? TORQ_GEMM_WHOLE_LINES : TORQ_GEMM_STRIPS;
   if (!lines) *strips = mxfp4_gemm_skinny_strips(M, N, d);
 }
 
 size_t mxfp4_gemm_workspace_bytes(int64_t M, int64_t N, int d) {
-  const GemmPlan plan = choose_plan(M, N, d, true);
+  const GemmPlan plan = choose_plan(M, N, d, true, true);
   const int64_t main_n = choose_main_columns(M, N, d, true, ~(size_t)0, plan);
-  if (main_n < N) return plan_bytes(choose_plan(M, N - main_n, d, true), M, N - main_n);
+  if (main_n < N) return plan_bytes(choose_plan(M, N - main_n, d, true, true), M, N - main_n);
   return plan_bytes(plan, M, N);
 }
 
@@ -889,9 +900,10 @@ static hipError_t launch_by_plan(const GemmPlan &plan, const uint8_t *A_q, const
 static hipError_t launch_planned(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q, const uint8_t *W_s,
                                  void *out_bf16, int64_t M, int64_t N, int d, int64_t ldc, bool fullk, bool ws_ok,
                                  void *workspace, size_t workspace_bytes, hipStream_t stream) {
-  GemmPlan plan = plan_with(M, N, d, ws_ok, ws_ok ? workspace_bytes : 0);
+  GemmPlan plan = plan_with(M, N, d, ws_ok, ws_ok ? workspace_bytes : 0, fullk);
   if (plan.skinny) {
     if (ldc != N) return hipErrorInvalidValue;            // (never planned for a remainder: see launch_mxfp4_gemm)
+    if (plan.stream) return launch_mxfp4_gemm_stream(A_q, A_s, W_q, W_s, out_bf16, M, N, d, stream);
     return launch_mxfp4_gemm_skinny(A_q, A_s, W_q, W_s, out_bf16, M, N, d, stream);
   }
   if (!fullk) {                                           // the plain form of the three larger tiles takes any d

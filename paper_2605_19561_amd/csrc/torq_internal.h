@@ -103,6 +103,12 @@ bool mxfp4_gemm_skinny_fits(int64_t M, int d);
 hipError_t launch_mxfp4_gemm_skinny(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q,
                                     const uint8_t *W_s, void *out_bf16, int64_t M, int64_t N, int d,
                                     hipStream_t stream);
+// The same product for wide layers, strip after strip through a ring (mxfp4_gemm_stream.hip): where it is taken, how many
+// strips a workgroup has under way at a time, and the launch (scale arrays 16-byte aligned).
+bool mxfp4_gemm_stream_takes(int64_t M, int64_t N, int d);
+int mxfp4_gemm_stream_strips(int d);
+hipError_t launch_mxfp4_gemm_stream(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q, const uint8_t *W_s, void *out_bf16,
+                                    int64_t M, int64_t N, int d, hipStream_t stream);
 // torq_linear for at most 64 rows in one launch: rotate + quantise (the 16-block body, G = 128) in the
 // first workgroups of the weight-streaming GEMM.  Preconditions: r->G == 128, dense R_inter,
 // 1 <= M <= 64, mxfp4_gemm_skinny_fits(M, r->d); A_q / A_s are the workspace's code and scale areas.

@@ -339,6 +339,33 @@ def test_gemm_weight_streaming_by_whole_lines(tq, oracle, M, N, d):
     _assert_every_output_within_one_ulp(_bits(out[:M][:, cols].contiguous()), want)
 
 
+# The streaming kernel's strips through a ring: every form the rule takes (activation tiles x line pairs per wave), at the first
+# and last strip counts of its ranges, a row and a column more than whole tiles, workgroups of unequal shares.  The bar is the
+# one of the other forms: one rounding of an fp32 sum to bf16.
+STREAM_RING = [(8, 28673, 2560), (16, 28700, 6144), (13, 25601, 8192), (17, 24577, 3072), (32, 28672, 4608), (20, 26000, 8192),
+               (33, 16385, 2560), (48, 12288, 5120), (40, 10248, 7168), (64, 10244, 3584), (49, 16391, 4608), (64, 24576, 8192)]
+
+
+@pytest.mark.parametrize("M,N,d", STREAM_RING)
+def test_gemm_weight_streaming_strips_through_a_ring(tq, oracle, M, N, d):
+    assert tq.torq_diag_gemm_form(M, N, d)[::3] == ("strips", True)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(M + N + d)
+    draw = lambda lo, hi, *shape: torch.randint(lo, hi, shape, dtype=torch.uint8, device=DEV, generator=gen)
+    A_q, W_q, A_s, W_s = draw(0, 256, M, d // 2), draw(0, 256, N, d // 2), draw(118, 136, M, d // 32), draw(110, 126, N, d // 32)
+    out = torch.full((M + 1, N), 7.0, dtype=torch.bfloat16, device=DEV)
+    tq.mxfp4_gemm(A_q, A_s, W_q, W_s, out=out[:M])
+    torch.cuda.synchronize()
+    assert torch.all(out[M] == 7.0)
+    cols = sorted({*range(0, N, 61), 15, 16, 4095, 4096, 4097, N - 17, N - 16, N - 2, N - 1})
+    want = oracle.gemm(A_q.cpu().numpy(), A_s.cpu().numpy(), W_q[cols].cpu().numpy(), W_s[cols].cpu().numpy())
+    _assert_every_output_within_one_ulp(_bits(out[:M][:, cols].contiguous()), want)
+    off = torch.empty(A_s.numel() + 4, dtype=torch.uint8, device=DEV)      # scale rows off the 16-byte grid: another form
+    off[4:] = A_s.flatten()
+    other = tq.mxfp4_gemm(A_q, off[4:].view(M, d // 32), W_q, W_s)
+    _assert_every_output_within_one_ulp(_bits(other[:, cols].contiguous()), want)
+
+
 def _random_gemm_shapes(n, seed):
     rng = np.random.default_rng(seed)
     return [(int(rng.integers(1, 700)), int(rng.integers(1, 900)), 128 * int(rng.integers(1, 17))) for _ in range(n)]

@@ -132,6 +132,25 @@ def test_lines_loop_holds_exactly_the_counted_requests():
     assert seen == 26
 
 
+# ---- mxfp4_gemm_stream_kernel: as above, and nothing but its own counted requests loads at all (a load of the compiler's
+# would have it wait for everything).
+def test_stream_kernel_waits_by_its_own_counts():
+    with tempfile.TemporaryDirectory() as tmp:
+        text = open(build.device_asm("mxfp4_gemm_stream.hip", os.path.join(tmp, "stream.s"))).read()
+    seen = 0
+    for m in re.finditer(r"^(_ZN4torq24mxfp4_gemm_stream_kernelILi(\d)ELi(\d)ELi(\d)\w+):(.*?)^\.Lfunc_end", text, re.M | re.S):
+        name, MT, PT, R, body = m.group(1), int(m.group(2)), int(m.group(3)), int(m.group(4)), m.group(5)
+        seen += 1
+        assert re.search(r"\.name:\s+" + name + r"\n(?:.*\n)*?\s+\.private_segment_fixed_size:\s+0\n", text), name
+        code = [c for c in (line.split(";")[0].strip() for line in body.splitlines()) if c]
+        loads = [c for c in code if re.match(r"(buffer_|global_load|flat_|scratch_)", c)]
+        assert loads and all(re.match(r"buffer_load_dwordx4 v\d+, s\[\d+:\d+\], s\d+ offen lds$", c) for c in loads), name
+        waits = [int(re.search(r"vmcnt\((\d+)\)", c).group(1)) for c in code if c.startswith("s_waitcnt") and "vmcnt(" in c]
+        counts = [2 * (R - 1) + (i + R - 1) // PT for i in range(PT)]
+        assert waits[:MT * PT] == MT * counts and set(waits[MT * PT:-1]) == set(counts) and waits[-1] == 0, (name, waits)
+    assert seen == 12
+
+
 # ---- torq_linear_local_kernel (mxfp4_gemm_skinny.hip): not correctness but the point of the kernel.  The
 # rotation's reads are issued ahead of the workgroup's weight reads and its LDS stores must wait for them
 # alone -- s_waitcnt vmcnt(N) with N >= the number of weight loads behind them.  A load that the compiler
