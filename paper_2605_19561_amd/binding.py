@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libtorq.so: same names as the C ABI (include/torq.h).
+"""Thin binding of libtorq.so (ctypes; the calls made again and again through csrc/host_calls.cpp): same names as the C ABI
+(include/torq.h).
 
 Argument marshalling only: torch supplies device memory and the current HIP
 stream, every step of the path runs in the library's kernels.  There is no CPU
@@ -168,6 +169,27 @@ def _dev(t: torch.Tensor, dtype, what):
     raise ValueError(f"{what}: expected a contiguous {dtype} device tensor")
 
 
+_host = None
+
+
+def _native():
+    """The C++ module that marshals the calls made again and again (csrc/host_calls.cpp)."""
+    global _host
+    if _host is None:
+        L = lib()
+        try:
+            from . import _host as module
+        except ImportError as e:
+            raise FileNotFoundError("paper_2605_19561_amd/_host.so is missing or not built for this interpreter: build it with "
+                                    "`python -m paper_2605_19561_amd.build`") from e
+        names = ["torq_linear", "torq_linear_workspace_bytes_n", "torq_rotate_quantize", "torq_rotate_quantize_fmt",
+                 "torq_block_gram", "torq_block_gram_positions", "torq_block_gram_workspace_bytes", "torq_code_histogram",
+                 "torq_code_histogram_workspace_bytes"]
+        module.bind({n: C.cast(getattr(L, n), C.c_void_p).value for n in names}, _stream, _check)
+        _host = module
+    return _host
+
+
 class Rotation:
     """Owner of a torq_rotation_t handle (R_inter [G, G], R_intra [32, 32], fp32 host arrays)."""
 
@@ -219,7 +241,13 @@ def torq_equalize_inter_butterfly(Sigma):
     return R, T
 
 
+# A function below that starts with a call of _native() goes on behind it only for arguments that are not plain (a wrong shape,
+# type or layout, a subclass): see csrc/host_calls.cpp.
+
 def torq_rotate_quantize(rot: Rotation, x_bf16: torch.Tensor, codes=None, scales=None, stream=None):
+    pair = (_host or _native()).rotate_quantize(rot, x_bf16, None, 1.0, codes, scales, stream)
+    if pair is not None:
+        return pair
     M, d = x_bf16.shape
     assert d == rot.d
     if codes is None:
@@ -262,6 +290,9 @@ def _scale_cols(d: int, fmt: int) -> int:
 
 def torq_rotate_quantize_fmt(rot: Rotation, x_bf16: torch.Tensor, fmt: int, global_scale: float = 1.0,
                              codes=None, scales=None, stream=None):
+    pair = (_host or _native()).rotate_quantize(rot, x_bf16, fmt, global_scale, codes, scales, stream)
+    if pair is not None:
+        return pair
     M, d = x_bf16.shape
     assert d == rot.d
     if codes is None:
@@ -385,6 +416,9 @@ def torq_linear_single_launch_gave_up(rot: Rotation) -> bool:
 
 
 def torq_linear(rot: Rotation, x_bf16, W_q, W_s, out=None, workspace=None, stream=None):
+    y = (_host or _native()).linear(rot, x_bf16, W_q, W_s, out, workspace, stream)
+    if y is not None:
+        return y
     M, d = x_bf16.shape
     N = W_q.shape[0]
     assert d == rot.d and W_q.shape == (N, d // 2) and W_s.shape == (N, d // 32)
@@ -518,6 +552,9 @@ def torq_block_gram_workspace_bytes(G: int) -> int:
 
 def torq_block_gram(x_bf16: torch.Tensor, G: int, Sigma=None, workspace=None, stream=None):
     """Sigma [G, G] float64 on the device: mean Gram matrix of the runs of G blocks of x's rows."""
+    y = (_host or _native()).gram(x_bf16, G, False, Sigma, workspace, stream)
+    if y is not None:
+        return y
     M, d = x_bf16.shape
     if Sigma is None:
         Sigma = torch.empty((G, G), dtype=torch.float64, device=x_bf16.device)
@@ -532,6 +569,9 @@ def torq_block_gram(x_bf16: torch.Tensor, G: int, Sigma=None, workspace=None, st
 
 def torq_block_gram_positions(x_bf16: torch.Tensor, G: int, Sigma_pos=None, workspace=None, stream=None):
     """Sigma_pos [32, G, G] float64 on the device: the Gram matrix kept apart by the position inside a block."""
+    y = (_host or _native()).gram(x_bf16, G, True, Sigma_pos, workspace, stream)
+    if y is not None:
+        return y
     M, d = x_bf16.shape
     if Sigma_pos is None:
         Sigma_pos = torch.empty((32, G, G), dtype=torch.float64, device=x_bf16.device)
@@ -566,6 +606,9 @@ def torq_code_histogram_workspace_bytes() -> int:
 def torq_code_histogram(codes: torch.Tensor, d: int, counts: torch.Tensor = None, workspace: torch.Tensor = None,
                         stream=None):
     """codes: uint8 [M, d/2] device (packed e2m1).  Returns counts int64 [32, 8] device (N_j^(k), Appendix A.5)."""
+    y = (_host or _native()).histogram(codes, d, counts, workspace, stream)
+    if y is not None:
+        return y
     M = codes.shape[0]
     if codes.dim() != 2 or codes.shape[1] * 2 != d:
         raise ValueError("codes must be [M, d/2]")

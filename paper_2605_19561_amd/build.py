@@ -1,4 +1,4 @@
-"""Compile libtorq.so (HIP kernels + C ABI) for gfx950 with hipcc.
+"""Compile libtorq.so (HIP kernels + C ABI) for gfx950 with hipcc, and the binding's C++ module _host.so with g++.
 
 `python -m paper_2605_19561_amd.build` or `build()`.  The library is built in-tree
 (paper_2605_19561_amd/libtorq.so) so that it travels with the source tree.
@@ -9,6 +9,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtorq.so")
+HOST_LIB = os.path.join(HERE, "_host.so")      # the module paper_2605_19561_amd._host
 SOURCES = ["api.hip", "quantize.hip", "rotate_quant.hip", "rotate_butterfly.hip", "mxfp4_gemm.hip", "mxfp4_gemm_ring.hip",
            "mxfp4_gemm_skinny.hip", "mxfp4_gemm_stream.hip", "block_gram.hip", "code_histogram.hip",
            "intra_calib.hip", "diag.hip"]
@@ -39,9 +40,21 @@ def device_asm(source: str, out_path: str) -> str:
     return out_path
 
 
+def host_command() -> list:
+    """The compiler's command for the binding's C++ module (host code only, against torch's own headers)."""
+    import sysconfig
+    import torch
+    root = os.path.dirname(os.path.abspath(torch.__file__))
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+            "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
+            "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"), "-Wall",
+            os.path.join(CSRC, "host_calls.cpp"), "-o", HOST_LIB, "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+
+
 def build(verbose: bool = False) -> str:
     objs = []
-    procs = []
+    cmd = host_command()
+    procs = [(cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))]
     for s in SOURCES:
         obj = os.path.join(CSRC, s.replace(".hip", ".o"))
         objs.append(obj)
@@ -51,7 +64,7 @@ def build(verbose: bool = False) -> str:
         out, _ = p.communicate()
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
         if p.returncode != 0:
-            raise RuntimeError("hipcc failed: %s\n%s" % (" ".join(cmd), out))
+            raise RuntimeError("compiler failed: %s\n%s" % (" ".join(cmd), out))
         if verbose and out.strip():
             print(out)
     cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB, *objs]

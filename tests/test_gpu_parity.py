@@ -660,6 +660,66 @@ def test_calls_launch_on_the_current_stream(tq):
     assert tq._stream(side) == side.cuda_stream != tq._stream()
 
 
+# The calls that are marshalled in C++: what they return and what they refuse is what the interpreter's own way through the
+# arguments returns and refuses (the module left out, every call goes that way).
+class _NoModule:
+    linear = rotate_quantize = gram = histogram = staticmethod(lambda *a: None)
+
+
+@pytest.mark.parametrize("case", ["plain", "kept", "subclass", "parameter", "stream", "numpy sizes", "three dimensions", "other d",
+                                  "transposed", "type", "host", "no tensor", "closed", "small workspace", "odd start", "bad format"])
+def test_calls_marshalled_in_native_code(tq, monkeypatch, case):
+    d, G, M, N = 1024, 32, 5, 48
+    rot = tq.Rotation(d, G, *synth.rotations(G, seed=4))
+    x = synth.activations(M, d, seed=5).to(DEV)
+    w = tq.torq_rotate_quantize(rot, synth.weights(N, d, seed=6).to(DEV))
+    ws = torch.empty(1 << 22, dtype=torch.uint8, device=DEV)
+    kw, out, fmt, Gn, dn = {}, {}, tq.TORQ_FMT_NVFP4, G, d
+    if case in ("kept", "small workspace"):
+        kw = {"workspace": ws if case == "kept" else ws[:16]}
+        out = {"out": torch.empty((M, N), dtype=torch.bfloat16, device=DEV)}
+    x = {"subclass": lambda: x.as_subclass(type("T", (torch.Tensor,), {})), "parameter": lambda: torch.nn.Parameter(x),
+         "three dimensions": lambda: x[None], "other d": lambda: x[:, :512].contiguous(), "transposed": lambda: x.t().contiguous().t(),
+         "type": lambda: x.half(), "host": lambda: x.cpu(), "no tensor": lambda: None,
+         "odd start": lambda: torch.cat([x.flatten(), x[0]])[1:M * d + 1].view(M, d)}.get(case, lambda: x)()
+    if case == "numpy sizes":
+        Gn, dn = np.int64(G), np.int64(d)
+    if case == "bad format":
+        fmt = 7
+    if case == "closed":
+        rot.close()
+    if case == "stream":
+        kw["stream"] = torch.cuda.current_stream()
+    s = {k: v for k, v in kw.items() if k == "stream"}
+    calls = {"linear": lambda: tq.torq_linear(rot, x, *w, **out, **kw), "rotate": lambda: tq.torq_rotate_quantize(rot, x, **s),
+             "fmt": lambda: tq.torq_rotate_quantize_fmt(rot, x, fmt, 0.01, **s), "gram": lambda: tq.torq_block_gram(x, Gn, **kw),
+             "positions": lambda: tq.torq_block_gram_positions(x, Gn, **kw),
+             "histogram": lambda: tq.torq_code_histogram(x if case in ("no tensor", "three dimensions") else w[0], dn, **kw)}
+
+    def answers():
+        got = {}
+        for name, call in calls.items():
+            try:
+                y = call()
+                got[name] = [t.clone() for t in (y if isinstance(y, tuple) else (y,))]
+                if name == "linear" and out:
+                    assert y is out["out"]
+            except Exception as e:
+                got[name] = (type(e), str(e))
+        torch.cuda.synchronize()
+        return got
+
+    native = answers()
+    monkeypatch.setattr(tq, "_host", _NoModule)
+    for name, want in answers().items():
+        if isinstance(want, tuple):
+            assert native[name] == want, name
+        else:
+            assert all(type(a) is type(b) and torch.equal(a, b) for a, b in zip(native[name], want, strict=True)), name
+    refused = case not in ("plain", "kept", "subclass", "parameter", "stream", "numpy sizes")
+    assert any(isinstance(v, tuple) for v in native.values()) == refused
+
+
 def test_linear_replays_from_a_hip_graph(tq):
     # Every entry point only enqueues kernels on the caller's stream and allocates nothing, so a
     # serving loop can capture it.  The graph is replayed several times, with eager work and
