@@ -236,6 +236,49 @@ block_gram_shared_kernel(const uint4 *__restrict__ x, int64_t TG, f32x4 *__restr
   }
 }
 
+// Sigma_k: how a launch is cut.  256 or 512 workgroups of nearly equal work (four chunks x parts x slices) for at
+// most GRAM_POS_TILES tiles a part; the slices are a multiple of the XCDs.
+constexpr int gram_pos_parts(int nt) {
+  const int tiles = nt * (nt + 1) / 2, fit = (tiles + GRAM_POS_TILES - 1) / GRAM_POS_TILES;
+  return fit > 8 ? 16 : fit > 4 ? 8 : tiles < 4 ? tiles : 4;
+}
+constexpr int gram_pos_slices(int nt) { return nt == 1 ? 64 : gram_pos_parts(nt) <= 4 ? 16 : 8; }
+
+// The tiles of part PART of gram_pos_parts(NT).  A wave widens the operands of its tiles' rows and columns once a step, so a
+// part's tiles are to share them: the parts are consecutive runs of the triangle gone through by blocks of 2 x 2 tiles, down
+// the columns of each (NT = 8: 22 operands for the 36 tiles of four parts; by rows 25, by blocks of 3 x 3 26, each tile its
+// own 72).
+template <int NT, int PART>
+struct GramPart {
+  static constexpr int TILES = NT * (NT + 1) / 2, PARTS = gram_pos_parts(NT);
+  static constexpr int FIRST = TILES * PART / PARTS, COUNT = TILES * (PART + 1) / PARTS - FIRST;
+  int operands = 0;
+  int row[2 * GRAM_POS_TILES] = {};                             // operand -> tile row of the block rows
+  int a[GRAM_POS_TILES] = {}, b[GRAM_POS_TILES] = {};           // tile -> its operands
+  int place[GRAM_POS_TILES] = {};                               // tile -> its number in the triangle, row by row
+  constexpr int operand(int r) {
+    for (int o = 0; o < operands; ++o)
+      if (row[o] == r) return o;
+    row[operands] = r;
+    return operands++;
+  }
+  constexpr GramPart() {
+    int i = 0;
+    for (int r0 = 0; r0 < NT; r0 += 2)
+      for (int c0 = r0; c0 < NT; c0 += 2)
+        for (int c = c0; c < NT && c < c0 + 2; ++c)
+          for (int r = r0; r < NT && r < r0 + 2; ++r) {
+            if (r > c) continue;
+            if (i >= FIRST && i < FIRST + COUNT) {
+              a[i - FIRST] = operand(r);
+              b[i - FIRST] = operand(c);
+              place[i - FIRST] = r * NT - r * (r - 1) / 2 + c - r;
+            }
+            ++i;
+          }
+  }
+};
+
 // Sigma_k, all 32 positions in one pass.  A workgroup takes the eight positions of one 16-byte chunk of
 // every block, a slice of the token-groups and a part of the tiles; the workgroups of a slice share the
 // input's lines through the L2 of the XCD that all of them are on.  Wave j owns position 8 chunk + j.  The
@@ -249,43 +292,28 @@ block_gram_shared_kernel(const uint4 *__restrict__ x, int64_t TG, f32x4 *__restr
 // (any order of the token-groups will do, as long as both operands have the same).  Products and sums are double:
 // bf16 instructions round 32 products at a time to 24 bits and lose the small ones beside an outlier, 5.5e-8 against
 // 2.1e-8 relative for sums of one product after the other (activations with outlier channels, X [8192, 8192],
-// G = 128), and still 2.5e-8 with eight products a sum, added up in double.  Bound: the matrix cores at the double rate;
-// an instruction is 64 cycles and no vector instruction runs beside it, so with the conversions it takes 97 (45
-// TFLOP/s).  X [4096, 4096], G = 128: 69 us with the reduction (26 with bf16 instructions, 736 with a pass over x for
-// each position), [8192, 28672] 745 (235 and 3470).  Operands widened once a tile row, the next tile's read ahead or
-// tiles interleaved changed nothing.
-template <int NT>
-__global__ void __launch_bounds__(64 * GRAM_WAVES)
-block_gram_positions_kernel(const uint4 *__restrict__ x, int64_t TG, int slices, int parts, f64x4 *__restrict__ partial) {
+// G = 128), and still 2.5e-8 with eight products a sum, added up in double.  Bound: the matrix cores at the double rate,
+// an instruction in 64 cycles, and no vector instruction runs beside it, so every conversion is paid for.  Each tile's
+// operands widened for it alone / those of a part's rows once for all its tiles, with the reduction: X [4096, 4096], G = 128,
+// 68.2 / 58.5 us (31 are the products; 7.5 the reduction; the first loads, the transposition and the stores are the rest),
+// [2048, 14336], G = 112, 92.5 / 77.8, [1024, 8192], G = 256, 100 / 85.  Eight parts and eight slices at G = 128 take 66 (each
+// part reads the lines from the L2 and widens again).
+template <int NT, int PART>
+__device__ __forceinline__ void gram_positions_part(const uint4 *__restrict__ x, int64_t TG, int chunk, int slice, int slices,
+                                                    f64x4 *__restrict__ partial, char *lds) {
+  constexpr GramPart<NT, PART> part;
+  constexpr int COUNT = GramPart<NT, PART>::COUNT;
   constexpr int G = 16 * NT, TILES = NT * (NT + 1) / 2;
   constexpr int KST = NT < 8 ? 8 / NT : 1;          // steps of 32 token-groups per stage
   constexpr int ITEMS = 4 * KST * G;                // (octet of token-groups, block row)
   constexpr int THR = 64 * GRAM_WAVES, IT = (ITEMS + THR - 1) / THR;
   constexpr int PLANE = ITEMS * 16, STAGE = 8 * PLANE;
   constexpr bool TWO = 2 * STAGE <= 128 * 1024;     // two LDS stages, one barrier per stage
-  extern __shared__ __attribute__((aligned(16))) char lds[];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // workgroup id mod 8 is the XCD: the chunks and parts of a slice share one
-  const int id = blockIdx.x, units = 4 * parts, unit = (id >> 3) % units, chunk = unit & 3, part = unit >> 2;
-  const int slice = (id >> 3) / units * 8 + (id & 7);
-  if (slice >= slices) return;
   const int64_t stages = (TG + 32 * KST - 1) / (32 * KST);
   const int64_t st0 = stages * slice / slices, st1 = stages * (slice + 1) / slices;
-
-  // this part's tiles: LDS offsets of their operands' rows
-  const int tile0 = TILES * part / parts, count = TILES * (part + 1) / parts - tile0;
-  int row_off[GRAM_POS_TILES], col_off[GRAM_POS_TILES];
-  {
-    int place = tile0, r = gram_tile_row(NT, place), c = r + place;
-#pragma unroll
-    for (int i = 0; i < GRAM_POS_TILES; ++i) {
-      row_off[i] = r * 256;
-      col_off[i] = c * 256;
-      if (++c == NT) c = ++r;
-    }
-  }
 
   int voff[IT];
 #pragma unroll
@@ -320,9 +348,9 @@ block_gram_positions_kernel(const uint4 *__restrict__ x, int64_t TG, int slices,
     }
   };
 
-  f64x4 acc[GRAM_POS_TILES];
+  f64x4 acc[COUNT];
 #pragma unroll
-  for (int i = 0; i < GRAM_POS_TILES; ++i) acc[i] = f64x4{0.0, 0.0, 0.0, 0.0};
+  for (int i = 0; i < COUNT; ++i) acc[i] = f64x4{0.0, 0.0, 0.0, 0.0};
 
   const int f_off = wave * PLANE + ((lane >> 4) * G + (lane & 15)) * 16;
   if (st0 < st1) load(st0);
@@ -335,28 +363,40 @@ block_gram_positions_kernel(const uint4 *__restrict__ x, int64_t TG, int slices,
 #pragma unroll 1
     for (int ks = 0; ks < KST; ++ks) {
       const char *const f = stage + f_off + ks * (4 * G * 16);
+      u32x4 v[part.operands];
 #pragma unroll
-      for (int i = 0; i < GRAM_POS_TILES; ++i) {
-        if (i < count) {
-          const u32x4 a = *reinterpret_cast<const u32x4 *>(f + row_off[i]);
-          const u32x4 b = *reinterpret_cast<const u32x4 *>(f + col_off[i]);
+      for (int o = 0; o < part.operands; ++o) v[o] = *reinterpret_cast<const u32x4 *>(f + part.row[o] * 256);
 #pragma unroll
-          for (int w = 0; w < 4; ++w) {
-            acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)__builtin_bit_cast(float, a[w] << 16),
-                                                          (double)__builtin_bit_cast(float, b[w] << 16), acc[i], 0, 0, 0);
-            acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)__builtin_bit_cast(float, a[w] & 0xFFFF0000u),
-                                                          (double)__builtin_bit_cast(float, b[w] & 0xFFFF0000u), acc[i], 0, 0, 0);
-          }
-        }
+      for (int h = 0; h < 8; ++h) {                 // token-groups h of the octets
+        double wide[part.operands];
+#pragma unroll
+        for (int o = 0; o < part.operands; ++o)
+          wide[o] = (double)__builtin_bit_cast(float, h & 1 ? v[o][h / 2] & 0xFFFF0000u : v[o][h / 2] << 16);
+#pragma unroll
+        for (int i = 0; i < COUNT; ++i)
+          acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(wide[part.a[i]], wide[part.b[i]], acc[i], 0, 0, 0);
       }
     }
     if (!TWO) __syncthreads();
     buf ^= 1;
   }
-  f64x4 *const out = partial + (((size_t)slice * 32 + chunk * 8 + wave) * TILES + tile0) * 64 + lane;
+  f64x4 *const out = partial + ((size_t)slice * 32 + chunk * 8 + wave) * TILES * 64 + lane;
 #pragma unroll
-  for (int i = 0; i < GRAM_POS_TILES; ++i)
-    if (i < count) out[i * 64] = acc[i];
+  for (int i = 0; i < COUNT; ++i) out[part.place[i] * 64] = acc[i];
+}
+
+template <int NT>
+__global__ void __launch_bounds__(64 * GRAM_WAVES)
+block_gram_positions_kernel(const uint4 *__restrict__ x, int64_t TG, int slices, f64x4 *__restrict__ partial) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  constexpr int PARTS = gram_pos_parts(NT);
+  // workgroup id mod 8 is the XCD: the chunks and parts of a slice share one
+  const int id = blockIdx.x, units = 4 * PARTS, unit = (id >> 3) % units, chunk = unit & 3, part = unit >> 2;
+  const int slice = (id >> 3) / units * 8 + (id & 7);
+  if (slice >= slices) return;
+  static_for<PARTS>([&](auto p) {                   // (uniform: one branch taken)
+    if (part == p) gram_positions_part<NT, decltype(p)::value>(x, TG, chunk, slice, slices, partial, lds);
+  });
 }
 
 // Adds n partial results in double and in a fixed order, divides by the number of token-groups and writes
@@ -421,15 +461,6 @@ block_gram_reduce_kernel(const Quad *__restrict__ partial, int n, int nt, double
   }
 }
 
-// Sigma_k: how a launch is cut.  256 or 512 workgroups of nearly equal work (four chunks x parts x slices) for at
-// most GRAM_POS_TILES tiles a part; the slices are a multiple of the XCDs.  X [4096, 4096], G = 128: four parts and
-// 16 slices 69 us, eight and eight 73 (each part reads the lines from the L2 again).
-static int gram_pos_parts(int nt) {
-  const int tiles = nt * (nt + 1) / 2, fit = (tiles + GRAM_POS_TILES - 1) / GRAM_POS_TILES;
-  return fit > 8 ? 16 : fit > 4 ? 8 : tiles < 4 ? tiles : 4;
-}
-static int gram_pos_slices(int nt) { return nt == 1 ? 64 : gram_pos_parts(nt) <= 4 ? 16 : 8; }
-
 // the larger of the two statistics' partial results: Sigma_k's slices of 32 positions, Sigma's workgroups
 size_t block_gram_workspace_bytes(int G) {
   const int nt = G / 16;
@@ -493,12 +524,13 @@ static hipError_t launch_positions(const uint4 *x, int64_t TG, double *Sigma, vo
   const int64_t stages = (TG + 32 * KST - 1) / (32 * KST);
   const int64_t room = (int64_t)(workspace_bytes / ((size_t)32 * GramTiles<NT>::N * 2048));
   const int64_t most = room < gram_pos_slices(NT) ? room : gram_pos_slices(NT);
-  const int parts = gram_pos_parts(NT), n = (int)(stages < most ? stages : most);
+  constexpr int parts = gram_pos_parts(NT);
+  const int n = (int)(stages < most ? stages : most);
   static std::atomic<uint64_t> raised{0};
   const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(block_gram_positions_kernel<NT>), lds, raised);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((block_gram_positions_kernel<NT>), dim3((n + 7) / 8 * 8 * 4 * parts), dim3(64 * GRAM_WAVES), lds,
-                     stream, x, TG, n, parts, partial);
+                     stream, x, TG, n, partial);
   return launch_reduce<f64x4, 64>(partial, n, NT, 32, TG, Sigma, stream);
 }
 

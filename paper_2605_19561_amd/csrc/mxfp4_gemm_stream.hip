@@ -10,8 +10,6 @@
 //     soon as an item is in registers: R x 16 KB of a CU are always on their way;
 //   * one barrier a strip: it says that the strip's scale bytes are in LDS and that the partial tiles of the strip before are,
 //     which one wave per activation tile, the waves in turn, adds in the order 0 + 1 + ... + 7 and stores.
-#include <utility>
-
 #include "torq_device.h"
 #include "torq_internal.h"
 
@@ -24,15 +22,6 @@ constexpr int WAVES = 8;
 constexpr int STREAM_RING = 4;                    // items of a wave's ring: 3 and 5 measured 1 - 4 % slower, 2, 6 and 8 more
 constexpr size_t STREAM_MAX_LDS = 160 * 1024;
 constexpr int OOB_VOFF = 0x7FFFFFF0;              // rejected by the range check of any buffer here: zeros
-
-template <class F, int... I>
-__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F &&f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
 
 template <int N>
 __device__ __forceinline__ void wait_vm() {

@@ -27,8 +27,6 @@
 // LDS (double-buffered, one barrier per batch) and each wave fetches its A
 // operands with ds_read_b64_tr_b16, which performs the (k, b') transpose that
 // the row-major input needs.
-#include <utility>
-
 #include "rotate16_body.h"
 #include "torq_device.h"
 #include "torq_internal.h"
@@ -351,15 +349,6 @@ rotate_kernel32(const uint4 *__restrict__ x, int64_t TG, int G,
 // 1: the R_inter low-part pass, 2: the hi/lo split of Y on the vector ALU (raw register pairs are fed
 // instead), 4: the amax and the conversion of step 4 (bit patterns are stored instead), 8: two of the
 // three R_intra passes.  The output is then meaningless.  SKIP = 0 is the product.
-template <class F, int... I>
-__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F &&f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
-
 template <int OFF>
 __device__ __forceinline__ i16x4 lds_tr_read(uint32_t addr) {
   i16x4 v;
