@@ -500,7 +500,7 @@ int torq_linear(const torq_rotation_t *r, const void *x_bf16, const uint8_t *W_q
   uint8_t *codes = static_cast<uint8_t *>(workspace);
   uint8_t *scales = codes + (((size_t)M * (size_t)(r->d / 2) + 255) & ~(size_t)255);
   // a row or two of a decode step: one launch, every workgroup rotates the rows itself (same bits out)
-  if (torq::torq_linear_local_pays(r, M, N) && (int64_t)r->d * 128 < 0x7FFFFFFF) {
+  if (torq::torq_linear_local_pays(r, M, N, W_s) && (int64_t)r->d * 128 < 0x7FFFFFFF) {
     hipError_t el = torq::launch_torq_linear_local(r, x_bf16, codes, scales, W_q, W_s, out_bf16, M, N, (hipStream_t)stream);
     return el == hipSuccess ? TORQ_OK : hip_fail(el);
   }
@@ -529,7 +529,7 @@ int torq_linear_static(const torq_rotation_t *r, const void *x_bf16, const uint8
   if (e != hipSuccess) return hip_fail(e);
   uint8_t *codes = ws;
   uint8_t *scales = codes + (((size_t)M * (size_t)(r->d / 2) + 255) & ~(size_t)255);
-  if (torq::torq_linear_local_pays(r, M, N) && (int64_t)r->d * 128 < 0x7FFFFFFF) {      // as torq_linear
+  if (torq::torq_linear_local_pays(r, M, N, W_s) && (int64_t)r->d * 128 < 0x7FFFFFFF) {      // as torq_linear
     e = torq::launch_torq_linear_local(r, x_bf16, codes, scales, W_q, W_s, out_bf16, M, N, (hipStream_t)stream);
     return e == hipSuccess ? TORQ_OK : hip_fail(e);
   }

@@ -315,7 +315,7 @@ torq_linear_decode_kernel(const uint4 *__restrict__ x, int64_t TG, const uint4 *
         }
       } sink{reinterpret_cast<unsigned long long *>(A_q), A_s, (int64_t)blockIdx.x * 128};
       rotate32_resident(x + (int64_t)blockIdx.x * 512, 1, 128, inter_hi, inter_lo, intra_hi_frag, intra_lo_frag,
-                        reinterpret_cast<char *>(smem), sink, []() {});
+                        reinterpret_cast<char *>(smem), sink, []() {}, []() {});
     }
     __builtin_amdgcn_s_waitcnt(0);                 // this lane's stores have been acknowledged
     __syncthreads();
@@ -464,23 +464,6 @@ torq_linear_decode_kernel(const uint4 *__restrict__ x, int64_t TG, const uint4 *
 // LDS: [weight-strip scales | activation scales (16 rows, zero beyond M) | codes, M rows of d / 2 + 16
 // bytes (the pad spreads the rows over the banks) | the token-groups' bf16 values (8 KiB each), later
 // the partial tiles of the reduction (8 NS KiB)].
-namespace {
-struct LocalSink {
-  unsigned char *a_c, *s_a;
-  int a_stride, s_stride, bpr;        // bytes per code row / scale row in LDS; blocks per activation row
-  uint2 *codes_g;                     // workgroup 0: the copy in device memory, else nullptr
-  uint8_t *scales_g;
-  __device__ __forceinline__ void operator()(int64_t blk, int h, uint2 packed, uint32_t byte) const {
-    const int b = (int)blk, row = b / bpr, bk = b - row * bpr;
-    *reinterpret_cast<uint2 *>(a_c + row * a_stride + bk * 16 + h * 8) = packed;
-    if (h == 0) s_a[row * s_stride + bk] = (unsigned char)byte;
-    if (codes_g) {
-      codes_g[blk * 2 + h] = packed;
-      if (h == 0) scales_g[blk] = (uint8_t)byte;
-    }
-  }
-};
-}  // namespace
 
 // The end of torq_linear_local_kernel: as skinny_reduce_store for one activation tile, but with wave n
 // adding strip n (every wave's partial tile goes through LDS, red_mem = 8 NS KiB): with up to four
@@ -597,7 +580,7 @@ torq_linear_local_kernel(const uint4 *__restrict__ x, int TG, int G, const uint4
     // (two barriers inside: the first also orders the clearing above before any scale byte, the second
     // makes the results visible)
     rotate32_resident(x, TG, G, inter_hi, inter_lo, intra_hi_frag, intra_lo_frag, reinterpret_cast<char *>(xs), sink,
-                      weights_first_trip);
+                      weights_first_trip, []() {});
   }
 
   // ---- the strip groups of this workgroup
@@ -1085,8 +1068,10 @@ bool torq_linear_local_fits(const torq_rotation *r, int64_t M) {
 // replayed, [4, 4096] x 1024 7.1 / 7.2, x 4096 8.4 / 7.6, [2, 8192] x 2048 8.7 / 8.1, [1, 14336] x 2048 (G = 112)
 // 10.7 / 9.5; called one after the other from Python, where a launch more is 3 us of the host, 7.0 / 10.0, 7.0 / 10.0,
 // 7.7 / 8.6 and 10.6 / 9.1 with buffers kept by the caller, 10.3 / 13.4, 10.3 / 13.3, 9.6 / 12.3 and 10.6 / 12.1 without.
-bool torq_linear_local_pays(const torq_rotation *r, int64_t M, int64_t N) {
+// (Where the strips come through a ring, mxfp4_gemm_stream.hip, one launch is ahead of two at any size that form takes.)
+bool torq_linear_local_pays(const torq_rotation *r, int64_t M, int64_t N, const uint8_t *W_s) {
   if (!torq_linear_local_fits(r, M) || N <= 0) return false;
+  if (torq_linear_stream_takes(r, M, N, W_s)) return true;
   const int64_t token_groups = M * (int64_t)(r->d / 32 / r->G);
   return (double)N * (double)r->d * 0.53125 <= (token_groups <= 2 ? 20e6 : 16e6);
 }
@@ -1117,6 +1102,7 @@ hipError_t launch_torq_linear_local(const torq_rotation *r, const void *x_bf16, 
                                     const uint8_t *W_q, const uint8_t *W_s, void *out, int64_t M, int64_t N,
                                     hipStream_t stream) {
   if (!torq_linear_local_fits(r, M) || N <= 0) return hipErrorInvalidValue;
+  if (torq_linear_stream_takes(r, M, N, W_s)) return launch_torq_linear_stream(r, x_bf16, A_q, A_s, W_q, W_s, out, M, N, stream);
   // PT: the line pairs of a wave, so that one trip covers the k range (at most 8); NS: as many strips per
   // workgroup as leave every CU a workgroup, within the registers (NS PT <= 8: 128 for the weight codes
   // of a trip) and the LDS

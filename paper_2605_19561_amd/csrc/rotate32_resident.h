@@ -1,6 +1,7 @@
 // Steps 1-4 of Algorithm 3 for at most four token-groups of G = 112 or 128 blocks inside a workgroup of
 // exactly 512 lanes, MXFP4 results handed to a functor instead of stored: the rotation of
-// torq_linear_local_kernel (mxfp4_gemm_skinny.hip), which keeps the packed activations in LDS.
+// torq_linear_local_kernel (mxfp4_gemm_skinny.hip) and torq_linear_stream_kernel (mxfp4_gemm_stream.hip), which keep
+// the packed activations in LDS.
 //
 // The arithmetic is that of rotate_kernel32<G / 16, 1, FMT_MXFP4> (rotate_quant.hip), operation for
 // operation -- the same MFMAs on the same operands in the same order, the same split of Y, the same
@@ -13,7 +14,8 @@
 // Wave w takes the 32 block rows 32 (w % 4) .. and the token-groups w / 4 and w / 4 + 2.  Every read
 // from memory is issued first; then after_loads() runs (a place for loads that may return later:
 // vector-memory reads return in order, so what the rotation waits for is requested before them); then
-// the token-groups go to LDS, one barrier, steps 2-4, results to sink, one barrier.
+// the token-groups go to LDS, one barrier, steps 2-4 (after_products() in the first token-group's, when R_inter has been used),
+// results to sink, one barrier.
 //   sink(block index, h, the lane's sixteen codes of positions 16 h .. 16 h + 15, the block's scale byte)
 //   lds: 4 * 8192 bytes.
 #pragma once
@@ -22,12 +24,29 @@
 
 namespace torq {
 
-template <class Sink, class Hook>
+// Results into LDS, rows of codes and of scale bytes, for the products of the same workgroup.
+struct LocalSink {
+  unsigned char *a_c, *s_a;
+  int a_stride, s_stride, bpr;        // bytes per code row / scale row in LDS; blocks per activation row
+  uint2 *codes_g;                     // workgroup 0: the copy in device memory, else nullptr
+  uint8_t *scales_g;
+  __device__ __forceinline__ void operator()(int64_t blk, int h, uint2 packed, uint32_t byte) const {
+    const int b = (int)blk, row = b / bpr, bk = b - row * bpr;
+    *reinterpret_cast<uint2 *>(a_c + row * a_stride + bk * 16 + h * 8) = packed;
+    if (h == 0) s_a[row * s_stride + bk] = (unsigned char)byte;
+    if (codes_g) {
+      codes_g[blk * 2 + h] = packed;
+      if (h == 0) scales_g[blk] = (uint8_t)byte;
+    }
+  }
+};
+
+template <class Sink, class Hook, class Hook2>
 __device__ __forceinline__ void rotate32_resident(const uint4 *__restrict__ x, int TG, int G,
                                                   const uint4 *__restrict__ inter_hi_frag, const uint4 *__restrict__ inter_lo_frag,
                                                   const uint4 *__restrict__ intra32_hi_frag,
                                                   const uint4 *__restrict__ intra32_lo_frag, char *lds, const Sink sink,
-                                                  Hook after_loads) {
+                                                  Hook after_loads, Hook2 after_products) {
   constexpr int KS16 = 8, NW = 4;                    // G = 112 or 128: four waves of 32 block rows
   const int TG_BYTES = G * 64;                       // one token-group: G rows of 64 bytes
   constexpr int TG_STRIDE = 8192;                    // its place in LDS: 512 chunks of 16 bytes
@@ -74,7 +93,7 @@ __device__ __forceinline__ void rotate32_resident(const uint4 *__restrict__ x, i
   const int blk = lane >> 4, s16 = lane & 15;
   const int tr_off = ((8 * (blk >> 1) + (s16 >> 2)) * 32 + 16 * (blk & 1) + 4 * (s16 & 3)) * 2;
 
-  auto token_group = [&](int tg) {
+  auto token_group = [&](int tg, auto between) {
     const char *stage = lds + tg * TG_STRIDE + tr_off;
     // ---- step 2: Y^T = X^T R_inter^T
     f32x16 acc;
@@ -89,6 +108,7 @@ __device__ __forceinline__ void rotate32_resident(const uint4 *__restrict__ x, i
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(u.v, Bh[ks], acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(u.v, Bl[ks], acc, 0, 0, 0);
     }
+    between();
     // ---- step 3: Z^T = R_intra^T Y^T with Y split into bf16 hi + lo
     bf16x8 yh[2], yl[2];
 #pragma unroll
@@ -124,8 +144,8 @@ __device__ __forceinline__ void rotate32_resident(const uint4 *__restrict__ x, i
     const bool live = 32 * tile + col < G && tg < TG;   // a block row, and a token-group, that exists
     if (live) sink((int64_t)tg * G + 32 * tile + col, h, make_uint2(pack8_e2m1(zz, sc), pack8_e2m1(zz + 8, sc)), byte);
   };
-  token_group(first_tg);                       // outside any condition (see above); dropped if there is none
-  if (first_tg + 2 < TG) token_group(first_tg + 2);
+  token_group(first_tg, after_products);       // outside any condition (see above); dropped if there is none
+  if (first_tg + 2 < TG) token_group(first_tg + 2, []() {});
   __syncthreads();
 }
 

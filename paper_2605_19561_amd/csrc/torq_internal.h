@@ -122,10 +122,15 @@ hipError_t launch_torq_linear_decode(const torq_rotation *r, const void *x_bf16,
 // A_q / A_s).  torq_linear_local_fits: dense R_inter, G = 112 or 128, at most four token-groups.
 bool torq_linear_local_fits(const torq_rotation *r, int64_t M);
 // ... and is measured faster than the two launches (what torq_linear itself then does)
-bool torq_linear_local_pays(const torq_rotation *r, int64_t M, int64_t N);
+bool torq_linear_local_pays(const torq_rotation *r, int64_t M, int64_t N, const uint8_t *W_s);
 hipError_t launch_torq_linear_local(const torq_rotation *r, const void *x_bf16, uint8_t *A_q, uint8_t *A_s,
                                     const uint8_t *W_q, const uint8_t *W_s, void *out, int64_t M, int64_t N,
                                     hipStream_t stream);
+// The same with the weight strips one after the other through a ring (mxfp4_gemm_stream.hip): where it takes the place of
+// the form above (its preconditions among them), and the launch.
+bool torq_linear_stream_takes(const torq_rotation *r, int64_t M, int64_t N, const uint8_t *W_s);
+hipError_t launch_torq_linear_stream(const torq_rotation *r, const void *x_bf16, uint8_t *A_q, uint8_t *A_s, const uint8_t *W_q,
+                                     const uint8_t *W_s, void *out_bf16, int64_t M, int64_t N, hipStream_t stream);
 // all of the handle's counters back to zero, the sticky error word included
 hipError_t launch_decode_ctr_reset(const torq_rotation *r, hipStream_t stream);
 

@@ -1501,6 +1501,40 @@ def test_rotate_random_shapes(tq, oracle, M, d, G):
 
 # ------------------------------------ torq_linear_single_launch (rotate + quantise inside the GEMM's launch) ----
 
+# The one launch with the strips through a ring, every line-pair count it is built for, first and later strips of unequal shares,
+# ragged widths, one to four token-groups; scale rows off the 16-byte grid take another form.  The bits and the codes left
+# in the workspace are those of the two calls.
+RING_LINEAR = [(1, 4097, 4096), (2, 12309, 4096), (1, 8, 3584), (2, 4100, 3584), (4, 4096, 3584), (1, 16, 8192), (1, 4113, 8192),
+               (2, 2047, 8192), (1, 9000, 7168), (2, 100, 7168), (1, 4096, 10752), (1, 520, 12288), (1, 4090, 14336)]
+
+
+@pytest.mark.parametrize("M,N,d", RING_LINEAR)
+def test_linear_in_one_launch_with_strips_through_a_ring(tq, M, N, d):
+    G = 128 if (d // 32) % 128 == 0 else 112
+    rot = tq.Rotation(d, G, *synth.rotations(G, seed=5 + M))
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(N + d)
+    W_q = torch.randint(0, 256, (N, d // 2), dtype=torch.uint8, device=DEV, generator=gen)
+    W_s = torch.randint(118, 128, (N, d // 32), dtype=torch.uint8, device=DEV, generator=gen)
+    off = torch.empty(W_s.numel() + 4, dtype=torch.uint8, device=DEV)
+    off[4:] = W_s.flatten()
+    ws = torch.zeros((tq.torq_linear_workspace_bytes_n(M, N, d),), dtype=torch.uint8, device=DEV)
+    out = torch.empty((M + 1, N), dtype=torch.bfloat16, device=DEV)
+    at = (M * d // 2 + 255) // 256 * 256
+    for seed in (1200, 1300):
+        x = synth.activations(M, d, nu=3.0, outliers=max(2, d // 200), outlier_scale=50.0, seed=seed + M).to(DEV)
+        A_q, A_s = tq.torq_rotate_quantize(rot, x)
+        want = tq.mxfp4_gemm(A_q, A_s, W_q, W_s)
+        for f in (tq.torq_linear, tq.torq_linear_single_launch):
+            out.fill_(7.0)
+            ws.zero_()
+            f(rot, x, W_q, W_s, out=out[:M], workspace=ws)
+            torch.cuda.synchronize()
+            assert torch.equal(out[:M], want) and torch.all(out[M] == 7.0)
+            assert torch.equal(ws[:M * d // 2].view(M, d // 2), A_q) and torch.equal(ws[at:at + M * d // 32].view(M, d // 32), A_s)
+        assert torch.equal(tq.torq_linear(rot, x, W_q, off[4:].view(N, d // 32)), want)
+
+
 @pytest.mark.parametrize("M,N,d", DECODE_CASES + LOCAL_CASES)
 def test_linear_single_launch_against_chain_and_oracle(tq, oracle, M, N, d):
     G = 128 if (d // 32) % 128 == 0 else 112

@@ -151,6 +151,29 @@ def test_stream_kernel_waits_by_its_own_counts():
     assert seen == 12
 
 
+# ---- torq_linear_stream_kernel: the compiler's own loads end at the one wait ahead of the ring, the LDS stores of the rows wait
+# for themselves and not for the weights behind them, and the ring's waits are its own counts.
+def test_linear_stream_kernel_waits_by_its_own_counts():
+    with tempfile.TemporaryDirectory() as tmp:
+        text = open(build.device_asm("mxfp4_gemm_stream.hip", os.path.join(tmp, "stream.s"))).read()
+    seen = 0
+    for m in re.finditer(r"^(_ZN4torq25torq_linear_stream_kernelILi(\d)ELi(\d)ELi(\d)\w+):(.*?)^\.Lfunc_end", text, re.M | re.S):
+        name, PT, H, R, body = m.group(1), int(m.group(2)), int(m.group(3)), int(m.group(4)), m.group(5)
+        seen += 1
+        assert re.search(r"\.name:\s+" + name + r"\n(?:.*\n)*?\s+\.private_segment_fixed_size:\s+0\n", text), name
+        code = [c for c in (line.split(";")[0].strip() for line in body.splitlines()) if c]
+        waits = [(i, int(re.search(r"vmcnt\((\d+)\)", c).group(1))) for i, c in enumerate(code) if c.startswith("s_waitcnt") and "vmcnt(" in c]
+        ring = next(k for k, (i, n) in enumerate(waits) if n == 0)
+        stores = [i for i, c in enumerate(code[:waits[ring][0]]) if c.startswith("ds_write_b128")]
+        assert len(stores) == 4 and min(n for i, n in waits[:ring] if i < stores[-1]) >= 2 * H, (name, waits)
+        own = [i for i, c in enumerate(code) if re.match(r"(buffer_load|global_load|flat_load|scratch_)", c) and not c.endswith("lds")]
+        assert own and max(own) < waits[ring][0], name
+        counts = [2 * (R - 1) + (i + R - 1) // PT for i in range(PT)]
+        later = [n for _, n in waits[ring + 1:]]
+        assert later[:PT - H] == counts[H:] and set(later[PT - H:-1]) == set(counts) and later[-1] == 0, (name, later)
+    assert seen == 4
+
+
 # ---- torq_linear_local_kernel (mxfp4_gemm_skinny.hip): not correctness but the point of the kernel.  The
 # rotation's reads are issued ahead of the workgroup's weight reads and its LDS stores must wait for them
 # alone -- s_waitcnt vmcnt(N) with N >= the number of weight loads behind them.  A load that the compiler
