@@ -67,7 +67,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t gram_rsrc(const void *p, uint3
 // A token-group past the end reads as zeros through the buffer's range check and adds nothing.  The
 // workgroup's waves add their tiles at the end: 256 partial results instead of the 512 of the form that
 // shares each token-group.  X [16384, 8192], G = 128: this kernel 51 us against 64 (5.2 TB/s, the rate of a copy).
-template <int NT>
+// ONCE: loads with the non-temporal hint (ONE_PASS_BYTES), X [16384, 8192] 55.4 -> 50.5 us with the reduction.
+template <int NT, bool ONCE>
 __global__ void __launch_bounds__(64 * GRAM_WAVES)
 block_gram_kernel(const uint4 *__restrict__ x, int64_t TG, f32x4 *__restrict__ partial) {
   constexpr GramTiles<NT> tiles;
@@ -94,7 +95,7 @@ block_gram_kernel(const uint4 *__restrict__ x, int64_t TG, f32x4 *__restrict__ p
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int f = 0; f < NT; ++f)
-        v[u][f] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, u * (G * 64) + f * 1024, 0);
+        v[u][f] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, u * (G * 64) + f * 1024, LOAD_POLICY<ONCE>);
   };
   auto multiply = [&](const u32x4 (&v)[U][NT]) {
 #pragma unroll
@@ -499,12 +500,18 @@ static hipError_t launch_sigma(const uint4 *x, int64_t TG, double *Sigma, void *
     constexpr int U = NT < 8 ? 8 / NT : 1;
     if (TG / U >= GRAM_WAVES * GRAM_MAX_WG) {
       constexpr size_t lds = (size_t)GRAM_WAVES * gram_box_tiles(TILES) * 1024;
-      if constexpr (lds > 64 * 1024) {
-        static std::atomic<uint64_t> raised{0};
-        const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(block_gram_kernel<NT>), lds, raised);
-        if (e != hipSuccess) return e;
-      }
-      hipLaunchKernelGGL((block_gram_kernel<NT>), dim3(GRAM_MAX_WG), dim3(64 * GRAM_WAVES), lds, stream, x, TG, partial);
+      auto go = [&](auto kernel, std::atomic<uint64_t> &raised) {
+        if constexpr (lds > 64 * 1024) {
+          const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(kernel), lds, raised);
+          if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(kernel, dim3(GRAM_MAX_WG), dim3(64 * GRAM_WAVES), lds, stream, x, TG, partial);
+        return hipSuccess;
+      };
+      static std::atomic<uint64_t> raised[2];
+      const hipError_t e = (double)TG * (1024.0 * NT) > ONE_PASS_BYTES ? go(block_gram_kernel<NT, true>, raised[1])
+                                                                       : go(block_gram_kernel<NT, false>, raised[0]);
+      if (e != hipSuccess) return e;
       return launch_reduce<f32x4, 16>(partial, GRAM_MAX_WG, NT, 1, TG, Sigma, stream);
     }
   }

@@ -21,7 +21,8 @@
 // wave, 3.4 us of the vector units' time at 2^21 blocks, beside 6 us of reading.  What follows the last load is
 // not hidden by anything, so it is kept short.  An earlier form widened the nibbles into byte counters after
 // 15 blocks and added the lanes through LDS: 14.7 us for the
-// call at 2^21 blocks (codes of [8192, 8192]), 7.5 us at 512; this one 11.8 us and 5.6 us.
+// call at 2^21 blocks (codes of [8192, 8192]), 7.5 us at 512; this one 11.8 us and 5.6 us.  The loads carry the non-temporal
+// hint: 11.8 -> 11.4 us there, 2^23 blocks 28.8 -> 26.5, 2^20 9.2 -> 8.6.
 #include "torq_device.h"
 #include "torq_internal.h"
 
@@ -63,7 +64,7 @@ code_histogram_kernel(const uint8_t *__restrict__ codes, int64_t nblk, uint32_t 
     __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint8_t *>(codes) + (left <= 0 ? 0 : first * 16), 0, (int)records, 0x00020000);
 #pragma unroll
-    for (int i = 0; i < HIST_GROUP; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, i * ROW_BYTES, 0);
+    for (int i = 0; i < HIST_GROUP; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, i * ROW_BYTES, LOAD_POLICY<true>);
   };
 
   uint32_t nib[HIST_MONO][4];

@@ -44,8 +44,10 @@ size_t stream_lds_bytes(int MT, int PT, int R, int d) {
 
 // What a wave of the two kernels below works with.  AT: how many activation tiles come through the ring ahead of the strips
 // (the "strips" 0 ... AT - 1 of a workgroup; its weight strips follow).
+// ONCE: the weights' codes with the non-temporal hint (ONE_PASS_BYTES; the activations come from the L2 in every workgroup and
+// go without: with it [64, 8192] x 20480 23.4 -> 24.5 us).
 // LDS from `mem` on: [rings | buffers of scale rows | two buffers of partial tiles]
-template <int MT, int PT, int R, int AT>
+template <int MT, int PT, int R, int AT, bool ONCE>
 struct Stream {
   static constexpr int BUFS = stream_scale_buffers(PT, R);
   static_assert(2 * R + BUFS <= 63, "the counter of loads in flight has six bits");
@@ -114,8 +116,13 @@ struct Stream {
   __device__ __forceinline__ void request(int s, int i, int to) {
     const int kp = wave + 8 * i;
     const i32x4 rs = uniform(raw_buffer((s < AT ? A_q : W_q) + (int64_t)row_of(s) * row_bytes, kp < KP ? (uint32_t)rows_of(s) * row_bytes : 0u));
-    load_to_lds16(rs, ring0 + to * 2048, v0, kp * 128);
-    load_to_lds16(rs, ring0 + to * 2048 + 1024, v1, kp * 128);
+    if (ONCE && s >= AT) {
+      load_to_lds16<true, true>(rs, ring0 + to * 2048, v0, kp * 128);
+      load_to_lds16<true, true>(rs, ring0 + to * 2048 + 1024, v1, kp * 128);
+    } else {
+      load_to_lds16(rs, ring0 + to * 2048, v0, kp * 128);
+      load_to_lds16(rs, ring0 + to * 2048 + 1024, v1, kp * 128);
+    }
   }
   __device__ __forceinline__ void request_scales(int s) {
     const i32x4 rs = uniform(raw_buffer((s < AT ? A_s : W_s) + (int64_t)row_of(s) * srow_bytes, (uint32_t)rows_of(s) * srow_bytes));
@@ -223,12 +230,12 @@ struct Stream {
   }
 };
 
-template <int MT, int PT, int R>
+template <int MT, int PT, int R, bool ONCE>
 __global__ void __launch_bounds__(64 * WAVES)
 mxfp4_gemm_stream_kernel(const uint8_t *__restrict__ A_q, const uint8_t *__restrict__ A_s, const uint8_t *__restrict__ W_q,
                          const uint8_t *__restrict__ W_s, uint16_t *__restrict__ out, int M, int N, int d, int strips_each, int strips_over) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  Stream<MT, PT, R, MT> st(A_q, A_s, W_q, W_s, out, M, N, d, strips_each, strips_over, smem);
+  Stream<MT, PT, R, MT, ONCE> st(A_q, A_s, W_q, W_s, out, M, N, d, strips_each, strips_over, smem);
   st.template start<0>();
   // the activations: operand (i, e, t) = line pair wave + 8 i, k-step e of it, tile t; zeros past M and d
   u32x4 aq[PT][2][MT];
@@ -263,7 +270,7 @@ torq_linear_stream_kernel(const uint4 *__restrict__ x, int TG, int G, const uint
   static_assert(H >= 1 && H <= PT, "items of the first strip");
   // LDS: [stream_lds_bytes | scale rows of the activations, 16 | their codes, M rows padded by 16 bytes | token-groups, 4 x 8 KB]
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  Stream<1, PT, R, 0> st(nullptr, nullptr, W_q, W_s, out, M, N, d, strips_each, strips_over, smem);
+  Stream<1, PT, R, 0, false> st(nullptr, nullptr, W_q, W_s, out, M, N, d, strips_each, strips_over, smem);
   const int s_stride = st.srow_bytes + 4, a_stride = st.row_bytes + 16;
   unsigned char *const s_a = reinterpret_cast<unsigned char *>(st.red + 2 * WAVES * 64);
   unsigned char *const a_c = s_a + 16 * s_stride;
@@ -334,20 +341,20 @@ torq_linear_stream_kernel(const uint4 *__restrict__ x, int TG, int G, const uint
   st.strips(1, aq, as);
 }
 
-template <int MT, int PT, int R>
+template <int MT, int PT, int R, bool ONCE>
 static hipError_t launch_cfg(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q, const uint8_t *W_s, void *out, int64_t M,
                              int64_t N, int d, hipStream_t stream) {
   const size_t lds = stream_lds_bytes(MT, PT, R, d);
   if (lds > STREAM_MAX_LDS) return hipErrorInvalidValue;
+  auto kernel = mxfp4_gemm_stream_kernel<MT, PT, R, ONCE>;
   if (lds > 64 * 1024) {
     static std::atomic<uint64_t> raised{0};
-    const hipError_t e =
-        raise_lds_limit(reinterpret_cast<const void *>(mxfp4_gemm_stream_kernel<MT, PT, R>), STREAM_MAX_LDS, raised);
+    const hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(kernel), STREAM_MAX_LDS, raised);
     if (e != hipSuccess) return e;
   }
   const int64_t strips = (N + 15) / 16;
   const int64_t grid = strips < 256 ? strips : 256;
-  hipLaunchKernelGGL((mxfp4_gemm_stream_kernel<MT, PT, R>), dim3((unsigned)grid), dim3(64 * WAVES), lds, stream, A_q, A_s, W_q, W_s,
+  hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * WAVES), lds, stream, A_q, A_s, W_q, W_s,
                      reinterpret_cast<uint16_t *>(out), (int)M, (int)N, d, (int)(strips / grid), (int)(strips % grid));
   return hipGetLastError();
 }
@@ -357,8 +364,10 @@ static hipError_t launch_cfg(const uint8_t *A_q, const uint8_t *A_s, const uint8
 // fit the registers beyond), and strips enough for a workgroup's start, the activations through its ring, to be paid off.
 // Weights from HBM, us, what the planner took before against this form:
 //   8 - 16 rows past 1600 strips (two strips a workgroup, persistent): [8, 8192] x 28672 27.8 / 25.8, [16, 8192] x 28672 28.7 /
-//     26.4; below that the whole-line form stays, and below 8 rows the strips straight to registers ([1, 8192] x 28672 24.4 /
-//     25.1)
+//     23.8; below that the whole-line form stays
+//   fewer than 8 rows (strips straight to registers, which are 3 % ahead of this form without the non-temporal hint): weights
+//     that take the hint, [1, 8192] x 28672 24.8 / 23.6, x 24576 21.3 / 20.4, [4, 8192] x 28672 27.1 / 23.9, [7, 8192] x 26624
+//     27.2 / 22.8
 //   17 - 32 rows past 1536 strips (tiles): [17, 5120] x 28672 18.8 / 17.0, [32, 8192] x 25600 29.8 / 25.0, [32, 2560] x 28672
 //     11.0 / 10.6; d = 2048 9.1 / 9.3, left to the tiles
 //   33 - 64 rows (tiles, cut or not), where it is ahead by more than the two were apart in other runs:
@@ -369,7 +378,9 @@ static hipError_t launch_cfg(const uint8_t *A_q, const uint8_t *A_s, const uint8
 //       / 12.8, [48, 8192] x 25600 30.6 / 26.1, [64, 4096] x 28672 16.4 / 16.3, but [33, 4096] x 16384 9.5 / 10.3; between them,
 //       [64, 5120] x 16384 13.8 / 13.0, [64, 7168] x 28672 26.0 / 26.2, [64, 2560] x 28672 11.8 / 12.8, the tiles keep theirs
 bool mxfp4_gemm_stream_takes(int64_t M, int64_t N, int d) {
-  if (M < 8 || M > 64 || d % 512 != 0 || d < 2560 || d > 8192 || N > (1 << 30)) return false;
+  if (d % 512 != 0 || d < 2560 || d > 8192 || N > (1 << 30)) return false;
+  if (M < 8) return (double)N * (double)d * 0.53125 > ONE_PASS_BYTES;
+  if (M > 64) return false;
   const int64_t strips = (N + 15) / 16;
   if (M <= 16) return strips > 1600;
   if (M <= 32) return strips > 1536;
@@ -384,8 +395,11 @@ int mxfp4_gemm_stream_strips(int d) { return stream_scale_buffers((d / 256 + WAV
 hipError_t launch_mxfp4_gemm_stream(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q, const uint8_t *W_s, void *out,
                                     int64_t M, int64_t N, int d, hipStream_t stream) {
   const int MT = (int)((M + 15) / 16), PT = (d / 256 + WAVES - 1) / WAVES;
-#define TORQ_STREAM(MT_, PT_) \
-  if (MT == MT_ && PT == PT_) return launch_cfg<MT_, PT_, STREAM_RING>(A_q, A_s, W_q, W_s, out, M, N, d, stream);
+  const bool once = (double)N * (double)d * 0.53125 > ONE_PASS_BYTES;
+#define TORQ_STREAM(MT_, PT_)                                                                                                   \
+  if (MT == MT_ && PT == PT_)                                                                                                  \
+    return once ? launch_cfg<MT_, PT_, STREAM_RING, true>(A_q, A_s, W_q, W_s, out, M, N, d, stream)                            \
+                : launch_cfg<MT_, PT_, STREAM_RING, false>(A_q, A_s, W_q, W_s, out, M, N, d, stream);
   TORQ_STREAM(1, 2) TORQ_STREAM(1, 3) TORQ_STREAM(1, 4) TORQ_STREAM(2, 2) TORQ_STREAM(2, 3) TORQ_STREAM(2, 4)
   TORQ_STREAM(3, 2) TORQ_STREAM(3, 3) TORQ_STREAM(3, 4) TORQ_STREAM(4, 2) TORQ_STREAM(4, 3) TORQ_STREAM(4, 4)
 #undef TORQ_STREAM

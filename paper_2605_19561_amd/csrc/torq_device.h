@@ -36,13 +36,21 @@ __device__ __forceinline__ i32x4 raw_buffer(const void *p, uint32_t bytes) {
   const uint64_t a = reinterpret_cast<uint64_t>(p);
   return i32x4{(int)(uint32_t)a, (int)((uint32_t)(a >> 32) & 0xFFFFu), (int)bytes, 0x00020000};
 }
+// ONCE: the non-temporal hint (see ONE_PASS_BYTES).
 #define TORQ_LOAD_TO_LDS16 "s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-template <bool FENCE = true>
+#define TORQ_LOAD_TO_LDS16_ONCE "s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+template <bool FENCE = true, bool ONCE = false>
 __device__ __forceinline__ void load_to_lds16(i32x4 rsrc, uint32_t lds_addr, int voff, int soff) {
-  if constexpr (FENCE) asm volatile(TORQ_LOAD_TO_LDS16 :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "m0", "memory");
+  static_assert(FENCE || !ONCE);
+  if constexpr (ONCE) asm volatile(TORQ_LOAD_TO_LDS16_ONCE :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "m0", "memory");
+  else if constexpr (FENCE) asm volatile(TORQ_LOAD_TO_LDS16 :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "m0", "memory");
   else asm volatile(TORQ_LOAD_TO_LDS16 :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "m0");
 }
 #undef TORQ_LOAD_TO_LDS16
+#undef TORQ_LOAD_TO_LDS16_ONCE
+// the same hint as the cache policy of a buffer load builtin
+template <bool ONCE>
+constexpr int LOAD_POLICY = ONCE ? 2 : 0;
 
 // The output tile of a GEMM workgroup whose wave holds acc[j][i][r] = out[m0 + 32 (wy WM + i) + lane % 32][n0 + 32 (wx WN
 // + j) + 8 (r / 4) + 4 (lane / 32) + r % 4] (m0, n0: the tile's corner; wy, wx: the wave's place in it).

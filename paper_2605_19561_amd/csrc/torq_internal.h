@@ -35,6 +35,15 @@ constexpr int DECODE_ERR = 32 * 130;      // the sticky "a workgroup gave up" wo
 
 namespace torq {
 
+// An input that a kernel reads once and that is larger than this is read with the non-temporal hint.  From HBM the hint is worth
+// 8 % (117 MB into LDS at 7.4 TB/s against 6.8; the sc bits change nothing): such loads leave the 256 MB Infinity Cache
+// alone.  An input that a program finds there is read slower with it, so it is for inputs of which the cache would not
+// hold a few: three in turn, with the hint against without, Sigma of [4096, 8192] (67 MB) 23.2 / 20.4 us, [6144, 8192] (101 MB)
+// 26.7 / 24.7, [8192, 8192] 31.1 / 32.5, [16384, 8192] 50.5 / 55.4; weights of 70 MB [33, 5120] x 25600 19.7 / 16.0, of
+// 125 MB [16, 28672] x 8192 23.8 / 26.3.  (In a model, where they come from HBM whatever their size, layers of 4 to
+// 70 MB would gain 3 - 10 % too; a call does not see that.)
+constexpr double ONE_PASS_BYTES = 96.0 * 1024 * 1024;
+
 // Raises a kernel's dynamic LDS limit to `bytes`, once for each device it is launched on (the limit belongs to
 // the function on one device, and the call is slow).  `raised`: the caller's, one per kernel, a bit a device;
 // a failed call leaves the bit clear, so the next launch tries again.

@@ -343,7 +343,8 @@ def test_gemm_weight_streaming_by_whole_lines(tq, oracle, M, N, d):
 # and last strip counts of its ranges, a row and a column more than whole tiles, workgroups of unequal shares.  The bar is the
 # one of the other forms: one rounding of an fp32 sum to bf16.
 STREAM_RING = [(8, 28673, 2560), (16, 28700, 6144), (13, 25601, 8192), (17, 24577, 3072), (32, 28672, 4608), (20, 26000, 8192),
-               (33, 16385, 2560), (48, 12288, 5120), (40, 10248, 7168), (64, 10244, 3584), (49, 16391, 4608), (64, 24576, 8192)]
+               (33, 16385, 2560), (48, 12288, 5120), (40, 10248, 7168), (64, 10244, 3584), (49, 16391, 4608), (64, 24576, 8192),
+               (1, 24585, 8192), (7, 32776, 6144), (2, 40003, 5120)]
 
 
 @pytest.mark.parametrize("M,N,d", STREAM_RING)
@@ -857,6 +858,17 @@ def test_block_gram_at_the_edges_of_steps_trips_and_stages(tq, TG, G):
     assert torch.equal(got, got.transpose(1, 2)) and torch.equal(S, S.T)
 
 
+# inputs past 96 MiB are read with the non-temporal hint: the first token-group past it, for every kernel of that form
+@pytest.mark.parametrize("G", [16, 32, 48, 64, 80, 96, 112, 128])
+def test_block_gram_of_inputs_read_past_the_cache(tq, G):
+    TG = 96 * 2 ** 20 // (64 * G) + 1
+    x = synth.weights(TG, 32 * G, seed=G, device=DEV)
+    S, W = tq.torq_block_gram(x, G), _block_gram_float64(x, G).sum(0) / TG
+    # an fp32 chain of TG / 2048 token-groups, each of them 32 products, and the sum of eight waves
+    assert (S - W).abs().max() <= (TG // 2048 + 2) * 2.0 ** -22 * W.abs().max()
+    assert torch.equal(S, S.T)
+
+
 def _block_gram_float64(x, G):
     """The 32 matrices Sigma_k in float64 on the GPU, undivided."""
     v = x.view(-1, G, 32)
@@ -1299,6 +1311,20 @@ def test_butterfly_rotate_quantize_against_oracle(tq, oracle, M, d, G):
     tiny = np.abs(z) <= np.broadcast_to(tol, z.shape)
     assert np.all(near[cdiff] | tiny[cdiff])
     assert cdiff.mean() <= 0.005
+    rot.close()
+
+
+# past 96 MiB of input the loads carry the non-temporal hint: bit for bit the two halves, which go without
+@pytest.mark.parametrize("G", [32, 64, 128, 256])
+def test_butterfly_of_inputs_read_past_the_cache(tq, G):
+    M, d = 6145, 8192
+    x = synth.activations(M, d, outliers=40, outlier_scale=50.0, seed=G, device=DEV)
+    T = np.random.default_rng(G).uniform(-1.0, 1.0, size=(G.bit_length() - 1, G // 2)).astype(np.float32)
+    rot = tq.ButterflyRotation(d, G, T, synth.rotations(G, seed=81 + G)[1])
+    for fmt in (tq.TORQ_FMT_MXFP4, tq.TORQ_FMT_MXINT4, tq.TORQ_FMT_NVFP4):
+        whole = tq.torq_rotate_quantize_fmt(rot, x, fmt, 0.05)
+        halves = [tq.torq_rotate_quantize_fmt(rot, part.contiguous(), fmt, 0.05) for part in (x[:3000], x[3000:])]
+        assert all(torch.equal(w, torch.cat(h)) for w, h in zip(whole, zip(*halves))), fmt
     rot.close()
 
 

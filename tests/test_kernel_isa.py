@@ -144,11 +144,11 @@ def test_stream_kernel_waits_by_its_own_counts():
         assert re.search(r"\.name:\s+" + name + r"\n(?:.*\n)*?\s+\.private_segment_fixed_size:\s+0\n", text), name
         code = [c for c in (line.split(";")[0].strip() for line in body.splitlines()) if c]
         loads = [c for c in code if re.match(r"(buffer_|global_load|flat_|scratch_)", c)]
-        assert loads and all(re.match(r"buffer_load_dwordx4 v\d+, s\[\d+:\d+\], s\d+ offen lds$", c) for c in loads), name
+        assert loads and all(re.match(r"buffer_load_dwordx4 v\d+, s\[\d+:\d+\], s\d+ offen (nt )?lds$", c) for c in loads), name
         waits = [int(re.search(r"vmcnt\((\d+)\)", c).group(1)) for c in code if c.startswith("s_waitcnt") and "vmcnt(" in c]
         counts = [2 * (R - 1) + (i + R - 1) // PT for i in range(PT)]
         assert waits[:MT * PT] == MT * counts and set(waits[MT * PT:-1]) == set(counts) and waits[-1] == 0, (name, waits)
-    assert seen == 12
+    assert seen == 24
 
 
 # ---- torq_linear_stream_kernel: the compiler's own loads end at the one wait ahead of the ring, the LDS stores of the rows wait
