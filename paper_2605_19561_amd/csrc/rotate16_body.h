@@ -182,7 +182,9 @@ __device__ __forceinline__ void rotate16_body(const uint4 *__restrict__ x, int64
           float amax = amax8(zz);
           amax = fmaxf(amax, __shfl_xor(amax, 16));
           const uint32_t sc = nvfp4_scale_code(amax, 6.0f * global_scale);
-          codes[blk * 4 + q] = pack8_nvfp4(zz, e4m3_to_f32(sc) * global_scale);
+          uint32_t c[1];
+          pack_nvfp4(zz, 1.0f, e4m3_to_f32(sc) * global_scale, c);
+          codes[blk * 4 + q] = c[0];
           if ((q & 1) == 0) scales[blk * 2 + (q >> 1)] = (uint8_t)sc;
         } else if constexpr (FMT != FMT_NONE) {
           // ---- step 4: MXFP4 (Section 4, Eq. 1), or MXINT4 on the same scale -----

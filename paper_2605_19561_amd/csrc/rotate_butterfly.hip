@@ -78,10 +78,14 @@ __device__ __forceinline__ float swizzle_f32(float v) {
 //   entry (log2 G) NJ + j:                      the row's final sigma
 // G <= 64 keeps the lane's coefficients in registers; G >= 128 (32 and 72 of them, next to 64 / 128
 // accumulators) reads them from a copy of the table in LDS where they are used.  Workgroups per CU
-// that the register counts admit: 8, 5, 4, 2 for G = 32, 64, 128, 256.
+// that the register counts admit: 8, 5, 4, 2 for G = 32, 64, 128, 256; 6 for G = 32 to NVFP4, which spills in the
+// registers of 8 or 7 (X [512, 8192] 6.4 us with 8 and with 7, 5.2 with 6).
+constexpr int butterfly_workgroups(int NJ, int FMT) {
+  return NJ == 1 ? (FMT == FMT_NVFP4 ? 6 : 8) : NJ == 2 ? 5 : NJ == 4 ? 4 : 2;
+}
 // ONCE: the input's loads with the non-temporal hint (ONE_PASS_BYTES).
 template <int NJ, int FMT, bool ONCE>
-__global__ void __launch_bounds__(256, NJ == 1 ? 8 : NJ == 2 ? 5 : NJ == 4 ? 4 : 2)
+__global__ void __launch_bounds__(256, butterfly_workgroups(NJ, FMT))
 rotate_butterfly_kernel(const uint4 *__restrict__ x, int64_t TG, const float *__restrict__ coef,
                         const uint4 *__restrict__ intra_hi_frag, const uint4 *__restrict__ intra_lo_frag,
                         uint2 *__restrict__ codes, uint8_t *__restrict__ scales, float *__restrict__ z_out,
@@ -183,9 +187,9 @@ rotate_butterfly_kernel(const uint4 *__restrict__ x, int64_t TG, const float *__
 #define TORQ_CF_FETCH(ROUND_)                                                                       \
   _Pragma("unroll") for (int j = 0; j < NJ; ++j) c[(ROUND_) & 1][j] = cf((ROUND_) * NJ + j);         \
   __builtin_amdgcn_sched_barrier(0);
-    // (MXINT4 and NVFP4 at G = 128 have no four registers to spare at 128 per lane: they fetch a round's
-    // coefficients where the round starts)
-    constexpr bool AHEAD = !(NJ == 4 && (FMT == FMT_MXINT4 || FMT == FMT_NVFP4));
+    // (NVFP4 at G = 128 has no four registers to spare at 128 per lane: it fetches a round's coefficients where the
+    // round starts)
+    constexpr bool AHEAD = !(NJ == 4 && FMT == FMT_NVFP4);
 #define TORQ_CF_ROUND(K_) if constexpr (AHEAD) { TORQ_CF_FETCH((K_) + 1) } else { TORQ_CF_FETCH(K_) }
     float c[2][NJ];
     if constexpr (AHEAD) { TORQ_CF_FETCH(0) }
@@ -233,20 +237,25 @@ rotate_butterfly_kernel(const uint4 *__restrict__ x, int64_t TG, const float *__
 #undef TORQ_CF_ROUND
 #undef TORQ_CF_FETCH
 
-    // ---- the rows' sigma, then step 4
+    // ---- the rows' sigma, then step 4.  Results go to a uniform base and a lane's 32-bit offset, the tile in the
+    // instruction (64-bit addresses of every tile, kept across the loop, are eight registers)
+    uint2 *const tg_codes = codes + tg * (2 * G);
+    uint8_t *const tg_scales = scales + tg * (FMT == FMT_NVFP4 ? 2 * G : G);
+    const uint32_t lane_block = (uint32_t)b0, lane_half = (uint32_t)(2 * b0 + h);
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
       const float rs = AHEAD ? c[(LJ + 5) & 1][j] : cf((LJ + 5) * NJ + j);
       float zz[16];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) zz[r] = v[j][r] * rs;
-      const int64_t blkidx = tg * G + 32 * j + b0;              // global block index
+      for (int r = 0; r < 16; ++r) zz[r] = v[j][r] * rs;         // (NVFP4 folds it into its own factors)
       if constexpr (FMT == FMT_NVFP4) {
-        const float amax = fmaxf(amax8(zz), amax8(zz + 8));
+        const float amax = fmaxf(amax8(v[j]), amax8(v[j] + 8)) * rs;     // rounding is monotone
         const uint32_t sc = nvfp4_scale_code(amax, 6.0f * global_scale);
         const float S = e4m3_to_f32(sc) * global_scale;
-        codes[blkidx * 2 + h] = make_uint2(pack8_nvfp4(zz, S), pack8_nvfp4(zz + 8, S));
-        scales[blkidx * 2 + h] = (uint8_t)sc;
+        uint32_t c2[2];
+        pack_nvfp4(v[j], rs, S, c2);
+        (tg_codes + 64 * j)[lane_half] = make_uint2(c2[0], c2[1]);
+        (tg_scales + 64 * j)[lane_half] = (uint8_t)sc;
       } else if constexpr (FMT != FMT_NONE) {
         float amax = fmaxf(amax8(zz), amax8(zz + 8));
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(amax), __float_as_uint(amax), false, false);
@@ -254,14 +263,14 @@ rotate_butterfly_kernel(const uint4 *__restrict__ x, int64_t TG, const float *__
         const uint32_t byte = e8m0_from_amax(amax);
         if constexpr (FMT == FMT_MXINT4) {
           const float inv = e8m0_inverse_f32(byte);
-          codes[blkidx * 2 + h] = make_uint2(pack8_int4(zz, inv), pack8_int4(zz + 8, inv));
+          (tg_codes + 64 * j)[lane_half] = make_uint2(pack8_int4(zz, inv), pack8_int4(zz + 8, inv));
         } else {
           const float sc = e8m0_to_f32(byte);
-          codes[blkidx * 2 + h] = make_uint2(pack8_e2m1(zz, sc), pack8_e2m1(zz + 8, sc));
+          (tg_codes + 64 * j)[lane_half] = make_uint2(pack8_e2m1(zz, sc), pack8_e2m1(zz + 8, sc));
         }
-        if (h == 0) scales[blkidx] = (uint8_t)byte;
+        if (h == 0) (tg_scales + 32 * j)[lane_block] = (uint8_t)byte;
       } else {
-        float4 *o = reinterpret_cast<float4 *>(z_out + blkidx * 32 + 16 * h);
+        float4 *o = reinterpret_cast<float4 *>(z_out + (tg * G + 32 * j + b0) * 32 + 16 * h);
 #pragma unroll
         for (int q = 0; q < 4; ++q) o[q] = make_float4(zz[4 * q], zz[4 * q + 1], zz[4 * q + 2], zz[4 * q + 3]);
       }
@@ -284,13 +293,13 @@ static hipError_t launch_nj(const torq_rotation *r, const void *x, int64_t TG, i
                             uint8_t *codes, uint8_t *scales, float *z_out, hipStream_t stream) {
   const size_t lds_bytes = 4 * (size_t)NJ * 32 * 64 + (NJ >= 4 ? (size_t)butterfly_coef_count(32 * NJ) * 32 * 4 : 0);
   // resident workgroups of 4 waves: what the kernel's register count (and LDS) admits per CU
-  int64_t grid = (NJ == 1 ? 8 : NJ == 2 ? 5 : NJ == 4 ? 4 : 2) * 256;
+  int64_t grid = butterfly_workgroups(NJ, z_out ? FMT_NONE : format) * 256;
   if (grid * 4 > TG) grid = (TG + 3) / 4;
   const uint4 *ih = reinterpret_cast<const uint4 *>(r->intra32_hi);
   const uint4 *il = reinterpret_cast<const uint4 *>(r->intra32_lo);
   const uint4 *xx = reinterpret_cast<const uint4 *>(x);
   uint2 *cc = reinterpret_cast<uint2 *>(codes);
-  // X [16384, 8192] to MXFP4, G = 32, 68.3 -> 62.1 us, to NVFP4, G = 128, 86.6 -> 84.4
+  // X [28672, 8192] to MXFP4, G = 32 / 64 / 128, 124 / 126 / 130 -> 110 / 113 / 117 us
   const bool once = (double)TG * (2048.0 * NJ) > ONE_PASS_BYTES;
   auto go = [&](auto kernel, float gs) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), lds_bytes, stream, xx, TG, r->butterfly, ih, il, cc, scales, z_out, gs);

@@ -287,7 +287,10 @@ rotate_kernel32(const uint4 *__restrict__ x, int64_t TG, int G,
           const uint32_t sc = nvfp4_scale_code(amax, 6.0f * global_scale);
           const float S = e4m3_to_f32(sc) * global_scale;
           if (live) {
-            codes[blkidx * 2 + h] = make_uint2(pack8_nvfp4(zz, S), pack8_nvfp4(zz + 8, S));
+            uint32_t c0[1], c1[1];
+            pack_nvfp4(zz, 1.0f, S, c0);
+            pack_nvfp4(zz + 8, 1.0f, S, c1);
+            codes[blkidx * 2 + h] = make_uint2(c0[0], c1[0]);
             scales[blkidx * 2 + h] = (uint8_t)sc;
           }
         } else if constexpr (FMT != FMT_NONE) {
@@ -524,7 +527,10 @@ rotate_ring_kernel32(const uint4 *__restrict__ x, int64_t TG, int G,
         const float amax = fmaxf(amax8(zz), amax8(zz + 8));
         byte = nvfp4_scale_code(amax, 6.0f * global_scale);
         const float S = e4m3_to_f32(byte) * global_scale;
-        c = u32x2{pack8_nvfp4(zz, S), pack8_nvfp4(zz + 8, S)};
+        uint32_t c0[1], c1[1];
+        pack_nvfp4(zz, 1.0f, S, c0);
+        pack_nvfp4(zz + 8, 1.0f, S, c1);
+        c = u32x2{c0[0], c1[0]};
       } else {
         float amax = fmaxf(amax8(zz), amax8(zz + 8));
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(amax), __float_as_uint(amax), false, false);

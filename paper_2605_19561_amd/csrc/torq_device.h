@@ -189,44 +189,67 @@ __device__ __forceinline__ float e4m3_to_f32(uint32_t code) {     // code <= 0x7
                      : (float)code * 0.001953125f;
 }
 // NVFP4's block scale: the E4M3 code of amax / (6 * tensor scale), an IEEE division by definition.  As in
-// pack8_nvfp4 below the division is carried out only where it can matter: the conversion is monotone, so
-// where both ends of a bracket around the quotient convert to the same code the quotient does too.
+// pack_nvfp4 below the division is carried out only where it can matter: the conversion is monotone, so
+// where both ends of a bracket around the quotient convert to the same code the quotient does too.  The hardware converts
+// both at once (e4m3_from_f32 up to 448, where that saturates; a NaN amax saturates too).
 __device__ __forceinline__ uint32_t nvfp4_scale_code(float amax, float six_gs) {
   if (six_gs >= 0x1p-100f && six_gs <= 0x1p100f) {
     const float t = amax * __builtin_amdgcn_rcpf(six_gs);
-    const uint32_t lo = e4m3_from_f32(t * 0.99999904632568359375f), hi = e4m3_from_f32(t * 1.00000095367431640625f);
-    if (lo == hi) return lo;
+    const uint32_t c = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(fminf(t * 0.99999904632568359375f, 448.0f),
+                                                                 fminf(t * 1.00000095367431640625f, 448.0f), 0, false);
+    const uint32_t lo = c & 255u;
+    if (lo == (c >> 8)) return lo;
   }
   return e4m3_from_f32(__fdiv_rn(amax, six_gs));
 }
 
-// NVFP4: eight values of a block with effective scale S = e4m3 value * tensor scale.  IEEE
-// division, then the e2m1 rounding of pack8_e2m1; a block whose scale rounded to zero keeps signs.
-// The division is only carried out where it can matter.  With r = 1 / S to one ulp, z r (1 - 2^-20) and
-// z r (1 + 2^-20), rounded wherever they are (within 2^-22 in all, relative), enclose the IEEE quotient q in magnitude; the
-// e2m1 rounding is monotone, so where both ends round to the same code it is q's.  Otherwise (a
-// quotient within 2^-20 of a rounding boundary, ties among them: a few
-// values in a million) the lane divides.  S outside [2^-100, 2^100]: always divides.
-// Two products and two halves of a conversion per value: with z r itself converted as well and the ends taken
-// from it, three of each, the butterfly rotation to NVFP4 (bound by its vector instructions) took 25.8 us at
-// X [4096, 8192], this way 24.4.
-__device__ __forceinline__ uint32_t pack8_nvfp4(const float z[8], float S) {
-  float a[8];
-  if (S >= 0x1p-100f && S <= 0x1p100f) {
+// NVFP4: 8 N values z[i] = v[i] f (rounded to fp32; f in (0, 1]) of a block with effective scale S = e4m3 value * tensor
+// scale.  IEEE division, then the e2m1 rounding of pack8_e2m1; a block whose scale rounded to zero keeps signs.
+// The division is only carried out where it can matter.  With r = 1 / S to one ulp, v (r (1 - 2^-20) f) and
+// v (r (1 + 2^-20) f), rounded wherever they are (z, r, three products and the quotient: 7 * 2^-24 in all, relative), enclose
+// the IEEE quotient q = z / S in magnitude; the e2m1 rounding is monotone, so where both ends round to the same code it is
+// q's.  Otherwise (a quotient within 2^-20 of a rounding boundary, ties among them: a few values in a million) the lane
+// divides.  S outside [2^-100, 2^100] or f below 2^-20: always divides.
+// Two products and two halves of a conversion per value and none for z itself, which only a division needs: the butterfly
+// rotation to NVFP4 (bound by its vector instructions), X [4096, 8192],
+// 24.4 -> 23.4 us at G = 128, 25.8 -> 22.1 at G = 32, 11.6 -> 10.9 for X [512, 8192] at G = 256.
+template <int N>
+__device__ __forceinline__ void pack_nvfp4(const float *v, float f, float S, uint32_t (&c)[N]) {
+  float a[8 * N];
+  if (S >= 0x1p-100f && S <= 0x1p100f && f >= 0x1p-20f) {
     const float r = __builtin_amdgcn_rcpf(S);
-    const float r_lo = r * 0.99999904632568359375f, r_hi = r * 1.00000095367431640625f;      // 1 -+ 2^-20
-    float hi[8];
+    const float r_lo = r * 0.99999904632568359375f * f, r_hi = r * 1.00000095367431640625f * f;      // 1 -+ 2^-20
+    uint32_t differ = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      a[i] = z[i] * r_lo;
-      hi[i] = z[i] * r_hi;
+    for (int n = 0; n < N; ++n) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) a[i] = v[8 * n + i] * r_lo;
+      c[n] = pack8_e2m1(a, 1.0f);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) a[i] = v[8 * n + i] * r_hi;
+      differ |= c[n] ^ pack8_e2m1(a, 1.0f);
     }
-    const uint32_t c = pack8_e2m1(a, 1.0f);
-    if (c == pack8_e2m1(hi, 1.0f)) return c;
+    if (differ == 0) return;
   }
+  // (rarely reached: a value at a time, so that it does not ask for registers the way above has no use for)
+  const float by = S > 0.0f ? S : 1.0f;
+  auto divide = [&](float value) {
+    const float z = __fmul_rn(value, f), q = __fdiv_rn(z, by);
+    __builtin_amdgcn_sched_barrier(0);
+    return S > 0.0f ? q : copysignf(0.0f, z);
+  };
 #pragma unroll
-  for (int i = 0; i < 8; ++i) a[i] = (S > 0.0f) ? __fdiv_rn(z[i], S) : copysignf(0.0f, z[i]);
-  return pack8_e2m1(a, 1.0f);
+  for (int n = 0; n < N; ++n) {
+    uint32_t r = 0;
+#define TORQ_DIVIDE_PAIR(I_)                                                                                         \
+  {                                                                                                                  \
+    const float q0 = divide(v[8 * n + 2 * I_]), q1 = divide(v[8 * n + 2 * I_ + 1]);                                   \
+    r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, q0, q1, 1.0f, I_);                                                \
+  }
+    TORQ_DIVIDE_PAIR(0) TORQ_DIVIDE_PAIR(1) TORQ_DIVIDE_PAIR(2) TORQ_DIVIDE_PAIR(3)
+#undef TORQ_DIVIDE_PAIR
+    c[n] = r;
+  }
 }
 
 // bf16 <-> fp32 bit moves

@@ -1328,6 +1328,23 @@ def test_butterfly_of_inputs_read_past_the_cache(tq, G):
     rot.close()
 
 
+# NVFP4 out of the butterfly divides only next to a rounding boundary and folds the row's factor into its own (below 2^-20,
+# tangents of 40 and more, it always divides): the codes are those of the rotated values
+@pytest.mark.parametrize("top", [1.0, 40.0])
+@pytest.mark.parametrize("G", [32, 64, 128, 256])
+def test_butterfly_nvfp4_is_the_division_of_the_rotated_values(tq, G, top):
+    M, d = 2049, 8192
+    x = synth.activations(M, d, outliers=40, outlier_scale=50.0, seed=G + 1, device=DEV)
+    x[::7, : 32 * G] = 0                                                # blocks whose scale is zero
+    T = np.random.default_rng(G).uniform(-top, top, size=(G.bit_length() - 1, G // 2)).astype(np.float32)
+    rot = tq.ButterflyRotation(d, G, T, synth.rotations(G, seed=82 + G)[1])
+    z = tq.torq_rotate(rot, x)
+    for gs in (0.05, 1e-30, 1e-36):                                     # the last: scales that divide for every value
+        want, got = tq.torq_quantize_f32_fmt(z, tq.TORQ_FMT_NVFP4, gs), tq.torq_rotate_quantize_fmt(rot, x, tq.TORQ_FMT_NVFP4, gs)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), gs
+    rot.close()
+
+
 def test_butterfly_identity_and_empty(tq, oracle):
     # all tangents 0 and R_intra = I: the kernel hands x through exactly
     M, d, G = 11, 4096, 64
