@@ -215,11 +215,11 @@ __device__ __forceinline__ uint32_t nvfp4_scale_code(float amax, float six_gs) {
 // 24.4 -> 23.4 us at G = 128, 25.8 -> 22.1 at G = 32, 11.6 -> 10.9 for X [512, 8192] at G = 256.
 template <int N>
 __device__ __forceinline__ void pack_nvfp4(const float *v, float f, float S, uint32_t (&c)[N]) {
-  float a[8 * N];
   if (S >= 0x1p-100f && S <= 0x1p100f && f >= 0x1p-20f) {
     const float r = __builtin_amdgcn_rcpf(S);
     const float r_lo = r * 0.99999904632568359375f * f, r_hi = r * 1.00000095367431640625f * f;      // 1 -+ 2^-20
     uint32_t differ = 0;
+    float a[8];
 #pragma unroll
     for (int n = 0; n < N; ++n) {
 #pragma unroll
@@ -231,12 +231,19 @@ __device__ __forceinline__ void pack_nvfp4(const float *v, float f, float S, uin
     }
     if (differ == 0) return;
   }
+  if (!(S > 0.0f)) {                       // (also where a tile has no block row: not the way of the divisions)
+    float a[8 * N];
+#pragma unroll
+    for (int i = 0; i < 8 * N; ++i) a[i] = copysignf(0.0f, v[i]);
+#pragma unroll
+    for (int n = 0; n < N; ++n) c[n] = pack8_e2m1(a + 8 * n, 1.0f);
+    return;
+  }
   // (rarely reached: a value at a time, so that it does not ask for registers the way above has no use for)
-  const float by = S > 0.0f ? S : 1.0f;
   auto divide = [&](float value) {
-    const float z = __fmul_rn(value, f), q = __fdiv_rn(z, by);
+    const float q = __fdiv_rn(__fmul_rn(value, f), S);
     __builtin_amdgcn_sched_barrier(0);
-    return S > 0.0f ? q : copysignf(0.0f, z);
+    return q;
   };
 #pragma unroll
   for (int n = 0; n < N; ++n) {
