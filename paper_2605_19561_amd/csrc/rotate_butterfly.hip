@@ -78,8 +78,8 @@ __device__ __forceinline__ float swizzle_f32(float v) {
 //   entry (log2 G) NJ + j:                      the row's final sigma
 // G <= 64 keeps the lane's coefficients in registers; G >= 128 (32 and 72 of them, next to 64 / 128
 // accumulators) reads them from a copy of the table in LDS where they are used.  Workgroups per CU
-// that the register counts admit: 8, 5, 4, 2 for G = 32, 64, 128, 256; 6 for G = 32 to NVFP4, which spills in the
-// registers of 8 or 7 (X [512, 8192] 6.4 us with 8 and with 7, 5.2 with 6).
+// that the register counts admit: 8, 5, 4, 2 for G = 32, 64, 128, 256.  G = 32 to NVFP4 runs on 6 (8 fit): X [2048, 5120] 8.9 us
+// against 10.1, [4000, 7168] 19.2 / 21.3, [4096, 8192] 21.8 / 23.0, [512, 8192] the same.
 constexpr int butterfly_workgroups(int NJ, int FMT) {
   return NJ == 1 ? (FMT == FMT_NVFP4 ? 6 : 8) : NJ == 2 ? 5 : NJ == 4 ? 4 : 2;
 }

@@ -1314,6 +1314,20 @@ def test_butterfly_rotate_quantize_against_oracle(tq, oracle, M, d, G):
     rot.close()
 
 
+# past 96 MiB of input the dense rotation's ring carries the non-temporal hint: bit for bit the two halves, which go without
+@pytest.mark.parametrize("G", [80, 96, 112, 128])
+def test_rotation_of_inputs_read_past_the_cache(tq, G):
+    d = 64 * G
+    M = 96 * 2 ** 20 // (2 * d) + 3
+    x = synth.activations(M, d, outliers=40, outlier_scale=50.0, seed=G, device=DEV)
+    rot = tq.Rotation(d, G, *synth.rotations(G, seed=83 + G))
+    for fmt in (tq.TORQ_FMT_MXFP4, tq.TORQ_FMT_MXINT4, tq.TORQ_FMT_NVFP4):
+        whole = tq.torq_rotate_quantize_fmt(rot, x, fmt, 0.05)
+        halves = [tq.torq_rotate_quantize_fmt(rot, part.contiguous(), fmt, 0.05) for part in (x[:M // 2], x[M // 2:])]
+        assert all(torch.equal(w, torch.cat(h)) for w, h in zip(whole, zip(*halves))), fmt
+    rot.close()
+
+
 # past 96 MiB of input the loads carry the non-temporal hint: bit for bit the two halves, which go without
 @pytest.mark.parametrize("G", [32, 64, 128, 256])
 def test_butterfly_of_inputs_read_past_the_cache(tq, G):
