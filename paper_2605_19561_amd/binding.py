@@ -6,7 +6,9 @@ stream, every step of the path runs in the library's kernels.  There is no CPU
 fallback: a missing library or a failing call raises.
 """
 import ctypes as C
+import importlib
 import os
+import warnings
 
 import torch  # loads the HIP runtime that libtorq.so binds to
 
@@ -169,19 +171,31 @@ def _dev(t: torch.Tensor, dtype, what):
     raise ValueError(f"{what}: expected a contiguous {dtype} device tensor")
 
 
+class _Interpreted:
+    """In the place of the C++ module where there is none for this interpreter and torch: it takes no call."""
+    linear = rotate_quantize = gram = histogram = staticmethod(lambda *args: None)
+
+
 _host = None
 
 
 def _native():
-    """The C++ module that marshals the calls made again and again (csrc/host_calls.cpp)."""
+    """The C++ module that marshals the calls made again and again (csrc/host_calls.cpp).  It is a faster way to the same entry
+    points of libtorq.so, not needed for any of them: where it cannot be loaded, or was built against another torch, the
+    functions below go through their arguments themselves."""
     global _host
     if _host is None:
         L = lib()
         try:
-            from . import _host as module
+            module = importlib.import_module(__package__ + "._host")
+            built = getattr(module, "torch_version", None)
         except ImportError as e:
-            raise FileNotFoundError("paper_2605_19561_amd/_host.so is missing or not built for this interpreter: build it with "
-                                    "`python -m paper_2605_19561_amd.build`") from e
+            module, built = None, e
+        if module is None or built != torch.__version__:
+            warnings.warn(f"paper_2605_19561_amd._host, which saves 5 us of the host a call, is not there for this interpreter and "
+                          f"torch ({built}): build it with `python -m paper_2605_19561_amd.build`", RuntimeWarning, stacklevel=3)
+            _host = _Interpreted
+            return _host
         names = ["torq_linear", "torq_linear_workspace_bytes_n", "torq_rotate_quantize", "torq_rotate_quantize_fmt",
                  "torq_block_gram", "torq_block_gram_positions", "torq_block_gram_workspace_bytes", "torq_code_histogram",
                  "torq_code_histogram_workspace_bytes"]

@@ -1,15 +1,17 @@
-"""Compile libtorq.so (HIP kernels + C ABI) for gfx950 with hipcc, and the binding's C++ module _host.so with g++.
+"""Compile libtorq.so (HIP kernels + C ABI) for gfx950 with hipcc, and the binding's C++ module _host with g++.
 
 `python -m paper_2605_19561_amd.build` or `build()`.  The library is built in-tree
 (paper_2605_19561_amd/libtorq.so) so that it travels with the source tree.
 """
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtorq.so")
-HOST_LIB = os.path.join(HERE, "_host.so")      # the module paper_2605_19561_amd._host
+# the module paper_2605_19561_amd._host, under the name that only this interpreter looks for
+HOST_LIB = os.path.join(HERE, "_host" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["api.hip", "quantize.hip", "rotate_quant.hip", "rotate_butterfly.hip", "mxfp4_gemm.hip", "mxfp4_gemm_ring.hip",
            "mxfp4_gemm_skinny.hip", "mxfp4_gemm_stream.hip", "block_gram.hip", "code_histogram.hip",
            "intra_calib.hip", "diag.hip"]
@@ -42,10 +44,10 @@ def device_asm(source: str, out_path: str) -> str:
 
 def host_command() -> list:
     """The compiler's command for the binding's C++ module (host code only, against torch's own headers)."""
-    import sysconfig
     import torch
     root = os.path.dirname(os.path.abspath(torch.__file__))
     return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+            '-DTORQ_TORCH_VERSION="%s"' % torch.__version__,
             "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
             "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"), "-Wall",
             os.path.join(CSRC, "host_calls.cpp"), "-o", HOST_LIB, "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]

@@ -265,5 +265,8 @@ PyMODINIT_FUNC PyInit__host() {
   s_value = PyUnicode_InternFromString("value");
   s_d = PyUnicode_InternFromString("d");
   if (!s_handle || !s_value || !s_d) return nullptr;
-  return PyModule_Create(&module);
+  PyObject *m = PyModule_Create(&module);
+  // (binding.py binds no module built against another torch)
+  if (m && PyModule_AddStringConstant(m, "torch_version", TORQ_TORCH_VERSION) != 0) Py_CLEAR(m);
+  return m;
 }

@@ -3,11 +3,14 @@ declares, and rejects bad arguments before touching a device."""
 import ctypes as C
 import os
 import re
+import sys
+import types
 
 import numpy as np
 import pytest
+import torch
 
-from paper_2605_19561_amd import binding
+from paper_2605_19561_amd import binding, build
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -302,3 +305,32 @@ def test_bench_refuses_more_than_one_gpu():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     p = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert p.returncode != 0 and "ONE GPU" in (p.stdout + p.stderr)
+
+
+# ---- the binding's C++ module saves time on the host and is needed for nothing: without it, and with one built against another
+# torch, a call goes through its arguments in Python (here as far as the refusal of a host tensor)
+@pytest.mark.parametrize("why", ["missing", "another torch", "no version"])
+def test_calls_do_without_the_native_module(monkeypatch, why):
+    module = types.SimpleNamespace(torch_version="1.0") if why == "another torch" else types.SimpleNamespace()
+    monkeypatch.setitem(sys.modules, binding.__package__ + "._host", None if why == "missing" else module)
+    monkeypatch.setattr(binding, "_host", None)
+    monkeypatch.delattr(sys.modules[binding.__package__], "_host", raising=False)
+    x = torch.zeros((4, 4096), dtype=torch.bfloat16)
+    codes = torch.zeros((4, 2048), dtype=torch.uint8)
+    rot = types.SimpleNamespace(d=4096, G=128, handle=None)
+    with pytest.warns(RuntimeWarning, match="_host"):
+        with pytest.raises(ValueError, match="x: expected a contiguous"):
+            binding.torq_block_gram(x, 128)
+    for call in (lambda: binding.torq_block_gram_positions(x, 128), lambda: binding.torq_code_histogram(codes, 4096),
+                 lambda: binding.torq_rotate_quantize(rot, x), lambda: binding.torq_rotate_quantize_fmt(rot, x, 1),
+                 lambda: binding.torq_linear(rot, x, codes, torch.zeros((4, 128), dtype=torch.uint8))):
+        with pytest.raises(ValueError, match="expected a contiguous"):
+            call()
+
+
+def test_the_native_module_is_built_for_this_interpreter_and_torch(monkeypatch):
+    if not os.path.exists(build.HOST_LIB):
+        build.build()
+    monkeypatch.setattr(binding, "_host", None)
+    module = binding._native()
+    assert module.__file__ == build.HOST_LIB and module.torch_version == torch.__version__
