@@ -114,6 +114,8 @@ PyObject *plain_or_none(F &&f) {
   try {
     return f();
   } catch (...) {
+    // (an interrupt that arrived while the interpreter was asked for something says nothing about the arguments)
+    if (PyErr_Occurred() && !PyErr_ExceptionMatches(PyExc_Exception)) return nullptr;
     PyErr_Clear();
     Py_RETURN_NONE;
   }

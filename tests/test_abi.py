@@ -334,3 +334,26 @@ def test_the_native_module_is_built_for_this_interpreter_and_torch(monkeypatch):
     monkeypatch.setattr(binding, "_host", None)
     module = binding._native()
     assert module.__file__ == build.HOST_LIB and module.torch_version == torch.__version__
+
+
+# an interrupt that arrives while the native module asks the interpreter for something is the caller's
+@pytest.mark.parametrize("name", ["linear", "rotate"])
+def test_an_interrupt_in_a_native_call_is_not_lost(monkeypatch, name):
+    monkeypatch.setattr(binding, "_host", None)
+
+    class Handle:
+        handle, G, asked = None, 128, 0
+
+        @property
+        def d(self):
+            self.asked += 1
+            if self.asked == 1:
+                raise KeyboardInterrupt
+            return 4096
+
+    x, w = torch.zeros((4, 4096), dtype=torch.bfloat16), torch.zeros((4, 2048), dtype=torch.uint8)
+    with pytest.raises(KeyboardInterrupt):
+        if name == "linear":
+            binding.torq_linear(Handle(), x, w, torch.zeros((4, 128), dtype=torch.uint8))
+        else:
+            binding.torq_rotate_quantize(Handle(), x)
