@@ -363,7 +363,8 @@ __device__ __forceinline__ void lds_wait4(i16x4 &a, i16x4 &b, i16x4 &c, i16x4 &d
 }
 typedef __attribute__((__vector_size__(2 * sizeof(unsigned)))) unsigned u32x2;
 
-template <int KS16, int FMT, int SKIP = 0>
+// ONCE: the input's loads with the non-temporal hint (ONE_PASS_BYTES): [28672, 8192] to MXFP4 159.8 -> 157.0 us (matrix cores and HBM).
+template <int KS16, int FMT, int SKIP = 0, bool ONCE = false>
 __global__ void __launch_bounds__(64 * ((KS16 + 1) / 2), 3)
 rotate_ring_kernel32(const uint4 *__restrict__ x, int64_t TG, int G,
                      const uint16_t *__restrict__ inter_hi, const uint16_t *__restrict__ inter_lo,
@@ -424,11 +425,8 @@ rotate_ring_kernel32(const uint4 *__restrict__ x, int64_t TG, int G,
       const uint64_t base = reinterpret_cast<uint64_t>(x) + (uint64_t)((ok ? tg : 0) * (int64_t)TG_BYTES);
       const i32x4 rs = i32x4{(int)(uint32_t)base, (int)((uint32_t)(base >> 32) & 0xFFFFu), ok ? TG_BYTES : 0, 0x00020000};
       const uint32_t la = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)(dst) + j * TG_STRIDE + wave_u * 64 * 16;
-      // (plain loads: with the non-temporal hint, inputs of 100 to 300 MB, us without / with it, three ways of use: from HBM
-      // G = 80 38.8 / 40.4 to 102.5 / 103.6, G = 128 40.2 / 40.4 to 110.3 / 107.0; one input again 38.4 / 39.3, 50.6 / 52.0; just
-      // written, with the writing, 68.5 / 70.0, 84.7 / 86.4.  Only 512 MB from HBM gain 2 %.)
 #pragma unroll
-      for (int i = 0; i < CH; ++i) load_to_lds16(rs, la + i * NTHR * 16, tid * 16, i * NTHR * 16);
+      for (int i = 0; i < CH; ++i) load_to_lds16<true, ONCE>(rs, la + i * NTHR * 16, tid * 16, i * NTHR * 16);
     }
   };
 
@@ -666,9 +664,13 @@ static hipError_t launch_ring32(const torq_rotation *r, const void *x, int64_t T
   const int64_t grid = balanced_grid(nbatch, KS16 == 5 ? 4 : 3);
   const uint4 *ih = reinterpret_cast<const uint4 *>(r->intra32_hi);
   const uint4 *il = reinterpret_cast<const uint4 *>(r->intra32_lo);
-#define TORQ_RING_LAUNCH(FMT_, GS_)                                                                                  \
-  hipLaunchKernelGGL((rotate_ring_kernel32<KS16, FMT_>), dim3((unsigned)grid), dim3(64 * nw), 0, stream,               \
-                     reinterpret_cast<const uint4 *>(x), TG, r->G, r->inter32f_hi, r->inter32f_lo, ih, il, codes, scales, GS_)
+  const bool once = (double)TG * (1024.0 * KS16) > ONE_PASS_BYTES;
+  auto go = [&](auto kernel, float gs) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * nw), 0, stream, reinterpret_cast<const uint4 *>(x), TG, r->G,
+                       r->inter32f_hi, r->inter32f_lo, ih, il, codes, scales, gs);
+  };
+#define TORQ_RING_LAUNCH(FMT_, GS_) \
+  once ? go(rotate_ring_kernel32<KS16, FMT_, 0, true>, GS_) : go(rotate_ring_kernel32<KS16, FMT_>, GS_)
   switch (format) {
     case FMT_MXFP4: TORQ_RING_LAUNCH(FMT_MXFP4, 1.0f); break;
     case FMT_MXINT4: TORQ_RING_LAUNCH(FMT_MXINT4, 1.0f); break;

@@ -1314,7 +1314,7 @@ def test_butterfly_rotate_quantize_against_oracle(tq, oracle, M, d, G):
     rot.close()
 
 
-# an input of which the Infinity Cache holds two at most: bit for bit its two halves
+# past 96 MiB of input the dense rotation's ring carries the non-temporal hint: bit for bit the two halves, which go without
 @pytest.mark.parametrize("G", [80, 96, 112, 128])
 def test_rotation_of_inputs_read_past_the_cache(tq, G):
     d = 64 * G

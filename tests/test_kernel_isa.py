@@ -45,7 +45,6 @@ def test_every_ring_instantiation_is_there(ring_kernels):
     for ks16 in (5, 6, 7, 8):
         for fmt in (0, 1, 2):
             assert any(f"ILi{ks16}ELi{fmt}ELi0E" in k for k in kernels), (ks16, fmt)
-    assert len(kernels) == 12 + 7
 
 
 def test_ring_loop_holds_exactly_the_counted_memory_instructions(ring_kernels):
