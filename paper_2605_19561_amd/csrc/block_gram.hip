@@ -67,7 +67,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t gram_rsrc(const void *p, uint3
 // A token-group past the end reads as zeros through the buffer's range check and adds nothing.  The
 // workgroup's waves add their tiles at the end: 256 partial results instead of the 512 of the form that
 // shares each token-group.  X [16384, 8192], G = 128: this kernel 51 us against 64 (5.2 TB/s, the rate of a copy).
-// ONCE: loads with the non-temporal hint (ONE_PASS_BYTES), X [16384, 8192] 55.4 -> 50.5 us with the reduction.
+// ONCE: loads with the non-temporal hint (ONE_PASS_INPUT_BYTES), X [16384, 8192] 55.4 -> 50.5 us with the reduction.
 template <int NT, bool ONCE>
 __global__ void __launch_bounds__(64 * GRAM_WAVES)
 block_gram_kernel(const uint4 *__restrict__ x, int64_t TG, f32x4 *__restrict__ partial) {
@@ -509,7 +509,7 @@ static hipError_t launch_sigma(const uint4 *x, int64_t TG, double *Sigma, void *
         return hipSuccess;
       };
       static std::atomic<uint64_t> raised[2];
-      const hipError_t e = (double)TG * (1024.0 * NT) > ONE_PASS_BYTES ? go(block_gram_kernel<NT, true>, raised[1])
+      const hipError_t e = (double)TG * (1024.0 * NT) > ONE_PASS_INPUT_BYTES ? go(block_gram_kernel<NT, true>, raised[1])
                                                                        : go(block_gram_kernel<NT, false>, raised[0]);
       if (e != hipSuccess) return e;
       return launch_reduce<f32x4, 16>(partial, GRAM_MAX_WG, NT, 1, TG, Sigma, stream);

@@ -22,7 +22,11 @@
 // not hidden by anything, so it is kept short.  An earlier form widened the nibbles into byte counters after
 // 15 blocks and added the lanes through LDS: 14.7 us for the
 // call at 2^21 blocks (codes of [8192, 8192]), 7.5 us at 512; this one 11.8 us and 5.6 us.  The loads carry the non-temporal
-// hint: 11.8 -> 11.4 us there, 2^23 blocks 28.8 -> 26.5, 2^20 9.2 -> 8.6.
+// hint at any size, us without / with it: from HBM 2^21 blocks 12.7 / 12.3, 2^23 29.8 / 27.5, 2^25 97.0 / 83.7, 31000 6.65 / 6.0; one
+// input again the same up to 2^21 and 18.2 / 16.0 at 2^22; codes that the rotation has just packed, with the rotation, 17.6 /
+// 16.9 at 2^18, 61.9 / 63.1 (a run's spread is 6) at 2^21, and of eight inputs rotated one after the other and counted then, a
+// pair, 63.6 / 61.9 at 2^21 and 109.3 / 107.6 at 2^22 (codes that a plain element-wise kernel has
+// just written, with it, 17.0 / 18.3 at 2^20, 37.8 / 39.2 at 2^22, 124 / 121 at 2^24).
 #include "torq_device.h"
 #include "torq_internal.h"
 

@@ -665,7 +665,7 @@ __device__ __forceinline__ void lines_wait() {
   asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
 }
 
-// ONCE: the weights' codes with the non-temporal hint (ONE_PASS_BYTES), [16, 28672] x 8192 24.2 -> 22.0 us.
+// ONCE: the weights' codes with the non-temporal hint (ONE_PASS_WEIGHT_BYTES), [16, 28672] x 8192 24.2 -> 22.0 us.
 template <int MT, int NS, int R, bool ONCE>
 __device__ __forceinline__ void
 gemm_lines(const uint8_t *__restrict__ A_q, const uint8_t *__restrict__ A_s, const uint8_t *__restrict__ W_q,
@@ -863,7 +863,7 @@ static hipError_t launch_lines(const uint8_t *A_q, const uint8_t *A_s, const uin
   static std::atomic<uint64_t> raised[2];
   // (one strip a workgroup, at most 4096 rows, would be as much from d = 46000 on: no layer here)
   if constexpr (NS >= 2)
-    if ((double)N * (double)d * 0.53125 > ONE_PASS_BYTES) return go(mxfp4_gemm_lines_once_kernel<MT, NS, R>, raised[1]);
+    if ((double)N * (double)d * 0.53125 > ONE_PASS_WEIGHT_BYTES) return go(mxfp4_gemm_lines_once_kernel<MT, NS, R>, raised[1]);
   return go(mxfp4_gemm_lines_kernel<MT, NS, R>, raised[0]);
 }
 

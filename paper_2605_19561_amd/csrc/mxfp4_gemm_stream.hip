@@ -44,7 +44,7 @@ size_t stream_lds_bytes(int MT, int PT, int R, int d) {
 
 // What a wave of the two kernels below works with.  AT: how many activation tiles come through the ring ahead of the strips
 // (the "strips" 0 ... AT - 1 of a workgroup; its weight strips follow).
-// ONCE: the weights' codes with the non-temporal hint (ONE_PASS_BYTES; the activations come from the L2 in every workgroup and
+// ONCE: the weights' codes with the non-temporal hint (ONE_PASS_WEIGHT_BYTES; the activations come from the L2 in every workgroup and
 // go without: with it [64, 8192] x 20480 23.4 -> 24.5 us).
 // LDS from `mem` on: [rings | buffers of scale rows | two buffers of partial tiles]
 template <int MT, int PT, int R, int AT, bool ONCE>
@@ -379,7 +379,7 @@ static hipError_t launch_cfg(const uint8_t *A_q, const uint8_t *A_s, const uint8
 //       [64, 5120] x 16384 13.8 / 13.0, [64, 7168] x 28672 26.0 / 26.2, [64, 2560] x 28672 11.8 / 12.8, the tiles keep theirs
 bool mxfp4_gemm_stream_takes(int64_t M, int64_t N, int d) {
   if (d % 512 != 0 || d < 2560 || d > 8192 || N > (1 << 30)) return false;
-  if (M < 8) return (double)N * (double)d * 0.53125 > ONE_PASS_BYTES;
+  if (M < 8) return (double)N * (double)d * 0.53125 > ONE_PASS_WEIGHT_BYTES;
   if (M > 64) return false;
   const int64_t strips = (N + 15) / 16;
   if (M <= 16) return strips > 1600;
@@ -395,7 +395,7 @@ int mxfp4_gemm_stream_strips(int d) { return stream_scale_buffers((d / 256 + WAV
 hipError_t launch_mxfp4_gemm_stream(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W_q, const uint8_t *W_s, void *out,
                                     int64_t M, int64_t N, int d, hipStream_t stream) {
   const int MT = (int)((M + 15) / 16), PT = (d / 256 + WAVES - 1) / WAVES;
-  const bool once = (double)N * (double)d * 0.53125 > ONE_PASS_BYTES;
+  const bool once = (double)N * (double)d * 0.53125 > ONE_PASS_WEIGHT_BYTES;
 #define TORQ_STREAM(MT_, PT_)                                                                                                   \
   if (MT == MT_ && PT == PT_)                                                                                                  \
     return once ? launch_cfg<MT_, PT_, STREAM_RING, true>(A_q, A_s, W_q, W_s, out, M, N, d, stream)                            \

@@ -83,7 +83,7 @@ __device__ __forceinline__ float swizzle_f32(float v) {
 constexpr int butterfly_workgroups(int NJ, int FMT) {
   return NJ == 1 ? (FMT == FMT_NVFP4 ? 6 : 8) : NJ == 2 ? 5 : NJ == 4 ? 4 : 2;
 }
-// ONCE: the input's loads with the non-temporal hint (ONE_PASS_BYTES).
+// ONCE: the input's loads with the non-temporal hint (ONE_PASS_INPUT_BYTES).
 template <int NJ, int FMT, bool ONCE>
 __global__ void __launch_bounds__(256, butterfly_workgroups(NJ, FMT))
 rotate_butterfly_kernel(const uint4 *__restrict__ x, int64_t TG, const float *__restrict__ coef,
@@ -300,7 +300,7 @@ static hipError_t launch_nj(const torq_rotation *r, const void *x, int64_t TG, i
   const uint4 *xx = reinterpret_cast<const uint4 *>(x);
   uint2 *cc = reinterpret_cast<uint2 *>(codes);
   // X [28672, 8192] to MXFP4, G = 32 / 64 / 128, 124 / 126 / 130 -> 110 / 113 / 117 us
-  const bool once = (double)TG * (2048.0 * NJ) > ONE_PASS_BYTES;
+  const bool once = (double)TG * (2048.0 * NJ) > ONE_PASS_INPUT_BYTES;
   auto go = [&](auto kernel, float gs) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), lds_bytes, stream, xx, TG, r->butterfly, ih, il, cc, scales, z_out, gs);
   };

@@ -351,7 +351,7 @@ rotate_kernel32(const uint4 *__restrict__ x, int64_t TG, int G,
 // SKIP (diagnostic builds only, torq_diag_rotate_ablation): work left out to measure what it costs --
 // 1: the R_inter low-part pass, 2: the hi/lo split of Y on the vector ALU (raw register pairs are fed
 // instead), 4: the amax and the conversion of step 4 (bit patterns are stored instead), 8: two of the
-// three R_intra passes.  The output is then meaningless.  SKIP = 0 is the product.
+// three R_intra passes.  The output is then meaningless.  SKIP = 0 is the product (up to ONE_PASS_INPUT_BYTES of input).
 template <int OFF>
 __device__ __forceinline__ i16x4 lds_tr_read(uint32_t addr) {
   i16x4 v;
@@ -363,7 +363,7 @@ __device__ __forceinline__ void lds_wait4(i16x4 &a, i16x4 &b, i16x4 &c, i16x4 &d
 }
 typedef __attribute__((__vector_size__(2 * sizeof(unsigned)))) unsigned u32x2;
 
-// ONCE: the input's loads with the non-temporal hint (ONE_PASS_BYTES): [28672, 8192] to MXFP4 159.8 -> 157.0 us (matrix cores and HBM).
+// ONCE: the input's loads with the non-temporal hint (ONE_PASS_INPUT_BYTES), 1 - 2 % there: bound by matrix cores and HBM together.
 template <int KS16, int FMT, int SKIP = 0, bool ONCE = false>
 __global__ void __launch_bounds__(64 * ((KS16 + 1) / 2), 3)
 rotate_ring_kernel32(const uint4 *__restrict__ x, int64_t TG, int G,
@@ -664,7 +664,7 @@ static hipError_t launch_ring32(const torq_rotation *r, const void *x, int64_t T
   const int64_t grid = balanced_grid(nbatch, KS16 == 5 ? 4 : 3);
   const uint4 *ih = reinterpret_cast<const uint4 *>(r->intra32_hi);
   const uint4 *il = reinterpret_cast<const uint4 *>(r->intra32_lo);
-  const bool once = (double)TG * (1024.0 * KS16) > ONE_PASS_BYTES;
+  const bool once = (double)TG * (1024.0 * KS16) > ONE_PASS_INPUT_BYTES;
   auto go = [&](auto kernel, float gs) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * nw), 0, stream, reinterpret_cast<const uint4 *>(x), TG, r->G,
                        r->inter32f_hi, r->inter32f_lo, ih, il, codes, scales, gs);
@@ -781,7 +781,7 @@ hipError_t launch_rotate(const torq_rotation *r, const void *x_bf16, int64_t M, 
 }
 
 // torq_diag_rotate_ablation: rotate_ring_kernel32<8, MXFP4> (G = 128) with work left out (see SKIP there),
-// in the launch shape of the product.
+// in the launch shape of the product and, at any size, with the plain loads that the product has up to ONE_PASS_INPUT_BYTES.
 hipError_t launch_rotate_ablated(const torq_rotation *r, const void *x, int64_t M, uint8_t *codes, uint8_t *scales,
                                  int skip, hipStream_t stream) {
   if (r->G != 128 || r->butterfly) return hipErrorInvalidValue;

@@ -36,7 +36,7 @@ __device__ __forceinline__ i32x4 raw_buffer(const void *p, uint32_t bytes) {
   const uint64_t a = reinterpret_cast<uint64_t>(p);
   return i32x4{(int)(uint32_t)a, (int)((uint32_t)(a >> 32) & 0xFFFFu), (int)bytes, 0x00020000};
 }
-// ONCE: the non-temporal hint (see ONE_PASS_BYTES).
+// ONCE: the non-temporal hint (see ONE_PASS_INPUT_BYTES).
 #define TORQ_LOAD_TO_LDS16 "s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
 #define TORQ_LOAD_TO_LDS16_ONCE "s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
 template <bool FENCE = true, bool ONCE = false>

@@ -35,14 +35,26 @@ constexpr int DECODE_ERR = 32 * 130;      // the sticky "a workgroup gave up" wo
 
 namespace torq {
 
-// An input that a kernel reads once and that is larger than this is read with the non-temporal hint.  From HBM the hint is worth
-// 8 % (117 MB into LDS at 7.4 TB/s against 6.8; the sc bits change nothing): such loads leave the 256 MB Infinity Cache
-// alone.  An input that a program finds there is read slower with it, so it is for inputs of which the cache would not
-// hold a few: three in turn, with the hint against without, Sigma of [4096, 8192] (67 MB) 23.2 / 20.4 us, [6144, 8192] (101 MB)
-// 26.7 / 24.7, [8192, 8192] 31.1 / 32.5, [16384, 8192] 50.5 / 55.4; weights of 70 MB [33, 5120] x 25600 19.7 / 16.0, of
-// 125 MB [16, 28672] x 8192 23.8 / 26.3.  (In a model, where they come from HBM whatever their size, layers of 4 to
-// 70 MB would gain 3 - 10 % too; a call does not see that.)
-constexpr double ONE_PASS_BYTES = 96.0 * 1024 * 1024;
+// What a kernel reads once and is larger than this is read with the non-temporal hint.  From HBM the hint is worth 8 % (117 MB
+// into LDS at 7.4 TB/s against 6.8; the sc bits change nothing): such loads leave the 256 MB Infinity Cache alone.  What a
+// program finds in that cache is read slower with it.
+// Inputs (Gram, rotations) may have been written just before the call, or read by one, so the line lies where none of three
+// ways of use loses by more than its runs differ (1 - 2 %), us without / with the hint, from HBM, one input again, and just written (with the writing):
+//   Gram d = 8192: 134 MB 34.4 / 33.0, 30.2 / 32.3, 70.0 / 73.9; 180 MB 42.8 / 40.0, 37.1 / 39.0, 93.6 / 92.9; 235 MB 54.4 / 49.9,
+//     45.2 / 50.9, 128.8 / 126.0; 262 MB 57.0 / 52.1, 51.5 / 51.1, 139.5 / 134.7; 512 MB 101 / 91, 100 / 89, 278 / 261
+//   butterfly to MXFP4, G = 32 and G = 128: 134 MB 34.9 / 33.2, 30.7 / 34.2, 69.4 / 74.7 and 39.8 / 39.6, 37.7 / 40.1, 74.3 / 77.5;
+//     220 MB 55.7 / 53.3, 48.9 / 53.3, 125 / 118 and 59.2 / 58.5, 57.4 / 58.1, 134 / 121; 250 MB 64.0 / 60.5, 61.2 / 59.8, 145 / 137
+//     and 70.4 / 65.0, 66.8 / 65.2, 154 / 137; 512 MB 133 / 118, 134 / 116, 300 / 281 and 140 / 130, 139 / 127, 304 / 283
+//   dense rotation to MXFP4, G = 128 and G = 80: 134 MB 50.3 / 51.5, 50.6 / 52.0, 84.7 / 86.4 and 48.2 / 49.2, 48.0 / 50.6, 91.2 / 91.3;
+//     260 MB 90.6 / 88.9, 90.0 / 89.9, 172 / 166 and 89.6 / 88.6, 89.6 / 90.2, 181 / 181; 470 MB 159 / 157, 162 / 157, 303 / 294 and
+//     160 / 156, 158 / 156, 321 / 323
+constexpr double ONE_PASS_INPUT_BYTES = 240.0 * 1024 * 1024;
+// Weights come round again when the program has read its other layers, so the way of use that counts is from HBM; a layer this
+// large that is multiplied again at once loses.  us without / with, from HBM, then the same layer again: [16, 8192] 95 MB 22.2 /
+// 20.2, 17.8 / 20.4, 128 MB 28.0 / 25.4, 24.2 / 25.3, 230 MB 46.3 / 43.1, 39.4 / 43.0, 300 MB 62.0 / 55.0, 59.1 / 55.0; [1, 8192]
+// 128 MB 25.9 / 23.9, 23.7 / 23.5, 230 MB 43.2 / 40.2, 38.5 / 40.7; whole lines [16, 28672] 128 MB 34.7 / 33.0, 22.2 / 32.9, 230 MB
+// 44.6 / 39.7, 36.8 / 38.9.  (From HBM layers of 4 to 70 MB would gain 3 - 10 % too; smaller models have theirs in the cache.)
+constexpr double ONE_PASS_WEIGHT_BYTES = 96.0 * 1024 * 1024;
 
 // Raises a kernel's dynamic LDS limit to `bytes`, once for each device it is launched on (the limit belongs to
 // the function on one device, and the call is slow).  `raised`: the caller's, one per kernel, a bit a device;

@@ -858,10 +858,11 @@ def test_block_gram_at_the_edges_of_steps_trips_and_stages(tq, TG, G):
     assert torch.equal(got, got.transpose(1, 2)) and torch.equal(S, S.T)
 
 
-# inputs past 96 MiB are read with the non-temporal hint: the first token-group past it, for every kernel of that form
+# inputs past 240 MiB are read with the non-temporal hint: the first token-group past it, for every kernel of that form
+@pytest.mark.parametrize("mib", [96, 240])
 @pytest.mark.parametrize("G", [16, 32, 48, 64, 80, 96, 112, 128])
-def test_block_gram_of_inputs_read_past_the_cache(tq, G):
-    TG = 96 * 2 ** 20 // (64 * G) + 1
+def test_block_gram_of_inputs_read_past_the_cache(tq, G, mib):
+    TG = mib * 2 ** 20 // (64 * G) + 1
     x = synth.weights(TG, 32 * G, seed=G, device=DEV)
     S, W = tq.torq_block_gram(x, G), _block_gram_float64(x, G).sum(0) / TG
     # an fp32 chain of TG / 2048 token-groups, each of them 32 products, and the sum of eight waves
@@ -1314,11 +1315,12 @@ def test_butterfly_rotate_quantize_against_oracle(tq, oracle, M, d, G):
     rot.close()
 
 
-# past 96 MiB of input the dense rotation's ring carries the non-temporal hint: bit for bit the two halves, which go without
+# past 240 MiB of input the dense rotation's ring carries the non-temporal hint: bit for bit the two halves, which go without
+@pytest.mark.parametrize("mib", [96, 240])
 @pytest.mark.parametrize("G", [80, 96, 112, 128])
-def test_rotation_of_inputs_read_past_the_cache(tq, G):
+def test_rotation_of_inputs_read_past_the_cache(tq, G, mib):
     d = 64 * G
-    M = 96 * 2 ** 20 // (2 * d) + 3
+    M = mib * 2 ** 20 // (2 * d) + 3
     x = synth.activations(M, d, outliers=40, outlier_scale=50.0, seed=G, device=DEV)
     rot = tq.Rotation(d, G, *synth.rotations(G, seed=83 + G))
     for fmt in (tq.TORQ_FMT_MXFP4, tq.TORQ_FMT_MXINT4, tq.TORQ_FMT_NVFP4):
@@ -1328,10 +1330,11 @@ def test_rotation_of_inputs_read_past_the_cache(tq, G):
     rot.close()
 
 
-# past 96 MiB of input the loads carry the non-temporal hint: bit for bit the two halves, which go without
+# past 240 MiB of input (15360 rows) the loads carry the non-temporal hint: bit for bit two parts, which go without
+@pytest.mark.parametrize("M", [6145, 15361])
 @pytest.mark.parametrize("G", [32, 64, 128, 256])
-def test_butterfly_of_inputs_read_past_the_cache(tq, G):
-    M, d = 6145, 8192
+def test_butterfly_of_inputs_read_past_the_cache(tq, G, M):
+    d = 8192
     x = synth.activations(M, d, outliers=40, outlier_scale=50.0, seed=G, device=DEV)
     T = np.random.default_rng(G).uniform(-1.0, 1.0, size=(G.bit_length() - 1, G // 2)).astype(np.float32)
     rot = tq.ButterflyRotation(d, G, T, synth.rotations(G, seed=81 + G)[1])

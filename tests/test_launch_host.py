@@ -54,6 +54,7 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *lds, hipStream_t 
 
 # the child loads the stand-in globally before the library, so that the library's calls bind to it
 CHILD = """
+import array
 import ctypes as C, sys
 stub = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
 L = C.CDLL(sys.argv[2])
@@ -68,6 +69,19 @@ def gemm(M, N, d):
     return L.mxfp4_gemm_ws(P, P, P, P, P, i64(M), i64(N), d, P, BIG, None)
 def on(device):
     stub.stub_device(device)
+adr = lambda a: vp(a.buffer_info()[0])
+def identity(n):
+    I = array.array("f", [0.0]) * (n * n)
+    for i in range(n): I[i * n + i] = 1.0
+    return I
+def rotation(d, G):
+    I, J, r = identity(G), identity(32), vp()
+    assert L.torq_rotation_create(C.byref(r), d, G, adr(I), adr(J)) == 0
+    return r
+def butterfly(d, G):
+    T, J, r = array.array("f", [0.5]) * (G * G), identity(32), vp()
+    assert L.torq_rotation_create_butterfly(C.byref(r), d, G, adr(T), adr(J)) == 0
+    return r
 """
 
 
@@ -98,15 +112,7 @@ LDS_CALLS = {
     "tiled": "assert gemm(2048, 14336, 4096) == 0",
     "streaming": "assert gemm(33, 15616, 15872) == 0",
     "one_launch": """
-        import array
-        G, d = 128, 28672
-        I = array.array("f", [0.0]) * (G * G)
-        for i in range(G): I[i * G + i] = 1.0
-        J = array.array("f", [0.0]) * 1024
-        for i in range(32): J[i * 33] = 1.0
-        adr = lambda a: vp(a.buffer_info()[0])
-        r = vp()
-        assert L.torq_rotation_create(C.byref(r), d, G, adr(I), adr(J)) == 0
+        r = rotation(28672, 128)
         assert L.torq_linear_single_launch_probe(r, P, P, P, P, i64(64), i64(4096), P, BIG, 1, 0, None) == 0
         """,
 }
@@ -159,3 +165,20 @@ def test_block_gram_takes_workspaces_of_earlier_sizes(record, G):
     launched = [e for e in events if "launch" in e]
     for size, e in zip(sizes, launched[0::4]):
         assert e["grid"][0] * tiles * 1024 <= size
+
+
+@pytest.mark.parametrize("what,G", [("gram", 32), ("gram", 80), ("gram", 128), ("dense", 80), ("dense", 96), ("dense", 112),
+                                    ("dense", 128), ("butterfly", 32), ("butterfly", 64), ("butterfly", 128), ("butterfly", 256)])
+def test_inputs_are_read_past_the_cache_from_240_mib_on(record, what, G):
+    # a form of its own, where the cache cannot hold the input; below that a program may find it there
+    rows = [m * 2 ** 20 // (64 * G) for m in (96, 110, 128, 180, 240)] + [240 * 2 ** 20 // (64 * G) + 1, 2 ** 30 // (64 * G)]
+    make = {"gram": f"r = None; call = lambda M: gram(L.torq_block_gram, M, {32 * G}, {G})",
+            "dense": f"r = rotation({32 * G}, {G})", "butterfly": f"r = butterfly({32 * G}, {G})"}[what]
+    events = record(f"""
+        {make}
+        if r: call = lambda M: L.torq_rotate_quantize(r, P, i64(M), P, P, None)
+        for M in {rows}:
+            assert call(M) == 0
+        """)
+    reads = [e["launch"] for e in events if "launch" in e][:: 2 if what == "gram" else 1]
+    assert len(reads) == 7 and len(set(reads[:5])) == 1 and len(set(reads[5:])) == 1 and reads[0] != reads[5]
