@@ -457,16 +457,18 @@ int torq_diag_gemm_ring(const uint8_t *A_q, const uint8_t *A_s, const uint8_t *W
  * there are two):
  *   staging   TORQ_GEMM_REGISTERS    tiled, operands staged through registers
  *             TORQ_GEMM_RING         tiled, operands staged in a ring
- *             TORQ_GEMM_STRIPS       weight-streaming, strips straight to registers; with padded = 1 one strip after the
- *                                    other through a ring of each wave, the activations kept in registers
+ *             TORQ_GEMM_STRIPS       weight-streaming, strips straight to registers
  *             TORQ_GEMM_WHOLE_LINES  weight-streaming, by whole lines through a ring of each wave
+ *             TORQ_GEMM_STRIP_RING   weight-streaming, one strip after the other through a ring of each wave, the
+ *                                    activations kept in registers
  *   strips    16-row weight strips that a workgroup of a weight-streaming form has under way at a time, else 0
- *   items     depth of a wave's ring, and padded = 1 where its scale rows are padded (whole lines, else 0 but for the above)
+ *   items     depth of a wave's ring, and padded = 1 where its scale rows are padded (whole lines, else 0)
  * Host only, launches nothing.  TORQ_EINVAL for arguments that mxfp4_gemm_plan rejects. */
 #define TORQ_GEMM_REGISTERS   0
 #define TORQ_GEMM_RING        1
 #define TORQ_GEMM_STRIPS      2
 #define TORQ_GEMM_WHOLE_LINES 3
+#define TORQ_GEMM_STRIP_RING  4
 int torq_diag_gemm_form(int64_t M, int64_t N, int d, size_t workspace_bytes, int *staging, int *strips, int *items,
                         int *padded);
 /* A plain device-to-device copy of n_bytes (a multiple of 16; src and dst 16-byte aligned, not

@@ -532,7 +532,7 @@ def torq_diag_gemm_ring(A_q, A_s, W_q, W_s, tile_m: int, tile_n: int, k_pieces: 
     return out
 
 
-GEMM_STAGING = ("registers", "ring", "strips", "whole lines")
+GEMM_STAGING = ("registers", "ring", "strips", "whole lines", "strip ring")
 
 
 def torq_diag_gemm_form(M: int, N: int, d: int, workspace_bytes: int = 0):

@@ -847,9 +847,8 @@ void mxfp4_gemm_form(int64_t M, int64_t N, int d, size_t workspace_bytes, int *s
     return;
   }
   if (plan.stream) {
-    *staging = TORQ_GEMM_STRIPS;
+    *staging = TORQ_GEMM_STRIP_RING;
     *strips = mxfp4_gemm_stream_strips(d);
-    *padded = 1;
     return;
   }
   const bool lines = mxfp4_gemm_lines_form(M, N, d, strips, items, padded);

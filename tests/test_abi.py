@@ -196,7 +196,8 @@ def test_gemm_plan_names_the_tile_and_the_form_that_run():
     assert binding.torq_diag_gemm_form(8192, 28672, 8192)[0] == "registers"
     assert binding.torq_diag_gemm_form(4096, 5120, 5120)[0] == "registers"       # the first launch of two
     assert binding.torq_diag_gemm_form(16, 8192, 28672) == ("whole lines", 2, 2, True)
-    assert binding.torq_diag_gemm_form(16, 28672, 8192)[:2] == ("strips", 2)
+    assert binding.torq_diag_gemm_form(16, 28672, 8192) == ("strip ring", 2, 0, False)
+    assert binding.torq_diag_gemm_form(16, 40000, 2048) == ("strips", 2, 0, False)
     L = binding.lib()
     v = [C.c_int() for _ in range(4)]
     assert L.torq_diag_gemm_form(0, 4, 128, 0, *(C.byref(x) for x in v)) == binding.TORQ_EINVAL
@@ -222,7 +223,7 @@ def test_gemm_planner_invariants_over_random_shapes():
                 staging, strips, items, _ = binding.torq_diag_gemm_form(M, n, d, ws)
                 assert (strips > 0) == streaming and (items > 0) == (staging == "whole lines"), (M, n, d, staging)
                 if streaming:
-                    assert M <= 64 and pieces == 1 and staging in ("strips", "whole lines")
+                    assert M <= 64 and pieces == 1 and staging in ("strips", "whole lines", "strip ring")
                     assert staging == "strips" or d % 512 == 0
                     continue
                 if staging == "registers":

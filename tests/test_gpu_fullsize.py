@@ -131,10 +131,12 @@ GEMM_FULL = [
     (4096, 25600, 5120),      # Qwen3-32B MLP up / gate
     (4096, 1024, 5120),       # Qwen3-32B k/v projection
     (4096, 8192, 5120),       # Qwen3-32B q projection
-    (16, 28672, 8192),        # LLaMA3-70B MLP up at decode size: workgroups that keep the activations across four strip groups
-    (12, 28000, 8192),        # ... with ragged rows and a ragged last group
-    (16, 11008, 4096),        # ... one strip per group, four groups per workgroup
-    (12, 8210, 8192),         # ... with ragged rows and a ragged last group
+    (16, 28672, 8192),        # LLaMA3-70B MLP up at decode size: strips through a ring, seven a workgroup
+    (12, 28000, 8192),        # ... with ragged rows and unequal shares
+    (16, 11008, 4096),        # whole lines, four strips a workgroup, the last workgroup without its four
+    (12, 8210, 8192),         # ... with ragged rows
+    (16, 57344, 2048),        # strips to registers, in workgroups that keep the activations across eight strip groups
+    (12, 57000, 2048),        # ... with ragged rows and a ragged last group
     (8, 8192, 8192),          # two strips per workgroup, one group each, the k range in one trip
     (32, 5120, 8192),         # ... with two 16-row activation tiles
     (64, 5120, 8192),         # ... with four, in two trips
