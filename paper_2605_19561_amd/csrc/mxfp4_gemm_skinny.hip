@@ -794,6 +794,12 @@ static size_t lines_lds_bytes(int MT, int NS, int R, int d, int pad) {
 
 static int lines_pad(int MT, int NS, int R, int d) { return lines_lds_bytes(MT, NS, R, d, 1) <= SKINNY_MAX_LDS ? 1 : 0; }
 
+// the bytes of the widest weights that a form takes: a workgroup a CU, and the k range whose scale rows fit beside its rings
+static constexpr double lines_most_weights(int MT, int NS, int R) {
+  const int pieces = (int)((SKINNY_MAX_LDS - (size_t)WAVES * R * (NS + MT) * 2048) / (256 * (size_t)(NS + MT)));
+  return 256.0 * 16 * NS * 512 * pieces * 0.53125;
+}
+
 // the deepest ring with room for the scale rows: 4 items of two tiles, 3 (2) of three, 2 (1) of four, 1 of five to eight;
 // 0: none
 static int lines_ring(int MT, int NS, int d) {
@@ -862,7 +868,7 @@ static hipError_t launch_lines(const uint8_t *A_q, const uint8_t *A_s, const uin
   };
   static std::atomic<uint64_t> raised[2];
   // (one strip a workgroup, at most 4096 rows, would be as much from d = 46000 on: no layer here)
-  if constexpr (NS >= 2)
+  if constexpr (NS >= 2 && lines_most_weights(MT, NS, R) > ONE_PASS_WEIGHT_BYTES)
     if ((double)N * (double)d * 0.53125 > ONE_PASS_WEIGHT_BYTES) return go(mxfp4_gemm_lines_once_kernel<MT, NS, R>, raised[1]);
   return go(mxfp4_gemm_lines_kernel<MT, NS, R>, raised[0]);
 }

@@ -298,7 +298,8 @@ def test_gemm_weight_streaming_strips(tq, oracle, M, N, d):
 
 
 # The streaming kernel's whole-line form, each that the rule takes: (M, N, d) -> strips per workgroup, items in a wave's
-# ring, scale rows padded or not (tests/test_abi.py walks the rule and finds no other); among them waves without a line pair,
+# ring, scale rows padded or not (tests/test_abi.py walks the rule and finds no other, with weights past 96 MiB, which are read
+# with the non-temporal hint, or without); among them waves without a line pair,
 # ragged rows and strips.  Its bits are those of the form by half lines, which scale rows off the 16-byte grid still take.
 WHOLE_LINES = {
     (1, 16, 3072): (1, 4, True), (3, 1000, 3584): (1, 4, True),
@@ -315,7 +316,16 @@ WHOLE_LINES = {
     (33, 70, 1024): (1, 2, True), (33, 16, 16384): (1, 2, False), (33, 256, 17408): (1, 1, True), (48, 5000, 2048): (2, 1, True),
     (40, 10000, 5120): (3, 1, True), (33, 8208, 21504): (3, 1, False), (48, 13824, 5120): (4, 1, True), (48, 12304, 13824): (4, 1, False),
     (49, 8, 512): (1, 1, True), (64, 4100, 4096): (2, 1, True), (64, 8190, 2048): (2, 1, True), (49, 4112, 21504): (2, 1, False),
-    (49, 8448, 4096): (3, 1, True)}
+    (49, 8448, 4096): (3, 1, True),
+    (3, 300, 40960): (1, 3, True), (2, 100, 65536): (1, 3, False), (4, 90, 32768): (1, 4, False), (6, 4112, 43520): (2, 2, False),
+    (13, 24600, 3072): (7, 1, True), (35, 4112, 32768): (2, 1, False),
+    # past 96 MiB
+    (16, 8192, 28672): (2, 2, True), (7, 8055, 23552): (2, 2, True), (5, 4363, 43520): (2, 2, False), (11, 8201, 32768): (4, 1, False),
+    (3, 19490, 9728): (5, 1, True), (16, 21770, 8704): (6, 1, True),
+    (30, 8050, 23552): (2, 1, True), (17, 4112, 49152): (2, 1, False), (25, 11960, 15872): (3, 1, True), (17, 8201, 32768): (3, 1, False),
+    (17, 16096, 11776): (4, 1, True), (32, 19490, 9728): (5, 1, True), (19, 23136, 8192): (6, 1, False),
+    (33, 8048, 23552): (2, 1, True), (40, 5792, 32768): (2, 1, False), (48, 11950, 15872): (3, 1, True), (33, 8816, 21504): (3, 1, False),
+    (37, 16379, 11776): (4, 1, True), (33, 13712, 13824): (4, 1, False)}
 
 
 # (the others: strips straight to registers, by 16 bytes of scales and by 4, in workgroups that keep the activations across

@@ -110,14 +110,16 @@ def test_strip_kernel_prologue_divides_by_nothing_that_varies():
     assert len(bodies) == 30 and all(len(re.findall(r"^\s+v_rcp_", b, re.M)) == 1 for b in bodies)
 
 
-# ---- mxfp4_gemm_lines_kernel (mxfp4_gemm_skinny.hip): "the oldest item has landed" is a count of the younger requests.
+# ---- mxfp4_gemm_lines_kernel and, with the non-temporal hint on the weights' loads, mxfp4_gemm_lines_once_kernel
+# (mxfp4_gemm_skinny.hip): "the oldest item has landed" is a count of the younger requests.
 def test_lines_loop_holds_exactly_the_counted_requests():
     with tempfile.TemporaryDirectory() as tmp:
         text = open(build.device_asm("mxfp4_gemm_skinny.hip", os.path.join(tmp, "skinny.s"))).read()
-    seen = 0
-    for m in re.finditer(r"^(_ZN4torq23mxfp4_gemm_lines_kernelILi(\d)ELi(\d)ELi(\d)\w+):(.*?)^\.Lfunc_end", text, re.M | re.S):
-        name, ops, ring, body = m.group(1), 2 * (int(m.group(2)) + int(m.group(3))), int(m.group(4)), m.group(5)
-        seen += 1
+    seen = {None: 0, "once_": 0}
+    for m in re.finditer(r"^(_ZN4torq\d\dmxfp4_gemm_lines_(once_)?kernelILi(\d)ELi(\d)ELi(\d)\w+):(.*?)^\.Lfunc_end", text, re.M | re.S):
+        name, once, tiles, strips, ring, body = m.group(1), m.group(2), int(m.group(3)), int(m.group(4)), int(m.group(5)), m.group(6)
+        ops = 2 * (tiles + strips)
+        seen[once] += 1
         assert re.search(r"\.name:\s+" + name + r"\n(?:.*\n)*?\s+\.private_segment_fixed_size:\s+0\n", text), name
         code = [c for c in (line.split(";")[0].strip() for line in body.splitlines()) if c]
         waits = [(i, int(re.search(r"vmcnt\((\d+)\)", c).group(1))) for i, c in enumerate(code) if c.startswith("s_waitcnt") and "vmcnt(" in c]
@@ -127,9 +129,11 @@ def test_lines_loop_holds_exactly_the_counted_requests():
         end = next(i for i, c in enumerate(code) if c.startswith("s_cbranch") and i > top)
         vmem = [c for c in code[top:end] if re.match(r"(buffer_|global_|flat_|scratch_)", c)]
         assert len(vmem) == ops and all(map(is_lds, vmem)), (name, len(vmem))
+        hinted = [c for c in code[top:end] if " nt " in c]
+        assert len(hinted) == (2 * strips if once else 0), (name, hinted)
         # the ring's first items lie between the scale bytes' requests (in a loop) and the first wait
         assert sum(map(is_lds, code[:waits[0][0]])) == ring * ops + 2, name
-    assert seen == 26
+    assert seen == {None: 26, "once_": 13}
 
 
 # ---- mxfp4_gemm_stream_kernel: as above, and nothing but its own counted requests loads at all (a load of the compiler's
