@@ -18,7 +18,6 @@ namespace torq {
 
 namespace {
 
-typedef __attribute__((__vector_size__(2 * sizeof(unsigned)))) unsigned u32x2;
 constexpr int WAVES = 8;
 constexpr int STREAM_RING = 4;                    // items of a wave's ring: 3 and 5 measured 1 - 4 % slower, 2, 6 and 8 more
 constexpr size_t STREAM_MAX_LDS = 160 * 1024;
@@ -396,11 +395,13 @@ hipError_t launch_mxfp4_gemm_stream(const uint8_t *A_q, const uint8_t *A_s, cons
                                     int64_t M, int64_t N, int d, hipStream_t stream) {
   const int MT = (int)((M + 15) / 16), PT = (d / 256 + WAVES - 1) / WAVES;
   const bool once = (double)N * (double)d * 0.53125 > ONE_PASS_WEIGHT_BYTES;
+  // (one activation tile of d > 6144 has as much wherever the rule takes it)
+  if (MT == 1 && PT == 4) return launch_cfg<1, 4, STREAM_RING, true>(A_q, A_s, W_q, W_s, out, M, N, d, stream);
 #define TORQ_STREAM(MT_, PT_)                                                                                                   \
   if (MT == MT_ && PT == PT_)                                                                                                  \
     return once ? launch_cfg<MT_, PT_, STREAM_RING, true>(A_q, A_s, W_q, W_s, out, M, N, d, stream)                            \
                 : launch_cfg<MT_, PT_, STREAM_RING, false>(A_q, A_s, W_q, W_s, out, M, N, d, stream);
-  TORQ_STREAM(1, 2) TORQ_STREAM(1, 3) TORQ_STREAM(1, 4) TORQ_STREAM(2, 2) TORQ_STREAM(2, 3) TORQ_STREAM(2, 4)
+  TORQ_STREAM(1, 2) TORQ_STREAM(1, 3) TORQ_STREAM(2, 2) TORQ_STREAM(2, 3) TORQ_STREAM(2, 4)
   TORQ_STREAM(3, 2) TORQ_STREAM(3, 3) TORQ_STREAM(3, 4) TORQ_STREAM(4, 2) TORQ_STREAM(4, 3) TORQ_STREAM(4, 4)
 #undef TORQ_STREAM
   return hipErrorInvalidValue;

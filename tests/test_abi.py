@@ -255,6 +255,21 @@ def test_every_whole_line_form_that_the_rule_takes_has_its_gpu_case():
                     assert staging != "whole lines" or key(M, 16 * strips, d, form) in tested, (M, 16 * strips, d, form)
 
 
+def test_every_strip_ring_form_that_the_rule_takes_has_its_gpu_case():
+    from test_gpu_parity import STREAM_RING
+    key = lambda M, N, d: ((M + 15) // 16, -(-d // 2048), N * d * 17 > 32 * 96 * 2 ** 20)
+    assert all(binding.torq_diag_gemm_form(*shape)[0] == "strip ring" for shape in STREAM_RING)
+    tested, taken = {key(*shape) for shape in STREAM_RING}, set()
+    for M in (1, 7, 8, 16, 17, 32, 33, 48, 49, 64):
+        for d in range(512, 28673, 512):
+            past = 32 * 96 * 2 ** 20 // 17 // d // 16
+            for strips in sorted({*range(1, 1793, 16), 641, 768, 769, 1025, 1536, 1537, 1600, 1601, 1793, 2048, 4096, past, past + 1}):
+                for workspace in (0, 1 << 40):
+                    if binding.torq_diag_gemm_form(M, 16 * strips, d, workspace)[0] == "strip ring":
+                        taken.add(key(M, 16 * strips, d))
+    assert taken == tested
+
+
 def test_format_entry_points_reject_unknown_formats_and_bad_scales():
     L = binding.lib()
     good = C.c_void_p(0x1000)

@@ -351,12 +351,15 @@ def test_gemm_weight_streaming_by_whole_lines(tq, oracle, M, N, d):
     _assert_every_output_within_one_ulp(_bits(out[:M][:, cols].contiguous()), want)
 
 
-# The streaming kernel's strips through a ring: every form the rule takes (activation tiles x line pairs per wave), at the first
+# The streaming kernel's strips through a ring: every form the rule takes (activation tiles x line pairs per wave, with the
+# non-temporal hint past 96 MiB of weights and without; tests/test_abi.py walks the rule), at the first
 # and last strip counts of its ranges, a row and a column more than whole tiles, workgroups of unequal shares.  The bar is the
 # one of the other forms: one rounding of an fp32 sum to bf16.
 STREAM_RING = [(8, 28673, 2560), (16, 28700, 6144), (13, 25601, 8192), (17, 24577, 3072), (32, 28672, 4608), (20, 26000, 8192),
                (33, 16385, 2560), (48, 12288, 5120), (40, 10248, 7168), (64, 10244, 3584), (49, 16391, 4608), (64, 24576, 8192),
-               (1, 24585, 8192), (7, 32776, 6144), (2, 40003, 5120)]
+               (1, 24585, 8192), (7, 32776, 6144), (2, 40003, 5120), (3, 46270, 4096),
+               (25, 24593, 6656), (30, 46275, 4096), (17, 30850, 6144), (33, 46264, 4096), (45, 30844, 6144), (48, 23140, 8192),
+               (49, 10257, 6656), (64, 46262, 4096), (50, 30843, 6144)]
 
 
 @pytest.mark.parametrize("M,N,d", STREAM_RING)

@@ -152,7 +152,7 @@ def test_stream_kernel_waits_by_its_own_counts():
         waits = [int(re.search(r"vmcnt\((\d+)\)", c).group(1)) for c in code if c.startswith("s_waitcnt") and "vmcnt(" in c]
         counts = [2 * (R - 1) + (i + R - 1) // PT for i in range(PT)]
         assert waits[:MT * PT] == MT * counts and set(waits[MT * PT:-1]) == set(counts) and waits[-1] == 0, (name, waits)
-    assert seen == 24
+    assert seen == 23
 
 
 # ---- torq_linear_stream_kernel: the compiler's own loads end at the one wait ahead of the ring, the LDS stores of the rows wait
