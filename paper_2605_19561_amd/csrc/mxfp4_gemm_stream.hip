@@ -434,18 +434,22 @@ static hipError_t launch_linear_cfg(const torq_rotation *r, const void *x, uint8
 //   one or two token-groups, up to 80 MB of weights ([1, 4096] x 14336 10.9 / 9.9, x 28672 16.9 / 14.5, [2, 4096] x 14336 10.9 /
 //     9.9, [1, 8192] x 1024 6.6 / 6.1, x 14336 17.9 / 15.7, [1, 3584] x 4096 6.9 / 6.3, [1, 7168] x 4096 9.0 / 7.4; [1, 8192] x
 //     28672 27.5 / 26.4 replayed from a graph, but 25.7 / 26.3 called one after the other) but where a workgroup's share is
-//     a strip of 32 KB, which is well requested all at once ([1, 4096] x 4096 5.7 / 6.5, x 1024 5.2 / 5.6)
+//     a strip that the other form requests all at once, in one full trip of each wave ([1, 4096] x 4096 5.7 / 6.5, x 1024 5.2 / 5.6;
+//     d = 3584 does not fill the trip, its loads there are under a condition, and a strip of d = 8192 is 64 KB)
 //   three or four: up to a strip a workgroup of d <= 7168, up to half as many beyond: [4, 3584] x 4096 8.4 / 7.6, [2, 7168] x
-//     4096 10.5 / 9.2, [1, 14336] x 2048 10.7 / 9.0, but [4, 4096] x 4096 7.1 / 8.0, [2, 8192] x 4096 9.2 / 9.4, [1, 14336] x 4096
-//     11.3 / 10.5 to 12.2; with more strips the second token-group of a wave keeps the ring waiting ([4, 4096] x 14336 11.0 /
+//     4096 10.5 / 9.2, [1, 14336] x 2048 10.7 / 9.0, but [4, 4096] x 4096 7.1 / 8.0 (all at once), [2, 8192] x 4096 9.2 / 9.4, [1, 14336] x
+//     4096 11.3 / 10.5 to 12.2 (and not beyond seven line pairs a wave, the most that are built); with more strips the second token-group of a wave keeps the ring waiting ([4, 4096] x 14336 11.0 /
 //     11.4, [2, 7168] x 14336 15.1 / 16.2)
 // (the first strip's items requested with the rotation's operands, one / two / three / four: [1, 8192] x 28672 26.3 / 26.4 / 26.0 /
 // 25.7, x 1024 6.0 / 6.1 / 6.4 / 6.8, [1, 14336] x 4096 11.6 / 10.5 / 10.5 / 11.1)
 bool torq_linear_stream_takes(const torq_rotation *r, int64_t M, int64_t N, const uint8_t *W_s) {
   if (!torq_linear_local_fits(r, M) || N < 1 || N > (1 << 30) || r->d % 512 != 0 || (reinterpret_cast<uintptr_t>(W_s) & 15u)) return false;
   const int64_t token_groups = M * (int64_t)(r->d / 32 / r->G), strips = (N + 15) / 16;
-  if (token_groups <= 2) return (r->d != 4096 || strips > 256) && (double)N * (double)r->d * 0.53125 <= 80e6;
-  return r->d != 4096 && r->d < 16384 && strips <= (r->d <= 7168 ? 256 : 128);
+  // the other form's EXACT loop on two line pairs a wave or fewer: a strip of 32 KB at most
+  const int trip = 256 * WAVES;
+  const bool at_once = r->d % trip == 0 && r->d <= 2 * trip;
+  if (token_groups <= 2) return !(at_once && strips <= 256) && (double)N * (double)r->d * 0.53125 <= 80e6;
+  return !at_once && r->d <= 7 * trip && strips <= (r->d <= 7168 ? 256 : 128);
 }
 
 hipError_t launch_torq_linear_stream(const torq_rotation *r, const void *x, uint8_t *A_q, uint8_t *A_s, const uint8_t *W_q,
