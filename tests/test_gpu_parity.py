@@ -677,7 +677,8 @@ def test_calls_launch_on_the_current_stream(tq):
 
 
 # The calls that are marshalled in C++: what they return and what they refuse is what the interpreter's own way through the
-# arguments returns and refuses (the module left out, every call goes that way).
+# arguments returns and refuses (the module left out, every call goes that way).  Plain arguments are taken by the module, and
+# those that are not are left to the interpreter.
 class _NoModule:
     linear = rotate_quantize = gram = histogram = staticmethod(lambda *a: None)
 
@@ -725,7 +726,22 @@ def test_calls_marshalled_in_native_code(tq, monkeypatch, case):
         torch.cuda.synchronize()
         return got
 
+    module, taken = tq._native(), []
+
+    class Recorder:
+        def __getattr__(self, name):
+            def call(*args):
+                y = getattr(module, name)(*args)
+                taken.append((name, y is not None))
+                return y
+            return call
+
+    monkeypatch.setattr(tq, "_host", Recorder())
     native = answers()
+    if case in ("plain", "kept", "parameter", "stream"):
+        assert len(taken) == 6 and all(y for _, y in taken)
+    elif case in ("subclass", "transposed", "type", "host", "no tensor"):
+        assert len(taken) == 6 and not any(y for name, y in taken if name != "histogram")
     monkeypatch.setattr(tq, "_host", _NoModule)
     for name, want in answers().items():
         if isinstance(want, tuple):
