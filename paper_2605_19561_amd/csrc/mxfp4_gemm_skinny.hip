@@ -820,8 +820,9 @@ static int lines_ring(int MT, int NS, int d) {
 // below 8 rows the other form also keeps d = 2048 (0.94 - 1.04) and rows a multiple of 4 KB apart past 448 strips
 // ([1, 8192] x 28672 0.93, [1, 16384] x 16384 0.91: all workgroups walk the same columns, whose lines share channels).
 // From 8 rows on past 1600 strips: seven strips a CU leave a ring of one item, and beside it the scale rows of d = 8192 at
-// most.  At that length (rows 4 KB apart again) the persistent form is ahead: [16, 8192] x 28672 in a decoder block 29.4 /
-// 27.5 (this form / the other), alone 31.0 / 31.0, whole calls [8, 8192] x 26624 30.5 / 28.4, [12, 8192] x 28672 31.8 / 30.3,
+// most.  At that length (rows 4 KB apart again) even the persistent form below was ahead, and the ring of strips
+// (mxfp4_gemm_stream.hip), which takes such a product, is ahead of both: [16, 8192] x 28672 in a decoder block 29.4 / 27.5 / 25.4
+// (this form, that one, the ring), alone 31.0 / 31.0 / 23.8; this form and the persistent one, whole calls [8, 8192] x 26624 30.5 / 28.4, [12, 8192] x 28672 31.8 / 30.3,
 // [16, 8192] x 26624 30.7 / 29.8, but x 25600 28.2 / 29.4, x 24576 27.6 / 28.8, x 20480 22.7 / 28.7.
 // Three strips of one activation tile: four measured up to 6 % ahead.
 int mxfp4_gemm_lines_strips(int64_t M, int64_t N, int d) {
@@ -917,7 +918,8 @@ static hipError_t launch_cfg(const uint8_t *A_q, const uint8_t *A_s, const uint8
   // The persistent form (activation codes loaded once per workgroup and kept in registers): 8 - 16 rows,
   // one trip over the k range, and weights enough for the re-reads to cost more than the parallelism
   // given up (measured: [16, 8192] x 28672 34.2 -> 28.4 us, [8, 8192] x 28672 32.2 -> 27.4,
-  // [16, 4096] x 14336 9.2 -> 9.0; below 24 MB of weights it loses).  Each
+  // [16, 4096] x 14336 9.2 -> 9.0; below 24 MB of weights it loses.  With 16-byte aligned scale rows d = 2560 ... 8192 go to the
+  // ring of strips or to whole lines; left are d up to 2048, rows that are no whole pieces and scale rows elsewhere).  Each
   // workgroup takes `per` groups, the smallest power of two that leaves at most 256 workgroups (one per CU,
   // evenly loaded: 3 or 7 groups per workgroup measured 15 - 20 % slower than 4, and half as many
   // workgroups as CUs 30 % slower than one each).
