@@ -93,11 +93,14 @@ int guarded(F &&body) noexcept {
   }
 }
 
-// the dense-matrix kernels, or the butterfly kernel for a handle made by torq_rotation_create_butterfly
+// the dense-matrix kernels, or the butterfly kernel for a handle made by torq_rotation_create_butterfly; inputs of more than
+// `one_pass` bytes are read past the cache
 hipError_t rotate_any(const torq_rotation *r, const void *x_bf16, int64_t M, int format, float global_scale,
-                      uint8_t *codes, uint8_t *scales, float *z_out, hipStream_t stream) {
-  return r->butterfly ? torq::launch_rotate_butterfly(r, x_bf16, M, format, global_scale, codes, scales, z_out, stream)
-                      : torq::launch_rotate(r, x_bf16, M, format, global_scale, codes, scales, z_out, stream);
+                      uint8_t *codes, uint8_t *scales, float *z_out, hipStream_t stream,
+                      double one_pass = torq::ONE_PASS_INPUT_BYTES) {
+  const bool once = 2.0 * (double)M * (double)r->d > one_pass;
+  return r->butterfly ? torq::launch_rotate_butterfly(r, x_bf16, M, format, global_scale, codes, scales, z_out, once, stream)
+                      : torq::launch_rotate(r, x_bf16, M, format, global_scale, codes, scales, z_out, once, stream);
 }
 
 }  // namespace
@@ -504,7 +507,8 @@ int torq_linear(const torq_rotation_t *r, const void *x_bf16, const uint8_t *W_q
     hipError_t el = torq::launch_torq_linear_local(r, x_bf16, codes, scales, W_q, W_s, out_bf16, M, N, (hipStream_t)stream);
     return el == hipSuccess ? TORQ_OK : hip_fail(el);
   }
-  hipError_t e = rotate_any(r, x_bf16, M, TORQ_FMT_MXFP4, 1.0f, codes, scales, nullptr, (hipStream_t)stream);
+  hipError_t e = rotate_any(r, x_bf16, M, TORQ_FMT_MXFP4, 1.0f, codes, scales, nullptr, (hipStream_t)stream,
+                            torq::ONE_PASS_LINEAR_INPUT_BYTES);
   if (e != hipSuccess) return hip_fail(e);
   // whatever the caller gave beyond the packed activations serves the GEMM's split-k pieces
   const size_t used = torq_linear_workspace_bytes(M, r->d);

@@ -290,7 +290,7 @@ int butterfly_coef_count(int G) {
 
 template <int NJ>
 static hipError_t launch_nj(const torq_rotation *r, const void *x, int64_t TG, int format, float global_scale,
-                            uint8_t *codes, uint8_t *scales, float *z_out, hipStream_t stream) {
+                            uint8_t *codes, uint8_t *scales, float *z_out, bool once, hipStream_t stream) {
   const size_t lds_bytes = 4 * (size_t)NJ * 32 * 64 + (NJ >= 4 ? (size_t)butterfly_coef_count(32 * NJ) * 32 * 4 : 0);
   // resident workgroups of 4 waves: what the kernel's register count (and LDS) admits per CU
   int64_t grid = butterfly_workgroups(NJ, z_out ? FMT_NONE : format) * 256;
@@ -300,7 +300,6 @@ static hipError_t launch_nj(const torq_rotation *r, const void *x, int64_t TG, i
   const uint4 *xx = reinterpret_cast<const uint4 *>(x);
   uint2 *cc = reinterpret_cast<uint2 *>(codes);
   // X [28672, 8192] to MXFP4, G = 32 / 64 / 128, 124 / 126 / 130 -> 110 / 113 / 117 us
-  const bool once = (double)TG * (2048.0 * NJ) > ONE_PASS_INPUT_BYTES;
   auto go = [&](auto kernel, float gs) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), lds_bytes, stream, xx, TG, r->butterfly, ih, il, cc, scales, z_out, gs);
   };
@@ -320,15 +319,15 @@ static hipError_t launch_nj(const torq_rotation *r, const void *x, int64_t TG, i
 
 // r->butterfly holds the coefficient table; G in {32, 64, 128, 256}
 hipError_t launch_rotate_butterfly(const torq_rotation *r, const void *x_bf16, int64_t M, int format,
-                                   float global_scale, uint8_t *codes, uint8_t *scales, float *z_out,
+                                   float global_scale, uint8_t *codes, uint8_t *scales, float *z_out, bool once,
                                    hipStream_t stream) {
   const int64_t TG = M * (int64_t)(r->d / 32 / r->G);
   if (TG == 0) return hipSuccess;
   switch (r->G / 32) {
-    case 1: return launch_nj<1>(r, x_bf16, TG, format, global_scale, codes, scales, z_out, stream);
-    case 2: return launch_nj<2>(r, x_bf16, TG, format, global_scale, codes, scales, z_out, stream);
-    case 4: return launch_nj<4>(r, x_bf16, TG, format, global_scale, codes, scales, z_out, stream);
-    case 8: return launch_nj<8>(r, x_bf16, TG, format, global_scale, codes, scales, z_out, stream);
+    case 1: return launch_nj<1>(r, x_bf16, TG, format, global_scale, codes, scales, z_out, once, stream);
+    case 2: return launch_nj<2>(r, x_bf16, TG, format, global_scale, codes, scales, z_out, once, stream);
+    case 4: return launch_nj<4>(r, x_bf16, TG, format, global_scale, codes, scales, z_out, once, stream);
+    case 8: return launch_nj<8>(r, x_bf16, TG, format, global_scale, codes, scales, z_out, once, stream);
   }
   return hipErrorInvalidValue;
 }

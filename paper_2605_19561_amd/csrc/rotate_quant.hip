@@ -657,14 +657,13 @@ static hipError_t launch_cfg32(const torq_rotation *r, const void *x, int64_t TG
 
 template <int KS16>
 static hipError_t launch_ring32(const torq_rotation *r, const void *x, int64_t TG, int format, float global_scale,
-                                uint8_t *codes, uint8_t *scales, hipStream_t stream) {
+                                uint8_t *codes, uint8_t *scales, bool once, hipStream_t stream) {
   const int nw = (KS16 + 1) / 2;
   const int64_t nbatch = (TG + 1) / 2;
   // 3 x <= 48 KiB of LDS, 12 waves of <= 160 registers (G = 80: 4 x 36 KiB, 12 waves of three per workgroup)
   const int64_t grid = balanced_grid(nbatch, KS16 == 5 ? 4 : 3);
   const uint4 *ih = reinterpret_cast<const uint4 *>(r->intra32_hi);
   const uint4 *il = reinterpret_cast<const uint4 *>(r->intra32_lo);
-  const bool once = (double)TG * (1024.0 * KS16) > ONE_PASS_INPUT_BYTES;
   auto go = [&](auto kernel, float gs) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * nw), 0, stream, reinterpret_cast<const uint4 *>(x), TG, r->G,
                        r->inter32f_hi, r->inter32f_lo, ih, il, codes, scales, gs);
@@ -708,7 +707,7 @@ static hipError_t launch_cfg(const torq_rotation *r, const void *x, int64_t TG, 
 
 // Exactly one of (codes, scales) / z_out is used; `format` (FMT_*) picks step 4's block format.
 hipError_t launch_rotate(const torq_rotation *r, const void *x_bf16, int64_t M, int format, float global_scale,
-                         uint8_t *codes, uint8_t *scales, float *z_out, hipStream_t stream) {
+                         uint8_t *codes, uint8_t *scales, float *z_out, bool once, hipStream_t stream) {
   const int64_t TG = M * (int64_t)(r->d / 32 / r->G);
   if (TG == 0) return hipSuccess;
   // A handful of token-groups, G = 64 ... 128: every 32 output blocks of a token-group by a workgroup of one
@@ -734,10 +733,10 @@ hipError_t launch_rotate(const torq_rotation *r, const void *x_bf16, int64_t M, 
   // [1024, 4096] 8.8 against 8.2, [2048, 14336] 27.1 against 25.5, [4096, 5120] 18.2 against 17.3; equal at
   // [8192, 4096]; from [16384, 4096] on the ring wins, 45.7 against 49.6 us there)
   if (!z_out && TG >= RING_MIN_TG) {
-    if (r->G == 128) return launch_ring32<8>(r, x_bf16, TG, format, global_scale, codes, scales, stream);
-    if (r->G == 112) return launch_ring32<7>(r, x_bf16, TG, format, global_scale, codes, scales, stream);
-    if (r->G == 96) return launch_ring32<6>(r, x_bf16, TG, format, global_scale, codes, scales, stream);
-    if (r->G == 80) return launch_ring32<5>(r, x_bf16, TG, format, global_scale, codes, scales, stream);
+    if (r->G == 128) return launch_ring32<8>(r, x_bf16, TG, format, global_scale, codes, scales, once, stream);
+    if (r->G == 112) return launch_ring32<7>(r, x_bf16, TG, format, global_scale, codes, scales, once, stream);
+    if (r->G == 96) return launch_ring32<6>(r, x_bf16, TG, format, global_scale, codes, scales, once, stream);
+    if (r->G == 80) return launch_ring32<5>(r, x_bf16, TG, format, global_scale, codes, scales, once, stream);
   }
   // Below that, batches of ONE token-group instead of two for G = 128, 112 and 80 (a) up to 256 token-groups
   // (they spread over twice as many workgroups) and (b) from 3072 on (three or more batches of two per

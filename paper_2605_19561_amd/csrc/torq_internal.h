@@ -49,6 +49,13 @@ namespace torq {
 //     260 MB 90.6 / 88.9, 90.0 / 89.9, 172 / 166 and 89.6 / 88.6, 89.6 / 90.2, 181 / 181; 470 MB 159 / 157, 162 / 157, 303 / 294 and
 //     160 / 156, 158 / 156, 321 / 323
 constexpr double ONE_PASS_INPUT_BYTES = 240.0 * 1024 * 1024;
+// In torq_linear the packed activations and the output come right behind, and the cache is better left to them: the line is where
+// it would not hold all of it.  Whole calls without / with the hint, us, three layers in turn, one again, and in turn with the input
+// just written, dense G = 128: [8192, 8192] x 28672 991 / 984, 991 / 985, 1041 / 1044, x 8192 332 / 327, 324 / 320, 373 / 370, x
+// 1024 97.0 / 95.6, 91.7 / 94.1, 137.4 / 134.7; [12288, 8192] x 8192 477 / 477, 476 / 472, 542 / 538; butterfly G = 32 [8192, 8192] x
+// 8192 323 / 315, 311 / 306, 364 / 352, x 1024 84.2 / 80.7, 75.2 / 81.5, 123.5 / 123.8; at 105 MB, [6400, 8192] x 8192, dense 278 /
+// 278, 272 / 274, 310 / 308
+constexpr double ONE_PASS_LINEAR_INPUT_BYTES = 96.0 * 1024 * 1024;
 // Weights come round again when the program has read its other layers, so the way of use that counts is from HBM; a layer this
 // large that is multiplied again at once loses.  us without / with, from HBM, then the same layer again: [16, 8192] 95 MB 22.2 /
 // 20.2, 17.8 / 20.4, 128 MB 28.0 / 25.4, 24.2 / 25.3, 230 MB 46.3 / 43.1, 39.4 / 43.0, 300 MB 62.0 / 55.0, 59.1 / 55.0; [1, 8192]
@@ -76,14 +83,15 @@ hipError_t launch_quantize_f32(const float *z, int64_t nblk, int format, float g
                                uint8_t *scales, hipStream_t stream);
 
 // Two-level rotation (+ quantisation).  Exactly one of (codes, scales) / z_out is used:
-// z_out != nullptr writes the rotated fp32 values instead of quantising to `format`.
+// z_out != nullptr writes the rotated fp32 values instead of quantising to `format`.  once: an input that is read past the
+// cache (where the kernel has a form for it).
 hipError_t launch_rotate(const torq_rotation *r, const void *x_bf16, int64_t M, int format, float global_scale,
-                         uint8_t *codes, uint8_t *scales, float *z_out, hipStream_t stream);
+                         uint8_t *codes, uint8_t *scales, float *z_out, bool once, hipStream_t stream);
 
 // The same for a handle whose R_inter is a butterfly (r->butterfly != nullptr; G in 32, 64, 128, 256).
 int butterfly_coef_count(int G);
 hipError_t launch_rotate_butterfly(const torq_rotation *r, const void *x_bf16, int64_t M, int format,
-                                   float global_scale, uint8_t *codes, uint8_t *scales, float *z_out,
+                                   float global_scale, uint8_t *codes, uint8_t *scales, float *z_out, bool once,
                                    hipStream_t stream);
 
 // workspace: optional device scratch of mxfp4_gemm_workspace_bytes(M, N, d) bytes; with it, shapes

@@ -182,3 +182,19 @@ def test_inputs_are_read_past_the_cache_from_240_mib_on(record, what, G):
         """)
     reads = [e["launch"] for e in events if "launch" in e][:: 2 if what == "gram" else 1]
     assert len(reads) == 7 and len(set(reads[:5])) == 1 and len(set(reads[5:])) == 1 and reads[0] != reads[5]
+
+
+@pytest.mark.parametrize("what,G", [("rotation", 80), ("rotation", 128), ("butterfly", 32), ("butterfly", 128)])
+def test_linear_reads_its_input_past_the_cache_from_96_mib_on(record, what, G):
+    # the codes and the output come right behind: the line is lower than for the rotation alone
+    rows = [96 * 2 ** 20 // (64 * G) + i for i in (0, 1)]
+    events = record(f"""
+        r = {what}({32 * G}, {G})
+        for M in {rows}:
+            assert L.torq_linear(r, P, P, P, P, i64(M), i64(4096), P, BIG, None) == 0
+            assert L.torq_rotate_quantize(r, P, i64(M), P, P, None) == 0
+        assert L.torq_rotate_quantize(r, P, i64({3 * rows[0]}), P, P, None) == 0
+        """)
+    launches = [e["launch"] for e in events if "launch" in e]
+    plain, once = launches[0], launches[-1]
+    assert plain != once and launches.count(plain) == 3 and launches.count(once) == 2
