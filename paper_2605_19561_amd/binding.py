@@ -171,6 +171,15 @@ def _dev(t: torch.Tensor, dtype, what):
     raise ValueError(f"{what}: expected a contiguous {dtype} device tensor")
 
 
+def _scratch(like: torch.Tensor, nbytes: int, stream) -> torch.Tensor:
+    """A workspace of the call's own.  It goes back to the allocator when the call returns, ahead of the kernels that use it: a
+    stream that is not the one it is allocated on has to be known there."""
+    t = torch.empty((nbytes,), dtype=torch.uint8, device=like.device)
+    if stream is not None and t.is_cuda:
+        t.record_stream(stream if isinstance(stream, torch.Stream) else torch.cuda.ExternalStream(stream.cuda_stream, t.device))
+    return t
+
+
 class _Interpreted:
     """In the place of the C++ module where there is none for this interpreter and torch: it takes no call."""
     linear = rotate_quantize = gram = histogram = staticmethod(lambda *args: None)
@@ -370,7 +379,7 @@ def mxfp4_gemm_ws(A_q, A_s, W_q, W_s, out=None, workspace=None, stream=None):
     if out is None:
         out = torch.empty((M, N), dtype=torch.bfloat16, device=A_q.device)
     if workspace is None:
-        workspace = torch.empty((max(mxfp4_gemm_workspace_bytes(M, N, d), 16),), dtype=torch.uint8, device=A_q.device)
+        workspace = _scratch(A_q, max(mxfp4_gemm_workspace_bytes(M, N, d), 16), stream)
     _check(lib().mxfp4_gemm_ws(_dev(A_q, torch.uint8, "A_q"), _dev(A_s, torch.uint8, "A_s"),
                                _dev(W_q, torch.uint8, "W_q"), _dev(W_s, torch.uint8, "W_s"),
                                _dev(out, torch.bfloat16, "out"), M, N, d, _dev(workspace, torch.uint8, "workspace"),
@@ -392,7 +401,7 @@ def torq_linear_single_launch(rot: Rotation, x_bf16, W_q, W_s, out=None, workspa
     N = W_q.shape[0]
     assert d == rot.d and W_q.shape == (N, d // 2) and W_s.shape == (N, d // 32)
     if workspace is None:
-        workspace = torch.empty((max(torq_linear_workspace_bytes(M, d), 1),), dtype=torch.uint8, device=x_bf16.device)
+        workspace = _scratch(x_bf16, max(torq_linear_workspace_bytes(M, d), 1), stream)
     if out is None:
         out = torch.empty((M, N), dtype=torch.bfloat16, device=x_bf16.device)
     _check(lib().torq_linear_single_launch(rot.handle, _dev(x_bf16, torch.bfloat16, "x"), _dev(W_q, torch.uint8, "W_q"),
@@ -409,7 +418,7 @@ def torq_linear_single_launch_probe(rot: Rotation, x_bf16, W_q, W_s, spin_limit,
     N = W_q.shape[0]
     assert d == rot.d and W_q.shape == (N, d // 2) and W_s.shape == (N, d // 32)
     if workspace is None:
-        workspace = torch.empty((max(torq_linear_workspace_bytes(M, d), 1),), dtype=torch.uint8, device=x_bf16.device)
+        workspace = _scratch(x_bf16, max(torq_linear_workspace_bytes(M, d), 1), stream)
     if out is None:
         out = torch.empty((M, N), dtype=torch.bfloat16, device=x_bf16.device)
     _check(lib().torq_linear_single_launch_probe(
@@ -437,7 +446,7 @@ def torq_linear(rot: Rotation, x_bf16, W_q, W_s, out=None, workspace=None, strea
     N = W_q.shape[0]
     assert d == rot.d and W_q.shape == (N, d // 2) and W_s.shape == (N, d // 32)
     if workspace is None:
-        workspace = x_bf16.new_empty((max(torq_linear_workspace_bytes_n(M, N, d), 1),), dtype=torch.uint8)
+        workspace = _scratch(x_bf16, max(torq_linear_workspace_bytes_n(M, N, d), 1), stream)
     if out is None:
         out = x_bf16.new_empty((M, N), dtype=torch.bfloat16)
     _check(lib().torq_linear(rot.handle, _dev(x_bf16, torch.bfloat16, "x"), _dev(W_q, torch.uint8, "W_q"),
@@ -505,7 +514,7 @@ def torq_diag_gemm_plan(A_q, A_s, W_q, W_s, tile: int, k_pieces: int = 1, deep: 
     if out is None:
         out = torch.empty((M, N), dtype=torch.bfloat16, device=A_q.device)
     if workspace is None and k_pieces > 1:
-        workspace = torch.empty((k_pieces * M * N * 4,), dtype=torch.uint8, device=A_q.device)
+        workspace = _scratch(A_q, k_pieces * M * N * 4, stream)
     ws_ptr = _dev(workspace, torch.uint8, "workspace") if workspace is not None else None
     _check(lib().torq_diag_gemm_plan(_dev(A_q, torch.uint8, "A_q"), _dev(A_s, torch.uint8, "A_s"),
                                      _dev(W_q, torch.uint8, "W_q"), _dev(W_s, torch.uint8, "W_s"),
@@ -522,7 +531,7 @@ def torq_diag_gemm_ring(A_q, A_s, W_q, W_s, tile_m: int, tile_n: int, k_pieces: 
     if out is None:
         out = torch.empty((M, N), dtype=torch.bfloat16, device=A_q.device)
     if workspace is None and k_pieces > 1:
-        workspace = torch.empty((k_pieces * M * N * 4,), dtype=torch.uint8, device=A_q.device)
+        workspace = _scratch(A_q, k_pieces * M * N * 4, stream)
     ws_ptr = _dev(workspace, torch.uint8, "workspace") if workspace is not None else None
     _check(lib().torq_diag_gemm_ring(_dev(A_q, torch.uint8, "A_q"), _dev(A_s, torch.uint8, "A_s"),
                                      _dev(W_q, torch.uint8, "W_q"), _dev(W_s, torch.uint8, "W_s"),
@@ -573,8 +582,7 @@ def torq_block_gram(x_bf16: torch.Tensor, G: int, Sigma=None, workspace=None, st
     if Sigma is None:
         Sigma = torch.empty((G, G), dtype=torch.float64, device=x_bf16.device)
     if workspace is None:
-        workspace = torch.empty((max(torq_block_gram_workspace_bytes(G), 16),), dtype=torch.uint8,
-                                device=x_bf16.device)
+        workspace = _scratch(x_bf16, max(torq_block_gram_workspace_bytes(G), 16), stream)
     _check(lib().torq_block_gram(_dev(x_bf16, torch.bfloat16, "x"), M, d, G, _dev(Sigma, torch.float64, "Sigma"),
                                  _dev(workspace, torch.uint8, "workspace"), workspace.numel(), _stream(stream)),
            "torq_block_gram")
@@ -590,8 +598,7 @@ def torq_block_gram_positions(x_bf16: torch.Tensor, G: int, Sigma_pos=None, work
     if Sigma_pos is None:
         Sigma_pos = torch.empty((32, G, G), dtype=torch.float64, device=x_bf16.device)
     if workspace is None:
-        workspace = torch.empty((max(torq_block_gram_workspace_bytes(G), 16),), dtype=torch.uint8,
-                                device=x_bf16.device)
+        workspace = _scratch(x_bf16, max(torq_block_gram_workspace_bytes(G), 16), stream)
     _check(lib().torq_block_gram_positions(_dev(x_bf16, torch.bfloat16, "x"), M, d, G,
                                            _dev(Sigma_pos, torch.float64, "Sigma_pos"),
                                            _dev(workspace, torch.uint8, "workspace"), workspace.numel(),
@@ -629,7 +636,7 @@ def torq_code_histogram(codes: torch.Tensor, d: int, counts: torch.Tensor = None
     if counts is None:
         counts = torch.empty((32, 8), dtype=torch.int64, device=codes.device)
     if workspace is None:
-        workspace = torch.empty(torq_code_histogram_workspace_bytes(), dtype=torch.uint8, device=codes.device)
+        workspace = _scratch(codes, torq_code_histogram_workspace_bytes(), stream)
     _check(lib().torq_code_histogram(_dev(codes, torch.uint8, "codes"), M, d, _dev(counts, torch.int64, "counts"),
                                      _dev(workspace, torch.uint8, "workspace"), workspace.numel(), _stream(stream)),
            "torq_code_histogram")

@@ -10,12 +10,14 @@
 // function; no state but the addresses handed over in bind().
 #include <Python.h>
 
+#include <torch/csrc/Stream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/ATen.h>
 
 #include <algorithm>
 #include <cstdint>
+#include <optional>
 
 namespace {
 
@@ -87,6 +89,15 @@ void *stream_of(PyObject *stream) {
   return pointer(s.p);
 }
 
+// The stream of a call that allocates its own workspace: that goes back to the allocator when the call returns, ahead of the
+// kernels that use it, so a stream that is not the one it is allocated on has to be known there.
+std::optional<c10::Stream> user_of(PyObject *stream, const Tensor *workspace) {
+  if (workspace || stream == Py_None) return std::nullopt;
+  if (!THPStream_Check(stream)) throw NotPlain{};
+  const THPStream *s = reinterpret_cast<const THPStream *>(stream);
+  return c10::Stream::unpack3(s->stream_id, (c10::DeviceIndex)s->device_index, (c10::DeviceType)s->device_type);
+}
+
 // allocations and launches without the interpreter's lock, as ctypes and torch's own functions do them
 struct Unlocked {
   PyThreadState *state = PyEval_SaveThread();
@@ -95,6 +106,12 @@ struct Unlocked {
 
 Tensor given_or_new(const Tensor *given, const Tensor &like, at::IntArrayRef sizes, at::ScalarType type) {
   return given ? *given : like.new_empty(sizes, like.options().dtype(type));
+}
+Tensor scratch(const Tensor *given, const Tensor &like, int64_t bytes, const std::optional<c10::Stream> &user) {
+  if (given) return *given;
+  Tensor t = like.new_empty({bytes}, like.options().dtype(at::kByte));
+  if (user) t.record_stream(*user);
+  return t;
 }
 const Tensor *optional(PyObject *o) { return o == Py_None ? nullptr : &tensor(o); }
 PyObject *wrapped(PyObject *given, const Tensor &t) {
@@ -133,11 +150,12 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (d != d_of(a[0]) || W_q.size(1) != d / 2 || W_s.size(0) != N || W_s.size(1) != d / 32) throw NotPlain{};
     void *const handle = handle_of(a[0]), *const xp = address(x, at::kBFloat16), *const qp = address(W_q, at::kByte),
                 *const sp = address(W_s, at::kByte), *const stream = stream_of(a[6]);
+    const std::optional<c10::Stream> user = user_of(a[6], ws_in);
     Tensor out;
     int status;
     {
       Unlocked unlocked;
-      const Tensor ws = given_or_new(ws_in, x, {ws_in ? 1 : std::max<int64_t>((int64_t)f_linear_bytes(M, N, (int)d), 1)}, at::kByte);
+      const Tensor ws = scratch(ws_in, x, ws_in ? 1 : std::max<int64_t>((int64_t)f_linear_bytes(M, N, (int)d), 1), user);
       out = given_or_new(out_in, x, {M, N}, at::kBFloat16);
       status = f_linear(handle, xp, qp, sp, address(out, at::kBFloat16), M, N, address(ws, at::kByte), (size_t)ws.numel(), stream);
     }
@@ -187,13 +205,14 @@ PyObject *gram(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (x.dim() != 2 || x.size(1) > 0x7FFFFFFF) throw NotPlain{};
     const int64_t M = x.size(0), d = x.size(1);
     void *const xp = address(x, at::kBFloat16), *const stream = stream_of(a[5]);
+    const std::optional<c10::Stream> user = user_of(a[5], ws_in);
     Tensor sigma;
     int status;
     {
       Unlocked unlocked;
       const int64_t shape[3] = {32, G, G};
       sigma = given_or_new(sigma_in, x, positions ? at::IntArrayRef(shape, 3) : at::IntArrayRef(shape + 1, 2), at::kDouble);
-      const Tensor ws = given_or_new(ws_in, x, {ws_in ? 1 : std::max<int64_t>((int64_t)f_gram_bytes(G), 16)}, at::kByte);
+      const Tensor ws = scratch(ws_in, x, ws_in ? 1 : std::max<int64_t>((int64_t)f_gram_bytes(G), 16), user);
       status = (positions ? f_gram_positions : f_gram)(xp, M, (int)d, G, address(sigma, at::kDouble), address(ws, at::kByte),
                                                        (size_t)ws.numel(), stream);
     }
@@ -210,12 +229,13 @@ PyObject *histogram(PyObject *, PyObject *const *a, Py_ssize_t n) {
     const int d = small_integer(a[1]);
     if (codes.dim() != 2 || codes.size(1) * 2 != d) throw NotPlain{};
     void *const cp = address(codes, at::kByte), *const stream = stream_of(a[4]);
+    const std::optional<c10::Stream> user = user_of(a[4], ws_in);
     Tensor counts;
     int status;
     {
       Unlocked unlocked;
       counts = given_or_new(counts_in, codes, {32, 8}, at::kLong);
-      const Tensor ws = given_or_new(ws_in, codes, {ws_in ? 1 : (int64_t)f_histogram_bytes()}, at::kByte);
+      const Tensor ws = scratch(ws_in, codes, ws_in ? 1 : (int64_t)f_histogram_bytes(), user);
       status = f_histogram(cp, codes.size(0), d, address(counts, at::kLong), address(ws, at::kByte), (size_t)ws.numel(), stream);
     }
     return ok(status, "torq_code_histogram") ? wrapped(a[2], counts) : nullptr;

@@ -752,6 +752,38 @@ def test_calls_marshalled_in_native_code(tq, monkeypatch, case):
     assert any(isinstance(v, tuple) for v in native.values()) == refused
 
 
+# A workspace that a call allocates itself goes back to the allocator when the call returns: on a stream that has not got to
+# the call's kernels yet, the allocator has to keep it until it has.
+@pytest.mark.parametrize("native", [True, False])
+def test_a_calls_own_workspace_is_kept_for_a_stream_that_lags(tq, monkeypatch, native):
+    d, G, M, N = 4096, 128, 80, 1024
+    rot = tq.Rotation(d, G, *synth.rotations(G, seed=7))
+    x, side = synth.activations(M, d, seed=8).to(DEV), torch.cuda.Stream()
+    w = tq.torq_rotate_quantize(rot, synth.weights(N, d, seed=9).to(DEV))
+    a = tq.torq_rotate_quantize(rot, x)
+    calls = [(lambda **k: tq.torq_linear(rot, x, *w, **k), tq.torq_linear_workspace_bytes_n(M, N, d)),
+             (lambda **k: tq.torq_linear_single_launch(rot, x[:4].contiguous(), *w, **k), tq.torq_linear_workspace_bytes(4, d)),
+             (lambda **k: tq.mxfp4_gemm_ws(*a, *w, **k), max(16, tq.mxfp4_gemm_workspace_bytes(M, N, d))),
+             (lambda **k: tq.torq_block_gram(x, G, **k), tq.torq_block_gram_workspace_bytes(G)),
+             (lambda **k: tq.torq_block_gram_positions(x, G, **k), tq.torq_block_gram_workspace_bytes(G)),
+             (lambda **k: tq.torq_code_histogram(a[0], d, **k), tq.torq_code_histogram_workspace_bytes())]
+    if not native:
+        monkeypatch.setattr(tq, "_host", _NoModule)
+    side.wait_stream(torch.cuda.current_stream())
+    for call, nbytes in calls:
+        want = call()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            torch.cuda._sleep(20_000_000)
+        got = call(stream=side)
+        stats = torch.cuda.memory_stats()
+        assert not side.query()
+        assert stats["active_bytes.all.current"] - stats["allocated_bytes.all.current"] >= nbytes
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+    rot.close()
+
+
 def test_linear_replays_from_a_hip_graph(tq):
     # Every entry point only enqueues kernels on the caller's stream and allocates nothing, so a
     # serving loop can capture it.  The graph is replayed several times, with eager work and
