@@ -1,7 +1,7 @@
 // The calls of the binding that a program makes again and again, marshalled in C++ (module _host): torq_linear,
 // torq_rotate_quantize (and _fmt), torq_block_gram (and _positions) and torq_code_histogram.  The kernels of the smallest of
 // them take 3 to 6 us, the interpreter 8 to 13 for the attribute look-ups, checks, allocations and a ctypes call.  One row
-// through a 4096 x 4096 layer, a call among others: 10.2 us -> 5.7 to 6.4 from machine to machine (the kernel, replayed from a
+// through a 4096 x 4096 layer, a call among others: 10.2 us -> 5.6 or 6.4 from one process to the next (the kernel, replayed from a
 // graph, 5.7).
 //
 // A function here takes a call only where everything about it is plain: exact tensors (no subclass), the shapes, types and
